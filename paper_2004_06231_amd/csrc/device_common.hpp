@@ -54,6 +54,25 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+// Two float32 numbers as the exact sums of three bfloat16 numbers each: hi = the number rounded to bfloat16, mid = the
+// rest rounded, lo = the rest of the rest (8 + 8 + 8 mantissa bits hold the 24 of a float32; rests below the smallest
+// float32 exponents are lost).  The pairs come packed, a in the low half.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+}
+__device__ __forceinline__ float bf16_low(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float bf16_high(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+__device__ __forceinline__ void split_bf16x3(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    hi = pack_bf16(a, b);
+    a -= bf16_low(hi);
+    b -= bf16_high(hi);
+    mid = pack_bf16(a, b);
+    a -= bf16_low(mid);
+    b -= bf16_high(mid);
+    lo = pack_bf16(a, b);
+}
+
 }  // namespace einet_impl
 
 #endif

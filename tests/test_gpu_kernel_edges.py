@@ -1,0 +1,54 @@
+"""GPU parity at the sizes where a kernel's tiles, passes and dispatch rules have their edges: an E-step, the same E-step
+added to it, and an M-step against the float64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from oracle.einet import BERNOULLI, BINOMIAL, CATEGORICAL, GAUSSIAN
+from tests.common import make_oracle
+from tests.gpu_common import gpu_model, dev, assert_logp_close, assert_stats_close
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(family, param, spec, K, C, B, mask_kind, seed, stat_rtol=1e-3, atol_rel=1e-6):
+    oracle, flat, rng = make_oracle(spec, K, C, family, seed, (0.2, 0.8), leaf_param=param)
+    D = oracle.g.num_vars
+    data = {GAUSSIAN: dict(kind="gaussian_mixture", components=3, std=0.3),
+            BERNOULLI: dict(kind="bernoulli_iid", p=0.4),
+            BINOMIAL: dict(kind="binomial_mixture", components=3, trials=param, lo=0.1, hi=0.9),
+            CATEGORICAL: dict(kind="categorical_mixture", components=3, values=param)}[family]
+    x = workloads.draw_data(rng, data, B, D, C)
+    mask = workloads.draw_mask(rng, None if mask_kind is None else dict(kind=mask_kind, observed_fraction=0.6), B, D)
+    m = gpu_model(spec, K, C, family, B, seed, flat, param)
+    ref_stats, ref_logp = oracle.em_accumulate(x, mask)
+    ref_flat = oracle.stats_to_flat(ref_stats)
+    assert_logp_close(m.logp(dev(x), dev(mask)), ref_logp)
+    lp = torch.empty(B, device="cuda")
+    m.em_accumulate(dev(x), dev(mask), lp)
+    assert_logp_close(lp, ref_logp)
+    assert_stats_close(m.stats, ref_flat, oracle.layout, m.n_params, stat_rtol, atol_rel)
+    m.em_accumulate(dev(x), dev(mask), lp)               # added to, not overwritten
+    assert_stats_close(m.stats, 2.0 * ref_flat, oracle.layout, m.n_params, stat_rtol, atol_rel)
+    kw = dict(step=0.6, w_floor=1e-9)
+    m.em_update(**kw)
+    oracle.em_update(ref_stats, **kw)                    # (the M-step does not depend on the scale of the statistics)
+    got, ref = m.params.cpu().numpy().astype(np.float64), oracle.get_flat_params()
+    assert np.all(np.isfinite(got))
+    assert np.all(np.abs(got - ref) <= 1e-3 * np.abs(ref) + 1e-7)
+    m.close()
+
+
+# tables of 16, 32, 64, 128 and 256 values, entries in tiles of 16, four pairs per workgroup, passes of 128 samples
+@pytest.mark.parametrize("V,spec,K,C,B,mask_kind", [
+    (16, dict(kind="rat", D=20, depth=2, R=2), 16, 1, 128, None),
+    (17, dict(kind="pd", H=5, W=5, deltas=[3]), 17, 1, 129, "shared"),
+    (33, dict(kind="rat", D=13, depth=2, R=3), 15, 3, 33, "per_sample"),
+    (65, dict(kind="pd", H=4, W=6, deltas=[2]), 33, 1, 31, None),
+    (129, dict(kind="rat", D=9, depth=1, R=1), 64, 2, 257, "per_sample"),
+    (256, dict(kind="pd", H=6, W=6, deltas=[3]), 1, 1, 1, None),
+])
+def test_categorical_statistics_edges(V, spec, K, C, B, mask_kind):
+    print("categorical statistics", V, spec, K, C, B, mask_kind, flush=True)
+    _check(CATEGORICAL, V, spec, K, C, B, mask_kind, 300 + V)
