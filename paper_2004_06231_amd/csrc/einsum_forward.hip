@@ -1,5 +1,5 @@
 // Bottom-up pass: einsum layers (Eq. 3-5) and mixing layers (App. B).
-#include "device_common.hpp"
+#include "bf16x6.hpp"
 
 #include <mutex>
 
@@ -205,91 +205,151 @@ __global__ __launch_bounds__(512, KQ >= 14 ? 2 : 4) void k_einsum_forward(const 
     }
 }
 
-// ------------------------------------------------------------------ einsum layer, forward, K a multiple of 8
-// The same factorisation on v_mfma_f32_32x32x2_f32 (the fp32 shape that issues at the full rate of the matrix
-// pipe), as one workgroup per compute unit that walks a run of work units.  A tile of the product T has 32 rows
-// (k, i) and 32 samples; with i fastest, groups of 8 rows stay inside one k, and a lane holds four consecutive i of
-// four such groups, so the i-reduction is again in-lane: 16 FMAs per tile.  K / 8 tiles hold exactly four k.
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
+// ------------------------------------------------------------------ einsum layer, forward, K from 17 to 40
+// The same factorisation on the bfloat16 matrix pipe at float32 precision (bf16x6.hpp), as one workgroup per compute unit
+// that walks a run of work units.  A unit is (item, chunk of 128 samples, 4 outputs k).  A tile of the product T has 16
+// rows (four left entries i x four outputs k) and 16 samples; with row m = 4 (i % 4) + k % 4 the lane group kg holds the
+// left entries i = 4 t + kg and its four accumulators the four outputs, so the i-reduction of Eq. 4 is four in-lane FMAs
+// per tile and the four lane groups' shares are added when the sums are turned into logarithms.
+//
+// Waves 0-3 only run the matrix pipe: wave w owns samples 32 w .. 32 w + 31 of the chunk as two sets of 16, keeps the
+// operand of eR (split into bfloat16 octets) and eL in registers, reads the operand of the W rows from LDS (16 bytes per
+// lane and register, each used for both sets) and leaves its sums in LDS.  Waves 4-7 do everything else: they bring the W
+// slices in and split them (the slice of the next unit, requested one unit ahead), bring the rows of the next item in
+// (also requested one unit ahead), form exp(x - max), and turn the sums of the previous unit into log values.
+// K need not be a multiple of 8: entries beyond K are zeros in the operands (EXACT = false; rows of W and of A then start
+// at any multiple of four bytes).  kout: output entries of every item of the launch (K, or 1 in the root's layer).
+//
+// At K = 40 a unit is 160 instructions of 16 cycles per matrix wave (2560 cycles, the float32 shape needed 6400); with 128
+// samples a launch is bound by its start (tables, rows, first slice) and by the W slices coming in, with many chunks by the
+// matrix pipe and the vector instructions beside it.  Layers of 24 / 50 / 60 / 40 / 20 items, K = 40: 8 / 12 / 14 / 12 / 8 us
+// with 128 samples (9 / 13.5 / 17 / 13 / 8 on v_mfma_f32_32x32x2_f32), 23 / 41 / 48 / 34 / 21 us with 1000 (34 / 64 / 74 / 52 /
+// 31).  Spreading the producers' work over eight matrix waves, so that it interleaves with their instructions, was slower
+// (56 us for the layer of 60): reading the W operand for half of the tiles by twice as many waves costs more LDS time.
 template <int K8>
-struct FwdSLayout {
-    static constexpr int K = 8 * K8;
-    static constexpr int RS = K + 4;                 // row stride (floats): RS/4 odd -> 16-byte operand reads of 8 lanes hit 32 banks
-    static constexpr int SLICE = 4 * K * RS;         // W[4 k][K i][RS]
-    static constexpr int OFF_E = 2 * SLICE;          // eR, eL of the four sample tiles: [tile][2][K8][64 lanes][4]
-    static constexpr int OFF_S = OFF_E + 4 * 2 * K8 * 256;   // sums of a unit: [2 slots][tile][64 lanes][4]
-    static constexpr int LDS_FLOATS = OFF_S + 2 * 4 * 256;
-    static constexpr int NQ4 = 4 * K * (K / 4);      // float4 of a slice
-    static constexpr int NL = (NQ4 + 255) / 256;     // per producer thread
+struct FwdXLayout {
+    using X = X6<K8>;
+    static constexpr int KP = X::KP, NT = X::NT;
+    static constexpr int SLICE = NT * X::BYTES;      // bytes of a W slice
+    static constexpr int RS = KP + 4;                     // row stride (floats) of eR, eL: RS/4 odd
+    static constexpr int OFF_E = 2 * SLICE;               // eR [128][RS], eL [128][RS]
+    static constexpr int OFF_S = OFF_E + 2 * 128 * RS * 4;   // sums: [2 slots][4 waves][2 sets][64 lanes][4]
+    static constexpr int LDS_BYTES = OFF_S + 2 * 4 * 2 * 1024;
+    static constexpr int NI = 4 * KP * K8;           // octets of a slice
+    static constexpr int NL = (NI + 255) / 256;           // per producer thread
 };
 
-// A workgroup owns a run of units; a unit is (item, batch chunk of 128 samples, 4 outputs k) = K8 tiles of 32 rows
-// (k, i) of the product W[(k,i), j] eR[j, b].  Waves 0-3 only run the matrix pipe: wave w owns samples 32 w .. 32 w + 31
-// of the chunk, reads its operands from LDS and leaves four sums per lane in LDS.  Waves 4-7 do everything else: they
-// bring the W slices and the child rows in, form exp(x - max), and turn the sums of the previous unit into log values.
-template <int K8>
-__global__ __launch_bounds__(512, 1) void k_einsum_forward_s(const int32_t* __restrict__ e_left,
-                                                           const int32_t* __restrict__ e_right,
-                                                           const int32_t* __restrict__ e_out,
-                                                           const int32_t* __restrict__ e_woff,
-                                                           const float* __restrict__ params, float* __restrict__ A,
-                                                           double* __restrict__ Off, float* __restrict__ amax,
-                                                           int item0, int count, int B) {
-    using LY = FwdSLayout<K8>;
-    constexpr int K = LY::K, RS = LY::RS, NQ = K / 4, NL = LY::NL;
-    extern __shared__ float lds[];
+template <int K8, bool EXACT>
+__global__ __launch_bounds__(512, 1) void k_einsum_forward_x(const int32_t* __restrict__ e_rec, const float* __restrict__ params,
+                                                           float* __restrict__ A, double* __restrict__ Off,
+                                                           float* __restrict__ amax, int item0, int count, int B, int K_, int kout) {
+    using LY = FwdXLayout<K8>;
+    using X = X6<K8>;
+    constexpr int KP = LY::KP, NT = LY::NT, RS = LY::RS, NL = LY::NL;
+    extern __shared__ __attribute__((aligned(16))) char lds_c[];
+    const int K = EXACT ? KP : K_;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 31, h = lane >> 5;
-    const int nt = wave & 3;                          // sample tile of this wave (both roles)
+    const int nt = wave & 3;                          // sample tile (32 samples) of this wave (both roles)
     const int nchunks = (B + 127) >> 7;
-    const int U = count * nchunks * NQ;              // unit = (item, chunk, quad), quad fastest
-    const int g = xcd_contiguous_block();
-    const int u0 = (int)((long long)g * U / gridDim.x), u1 = (int)((long long)(g + 1) * U / gridDim.x);
+    const int NG = (kout + 3) / 4;    // groups of outputs per item
+    const int U = count * nchunks * NG;               // unit = (item, chunk, group), group fastest
+    const int wg = xcd_contiguous_block();
+    const int u0 = (int)((long long)wg * U / gridDim.x), u1 = (int)((long long)(wg + 1) * U / gridDim.x);
     if (u0 >= u1) return;
-    // position of the first unit
-    int quad = u0 % NQ, chunk = (u0 / NQ) % nchunks, li = u0 / (NQ * nchunks);
-    float* erl = lds + LY::OFF_E + nt * (2 * K8 * 256) + lane * 4;       // + (2 * which + t) * 256 ... see below
+    struct Pos { int g, c, li; };
+    auto advance = [&](Pos& q) {
+        if (++q.g == NG) { q.g = 0; if (++q.c == nchunks) { q.c = 0; ++q.li; } }
+    };
+    Pos pos{u0 % NG, (u0 / NG) % nchunks, u0 / (NG * nchunks)};
+    float* eRl = reinterpret_cast<float*>(lds_c + LY::OFF_E);
+    float* eLl = eRl + 128 * RS;
+    float* sums = reinterpret_cast<float*>(lds_c + LY::OFF_S);
+
+    // W octets of a unit: thread t of 256 takes every 256th octet (row (k, i), octet of j; consecutive threads consecutive
+    // addresses; threads beyond the last octet repeat it: the same values to the same place); entries that do not exist
+    // are zero.  When K is not a multiple of 8 the last octet of a row starts at K - 8, so that it too is two 16-byte
+    // loads: its first entries, which the octet before holds already, are zeros in W, and the operand of eR starts its
+    // last octet there as well.
+    floatx4 wv[NL][2];
+    int wsrc[NL], wdst[NL][3], wk[NL];
+    uint32_t wlive[NL];                               // entries of the octet that count, a bit each
+#pragma unroll
+    for (int x = 0; x < NL; ++x) {
+        const int f = min((tid & 255) + 256 * x, LY::NI - 1);
+        const int o = f % K8, i = (f / K8) % KP, kl = f / (K8 * KP), start = EXACT ? 8 * o : min(8 * o, K - 8);
+        wk[x] = kl;
+        wsrc[x] = (kl * K + min(i, K - 1)) * K + start;
+        wlive[x] = i >= K ? 0u : (0xffu << (8 * o - start)) & 0xffu;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)                   // (the rows of the three parts are swizzled differently)
+            wdst[x][p] = (i >> 2) * X::UNITS + x6_unit<K8>(p, o, 4 * (i & 3) + kl);
+    }
+    auto fetch_w = [&](const Pos& q) {
+        const float* W = params + e_rec[q.li * EIN_REC_INTS + 4] + (size_t)q.g * 4 * K * K;
+#pragma unroll
+        for (int x = 0; x < NL; ++x) {
+            const float* p = W + wsrc[x];
+            if (!EXACT && 4 * q.g + wk[x] >= kout) p -= wk[x] * K * K;     // (outputs beyond the last one)
+            wv[x][0] = *reinterpret_cast<const floatx4u*>(p);
+            wv[x][1] = *reinterpret_cast<const floatx4u*>(p + 4);
+        }
+    };
+    auto store_w = [&](int buf, int g) {
+        uint32x4* dst = reinterpret_cast<uint32x4*>(lds_c + buf * LY::SLICE);
+#pragma unroll
+        for (int x = 0; x < NL; ++x) {
+            const uint32_t live = 4 * g + wk[x] < kout ? wlive[x] : 0u;
+            float v[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) v[c] = EXACT || ((live >> c) & 1) ? wv[x][c >> 2][c & 3] : 0.f;
+            uint32x4 part[3];
+            split_octet(v, part[0], part[1], part[2]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) dst[wdst[x][p]] = part[p];
+        }
+    };
 
     if (wave >= 4) {
         // ------------------------------------------------------------ producer waves
-        const int pt = tid - 256;
-        floatx4 wv[NL];
-#define FETCH_W(li_, quad_)                                                                \
-    {                                                                                      \
-        const float* W_ = params + e_woff[li_] + (size_t)(quad_) * 4 * K * K;              \
-        _Pragma("unroll") for (int q = 0; q < NL; ++q) {                                   \
-            const int f = min(pt + 256 * q, LY::NQ4 - 1);                                  \
-            wv[q] = *reinterpret_cast<const floatx4*>(W_ + (size_t)4 * f);                 \
-        }                                                                                  \
-    }
-#define STORE_W(buf_)                                                                      \
-    {                                                                                      \
-        _Pragma("unroll") for (int q = 0; q < NL; ++q) {                                   \
-            const int f = pt + 256 * q;                                                    \
-            const int row = f / (K / 4), c4 = f - row * (K / 4);                           \
-            if (f < LY::NQ4) *reinterpret_cast<floatx4*>((buf_) + row * RS + 4 * c4) = wv[q]; \
-        }                                                                                  \
-    }
+        const int n = lane & 31, h = lane >> 5;
         // rows of (item, chunk): lane (n, h) of tile nt takes entries 8 t + 4 h .. + 3 of sample 32 nt + n; exp(x - max)
-        // goes to LDS for the matrix wave of the same tile; the item's first unit also owns the offsets and shifts
-        auto rows = [&](int rli, int rchunk, bool owner) {
-            const int b = rchunk * 128 + nt * 32 + n;
-            const int bc = min(b, B - 1);              // rows beyond the batch read the last one again
-            const int left = e_left[rli], right = e_right[rli];
-            const float* Lp = A + ((size_t)left * B + bc) * K + 4 * h;
-            const float* Rp = A + ((size_t)right * B + bc) * K + 4 * h;
-            floatx4 rawR[K8], rawL[K8];
+        // goes to LDS for the matrix waves; the item's first unit also owns the offsets and shifts
+        floatx4 rawR[K8], rawL[K8];
+        double off_children = 0.0;
+        auto fetch_rows = [&](const Pos& q) {
+            const int32_t* rec = e_rec + q.li * EIN_REC_INTS;
+            const int bc = min(q.c * 128 + nt * 32 + n, B - 1);    // rows beyond the batch read the last one again
+            const size_t rl = (size_t)rec[0] * B + bc, rr = (size_t)rec[1] * B + bc;
+            const float* Lp = A + rl * K;
+            const float* Rp = A + rr * K;
 #pragma unroll
             for (int t = 0; t < K8; ++t) {
-                rawR[t] = *reinterpret_cast<const floatx4*>(Rp + 8 * t);
-                rawL[t] = *reinterpret_cast<const floatx4*>(Lp + 8 * t);
+                const int e = 8 * t + 4 * h;
+                if (EXACT) {
+                    rawR[t] = *reinterpret_cast<const floatx4*>(Rp + e);
+                    rawL[t] = *reinterpret_cast<const floatx4*>(Lp + e);
+                } else if (e + 4 <= K) {
+                    rawR[t] = *reinterpret_cast<const floatx4u*>(Rp + e);
+                    rawL[t] = *reinterpret_cast<const floatx4u*>(Lp + e);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        rawR[t][c] = Rp[min(e + c, K - 1)];
+                        rawL[t][c] = Lp[min(e + c, K - 1)];
+                    }
+                }
             }
-            double off_children = 0.0;
-            if (owner && h == 0) off_children = Off[(size_t)left * B + bc] + Off[(size_t)right * B + bc];
+            if (q.g == 0 && h == 0) off_children = Off[rl] + Off[rr];
+        };
+        auto stage_rows = [&](const Pos& q) {
             float xr = -INFINITY, xl = -INFINITY;
 #pragma unroll
             for (int t = 0; t < K8; ++t) {
+                if (!EXACT) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (8 * t + 4 * h + c >= K) rawR[t][c] = rawL[t][c] = -INFINITY;
+                }
                 xr = fmaxf(fmaxf(xr, fmaxf(rawR[t][0], rawR[t][1])), fmaxf(rawR[t][2], rawR[t][3]));
                 xl = fmaxf(fmaxf(xl, fmaxf(rawL[t][0], rawL[t][1])), fmaxf(rawL[t][2], rawL[t][3]));
             }
@@ -302,136 +362,419 @@ __global__ __launch_bounds__(512, 1) void k_einsum_forward_s(const int32_t* __re
                 floatx4 er, el;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    er[c] = __expf(rawR[t][c] - xr);
+                    er[c] = __expf(rawR[t][c] - xr) * X6_SCALE;
                     el[c] = __expf(rawL[t][c] - xl);
                 }
-                *reinterpret_cast<floatx4*>(erl + t * 256) = er;
-                *reinterpret_cast<floatx4*>(erl + (K8 + t) * 256) = el;
+                *reinterpret_cast<floatx4*>(eRl + (nt * 32 + n) * RS + 8 * t + 4 * h) = er;
+                *reinterpret_cast<floatx4*>(eLl + (nt * 32 + n) * RS + 8 * t + 4 * h) = el;
             }
-            if (owner && h == 0 && b < B) {
-                const int out = e_out[rli];
-                Off[(size_t)out * B + b] = off_children + (double)xl + (double)xr;
-                amax[((size_t)(item0 + rli) * 2) * B + b] = xl;
-                amax[((size_t)(item0 + rli) * 2 + 1) * B + b] = xr;
+            const int b = q.c * 128 + nt * 32 + n;
+            if (q.g == 0 && h == 0 && b < B) {
+                Off[(size_t)e_rec[q.li * EIN_REC_INTS + 2] * B + b] = off_children + (double)xl + (double)xr;
+                amax[((size_t)(item0 + q.li) * 2) * B + b] = xl;
+                amax[((size_t)(item0 + q.li) * 2 + 1) * B + b] = xr;
             }
         };
-        // sums of a finished unit -> residuals log S~
-        auto finish = [&](int fli, int fchunk, int fquad, int slot) {
-            const float* sp = lds + LY::OFF_S + (slot * 4 + nt) * 256 + n * 4;
-            const floatx4 s0 = *reinterpret_cast<const floatx4*>(sp);
-            const floatx4 s1 = *reinterpret_cast<const floatx4*>(sp + 128);
-            const int b = fchunk * 128 + nt * 32 + n;
-            if (h == 0 && b < B) {
-                floatx4 r;
+        // sums of a finished unit -> residuals log S~ of sample 32 nt + n
+        auto finish = [&](const Pos& q, int slot) {
+            const int b = q.c * 128 + nt * 32 + n;
+            const float* sp = sums + ((slot * 4 + nt) * 2 + (n >> 4)) * 256 + (n & 15) * 4;
+            if (h != 0 || b >= B) return;
+            floatx4 r = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int c = 0; c < 4; ++c) r[c] = __logf(s0[c] + s1[c]);
-                *reinterpret_cast<floatx4*>(A + ((size_t)e_out[fli] * B + b) * K + 4 * fquad) = r;
-            }
+            for (int kg = 0; kg < 4; ++kg) r += *reinterpret_cast<const floatx4*>(sp + kg * 64);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r[c] = __logf(r[c] * X6_UNSCALE);
+            const int k = 4 * q.g;
+            float* out = A + ((size_t)e_rec[q.li * EIN_REC_INTS + 2] * B + b) * K + k;
+            if (EXACT) *reinterpret_cast<floatx4*>(out) = r;
+            else
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (k + c < kout) out[c] = r[c];
         };
-        rows(li, chunk, quad == 0);                     // (the matrix waves bring the first slice in)
-        // position of the unit whose slice is in flight
-        int lq = quad, lc = chunk, lli = li;
-        auto advance = [&](int& q_, int& c_, int& i_) {
-            if (++q_ == NQ) { q_ = 0; if (++c_ == nchunks) { c_ = 0; ++i_; } }
-        };
-        advance(lq, lc, lli);
-        if (u0 + 1 < u1) FETCH_W(lli, lq)
+        fetch_rows(pos);
+        stage_rows(pos);                                // (the matrix waves bring the first slice in)
+        Pos nxt = pos;                                  // unit whose slice is in flight
+        advance(nxt);
+        if (u0 + 1 < u1) {
+            fetch_w(nxt);
+            if (nxt.g == 0) fetch_rows(nxt);
+        }
         __syncthreads();                                // B0: slice u0 and the first rows are in LDS
         __syncthreads();                                // X: the matrix waves hold the rows in registers
-        int pq = quad, pc = chunk, pli = li;            // previous unit
+        Pos prev = pos;
         for (int u = u0; u < u1; ++u) {
-            // the matrix waves work on unit u = (li, chunk, quad)
-            if (u + 1 < u1) {
-                STORE_W(lds + ((u + 1 - u0) & 1) * LY::SLICE)
-                int q2 = lq, c2 = lc, i2 = lli;
-                advance(q2, c2, i2);
-                if (u + 2 < u1) FETCH_W(i2, q2)
+            // the matrix waves work on unit u = pos
+            const bool more = u + 1 < u1, new_rows = more && nxt.g == 0;
+            Pos n2 = nxt;
+            advance(n2);
+            if (more) store_w((u + 1 - u0) & 1, nxt.g);
+            if (new_rows) stage_rows(nxt);
+            if (u + 2 < u1) {
+                fetch_w(n2);
+                if (n2.g == 0) fetch_rows(n2);
             }
-            if (u > u0) finish(pli, pc, pq, (u - 1 - u0) & 1);
-            const bool new_rows = u + 1 < u1 && quad == NQ - 1;
-            if (new_rows) rows(lli, lc, true);
-            pq = quad; pc = chunk; pli = li;
-            quad = lq; chunk = lc; li = lli;
-            advance(lq, lc, lli);
+            if (u > u0) finish(prev, (u - 1 - u0) & 1);
+            prev = pos;
+            pos = nxt;
+            nxt = n2;
             __syncthreads();                            // B(u+1)
             if (new_rows) __syncthreads();              // X
         }
-        finish(pli, pc, pq, (u1 - 1 - u0) & 1);
+        finish(prev, (u1 - 1 - u0) & 1);
     } else {
         // ------------------------------------------------------------ matrix waves
-        float er[4 * K8], el[K8][4];
-        const bool active = chunk * 128 + nt * 32 < B || nchunks > 1;     // (a tile beyond a short batch does nothing)
-        {
-            // the first W slice, while the producer waves fetch and shift the first rows
-            const float* W_ = params + e_woff[li] + (size_t)quad * 4 * K * K;
-            floatx4 w0[NL];
+        const int c16 = lane & 15, kg = lane >> 4;
+        fetch_w(pos);                                   // the first slice, while the producers fetch and shift the first rows
+        store_w(0, pos.g);
+        int unit[X::NR];
 #pragma unroll
-            for (int q = 0; q < NL; ++q) w0[q] = *reinterpret_cast<const floatx4*>(W_ + (size_t)4 * min(tid + 256 * q, LY::NQ4 - 1));
-#pragma unroll
-            for (int q = 0; q < NL; ++q) {
-                const int f = tid + 256 * q;
-                const int row = f / (K / 4), c4 = f - row * (K / 4);
-                if (f < LY::NQ4) *reinterpret_cast<floatx4*>(lds + row * RS + 4 * c4) = w0[q];
-            }
-        }
+        for (int a = 0; a < X::NR; ++a) unit[a] = x6_row_unit<K8>(a, kg, c16);
+        uint32x4 er[2][X::NR];
+        float el[NT][2];
+        const bool active = pos.c * 128 + nt * 32 < B || nchunks > 1;    // (a tile beyond a short batch does nothing)
         __syncthreads();                                // B0
         bool load_rows = true;
         for (int u = u0; u < u1; ++u) {
             if (load_rows) {
+                if (active) {
 #pragma unroll
-                for (int t = 0; t < K8; ++t) {
-                    const floatx4 r = *reinterpret_cast<const floatx4*>(erl + t * 256);
-                    const floatx4 l = *reinterpret_cast<const floatx4*>(erl + (K8 + t) * 256);
+                    for (int s = 0; s < 2; ++s) {
+                        const float* row = eRl + (nt * 32 + 16 * s + c16) * RS;
+                        x6_sample_operand<K8>(kg, [&](int o, float* v) {
+                            if constexpr (!EXACT) {
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) { er[4 * t + c] = r[c]; el[t][c] = l[c]; }
+                                for (int c = 0; c < 8; ++c) v[c] = row[min(8 * o, K - 8) + c];
+                                return;
+                            }
+                            const floatx4 v0 = *reinterpret_cast<const floatx4*>(row + 8 * o);
+                            const floatx4 v1 = *reinterpret_cast<const floatx4*>(row + 8 * o + 4);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) { v[c] = v0[c]; v[4 + c] = v1[c]; }
+                        }, er[s]);
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) el[t][s] = eLl[(nt * 32 + 16 * s + c16) * RS + 4 * t + kg];
+                    }
                 }
                 __syncthreads();                        // X
             }
-            const float* wrow = lds + ((u - u0) & 1) * LY::SLICE + n * RS + 4 * h;
-            float sk[4] = {0.f, 0.f, 0.f, 0.f};
+            const uint32x4* wt = reinterpret_cast<const uint32x4*>(lds_c + ((u - u0) & 1) * LY::SLICE);
             if (active) {
-                floatx4 a[2][K8];
-                floatx16 acc[2];
+                uint32x4 a[2][X::NR];
+                floatx4 sk[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                floatx4 acc[2][2];
 #pragma unroll
-                for (int t = 0; t < K8; ++t) a[0][t] = *reinterpret_cast<const floatx4*>(wrow + 8 * t);
+                for (int z = 0; z < X::NR; ++z) a[0][z] = wt[unit[z]];
 #pragma unroll
-                for (int m = 0; m <= K8; ++m) {
-                    if (m + 1 < K8) {
+                for (int t = 0; t <= NT; ++t) {
+                    if (t + 1 < NT) {
 #pragma unroll
-                        for (int t = 0; t < K8; ++t)
-                            a[(m + 1) & 1][t] = *reinterpret_cast<const floatx4*>(wrow + 32 * (m + 1) * RS + 8 * t);
+                        for (int z = 0; z < X::NR; ++z) a[(t + 1) & 1][z] = wt[(t + 1) * X::UNITS + unit[z]];
                     }
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (m < K8) {
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[m & 1][r] = 0.f;
-#pragma unroll
-                        for (int t = 0; t < K8; ++t) {
-#pragma unroll
-                            for (int c = 0; c < 4; ++c)
-                                acc[m & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m & 1][t][c], er[4 * t + c], acc[m & 1], 0, 0, 0);
-                        }
+                    if (t < NT) {
+                        acc[t & 1][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+                        acc[t & 1][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+                        x6_tile<K8, 2>(a[t & 1], er, acc[t & 1]);
                     }
-                    if (m > 0) {
-                        // acc[4 a + c]: row 8 a + 4 h + c of tile m - 1; group g = 4 (m - 1) + a: k = g / K8, i = 8 (g % K8) + 4 h + c
+                    if (t > 0) {
+                        // (the tile before: its accumulators are ready while this one's instructions run)
 #pragma unroll
-                        for (int a4 = 0; a4 < 4; ++a4) {
-                            const int gg = 4 * (m - 1) + a4, kq = gg / K8, uu = gg % K8;
+                        for (int s = 0; s < 2; ++s)
 #pragma unroll
-                            for (int c = 0; c < 4; ++c) sk[kq] = fmaf(acc[(m - 1) & 1][4 * a4 + c], el[uu][c], sk[kq]);
-                        }
+                            for (int c = 0; c < 4; ++c) sk[s][c] = fmaf(acc[(t - 1) & 1][s][c], el[t - 1][s], sk[s][c]);
                     }
                 }
+                float* sp = sums + (((u - u0) & 1) * 4 + nt) * 512 + lane * 4;
+                *reinterpret_cast<floatx4*>(sp) = sk[0];
+                *reinterpret_cast<floatx4*>(sp + 256) = sk[1];
             }
-            floatx4 sv = {sk[0], sk[1], sk[2], sk[3]};
-            *reinterpret_cast<floatx4*>(lds + LY::OFF_S + (((u - u0) & 1) * 4 + nt) * 256 + lane * 4) = sv;
-            load_rows = u + 1 < u1 && quad == NQ - 1;
-            if (++quad == NQ) quad = 0;
+            load_rows = u + 1 < u1 && pos.g == NG - 1;
+            advance(pos);
             __syncthreads();                            // B(u+1)
         }
     }
-#undef FETCH_W
-#undef STORE_W
+}
+
+// ------------------------------------------------------------------ einsum layer, forward, K from 9 to 16
+// Small items are bound by the chain of requests in front of their arithmetic, so many small workgroups per compute unit
+// take them: four waves per (item, group of chunks), a chunk being 128 samples, 32 per wave.  The whole item's weights are
+// split into LDS once (at most 24 KB); a lane loads the rows of its own samples straight from memory, so nothing but the
+// weights is shared.  Same tiles as above with row m = 4 (k % 4) + i % 4: lane group kg holds output k = 4 q + kg of group
+// q, its four accumulators four consecutive left entries, so a sum of Eq. 4 is complete in one lane.
+// K = 10: 15 / 10 / 7 / 5.7 us for 1280 / 640 / 320 / 160 items and 100 samples (19 / 11.5 / 8 / 5.4 with the float32 kernel),
+// 79 / 44 / 27 / 17 / 11 us for 1280 .. 80 items and 1000 samples (106 / 59 / 33 / 21 / 16).  Registers must not spill: with
+// 128 instead of 168 of them and 28 spilled every launch took 4 us longer.
+struct FwdSmallLayout {
+    using X = X6<2>;
+    static constexpr int KP = X::KP, NT = X::NT;
+    static constexpr int LDS_BYTES = NT * NT * X::BYTES;  // NT groups of four outputs x NT tiles
+    static constexpr int NI = KP * KP * 2;                // octets of the weights
+    static constexpr int NL = (NI + 255) / 256;
+};
+
+__global__ __launch_bounds__(256, 3) void k_einsum_forward_small(const int32_t* __restrict__ e_rec, const float* __restrict__ params,
+                                                               float* __restrict__ A, double* __restrict__ Off,
+                                                               float* __restrict__ amax, int item0, int ngrp, int cpg, int nsplit,
+                                                               int B, int K, int kout) {
+    using LY = FwdSmallLayout;
+    using X = LY::X;
+    constexpr int K8 = 2;
+    constexpr int KP = LY::KP, NT = LY::NT, NL = LY::NL;
+    extern __shared__ __attribute__((aligned(16))) char lds_c[];
+    uint32x4* wl = reinterpret_cast<uint32x4*>(lds_c);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c16 = lane & 15, kg = lane >> 4;
+    const int vb = xcd_contiguous_block();
+    const int part = vb % nsplit, grp = (vb / nsplit) % ngrp, li = vb / (nsplit * ngrp);
+    const int NG = (kout + 3) >> 2, q0 = part * NG / nsplit, q1 = (part + 1) * NG / nsplit;   // groups of four outputs
+    const int ni = (q1 - q0) * 4 * KP * K8;           // octets of their weights
+    const int32_t* rec = e_rec + li * EIN_REC_INTS;
+    const int left = rec[0], right = rec[1], out = rec[2];
+    const int nchunks = (B + 127) >> 7, c0 = grp * cpg, c1 = min(c0 + cpg, nchunks);
+    const float* W = params + rec[4];
+
+    floatx4 wv[NL][2];
+#pragma unroll
+    for (int x = 0; x < NL; ++x) {
+        if (256 * x >= ni) break;
+        const int f = min(tid + 256 * x, ni - 1);
+        const int o = f % K8, i = (f / K8) % KP, k = 4 * q0 + f / (K8 * KP);
+        const float* p = W + ((size_t)min(k, kout - 1) * K + min(i, K - 1)) * K;
+        p += min(8 * o, K - 8);                       // (the last octet of a row starts at K - 8, as above)
+        wv[x][0] = *reinterpret_cast<const floatx4u*>(p);
+        wv[x][1] = *reinterpret_cast<const floatx4u*>(p + 4);
+    }
+    // rows of this lane's samples (two sets of 16): one octet of R, all of L
+    float rr[2][8], rl[2][KP];
+    double off_children[2];
+    auto fetch_rows = [&](int chunk) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int b = min(chunk * 128 + 32 * wave + 16 * s + c16, B - 1);
+            const float* Lp = A + ((size_t)left * B + b) * K;
+            const float* Rp = A + ((size_t)right * B + b) * K;
+            const int st = (kg & 1) ? K - 8 : 0;
+            const floatx4 r0 = *reinterpret_cast<const floatx4u*>(Rp + st), r1 = *reinterpret_cast<const floatx4u*>(Rp + st + 4);
+            const floatx4 l0 = *reinterpret_cast<const floatx4u*>(Lp), l1 = *reinterpret_cast<const floatx4u*>(Lp + 4);
+            // (the left entries of the tiles 2 and 3 are the row's last eight, those below 8 among them: their weights
+            // are zeros there)
+            const floatx4 l2 = *reinterpret_cast<const floatx4u*>(Lp + K - 8), l3 = *reinterpret_cast<const floatx4u*>(Lp + K - 4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                rr[s][c] = r0[c]; rr[s][4 + c] = r1[c];
+                rl[s][c] = l0[c]; rl[s][4 + c] = l1[c]; rl[s][8 + c] = l2[c]; rl[s][12 + c] = l3[c];
+            }
+            off_children[s] = Off[(size_t)left * B + b] + Off[(size_t)right * B + b];
+        }
+    };
+    fetch_rows(c0);
+#pragma unroll
+    for (int x = 0; x < NL; ++x) {
+        const int f = tid + 256 * x;
+        const int o = f % K8, i = (f / K8) % KP, kl = f / (K8 * KP), k = 4 * q0 + kl;
+        if (f < ni) {
+            float v[8];
+            const bool row = k < kout && i < K;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) v[c] = row && (o == 0 || c >= 16 - K) ? wv[x][c >> 2][c & 3] : 0.f;
+            uint32x4 part[3];
+            split_octet(v, part[0], part[1], part[2]);
+            // row slot of the tiles: left entry i < 8 in slot i, i >= 8 in slot 8 + (i - (K - 8)); the slots in between have
+            // no left entry of their own and get the zeros of the rows i >= K
+            const int slot = i < 8 ? i : i < K ? i + 16 - K : 8 + i - K;
+            uint32x4* d = wl + ((kl >> 2) * NT + (slot >> 2)) * X::UNITS;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) d[x6_unit<K8>(p, o, 4 * (kl & 3) + (slot & 3))] = part[p];
+        }
+    }
+    int unit[X::NR];
+#pragma unroll
+    for (int a = 0; a < X::NR; ++a) unit[a] = x6_row_unit<K8>(a, kg, c16);
+    __syncthreads();
+    for (int chunk = c0; chunk < c1; ++chunk) {
+        if (chunk > c0) fetch_rows(chunk);            // (the other workgroups of the compute unit hide the wait)
+        uint32x4 er[2][X::NR];
+        float el[2][KP];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            float xr = rr[s][0], xl = rl[s][0];
+#pragma unroll
+            for (int c = 1; c < 8; ++c) xr = fmaxf(xr, rr[s][c]);
+            xr = fmaxf(xr, __shfl_xor(xr, 16, 64));
+#pragma unroll
+            for (int c = 1; c < KP; ++c) xl = fmaxf(xl, rl[s][c]);
+            if (xr == -INFINITY) xr = 0.f;            // an all-zero input vector: exp(-inf) = 0, no NaN
+            if (xl == -INFINITY) xl = 0.f;
+            float e8[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) e8[c] = __expf(rr[s][c] - xr) * X6_SCALE;
+            x6_sample_operand<K8>(kg, [&](int, float* v) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) v[c] = e8[c];
+            }, er[s]);
+#pragma unroll
+            for (int c = 0; c < KP; ++c) el[s][c] = __expf(rl[s][c] - xl);
+            const int b = chunk * 128 + 32 * wave + 16 * s + c16;
+            if (kg == 0 && b < B && part == 0) {
+                Off[(size_t)out * B + b] = off_children[s] + (double)xl + (double)xr;
+                amax[((size_t)(item0 + li) * 2) * B + b] = xl;
+                amax[((size_t)(item0 + li) * 2 + 1) * B + b] = xr;
+            }
+        }
+#pragma unroll
+        for (int ql = 0; ql < NT; ++ql) {
+            if (q0 + ql >= q1) break;
+            float sk[2] = {0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                uint32x4 a[X::NR];
+#pragma unroll
+                for (int z = 0; z < X::NR; ++z) a[z] = wl[(ql * NT + t) * X::UNITS + unit[z]];
+                floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                x6_tile<K8, 2>(a, er, acc);
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) sk[s] = fmaf(acc[s][c], el[s][4 * t + c], sk[s]);
+            }
+            const int k = 4 * (q0 + ql) + kg;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int b = chunk * 128 + 32 * wave + 16 * s + c16;
+                if (b < B && k < kout) A[((size_t)out * B + b) * K + k] = __logf(sk[s] * X6_UNSCALE);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------ einsum layer, forward, K from 17 to 31, short launches
+// A launch with about one unit per compute unit is the chain of requests in front of its arithmetic; the persistent
+// kernel's producer waves and barriers only lengthen it.  Here a workgroup of four waves takes one (item, chunk of 128
+// samples, four outputs), every lane loads the rows of its own samples, and only the W slice goes through LDS.  The tiles
+// and the lane layout are those of the persistent kernel.
+// K = 30, 160 / 80 / 40 items, 100 samples: 9.8 / 7.8 / 6.0 us; the float32 kernel took 15.8 / 11.3 / 8.6 us.
+template <int K8>
+__global__ __launch_bounds__(256, 2) void k_einsum_forward_direct(const int32_t* __restrict__ e_rec, const float* __restrict__ params,
+                                                                float* __restrict__ A, double* __restrict__ Off,
+                                                                float* __restrict__ amax, int item0, int nchunks, int B, int K,
+                                                                int kout) {
+    using X = X6<K8>;
+    constexpr int KP = X::KP, NT = X::NT, NI = 4 * KP * K8, NL = (NI + 255) / 256, NO = X::NQ + X::R2 + X::R1;
+    __shared__ __attribute__((aligned(16))) uint32x4 wl[NT * X::UNITS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c16 = lane & 15, kg = lane >> 4;
+    const int NG = (kout + 3) >> 2;
+    const int vb = xcd_contiguous_block();
+    const int g = vb % NG, chunk = (vb / NG) % nchunks, li = vb / (NG * nchunks);
+    const int32_t* rec = e_rec + li * EIN_REC_INTS;
+    const int left = rec[0], right = rec[1], out = rec[2];
+    const float* W = params + rec[4] + (size_t)g * 4 * K * K;
+    // the octets of R that this lane's operand needs, the left entries 4 t + kg, of its two samples
+    float rr[2][NO][8], rl[2][NT];
+    double off_children[2];
+    auto oct_of = [&](int z) { return z < X::NQ ? 4 * z + kg : X::R2 && z == X::NQ ? 4 * X::NQ + (kg & 1) : K8 - 1; };
+    auto start_of = [&](int o) { return min(8 * o, K - 8); };
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int b = min(chunk * 128 + 32 * wave + 16 * s + c16, B - 1);
+        const float* Lp = A + ((size_t)left * B + b) * K;
+        const float* Rp = A + ((size_t)right * B + b) * K;
+#pragma unroll
+        for (int z = 0; z < NO; ++z) {
+            const int st = start_of(oct_of(z));
+            const floatx4 r0 = *reinterpret_cast<const floatx4u*>(Rp + st), r1 = *reinterpret_cast<const floatx4u*>(Rp + st + 4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { rr[s][z][c] = r0[c]; rr[s][z][4 + c] = r1[c]; }
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) rl[s][t] = Lp[min(4 * t + kg, K - 1)];
+        off_children[s] = Off[(size_t)left * B + b] + Off[(size_t)right * B + b];
+    }
+    floatx4 wv[NL][2];
+#pragma unroll
+    for (int x = 0; x < NL; ++x) {
+        const int f = min(tid + 256 * x, NI - 1);
+        const int o = f % K8, i = (f / K8) % KP, kl = f / (K8 * KP);
+        const float* p = W + ((size_t)min(kl, kout - 1 - 4 * g) * K + min(i, K - 1)) * K + start_of(o);
+        wv[x][0] = *reinterpret_cast<const floatx4u*>(p);
+        wv[x][1] = *reinterpret_cast<const floatx4u*>(p + 4);
+    }
+    // (entries that do not exist, and those that the octet before holds already, are zeros)
+#pragma unroll
+    for (int x = 0; x < NL; ++x) {
+        const int f = min(tid + 256 * x, NI - 1);
+        const int o = f % K8, i = (f / K8) % KP, kl = f / (K8 * KP);
+        const int first = i < K && 4 * g + kl < kout ? 8 * o - start_of(o) : 8;
+        float v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = c >= first ? wv[x][c >> 2][c & 3] : 0.f;
+        uint32x4 part[3];
+        split_octet(v, part[0], part[1], part[2]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) wl[(i >> 2) * X::UNITS + x6_unit<K8>(p, o, 4 * (i & 3) + kl)] = part[p];
+    }
+    uint32x4 er[2][X::NR];
+    float el[2][NT];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        float xr = -INFINITY, xl = -INFINITY;
+#pragma unroll
+        for (int z = 0; z < NO; ++z)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) xr = fmaxf(xr, rr[s][z][c]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) xl = fmaxf(xl, rl[s][t]);
+        xr = fmaxf(xr, __shfl_xor(xr, 16, 64));
+        xl = fmaxf(xl, __shfl_xor(xl, 16, 64));
+        xr = fmaxf(xr, __shfl_xor(xr, 32, 64));
+        xl = fmaxf(xl, __shfl_xor(xl, 32, 64));
+        if (xr == -INFINITY) xr = 0.f;                // an all-zero input vector: exp(-inf) = 0, no NaN
+        if (xl == -INFINITY) xl = 0.f;
+        int z = 0;
+        x6_sample_operand<K8>(kg, [&](int, float* v) {          // (called for the octets in the order of oct_of)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) v[c] = __expf(rr[s][z][c] - xr) * X6_SCALE;
+            ++z;
+        }, er[s]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) el[s][t] = __expf(rl[s][t] - xl);
+        const int b = chunk * 128 + 32 * wave + 16 * s + c16;
+        if (kg == 0 && b < B && g == 0) {
+            Off[(size_t)out * B + b] = off_children[s] + (double)xl + (double)xr;
+            amax[((size_t)(item0 + li) * 2) * B + b] = xl;
+            amax[((size_t)(item0 + li) * 2 + 1) * B + b] = xr;
+        }
+    }
+    int unit[X::NR];
+#pragma unroll
+    for (int a = 0; a < X::NR; ++a) unit[a] = x6_row_unit<K8>(a, kg, c16);
+    __syncthreads();
+    floatx4 sk[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        uint32x4 a[X::NR];
+#pragma unroll
+        for (int z = 0; z < X::NR; ++z) a[z] = wl[t * X::UNITS + unit[z]];
+        floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        x6_tile<K8, 2>(a, er, acc);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sk[s][c] = fmaf(acc[s][c], el[s][t], sk[s][c]);
+    }
+    // the lane groups' shares: afterwards every lane holds the four sums of its sample, lane group kg stores output kg
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            sk[s][c] += __shfl_xor(sk[s][c], 16, 64);
+            sk[s][c] += __shfl_xor(sk[s][c], 32, 64);
+        }
+        const float mine = kg == 0 ? sk[s][0] : kg == 1 ? sk[s][1] : kg == 2 ? sk[s][2] : sk[s][3];
+        const int b = chunk * 128 + 32 * wave + 16 * s + c16, k = 4 * g + kg;
+        if (b < B && k < kout) A[((size_t)out * B + b) * K + k] = __logf(mine * X6_UNSCALE);
+    }
 }
 
 // ------------------------------------------------------------------ mixing layer, forward (App. B)
@@ -541,36 +884,83 @@ static void launch_einsum_forward_kq(const DevTables& t, int first, int count, c
 }
 
 template <int K8>
-static void launch_einsum_forward_k8(const DevTables& t, int first, int count, const float* params, float* A,
-                                     double* Off, float* amax, const Dims& d, hipStream_t s) {
-    using LY = FwdSLayout<K8>;
-    const size_t lds = sizeof(float) * LY::LDS_FLOATS;
+static void launch_einsum_forward_x(const DevTables& t, int first, int count, int kout, const float* params, float* A,
+                                    double* Off, float* amax, const Dims& d, hipStream_t s) {
+    const size_t lds = FwdXLayout<K8>::LDS_BYTES;
     static std::once_flag attr_set[EINET_MAX_DEVICES];
     int dev = 0;
     (void)hipGetDevice(&dev);
-    std::call_once(attr_set[dev % EINET_MAX_DEVICES], [&] { allow_dynamic_lds(&k_einsum_forward_s<K8>, lds); });
-    const int units = count * ((d.B + 127) / 128) * (LY::K / 4);
-    hipLaunchKernelGGL(k_einsum_forward_s<K8>, dim3(units < EINET_NUM_CUS ? units : EINET_NUM_CUS), dim3(512), lds, s,
-                       t.ein_left + first, t.ein_right + first, t.ein_out + first, t.ein_woff + first, params, A, Off,
-                       amax, first, count, d.B);
+    std::call_once(attr_set[dev % EINET_MAX_DEVICES], [&] {
+        allow_dynamic_lds(&k_einsum_forward_x<K8, true>, lds);
+        allow_dynamic_lds(&k_einsum_forward_x<K8, false>, lds);
+    });
+    const int nchunks = (d.B + 127) / 128, units = count * nchunks * ((kout + 3) / 4);
+    const dim3 grid(units < EINET_NUM_CUS ? units : EINET_NUM_CUS);
+    const int32_t* rec = t.ein_rec + (size_t)first * EIN_REC_INTS;
+    if (d.K == 8 * K8 && kout == d.K) {
+        hipLaunchKernelGGL((k_einsum_forward_x<K8, true>), grid, dim3(512), lds, s, rec, params, A, Off, amax, first, count,
+                           d.B, d.K, kout);
+        return;
+    }
+    if constexpr (K8 <= 4) {
+        // K not a multiple of 8, at most four units per compute unit: 80 items of K = 30 and 100 samples (640 units) take
+        // 9.8 us with the kernel for short launches and 11.6 us with the persistent one; at 320 items and 500 samples both
+        // take 80 us; K = 18, 320 items, 500 samples (6400 units): 59 and 52 us.  With K a multiple of 8 (24, 32) or K8 = 5
+        // the persistent kernel is the faster one at every size measured (K = 40, 80 items, 100 samples: 16 against 22 us).
+        if (units <= 4 * EINET_NUM_CUS) {
+            hipLaunchKernelGGL(k_einsum_forward_direct<K8>, dim3(units), dim3(256), 0, s, rec, params, A, Off, amax, first,
+                               nchunks, d.B, d.K, kout);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_einsum_forward_x<K8, false>), grid, dim3(512), lds, s, rec, params, A, Off, amax, first, count, d.B,
+                       d.K, kout);
+}
+
+static void launch_einsum_forward_small(const DevTables& t, int first, int count, int kout, const float* params, float* A,
+                                        double* Off, float* amax, const Dims& d, hipStream_t s) {
+    // chunks of an item share its weights as long as four workgroups per compute unit remain
+    const int nchunks = (d.B + 127) / 128, want = (4 * EINET_NUM_CUS + count - 1) / count;
+    const int cpg = (nchunks + want - 1) / want, ngrp = (nchunks + cpg - 1) / cpg;
+    // few items: the groups of four outputs of an item side by side
+    const int groups = (kout + 3) / 4;
+    int nsplit = 2 * EINET_NUM_CUS / (count * ngrp);
+    nsplit = nsplit < 1 ? 1 : nsplit > groups ? groups : nsplit;
+    hipLaunchKernelGGL(k_einsum_forward_small, dim3(count * ngrp * nsplit), dim3(256), FwdSmallLayout::LDS_BYTES, s,
+                       t.ein_rec + (size_t)first * EIN_REC_INTS, params, A, Off, amax, first, ngrp, cpg, nsplit, d.B, d.K, kout);
+}
+
+// Launches that are a chain of requests rather than arithmetic keep the float32 kernel, which has no operands to split:
+// K up to 8 (K = 8, 320 items, 500 samples: 14 us against 27 us with split operands), and, where its rows are 16-byte
+// groups, small batches (K = 16, 320 items, 16 samples: 6.6 against 9.4 us) and K = 20, 24 up to 128 M multiply-adds in one
+// chunk of samples (K = 20, 60 items, 64 samples: 5.6 against 7.6 us; K = 24, 160 items, 100 samples, 221 M: 15 against
+// 13 us); beyond one chunk it walks the chunks one after the other (K = 24, 20 items, 500 samples: 15 against 10 us).
+static bool einsum_forward_plain_is_faster(int count, int kout, const Dims& d) {
+    if (d.K <= 8 || d.K > 40) return true;
+    if (d.K & 3) return false;
+    if (d.K <= 16) return d.B <= 32;
+    return d.K <= 24 && d.B <= 128 && (double)count * kout * d.K * d.K * d.B <= 128e6;
 }
 
 void launch_einsum_forward(const DevTables& t, int first, int count, bool full_k, const float* params, float* A,
                            double* Off, float* amax, float* logp, const Dims& d, hipStream_t s) {
-    if (full_k && (d.K & 7) == 0 && d.K <= 48) {
-        switch (d.K / 8) {
+    const int kout = full_k ? d.K : 1;
+    if (!einsum_forward_plain_is_faster(count, kout, d)) {
+        // (these never write logp: an item that writes the root's own node is the root's only partition, which
+        // k_root_forward takes)
+        switch ((d.K + 7) / 8) {
+            case 2: launch_einsum_forward_small(t, first, count, kout, params, A, Off, amax, d, s); return;
 #define EINET_CASE(J) \
-        case J: launch_einsum_forward_k8<J>(t, first, count, params, A, Off, amax, d, s); return;
-            EINET_CASE(1) EINET_CASE(2) EINET_CASE(3) EINET_CASE(4) EINET_CASE(5) EINET_CASE(6)
+            case J: launch_einsum_forward_x<J>(t, first, count, kout, params, A, Off, amax, d, s); return;
+            EINET_CASE(3) EINET_CASE(4) EINET_CASE(5)
 #undef EINET_CASE
         }
     }
     switch ((d.K + 3) / 4) {
 #define EINET_CASE(J) \
     case J: launch_einsum_forward_kq<J>(t, first, count, params, A, Off, amax, logp, d, s); break;
-        EINET_CASE(1) EINET_CASE(2) EINET_CASE(3) EINET_CASE(4) EINET_CASE(5) EINET_CASE(6) EINET_CASE(7) EINET_CASE(8)
-        EINET_CASE(9) EINET_CASE(10) EINET_CASE(11) EINET_CASE(12) EINET_CASE(13) EINET_CASE(14) EINET_CASE(15)
-        EINET_CASE(16)
+        EINET_CASE(1) EINET_CASE(2) EINET_CASE(3) EINET_CASE(4) EINET_CASE(5) EINET_CASE(6)
+        EINET_CASE(11) EINET_CASE(12) EINET_CASE(13) EINET_CASE(14) EINET_CASE(15) EINET_CASE(16)
 #undef EINET_CASE
     }
 }

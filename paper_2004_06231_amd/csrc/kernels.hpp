@@ -14,7 +14,7 @@ namespace einet_impl {
 // the float32 bit patterns of log C(N, v), v = 0..N, for binomial leaves.
 #define EINET_TABLES(X)                                                                                    \
     X(ein_left) X(ein_right) X(ein_out) X(ein_reg) X(ein_kout) X(ein_woff) X(ein_voff) X(ein_vstr) X(ein_part) \
-    X(ein_gsrc) X(leaf_gsrc)                                                                               \
+    X(ein_gsrc) X(ein_rec) X(leaf_gsrc)                                                                               \
     X(mix_node) X(mix_kout) X(mix_cptr) X(mix_child) X(mix_voff) X(mix_rec)                                \
     X(leaf_node) X(leaf_replica) X(leaf_sptr) X(leaf_var) X(lv_leaf) X(lv_var)                             \
     X(rb_node) X(rb_kout) X(rb_pptr) X(rb_pblk) X(row_off) X(row_len) X(leaf_logc)                         \
@@ -39,6 +39,10 @@ void launch_leaf_forward(const DevTables& t, int n_leaves, int max_scope, const 
 // launch has K output entries (all layers but the root's).
 void launch_einsum_forward(const DevTables& t, int first, int count, bool full_k, const float* params, float* A,
                            double* Off, float* amax, float* logp, const Dims& d, hipStream_t s);
+// Every einsum item also has a record of EIN_REC_INTS ints in ein_rec, which a kernel gets with one scalar load: left node,
+// right node, node of its output, node of its region, offset of W, offset and stride of its mixing weights (ein_voff,
+// ein_vstr), source of its region's posterior (ein_gsrc).
+constexpr int EIN_REC_INTS = 8;
 // A mixing item with at most MIX_REC_CHILDREN partitions also has a record of MIX_REC_INTS ints in mix_rec:
 // node, entries, offset of its weights, number of partitions, then the nodes of the partitions.  The kernel gets
 // all of it with one request instead of walking three tables one after the other.

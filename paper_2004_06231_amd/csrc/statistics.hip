@@ -1,5 +1,5 @@
 // End of the top-down pass: statistics of the mixing weights and of the leaves (Eq. 6-7).
-#include "device_common.hpp"
+#include "bf16x6.hpp"
 
 #include <mutex>
 
@@ -159,10 +159,9 @@ __device__ __forceinline__ void leaf_backward_body(
 // Bound by the posteriors' comparisons (20 vector instructions per three MFMAs) and by the read-modify-write of the table:
 // 784 pairs, V = 256, K = 16, 200 samples: 18 us, where one wave per pair, a lane per entry walking the samples one
 // after the other with its column of a histogram in LDS, took 125 us.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
 constexpr int CAT_BC = 128;                            // samples per pass
 constexpr int CAT_ST = CAT_BC + 8;                     // row stride (16-bit entries): rows 16 bytes apart modulo 128
+constexpr float CAT_SCALE = 0x1p+100f;                 // keeps the rests of the smallest posteriors above the smallest bfloat16
 constexpr int CAT_PAIRS = 4;                           // pairs per workgroup, one per wave
 
 template <int RT>
@@ -207,7 +206,7 @@ __global__ __launch_bounds__(256) void k_leaf_backward_categorical(
         if (b0 > 0) __syncthreads();                   // readers of the previous pass are done
         uint32_t hi[4], mid[4], lo[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) split_bf16x3(g[2 * q], g[2 * q + 1], hi[q], mid[q], lo[q]);
+        for (int q = 0; q < 4; ++q) split_bf16x3(g[2 * q] * CAT_SCALE, g[2 * q + 1] * CAT_SCALE, hi[q], mid[q], lo[q]);
         *reinterpret_cast<uint32x4*>(&gs[0][sk][8 * sb]) = uint32x4{hi[0], hi[1], hi[2], hi[3]};
         *reinterpret_cast<uint32x4*>(&gs[1][sk][8 * sb]) = uint32x4{mid[0], mid[1], mid[2], mid[3]};
         *reinterpret_cast<uint32x4*>(&gs[2][sk][8 * sb]) = uint32x4{lo[0], lo[1], lo[2], lo[3]};
@@ -238,6 +237,8 @@ __global__ __launch_bounds__(256) void k_leaf_backward_categorical(
     // acc[t][q]: value 16 t + 4 kg + q, entry k0 + c16
     const bool own = p0 + wave < npairs && k < d.K;
     float den = 0.f;
+#pragma unroll
+    for (int t = 0; t < RT; ++t) acc[t] *= 1.f / CAT_SCALE;
     if (own) {
         const size_t ph = phi_off + ((size_t)(wvar * d.C + wc) * d.R + r) * V * d.K + k;
         // (the old statistics are requested before the first store: one memory latency, not one per value)

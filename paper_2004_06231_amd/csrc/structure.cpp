@@ -401,7 +401,20 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
         if (!all)
             for (int e = p.ein_layer_ptr[l]; e < p.ein_layer_ptr[l + 1]; ++e) p.ein_gsrc[e] = 0;
     }
-    // the same for the leaves (element-wise statistics kernels only: no categorical leaves, scopes below the 512
+    // ---- one record per einsum item (see EIN_REC_INTS)
+    p.ein_rec.assign((size_t)np * EIN_REC_INTS, 0);
+    for (int e = 0; e < np; ++e) {
+        int32_t* rec = p.ein_rec.data() + (size_t)e * EIN_REC_INTS;
+        rec[0] = p.ein_left[e];
+        rec[1] = p.ein_right[e];
+        rec[2] = p.ein_out[e];
+        rec[3] = p.ein_reg[e];
+        rec[4] = p.ein_woff[e];
+        rec[5] = p.ein_voff[e];
+        rec[6] = p.ein_vstr[e];
+        rec[7] = p.ein_gsrc[e];
+    }
+    // ---- posterior blocks of the leaves (element-wise statistics kernels only: no categorical leaves, scopes below the 512
     // pairs from which the matrix-pipe kernel may be chosen)
     p.leaf_gsrc.assign(p.leaf_node.size(), 0);
     p.leaves_direct = family != EINET_LEAF_CATEGORICAL && p.max_leaf_scope * C < 512 && !p.leaf_node.empty();

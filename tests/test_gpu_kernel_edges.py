@@ -52,3 +52,28 @@ def _check(family, param, spec, K, C, B, mask_kind, seed, stat_rtol=1e-3, atol_r
 def test_categorical_statistics_edges(V, spec, K, C, B, mask_kind):
     print("categorical statistics", V, spec, K, C, B, mask_kind, flush=True)
     _check(CATEGORICAL, V, spec, K, C, B, mask_kind, 300 + V)
+
+
+# Bottom-up einsum kernels: K around the widths of the operands (9 .. 16, 17 .. 31, up to 40, above), chunks of 128 samples
+# and waves of 32, layers with less and more than four units per compute unit, with items of few outputs per workgroup.
+# All operands are positive, so the relative error of a sum is that of its terms (2^-24 each) and of the exponentials
+# (about 1e-6 for exponents up to 10): 3e-5 leaves a factor of ten.
+@pytest.mark.parametrize("spec,K,C,B,mask_kind", [
+    (dict(kind="rat", D=24, depth=3, R=2), 8, 1, 129, None),
+    (dict(kind="rat", D=24, depth=3, R=2), 9, 1, 127, "shared"),
+    (dict(kind="rat", D=12, depth=2, R=40), 13, 1, 300, None),
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 16, 1, 33, "per_sample"),
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 17, 1, 1, None),
+    (dict(kind="rat", D=12, depth=2, R=40), 18, 1, 260, None),          # persistent: more than 1024 units
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 20, 1, 140, None),
+    (dict(kind="rat", D=24, depth=3, R=2), 24, 1, 129, None),
+    (dict(kind="pd", H=4, W=6, deltas=[2]), 25, 3, 64, None),
+    (dict(kind="rat", D=12, depth=2, R=40), 31, 1, 140, None),          # persistent: more than 1024 units
+    (dict(kind="pd", H=4, W=6, deltas=[2]), 32, 1, 257, "shared"),
+    (dict(kind="pd", H=4, W=6, deltas=[2]), 33, 1, 100, None),
+    (dict(kind="rat", D=16, depth=2, R=3), 39, 1, 130, None),
+    (dict(kind="rat", D=16, depth=2, R=70), 40, 1, 2, None),
+])
+def test_einsum_forward_edges(spec, K, C, B, mask_kind):
+    print("einsum forward", spec, K, C, B, mask_kind, flush=True)
+    _check(GAUSSIAN, 0, spec, K, C, B, mask_kind, 600 + K, stat_rtol=3e-5)
