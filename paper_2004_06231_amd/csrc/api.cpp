@@ -97,6 +97,7 @@ Dims dims_of(const einet_t* h, int B) {
     d.TD = h->plan.TD;
     d.family = h->plan.family;
     d.P = h->plan.leaf_param;
+    d.nodes = h->plan.num_nodes;
     return d;
 }
 
@@ -565,15 +566,12 @@ int einet_sample(einet_t* h, int B, const float* x_dev, const uint8_t* mask_dev,
     const float* A = reinterpret_cast<const float*>(h->ws + h->off_A);
     const double* Off = reinterpret_cast<const double*>(h->ws + h->off_Off);
     const float* amax = reinterpret_cast<const float*>(h->ws + h->off_amax);
-    // the chosen entries live where the posterior arena of the EM pass lives (one int32 per node and sample)
+    // the chosen entries live where the posterior arena of the EM pass lives (a byte per node and sample)
     int32_t* sel = reinterpret_cast<int32_t*>(h->ws + h->off_G);
     h->root_ones_batch = 0;
     const int n_part = (int)h->graph.partition.size();
     run(h, KC_SAMPLE, s, [&] {
-        launch_sample_init(sel, p.num_nodes, B, s);
-        for (int l = p.num_layers - 1; l >= 0; --l)
-            launch_sample_regions(h->dt, p.sr_layer_ptr[l], p.sr_layer_ptr[l + 1] - p.sr_layer_ptr[l], evidence,
-                                  h->params, A, Off, amax, u_dev, n_part, sel, d, s);
+        launch_sample_regions(h->dt, p.num_layers, n_part, evidence, h->params, A, Off, amax, u_dev, p.num_nodes, sel, d, s);
         launch_sample_leaves(h->dt, (int)p.lv_leaf.size(), x_dev, mask_dev, mask_mode, h->params + p.phi_offset,
                              noise_dev, sel, out_dev, d, s);
     });

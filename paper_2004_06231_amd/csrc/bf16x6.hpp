@@ -24,8 +24,6 @@ namespace einet_impl {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
-// four consecutive floats at any multiple of four bytes (the hardware's 16-byte loads need no more)
-typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr float X6_SCALE = 0x1p+64f, X6_UNSCALE = 0x1p-64f;
 

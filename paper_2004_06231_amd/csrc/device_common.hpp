@@ -27,6 +27,8 @@
 namespace einet_impl {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+// four consecutive floats at any multiple of four bytes (the hardware's 16-byte loads need no more)
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int EINET_NUM_CUS = 256;        // compute units of an MI355X: workgroups of a one-per-unit launch
 constexpr int EINET_MAX_DEVICES = 16;     // per-device once-flags of the launchers

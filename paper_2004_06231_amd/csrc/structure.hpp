@@ -44,7 +44,8 @@ struct Plan {
     // grouped by the layer whose einsum they follow; leaves; top-down items (sum layers from the root
     // down, then the leaves) with, per region, the runs of posterior blocks its parents write; M-step rows;
     // sampling items: every sum region with the einsum items of its partitions (sr_item[sr_pptr[r] ..], in the
-    // order of the region's mixing weights) and its mixing item (sr_mix, -1 for a single partition).
+    // order of the region's mixing weights) and its mixing item (sr_mix, -1 for a single partition), those of layer l
+    // (bottom-up) at sr_layer_ptr[l] .. sr_layer_ptr[l + 1] - 1.
 #define X(name) std::vector<int32_t> name;
     EINET_TABLES(X)
 #undef X
@@ -56,7 +57,6 @@ struct Plan {
                                                     // parents' blocks (leaf_gsrc); G of the leaves is not assembled
     std::vector<int32_t> mix_layer_ptr;             // [num_layers+1]
     std::vector<int32_t> rb_layer_ptr;              // [num_layers+2]
-    std::vector<int32_t> sr_layer_ptr;              // [num_layers+1]: sampling items (sum regions) per layer, bottom-up
 
     // ABI view data
     std::vector<int32_t> scope_ptr, scope_var, layer_partition, layer_ptr, partition_flat;

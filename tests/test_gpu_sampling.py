@@ -93,6 +93,15 @@ def test_samples_match_oracle(spec, K, C, family, B, evidence, values):
     m.close()
 
 
+def test_samples_of_more_nodes_than_fit_in_lds():
+    """More than 60 x 1024 nodes: the choices of a sample are kept in memory; 300 samples: four waves per sample."""
+    spec = dict(kind="rat", D=64, depth=6, R=500)
+    oracle, flat, rng = make_oracle(spec, 2, 1, BERNOULLI, 41, leaf_range=(0.15, 0.85))
+    m = gpu_model(spec, 2, 1, BERNOULLI, 300, 41, flat)
+    _compare(oracle, m, 300, rng, None, None, "draw", BERNOULLI)
+    m.close()
+
+
 def test_inpainting_on_benchmark_configuration_4():
     """Full-size structure and K (PD 32x32x3, K = 40): the left half of every image is observed, the right half is
     drawn from the conditional, once with leaf samples and once with leaf means."""
