@@ -77,3 +77,27 @@ def test_categorical_statistics_edges(V, spec, K, C, B, mask_kind):
 def test_einsum_forward_edges(spec, K, C, B, mask_kind):
     print("einsum forward", spec, K, C, B, mask_kind, flush=True)
     _check(GAUSSIAN, 0, spec, K, C, B, mask_kind, 600 + K, stat_rtol=3e-5)
+
+
+# Leaf layer for short scopes and many outputs (at least a million): K around its register sizes 8, 16, 32, 64 and not a
+# multiple of four, workgroups of 128 samples that are full, nearly empty and one short, several channels, both masks.
+# The sums are float64 as in the oracle, so the log-densities are held to the suite's tolerance and nothing else.
+@pytest.mark.parametrize("family,param,spec,K,C,B,mask_kind", [
+    (BINOMIAL, 255, dict(kind="rat", D=40, depth=4, R=40), 10, 1, 200, None),
+    (BINOMIAL, 7, dict(kind="rat", D=24, depth=3, R=150), 8, 2, 129, "per_sample"),
+    (BERNOULLI, 0, dict(kind="rat", D=32, depth=5, R=520), 1, 1, 64, "shared"),
+    (BERNOULLI, 0, dict(kind="rat", D=20, depth=2, R=20), 64, 1, 257, None),
+    (GAUSSIAN, 0, dict(kind="rat", D=16, depth=2, R=30), 33, 3, 255, "per_sample"),
+    (GAUSSIAN, 0, dict(kind="rat", D=30, depth=3, R=60), 17, 1, 128, None),
+])
+def test_short_leaf_edges(family, param, spec, K, C, B, mask_kind):
+    print("short leaves", family, spec, K, C, B, mask_kind, flush=True)
+    oracle, flat, rng = make_oracle(spec, K, C, family, 900 + K, (0.2, 0.8), leaf_param=param)
+    D = oracle.g.num_vars
+    data = {GAUSSIAN: dict(kind="gaussian_mixture", components=3, std=0.3), BERNOULLI: dict(kind="bernoulli_iid", p=0.4),
+            BINOMIAL: dict(kind="binomial_mixture", components=3, trials=param, lo=0.1, hi=0.9)}[family]
+    x = workloads.draw_data(rng, data, B, D, C)
+    mask = workloads.draw_mask(rng, None if mask_kind is None else dict(kind=mask_kind, observed_fraction=0.6), B, D)
+    m = gpu_model(spec, K, C, family, B, 900 + K, flat, param)
+    assert_logp_close(m.logp(dev(x), dev(mask)), oracle.logp(x, mask))
+    m.close()
