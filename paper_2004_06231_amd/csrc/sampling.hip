@@ -64,8 +64,9 @@ __device__ __forceinline__ int wave_choice(float w, float incl, float tau) {
 }
 
 // All choices of a sample, the root's first: a workgroup takes one sample through the sum layers top-down, a barrier
-// between two layers.  A wave looks at every (waves)-th region of a layer, all of them side by side in its lanes, and works
-// on those that the sample reaches, one after the other.
+// between two layers.  In a layer of at most 64 regions every wave looks at all of them, one per lane, and those that the
+// sample reaches are dealt to the waves in turn; in a larger one a wave looks at every (waves)-th region (those
+// that a sample reaches are then many and consecutive) and works on what it finds, one after the other.
 //
 // Region with several partitions: the partition first (as above).  Partition: the pair (i, j) has weight
 // W[k][i][j] * eL[i] * eR[j] given the evidence (the posterior of Eq. 6 for the chosen output entry k), W[k][i][j]
@@ -75,7 +76,7 @@ __device__ __forceinline__ int wave_choice(float w, float incl, float tau) {
 //
 // Bound by the chain of requests per layer (choice -> record -> rows and weights -> row i), which is why the weights
 // are requested before the evidence is there, and why the layers share a launch: a sample meets 15 partitions of
-// a 32x32x3 image in six layers.  With 128 samples, K = 40: 44 us for all choices; a launch per layer, with a wave
+// a 32x32x3 image in six layers.  With 128 samples, K = 40: 38 us for all choices (44 with every (waves)-th region for each wave in small layers too); a launch per layer, with a wave
 // for every (region, sample) of the layer and the K*K products of a pair in LDS, took 81.
 template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void k_sample_regions(
@@ -98,15 +99,19 @@ __global__ __launch_bounds__(1024) void k_sample_regions(
     const int KK = K * K;
     for (int l = num_layers - 1; l >= 0; --l) {
         const int first = layer_ptr[l], count = layer_ptr[l + 1] - first;
-        for (int r0 = wave; r0 < count; r0 += 64 * nwaves) {
-            const int mine = r0 + lane * nwaves;
+        const bool dealt = count <= 64;
+        const int step = dealt ? 1 : nwaves;
+        int turn = 0;
+        for (int r0 = dealt ? 0 : wave; r0 < count; r0 += 64 * nwaves) {
+            const int mine = r0 + lane * step;
             const int k_mine = mine < count ? sel[sr_node[first + mine]] : -1;
             unsigned long long reached = __ballot(k_mine >= 0);
             while (reached != 0ull) {
                 const int ln = __ffsll((long long)reached) - 1;
                 reached &= reached - 1;
+                if (dealt && (turn++ & (nwaves - 1)) != wave) continue;
                 const int k = __builtin_amdgcn_readlane(k_mine, ln);
-                const int ri = first + r0 + ln * nwaves;
+                const int ri = first + r0 + ln * step;
                 // the region's record: node, partitions, mixing weights, and per partition its einsum item and nodes
                 const int32_t* rec = sr_rec + (size_t)ri * SR_REC_INTS;
                 const int s = rec[0], nparts = rec[1];
