@@ -76,8 +76,9 @@ __device__ __forceinline__ int wave_choice(float w, float incl, float tau) {
 //
 // Bound by the chain of requests per layer (choice -> record -> rows and weights -> row i), which is why the weights
 // are requested before the evidence is there, and why the layers share a launch: a sample meets 15 partitions of
-// a 32x32x3 image in six layers.  With 128 samples, K = 40: 38 us for all choices (44 with every (waves)-th region for each wave in small layers too); a launch per layer, with a wave
-// for every (region, sample) of the layer and the K*K products of a pair in LDS, took 81.
+// a 32x32x3 image in six layers.  With 128 samples, K = 40: 38 us for all choices (44 with every (waves)-th region for
+// each wave in small layers too); a launch per layer, with a wave for every (region, sample) of the layer and the K*K
+// products of a pair in LDS, took 81.
 template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void k_sample_regions(
     const int32_t* __restrict__ layer_ptr, int num_layers, const int32_t* __restrict__ sr_node,
