@@ -6,8 +6,10 @@
 // accumulated in float32 (the scheme of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence
 // Datatype For Higher-Precision Computations", 2019).  All operands of the circuit are non-negative, so no sum cancels
 // and the error of a result is the error of its terms plus that of the float32 accumulation, as with float32 operands.
-// (A rest below 2^-133, the smallest bfloat16, is lost: numbers below 2^-109 keep fewer bits.  The exponentials, which are
-// at most 1, are therefore multiplied by the power of two X6_SCALE first and the sums by its inverse at the end.)
+// (A rest below 2^-133, the smallest bfloat16, is lost: numbers below 2^-109 would keep fewer bits.  Both operands, the
+// exponentials and the weights, are therefore multiplied by the power of two X6_SCALE before they are split and the sums by
+// X6_UNSCALE at the end: the smallest normal float32 becomes 2^-102, whose last bit is a normal bfloat16.  Sums stay below
+// 2^48 for rows of weights that add up to 1.)
 // v_mfma_f32_16x16x32_bf16 does 16 times as many multiply-adds per cycle as the float32 shapes: with six products 2.67 times.
 //
 // One tile: 16 rows x 16 columns (samples), contraction over KP = 8 K8 entries in octets.  An operand register holds one
@@ -25,7 +27,7 @@ namespace einet_impl {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
 
-constexpr float X6_SCALE = 0x1p+64f, X6_UNSCALE = 0x1p-64f;
+constexpr float X6_SCALE = 0x1p+24f, X6_UNSCALE = 0x1p-48f;
 
 template <int K8>
 struct X6 {

@@ -301,7 +301,7 @@ __global__ __launch_bounds__(512, 1) void k_einsum_forward_x(const int32_t* __re
             const uint32_t live = 4 * g + wk[x] < kout ? wlive[x] : 0u;
             float v[8];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) v[c] = EXACT || ((live >> c) & 1) ? wv[x][c >> 2][c & 3] : 0.f;
+            for (int c = 0; c < 8; ++c) v[c] = EXACT || ((live >> c) & 1) ? wv[x][c >> 2][c & 3] * X6_SCALE : 0.f;
             uint32x4 part[3];
             split_octet(v, part[0], part[1], part[2]);
 #pragma unroll
@@ -577,7 +577,7 @@ __global__ __launch_bounds__(256, 3) void k_einsum_forward_small(const int32_t* 
             float v[8];
             const bool row = k < kout && i < K;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) v[c] = row && (o == 0 || c >= 16 - K) ? wv[x][c >> 2][c & 3] : 0.f;
+            for (int c = 0; c < 8; ++c) v[c] = row && (o == 0 || c >= 16 - K) ? wv[x][c >> 2][c & 3] * X6_SCALE : 0.f;
             uint32x4 part[3];
             split_octet(v, part[0], part[1], part[2]);
             // row slot of the tiles: left entry i < 8 in slot i, i >= 8 in slot 8 + (i - (K - 8)); the slots in between have
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(256, 2) void k_einsum_forward_direct(const int32_t*
         const int first = i < K && 4 * g + kl < kout ? 8 * o - start_of(o) : 8;
         float v[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] = c >= first ? wv[x][c >> 2][c & 3] : 0.f;
+        for (int c = 0; c < 8; ++c) v[c] = c >= first ? wv[x][c >> 2][c & 3] * X6_SCALE : 0.f;
         uint32x4 part[3];
         split_octet(v, part[0], part[1], part[2]);
 #pragma unroll

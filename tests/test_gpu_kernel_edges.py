@@ -101,3 +101,31 @@ def test_short_leaf_edges(family, param, spec, K, C, B, mask_kind):
     m = gpu_model(spec, K, C, family, B, 900 + K, flat, param)
     assert_logp_close(m.logp(dev(x), dev(mask)), oracle.logp(x, mask))
     m.close()
+
+
+# Weights down to the smallest normal float32 (an M-step without a floor reaches them): a sum that consists of such a weight
+# alone must be as good as one of ordinary weights.  Only entry 1 of a leaf allows the value 1, and all pairs of entries but
+# (0, 0) have weights of 2^-125 to 2^-124, so the sum of every inner entry is the weight of the pair (1, 1).  Its float32
+# logarithm is near -86 (rounding 4e-6, twice per path), the log-density near -170 (rounding 8e-6).
+@pytest.mark.parametrize("K,R,B", [(9, 2, 5), (10, 2, 64), (16, 2, 129), (18, 2, 33), (24, 2, 130), (30, 2, 64),
+                                   (18, 110, 129), (36, 2, 64), (40, 2, 129)])
+def test_smallest_weights_keep_their_bits(K, R, B):
+    print("smallest weights", K, R, B, flush=True)
+    spec = dict(kind="rat", D=8, depth=2, R=R)
+    oracle, flat, rng = make_oracle(spec, K, 1, BERNOULLI, 700 + K, (0.2, 0.8))
+    flat = flat.copy()
+    g, lay = oracle.g, oracle.layout
+    for n, (parent, _, _) in enumerate(g.partitions):
+        if g.k_out(parent, K) == K:
+            w = np.ldexp(rng.uniform(1.0, 2.0, (K, K, K)), -125)
+            w[:, 0, 0] = 1.0
+            flat[lay.w_off[n]:lay.w_off[n] + K ** 3] = w.ravel()
+    phi = flat[lay.phi_off:lay.phi_off + g.num_vars * g.num_replica * K].reshape(g.num_vars, g.num_replica, K)
+    phi[:, :, 0] = 0.0
+    phi[:, :, 2:] = 0.0
+    oracle.set_flat_params(flat)
+    m = gpu_model(spec, K, 1, BERNOULLI, B, 700 + K, flat)
+    got = m.logp(torch.ones(B, 8, 1, device="cuda")).cpu().numpy().astype(np.float64)
+    ref = oracle.logp(np.ones((B, 8, 1)))
+    assert np.all(np.abs(got - ref) <= 5e-5), np.abs(got - ref).max()
+    m.close()
