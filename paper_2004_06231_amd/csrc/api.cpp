@@ -571,7 +571,8 @@ int einet_sample(einet_t* h, int B, const float* x_dev, const uint8_t* mask_dev,
     h->root_ones_batch = 0;
     const int n_part = (int)h->graph.partition.size();
     run(h, KC_SAMPLE, s, [&] {
-        launch_sample_regions(h->dt, p.num_layers, n_part, evidence, h->params, A, Off, amax, u_dev, p.num_nodes, sel, d, s);
+        launch_sample_regions(h->dt, p.sr_layer_ptr.data(), p.sr_reach.data(), p.num_layers, n_part, evidence, h->params, A,
+                              Off, amax, u_dev, p.num_nodes, sel, d, s);
         launch_sample_leaves(h->dt, (int)p.lv_leaf.size(), x_dev, mask_dev, mask_mode, h->params + p.phi_offset,
                              noise_dev, sel, out_dev, d, s);
     });

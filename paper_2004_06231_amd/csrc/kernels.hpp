@@ -253,11 +253,11 @@ void launch_init_params(const DevTables& t, int n_rows, float* params, int64_t p
 // own output (-1: the region itself), unused.  Regions with more partitions have nparts only (the kernel then walks
 // the tables).
 constexpr int SR_REC_INTS = 64, SR_REC_PARTS = 8, SR_REC_STRIDE = 7;
-// All choices in one launch: for every region that a sample reaches, the choice of a partition (regions with several) and
-// then of a pair of child entries.
-void launch_sample_regions(const DevTables& t, int num_layers, int num_partitions, bool evidence, const float* params,
-                           const float* A, const double* Off, const float* amax, const float* u, int num_nodes,
-                           int32_t* sel, const Dims& d, hipStream_t s);
+// The choices: for every region that a sample reaches, that of a partition (regions with several) and then of a pair of
+// child entries.  One launch per sum layer, or one for all; layer_ptr, reach: Plan::sr_layer_ptr and Plan::sr_reach.
+void launch_sample_regions(const DevTables& t, const int32_t* layer_ptr, const int32_t* reach, int num_layers,
+                           int num_partitions, bool evidence, const float* params, const float* A, const double* Off,
+                           const float* amax, const float* u, int num_nodes, int32_t* sel, const Dims& d, hipStream_t s);
 void launch_sample_leaves(const DevTables& t, int n_lv, const float* x, const uint8_t* mask, int mask_mode,
                           const float* phi, const float* noise, const int32_t* sel, float* out, const Dims& d,
                           hipStream_t s);

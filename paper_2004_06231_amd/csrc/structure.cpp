@@ -330,6 +330,13 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
                 p.sr_pptr.push_back((int32_t)p.sr_item.size());
             }
             p.sr_layer_ptr.push_back((int32_t)p.sr_node.size());
+            // the regions that a sample reaches have disjoint scopes: as many as fit into all variables, smallest first
+            std::vector<size_t> sizes;
+            for (int s : layer) sizes.push_back(g.scope[s].size());
+            std::sort(sizes.begin(), sizes.end());
+            int reach = 0;
+            for (size_t used = 0; reach < (int)sizes.size() && (used += sizes[reach]) <= (size_t)g.num_vars;) ++reach;
+            p.sr_reach.push_back(reach);
         }
     }
 

@@ -57,6 +57,8 @@ struct Plan {
                                                     // parents' blocks (leaf_gsrc); G of the leaves is not assembled
     std::vector<int32_t> mix_layer_ptr;             // [num_layers+1]
     std::vector<int32_t> rb_layer_ptr;              // [num_layers+2]
+    std::vector<int32_t> sr_reach;                  // [num_layers]: a bound on the sampling items of a layer that one sample
+                                                    // reaches (their scopes are disjoint)
 
     // ABI view data
     std::vector<int32_t> scope_ptr, scope_var, layer_partition, layer_ptr, partition_flat;

@@ -43,9 +43,8 @@ void launch_em_update(const DevTables&, int, int, bool, float*, float*, float*, 
                       float, float, const Dims&, hipStream_t) {}
 void launch_fill(float*, float, int64_t, hipStream_t) {}
 void launch_init_params(const DevTables&, int, float*, int64_t, uint64_t, float, float, const Dims&, hipStream_t) {}
-void launch_sample_init(int32_t*, int, int, hipStream_t) {}
-void launch_sample_regions(const DevTables&, int, int, bool, const float*, const float*, const double*, const float*,
-                           const float*, int, int32_t*, const Dims&, hipStream_t) {}
+void launch_sample_regions(const DevTables&, const int32_t*, const int32_t*, int, int, bool, const float*, const float*,
+                           const double*, const float*, const float*, int, int32_t*, const Dims&, hipStream_t) {}
 void launch_sample_leaves(const DevTables&, int, const float*, const uint8_t*, int, const float*, const float*,
                           const int32_t*, float*, const Dims&, hipStream_t) {}
 hipError_t static_scratch_address(void** ptr) {

@@ -36,6 +36,16 @@ CASES = [
     (dict(kind="pd", H=6, W=6, deltas=[2]), 6, 3, GAUSSIAN, 19, "shared", "mean"),
     (dict(kind="pd", H=8, W=4, deltas=[4, 2]), 9, 1, BERNOULLI, 40, None, "draw"),
     (dict(kind="pd", H=4, W=12, deltas=[4], axes=2), 17, 2, GAUSSIAN, 200, "per_sample", "draw"),
+    # all choices in one launch (larger K): layers of at most 64 regions, dealt to the waves, and of more; sixteen waves per
+    # sample up to 256 samples, four beyond
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 26, 1, GAUSSIAN, 257, None, "mean"),
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 26, 1, GAUSSIAN, 300, "per_sample", "draw"),
+    (dict(kind="rat", D=64, depth=4, R=10), 33, 1, BERNOULLI, 200, "per_sample", "draw"),
+    (dict(kind="rat", D=64, depth=4, R=10), 33, 1, BERNOULLI, 300, None, "draw"),
+    (dict(kind="rat", D=64, depth=4, R=10), 33, 1, BERNOULLI, 300, "per_sample", "draw"),
+    # a launch per layer (deep trees, small K)
+    (dict(kind="rat", D=300, depth=8, R=2), 3, 1, BERNOULLI, 270, None, "draw"),
+    (dict(kind="rat", D=300, depth=8, R=2), 5, 1, BERNOULLI, 30, "per_sample", "draw"),
 ]
 
 
@@ -94,11 +104,14 @@ def test_samples_match_oracle(spec, K, C, family, B, evidence, values):
 
 
 def test_samples_of_more_nodes_than_fit_in_lds():
-    """More than 60 x 1024 nodes: the choices of a sample are kept in memory; 300 samples: four waves per sample."""
+    """More than 60 x 1024 nodes: a launch per layer whatever else holds."""
     spec = dict(kind="rat", D=64, depth=6, R=500)
     oracle, flat, rng = make_oracle(spec, 2, 1, BERNOULLI, 41, leaf_range=(0.15, 0.85))
     m = gpu_model(spec, 2, 1, BERNOULLI, 300, 41, flat)
     _compare(oracle, m, 300, rng, None, None, "draw", BERNOULLI)
+    x = workloads.draw_data(rng, dict(kind="bernoulli_iid", p=0.4), 20, 64, 1)
+    _compare(oracle, m, 20, rng, x, workloads.draw_mask(rng, dict(kind="per_sample", observed_fraction=0.5), 20, 64), "draw",
+             BERNOULLI)
     m.close()
 
 
