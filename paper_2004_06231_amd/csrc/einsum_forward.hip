@@ -205,6 +205,235 @@ __global__ __launch_bounds__(512, KQ >= 14 ? 2 : 4) void k_einsum_forward(const 
     }
 }
 
+// ------------------------------------------------------------------ einsum layer, forward, K = 8, 24 and 48
+// The same factorisation on v_mfma_f32_32x32x2_f32 (the fp32 shape that issues at the full rate of the matrix
+// pipe), as one workgroup per compute unit that walks a run of work units.  A tile of the product T has 32 rows
+// (k, i) and 32 samples; with i fastest, groups of 8 rows stay inside one k, and a lane holds four consecutive i of
+// four such groups, so the i-reduction is again in-lane: 16 FMAs per tile.  K / 8 tiles hold exactly four k.
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+template <int K8>
+struct FwdSLayout {
+    static constexpr int K = 8 * K8;
+    static constexpr int RS = K + 4;                 // row stride (floats): RS/4 odd -> 16-byte operand reads of 8 lanes hit 32 banks
+    static constexpr int SLICE = 4 * K * RS;         // W[4 k][K i][RS]
+    static constexpr int OFF_E = 2 * SLICE;          // eR, eL of the four sample tiles: [tile][2][K8][64 lanes][4]
+    static constexpr int OFF_S = OFF_E + 4 * 2 * K8 * 256;   // sums of a unit: [2 slots][tile][64 lanes][4]
+    static constexpr int LDS_FLOATS = OFF_S + 2 * 4 * 256;
+    static constexpr int NQ4 = 4 * K * (K / 4);      // float4 of a slice
+    static constexpr int NL = (NQ4 + 255) / 256;     // per producer thread
+};
+
+// A workgroup owns a run of units; a unit is (item, batch chunk of 128 samples, 4 outputs k) = K8 tiles of 32 rows
+// (k, i) of the product W[(k,i), j] eR[j, b].  Waves 0-3 only run the matrix pipe: wave w owns samples 32 w .. 32 w + 31
+// of the chunk, reads its operands from LDS and leaves four sums per lane in LDS.  Waves 4-7 do everything else: they
+// bring the W slices and the child rows in, form exp(x - max), and turn the sums of the previous unit into log values.
+template <int K8>
+__global__ __launch_bounds__(512, 1) void k_einsum_forward_s(const int32_t* __restrict__ e_left,
+                                                           const int32_t* __restrict__ e_right,
+                                                           const int32_t* __restrict__ e_out,
+                                                           const int32_t* __restrict__ e_woff,
+                                                           const float* __restrict__ params, float* __restrict__ A,
+                                                           double* __restrict__ Off, float* __restrict__ amax,
+                                                           int item0, int count, int B) {
+    using LY = FwdSLayout<K8>;
+    constexpr int K = LY::K, RS = LY::RS, NQ = K / 4, NL = LY::NL;
+    extern __shared__ float lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 31, h = lane >> 5;
+    const int nt = wave & 3;                          // sample tile of this wave (both roles)
+    const int nchunks = (B + 127) >> 7;
+    const int U = count * nchunks * NQ;              // unit = (item, chunk, quad), quad fastest
+    const int g = xcd_contiguous_block();
+    const int u0 = (int)((long long)g * U / gridDim.x), u1 = (int)((long long)(g + 1) * U / gridDim.x);
+    if (u0 >= u1) return;
+    // position of the first unit
+    int quad = u0 % NQ, chunk = (u0 / NQ) % nchunks, li = u0 / (NQ * nchunks);
+    float* erl = lds + LY::OFF_E + nt * (2 * K8 * 256) + lane * 4;       // + (2 * which + t) * 256 ... see below
+
+    if (wave >= 4) {
+        // ------------------------------------------------------------ producer waves
+        const int pt = tid - 256;
+        floatx4 wv[NL];
+#define FETCH_W(li_, quad_)                                                                \
+    {                                                                                      \
+        const float* W_ = params + e_woff[li_] + (size_t)(quad_) * 4 * K * K;              \
+        _Pragma("unroll") for (int q = 0; q < NL; ++q) {                                   \
+            const int f = min(pt + 256 * q, LY::NQ4 - 1);                                  \
+            wv[q] = *reinterpret_cast<const floatx4*>(W_ + (size_t)4 * f);                 \
+        }                                                                                  \
+    }
+#define STORE_W(buf_)                                                                      \
+    {                                                                                      \
+        _Pragma("unroll") for (int q = 0; q < NL; ++q) {                                   \
+            const int f = pt + 256 * q;                                                    \
+            const int row = f / (K / 4), c4 = f - row * (K / 4);                           \
+            if (f < LY::NQ4) *reinterpret_cast<floatx4*>((buf_) + row * RS + 4 * c4) = wv[q]; \
+        }                                                                                  \
+    }
+        // rows of (item, chunk): lane (n, h) of tile nt takes entries 8 t + 4 h .. + 3 of sample 32 nt + n; exp(x - max)
+        // goes to LDS for the matrix wave of the same tile; the item's first unit also owns the offsets and shifts
+        auto rows = [&](int rli, int rchunk, bool owner) {
+            const int b = rchunk * 128 + nt * 32 + n;
+            const int bc = min(b, B - 1);              // rows beyond the batch read the last one again
+            const int left = e_left[rli], right = e_right[rli];
+            const float* Lp = A + ((size_t)left * B + bc) * K + 4 * h;
+            const float* Rp = A + ((size_t)right * B + bc) * K + 4 * h;
+            floatx4 rawR[K8], rawL[K8];
+#pragma unroll
+            for (int t = 0; t < K8; ++t) {
+                rawR[t] = *reinterpret_cast<const floatx4*>(Rp + 8 * t);
+                rawL[t] = *reinterpret_cast<const floatx4*>(Lp + 8 * t);
+            }
+            double off_children = 0.0;
+            if (owner && h == 0) off_children = Off[(size_t)left * B + bc] + Off[(size_t)right * B + bc];
+            float xr = -INFINITY, xl = -INFINITY;
+#pragma unroll
+            for (int t = 0; t < K8; ++t) {
+                xr = fmaxf(fmaxf(xr, fmaxf(rawR[t][0], rawR[t][1])), fmaxf(rawR[t][2], rawR[t][3]));
+                xl = fmaxf(fmaxf(xl, fmaxf(rawL[t][0], rawL[t][1])), fmaxf(rawL[t][2], rawL[t][3]));
+            }
+            xr = fmaxf(xr, __shfl_xor(xr, 32, 64));
+            xl = fmaxf(xl, __shfl_xor(xl, 32, 64));
+            if (xr == -INFINITY) xr = 0.f;             // an all-zero input vector: exp(-inf) = 0, no NaN
+            if (xl == -INFINITY) xl = 0.f;
+#pragma unroll
+            for (int t = 0; t < K8; ++t) {
+                floatx4 er, el;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    er[c] = __expf(rawR[t][c] - xr);
+                    el[c] = __expf(rawL[t][c] - xl);
+                }
+                *reinterpret_cast<floatx4*>(erl + t * 256) = er;
+                *reinterpret_cast<floatx4*>(erl + (K8 + t) * 256) = el;
+            }
+            if (owner && h == 0 && b < B) {
+                const int out = e_out[rli];
+                Off[(size_t)out * B + b] = off_children + (double)xl + (double)xr;
+                amax[((size_t)(item0 + rli) * 2) * B + b] = xl;
+                amax[((size_t)(item0 + rli) * 2 + 1) * B + b] = xr;
+            }
+        };
+        // sums of a finished unit -> residuals log S~
+        auto finish = [&](int fli, int fchunk, int fquad, int slot) {
+            const float* sp = lds + LY::OFF_S + (slot * 4 + nt) * 256 + n * 4;
+            const floatx4 s0 = *reinterpret_cast<const floatx4*>(sp);
+            const floatx4 s1 = *reinterpret_cast<const floatx4*>(sp + 128);
+            const int b = fchunk * 128 + nt * 32 + n;
+            if (h == 0 && b < B) {
+                floatx4 r;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) r[c] = __logf(s0[c] + s1[c]);
+                *reinterpret_cast<floatx4*>(A + ((size_t)e_out[fli] * B + b) * K + 4 * fquad) = r;
+            }
+        };
+        rows(li, chunk, quad == 0);                     // (the matrix waves bring the first slice in)
+        // position of the unit whose slice is in flight
+        int lq = quad, lc = chunk, lli = li;
+        auto advance = [&](int& q_, int& c_, int& i_) {
+            if (++q_ == NQ) { q_ = 0; if (++c_ == nchunks) { c_ = 0; ++i_; } }
+        };
+        advance(lq, lc, lli);
+        if (u0 + 1 < u1) FETCH_W(lli, lq)
+        __syncthreads();                                // B0: slice u0 and the first rows are in LDS
+        __syncthreads();                                // X: the matrix waves hold the rows in registers
+        int pq = quad, pc = chunk, pli = li;            // previous unit
+        for (int u = u0; u < u1; ++u) {
+            // the matrix waves work on unit u = (li, chunk, quad)
+            if (u + 1 < u1) {
+                STORE_W(lds + ((u + 1 - u0) & 1) * LY::SLICE)
+                int q2 = lq, c2 = lc, i2 = lli;
+                advance(q2, c2, i2);
+                if (u + 2 < u1) FETCH_W(i2, q2)
+            }
+            if (u > u0) finish(pli, pc, pq, (u - 1 - u0) & 1);
+            const bool new_rows = u + 1 < u1 && quad == NQ - 1;
+            if (new_rows) rows(lli, lc, true);
+            pq = quad; pc = chunk; pli = li;
+            quad = lq; chunk = lc; li = lli;
+            advance(lq, lc, lli);
+            __syncthreads();                            // B(u+1)
+            if (new_rows) __syncthreads();              // X
+        }
+        finish(pli, pc, pq, (u1 - 1 - u0) & 1);
+    } else {
+        // ------------------------------------------------------------ matrix waves
+        float er[4 * K8], el[K8][4];
+        const bool active = chunk * 128 + nt * 32 < B || nchunks > 1;     // (a tile beyond a short batch does nothing)
+        {
+            // the first W slice, while the producer waves fetch and shift the first rows
+            const float* W_ = params + e_woff[li] + (size_t)quad * 4 * K * K;
+            floatx4 w0[NL];
+#pragma unroll
+            for (int q = 0; q < NL; ++q) w0[q] = *reinterpret_cast<const floatx4*>(W_ + (size_t)4 * min(tid + 256 * q, LY::NQ4 - 1));
+#pragma unroll
+            for (int q = 0; q < NL; ++q) {
+                const int f = tid + 256 * q;
+                const int row = f / (K / 4), c4 = f - row * (K / 4);
+                if (f < LY::NQ4) *reinterpret_cast<floatx4*>(lds + row * RS + 4 * c4) = w0[q];
+            }
+        }
+        __syncthreads();                                // B0
+        bool load_rows = true;
+        for (int u = u0; u < u1; ++u) {
+            if (load_rows) {
+#pragma unroll
+                for (int t = 0; t < K8; ++t) {
+                    const floatx4 r = *reinterpret_cast<const floatx4*>(erl + t * 256);
+                    const floatx4 l = *reinterpret_cast<const floatx4*>(erl + (K8 + t) * 256);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) { er[4 * t + c] = r[c]; el[t][c] = l[c]; }
+                }
+                __syncthreads();                        // X
+            }
+            const float* wrow = lds + ((u - u0) & 1) * LY::SLICE + n * RS + 4 * h;
+            float sk[4] = {0.f, 0.f, 0.f, 0.f};
+            if (active) {
+                floatx4 a[2][K8];
+                floatx16 acc[2];
+#pragma unroll
+                for (int t = 0; t < K8; ++t) a[0][t] = *reinterpret_cast<const floatx4*>(wrow + 8 * t);
+#pragma unroll
+                for (int m = 0; m <= K8; ++m) {
+                    if (m + 1 < K8) {
+#pragma unroll
+                        for (int t = 0; t < K8; ++t)
+                            a[(m + 1) & 1][t] = *reinterpret_cast<const floatx4*>(wrow + 32 * (m + 1) * RS + 8 * t);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (m < K8) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[m & 1][r] = 0.f;
+#pragma unroll
+                        for (int t = 0; t < K8; ++t) {
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                acc[m & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m & 1][t][c], er[4 * t + c], acc[m & 1], 0, 0, 0);
+                        }
+                    }
+                    if (m > 0) {
+                        // acc[4 a + c]: row 8 a + 4 h + c of tile m - 1; group g = 4 (m - 1) + a: k = g / K8, i = 8 (g % K8) + 4 h + c
+#pragma unroll
+                        for (int a4 = 0; a4 < 4; ++a4) {
+                            const int gg = 4 * (m - 1) + a4, kq = gg / K8, uu = gg % K8;
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) sk[kq] = fmaf(acc[(m - 1) & 1][4 * a4 + c], el[uu][c], sk[kq]);
+                        }
+                    }
+                }
+            }
+            floatx4 sv = {sk[0], sk[1], sk[2], sk[3]};
+            *reinterpret_cast<floatx4*>(lds + LY::OFF_S + (((u - u0) & 1) * 4 + nt) * 256 + lane * 4) = sv;
+            load_rows = u + 1 < u1 && quad == NQ - 1;
+            if (++quad == NQ) quad = 0;
+            __syncthreads();                            // B(u+1)
+        }
+    }
+#undef FETCH_W
+#undef STORE_W
+}
+
 // ------------------------------------------------------------------ einsum layer, forward, K from 17 to 40
 // The same factorisation on the bfloat16 matrix pipe at float32 precision (bf16x6.hpp), as one workgroup per compute unit
 // that walks a run of work units.  A unit is (item, chunk of 128 samples, 4 outputs k).  A tile of the product T has 16
@@ -884,6 +1113,21 @@ static void launch_einsum_forward_kq(const DevTables& t, int first, int count, c
 }
 
 template <int K8>
+static void launch_einsum_forward_s(const DevTables& t, int first, int count, const float* params, float* A,
+                                     double* Off, float* amax, const Dims& d, hipStream_t s) {
+    using LY = FwdSLayout<K8>;
+    const size_t lds = sizeof(float) * LY::LDS_FLOATS;
+    static std::once_flag attr_set[EINET_MAX_DEVICES];
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    std::call_once(attr_set[dev % EINET_MAX_DEVICES], [&] { allow_dynamic_lds(&k_einsum_forward_s<K8>, lds); });
+    const int units = count * ((d.B + 127) / 128) * (LY::K / 4);
+    hipLaunchKernelGGL(k_einsum_forward_s<K8>, dim3(units < EINET_NUM_CUS ? units : EINET_NUM_CUS), dim3(512), lds, s,
+                       t.ein_left + first, t.ein_right + first, t.ein_out + first, t.ein_woff + first, params, A, Off,
+                       amax, first, count, d.B);
+}
+
+template <int K8>
 static void launch_einsum_forward_x(const DevTables& t, int first, int count, int kout, const float* params, float* A,
                                     double* Off, float* amax, const Dims& d, hipStream_t s) {
     const size_t lds = FwdXLayout<K8>::LDS_BYTES;
@@ -902,19 +1146,16 @@ static void launch_einsum_forward_x(const DevTables& t, int first, int count, in
                            d.B, d.K, kout);
         return;
     }
-    if constexpr (K8 <= 4) {
-        // K not a multiple of 8, at most four units per compute unit: 80 items of K = 30 and 100 samples (640 units) take
-        // 9.8 us with the kernel for short launches and 11.6 us with the persistent one; at 320 items and 500 samples both
-        // take 80 us; K = 18, 320 items, 500 samples (6400 units): 59 and 52 us.  With K a multiple of 8 (24, 32) or K8 = 5
-        // the persistent kernel is the faster one at every size measured (K = 40, 80 items, 100 samples: 16 against 22 us).
-        if (units <= 4 * EINET_NUM_CUS) {
-            hipLaunchKernelGGL(k_einsum_forward_direct<K8>, dim3(units), dim3(256), 0, s, rec, params, A, Off, amax, first,
-                               nchunks, d.B, d.K, kout);
-            return;
-        }
-    }
     hipLaunchKernelGGL((k_einsum_forward_x<K8, false>), grid, dim3(512), lds, s, rec, params, A, Off, amax, first, count, d.B,
                        d.K, kout);
+}
+
+template <int K8>
+static void launch_einsum_forward_direct(const DevTables& t, int first, int count, int kout, const float* params, float* A,
+                                         double* Off, float* amax, const Dims& d, hipStream_t s) {
+    const int nchunks = (d.B + 127) / 128;
+    hipLaunchKernelGGL(k_einsum_forward_direct<K8>, dim3(count * nchunks * ((kout + 3) / 4)), dim3(256), 0, s,
+                       t.ein_rec + (size_t)first * EIN_REC_INTS, params, A, Off, amax, first, nchunks, d.B, d.K, kout);
 }
 
 static void launch_einsum_forward_small(const DevTables& t, int first, int count, int kout, const float* params, float* A,
@@ -930,37 +1171,79 @@ static void launch_einsum_forward_small(const DevTables& t, int first, int count
                        t.ein_rec + (size_t)first * EIN_REC_INTS, params, A, Off, amax, first, ngrp, cpg, nsplit, d.B, d.K, kout);
 }
 
-// Launches that are a chain of requests rather than arithmetic keep the float32 kernel, which has no operands to split:
-// K up to 8 (K = 8, 320 items, 500 samples: 14 us against 27 us with split operands), and, where its rows are 16-byte
-// groups, small batches (K = 16, 320 items, 16 samples: 6.6 against 9.4 us) and K = 20, 24 up to 128 M multiply-adds in one
-// chunk of samples (K = 20, 60 items, 64 samples: 5.6 against 7.6 us; K = 24, 160 items, 100 samples, 221 M: 15 against
-// 13 us); beyond one chunk it walks the chunks one after the other (K = 24, 20 items, 500 samples: 15 against 10 us).
-static bool einsum_forward_plain_is_faster(int count, int kout, const Dims& d) {
-    if (d.K <= 8 || d.K > 40) return true;
-    if (d.K & 3) return false;
-    if (d.K <= 16) return d.B <= 32;
-    return d.K <= 24 && d.B <= 128 && (double)count * kout * d.K * d.K * d.B <= 128e6;
+// Which kernel a layer takes.  Microseconds of a log-density of a tree of depth 2 (leaf layer, one layer of `count` items,
+// root: about 8 us besides the layer for few items, 2 to 3 times the layer's for many), measured for K 8 to 48, 2 to 1280
+// items, 1 to 1000 samples.  PLAIN: the float32 kernel with a workgroup per (item, four outputs), which has no operands to
+// split and walks the chunks of 128 samples one after the other.  WAVES: the float32 kernel with specialised waves.
+enum FwdKernel { FWD_PLAIN, FWD_WAVES, FWD_SMALL, FWD_DIRECT, FWD_X };
+static FwdKernel einsum_forward_kernel(int count, int kout, const Dims& d) {
+    const int K = d.K, B = d.B;
+    const bool quads = (K & 3) == 0;                  // rows of 16-byte groups
+    const int64_t units = (int64_t)count * ((B + 127) / 128) * ((kout + 3) / 4);
+    // K = 8, 20 items, 1000 samples: plain 25, waves 18; 80 items, 256 samples: 23.8, 23.5; 1280 items: 180, 183
+    if (K == 8 && kout == K) return B > 128 && count <= 256 ? FWD_WAVES : FWD_PLAIN;
+    // K = 48, 2 items, 1000 samples: plain 63, waves 19; 320 items, 16 samples: 171, 148; 64 samples: 155, 157
+    if (K == 48 && kout == K) return B > 32 && B <= 64 ? FWD_PLAIN : FWD_WAVES;
+    if (K <= 8 || K > 40) return FWD_PLAIN;
+    if (K <= 16) {
+        // K = 16, 320 items: 16 samples plain 50.3, small 53.4; 128 samples 57.0, 55.7; 1000 samples 107, 87
+        if (quads) return B <= 64 ? FWD_PLAIN : FWD_SMALL;
+        // K = 9, 20 items: 16 samples plain 14.8, small 14.2; 320 items, 64 samples 59.5, 61.2; 128 samples 69.8, 69.4
+        return B <= 64 && count >= 64 && (B > 16 || count >= 192) && (K <= 12 || count <= 512) ? FWD_PLAIN : FWD_SMALL;
+    }
+    if (K <= 20) {
+        // three octets for 17 to 20 entries: the split pays for few items only.  K = 18, 20 items, 16 samples: plain 18.3,
+        // direct 16.0; 500 samples 27.6, 23.1; 80 items, 1000 samples: 63.4, persistent 60.5; 1280 items, 1000 samples: 637,
+        // 723.  K = 20, 20 items, 64 samples: 15.2, direct 16.4; 256 samples 18.6, 17.2
+        if (units <= 1024 && (count < 64 ? !quads || B > 128 : !quads && B <= 16)) return FWD_DIRECT;
+        return count <= 128 && B > 512 ? FWD_X : FWD_PLAIN;
+    }
+    // K = 24, 20 items: 16 samples plain 15.5, direct 15.3, persistent 15.4, waves 15.0; 64 samples 15.6, 16.7, 16.2, 15.8;
+    // 256 samples 21.4, 20.1, 19.2, 18.7; 320 items: 64 samples 79.1, 87.3, 80.4, 81.8; 256 samples 101, 105, 90, 92
+    if (K == 24 && B <= 128) return count < 64 && B <= 16 ? FWD_DIRECT : B <= 64 || count <= 128 ? FWD_PLAIN : FWD_X;
+    if (K == 24 && count < 64 && kout == K) return FWD_WAVES;
+    // K = 28, 80 items: 16 samples plain 25.2, direct 26.4; 48 samples 29.8, 29.5; 320 items, 16 samples: 83.8, 82.8
+    if ((K == 28 || K == 32) && B <= 32 && count >= 64 && count <= 160) return FWD_PLAIN;
+    // K = 36, 20 items: 16 samples plain 19.6, persistent 18.9; 64 samples 18.5, 19.8; 80 items: 34.4, 38.2; 96 samples 42.9,
+    // 41.9
+    if (K == 36 && (count < 64 ? B > 16 && B <= 128 : count <= 160 && B <= 64)) return FWD_PLAIN;
+    // K = 30, 80 items, 100 samples (640 units): direct 36.1, persistent 37.4; 320 items, 500 samples (10240): 165, 167;
+    // K = 21, 320 items, 1000 samples: 205, 190.  With K a multiple of 8 or above 32 the persistent one is always faster.
+    return K <= 32 && (K & 7) != 0 && units <= 4 * EINET_NUM_CUS ? FWD_DIRECT : FWD_X;
 }
 
 void launch_einsum_forward(const DevTables& t, int first, int count, bool full_k, const float* params, float* A,
                            double* Off, float* amax, float* logp, const Dims& d, hipStream_t s) {
-    const int kout = full_k ? d.K : 1;
-    if (!einsum_forward_plain_is_faster(count, kout, d)) {
-        // (these never write logp: an item that writes the root's own node is the root's only partition, which
-        // k_root_forward takes)
-        switch ((d.K + 7) / 8) {
-            case 2: launch_einsum_forward_small(t, first, count, kout, params, A, Off, amax, d, s); return;
-#define EINET_CASE(J) \
-            case J: launch_einsum_forward_x<J>(t, first, count, kout, params, A, Off, amax, d, s); return;
-            EINET_CASE(3) EINET_CASE(4) EINET_CASE(5)
-#undef EINET_CASE
+    const int kout = full_k ? d.K : 1, K8 = (d.K + 7) / 8;
+    // (only the plain kernel writes logp: an item that writes the root's own node is the root's only partition, which
+    // k_root_forward takes)
+    switch (einsum_forward_kernel(count, kout, d)) {
+#define EINET_CASE(J, F) case J: F<J>(t, first, count, kout, params, A, Off, amax, d, s); return;
+    case FWD_SMALL:
+        launch_einsum_forward_small(t, first, count, kout, params, A, Off, amax, d, s);
+        return;
+    case FWD_DIRECT:
+        switch (K8) { EINET_CASE(3, launch_einsum_forward_direct) EINET_CASE(4, launch_einsum_forward_direct) }
+        return;
+    case FWD_X:
+        switch (K8) {
+            EINET_CASE(3, launch_einsum_forward_x) EINET_CASE(4, launch_einsum_forward_x) EINET_CASE(5, launch_einsum_forward_x)
         }
+        return;
+#undef EINET_CASE
+    case FWD_WAVES:
+#define EINET_CASE(J) case J: launch_einsum_forward_s<J>(t, first, count, params, A, Off, amax, d, s); return;
+        switch (K8) { EINET_CASE(1) EINET_CASE(3) EINET_CASE(6) }
+        return;
+#undef EINET_CASE
+    case FWD_PLAIN:
+        break;
     }
     switch ((d.K + 3) / 4) {
 #define EINET_CASE(J) \
     case J: launch_einsum_forward_kq<J>(t, first, count, params, A, Off, amax, logp, d, s); break;
-        EINET_CASE(1) EINET_CASE(2) EINET_CASE(3) EINET_CASE(4) EINET_CASE(5) EINET_CASE(6)
-        EINET_CASE(11) EINET_CASE(12) EINET_CASE(13) EINET_CASE(14) EINET_CASE(15) EINET_CASE(16)
+        EINET_CASE(1) EINET_CASE(2) EINET_CASE(3) EINET_CASE(4) EINET_CASE(5) EINET_CASE(6) EINET_CASE(7) EINET_CASE(8)
+        EINET_CASE(9) EINET_CASE(11) EINET_CASE(12) EINET_CASE(13) EINET_CASE(14) EINET_CASE(15) EINET_CASE(16)
 #undef EINET_CASE
     }
 }

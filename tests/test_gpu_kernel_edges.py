@@ -54,29 +54,50 @@ def test_categorical_statistics_edges(V, spec, K, C, B, mask_kind):
     _check(CATEGORICAL, V, spec, K, C, B, mask_kind, 300 + V)
 
 
-# Bottom-up einsum kernels: K around the widths of the operands (9 .. 16, 17 .. 31, up to 40, above), chunks of 128 samples
-# and waves of 32, layers with less and more than four units per compute unit, with items of few outputs per workgroup.
+# Bottom-up einsum kernels: K around the widths of the operands (up to 8, 9 .. 16, 17 .. 20, 21 .. 32, up to 40, above), chunks
+# of 128 samples and waves of 32, launches on both sides of the rules (items, samples), several chunks per workgroup.
 # All operands are positive, so the relative error of a sum is that of its terms (2^-24 each) and of the exponentials
 # (about 1e-6 for exponents up to 10): 3e-5 leaves a factor of ten.
 @pytest.mark.parametrize("spec,K,C,B,mask_kind", [
-    (dict(kind="rat", D=24, depth=3, R=2), 8, 1, 129, None),
+    (dict(kind="rat", D=24, depth=3, R=2), 8, 1, 129, None),            # specialised waves, float32
+    (dict(kind="rat", D=12, depth=2, R=140), 8, 1, 130, None),          # a workgroup per four outputs: many items
     (dict(kind="rat", D=24, depth=3, R=2), 9, 1, 127, "shared"),
+    (dict(kind="rat", D=12, depth=2, R=40), 9, 1, 33, None),            # many items, few samples: the float32 kernel
+    (dict(kind="rat", D=12, depth=2, R=70), 10, 1, 1100, None),         # two chunks per workgroup, the last one of 76 samples
+    (dict(kind="rat", D=12, depth=2, R=80), 13, 1, 1025, "per_sample"),  # ... of a single sample, a chunk of its own
     (dict(kind="rat", D=12, depth=2, R=40), 13, 1, 300, None),
     (dict(kind="pd", H=6, W=6, deltas=[2]), 16, 1, 33, "per_sample"),
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 16, 1, 65, None),
     (dict(kind="pd", H=6, W=6, deltas=[2]), 17, 1, 1, None),
-    (dict(kind="rat", D=12, depth=2, R=40), 18, 1, 260, None),          # persistent: more than 1024 units
+    (dict(kind="rat", D=12, depth=2, R=40), 18, 1, 260, None),          # many items: the float32 kernel
+    (dict(kind="rat", D=12, depth=2, R=40), 18, 1, 520, None),          # ... with more than four chunks: persistent
     (dict(kind="pd", H=6, W=6, deltas=[2]), 20, 1, 140, None),
-    (dict(kind="rat", D=24, depth=3, R=2), 24, 1, 129, None),
+    (dict(kind="rat", D=24, depth=3, R=2), 24, 1, 129, None),           # specialised waves, float32
+    (dict(kind="rat", D=24, depth=3, R=2), 24, 1, 5, None),
+    (dict(kind="rat", D=12, depth=2, R=40), 24, 1, 129, None),          # persistent
     (dict(kind="pd", H=4, W=6, deltas=[2]), 25, 3, 64, None),
+    (dict(kind="rat", D=12, depth=2, R=40), 28, 1, 20, None),           # the float32 kernel between two counts of items
     (dict(kind="rat", D=12, depth=2, R=40), 31, 1, 140, None),          # persistent: more than 1024 units
     (dict(kind="pd", H=4, W=6, deltas=[2]), 32, 1, 257, "shared"),
     (dict(kind="pd", H=4, W=6, deltas=[2]), 33, 1, 100, None),
+    (dict(kind="pd", H=4, W=6, deltas=[2]), 36, 1, 100, None),          # the float32 kernel
     (dict(kind="rat", D=16, depth=2, R=3), 39, 1, 130, None),
     (dict(kind="rat", D=16, depth=2, R=70), 40, 1, 2, None),
+    (dict(kind="pd", H=4, W=6, deltas=[2]), 41, 1, 33, None),
+    (dict(kind="rat", D=16, depth=2, R=3), 48, 1, 64, None),            # a workgroup per four outputs
+    (dict(kind="rat", D=16, depth=2, R=3), 48, 1, 257, "shared"),       # specialised waves, float32
 ])
 def test_einsum_forward_edges(spec, K, C, B, mask_kind):
     print("einsum forward", spec, K, C, B, mask_kind, flush=True)
     _check(GAUSSIAN, 0, spec, K, C, B, mask_kind, 600 + K, stat_rtol=3e-5)
+
+
+# Items with a single output entry in the kernels of the inner layers: a root with more partitions than its own kernel takes.
+@pytest.mark.parametrize("R,K,B", [(3300, 13, 70), (3300, 16, 5), (3100, 18, 3), (2900, 22, 5), (2900, 24, 66), (2300, 36, 3),
+                                   (2300, 40, 2)])
+def test_many_root_partitions(R, K, B):
+    print("many root partitions", R, K, B, flush=True)
+    _check(GAUSSIAN, 0, dict(kind="rat", D=4, depth=1, R=R), K, 1, B, None, 800 + K, stat_rtol=3e-5)
 
 
 # Leaf layer for short scopes and many outputs (at least a million): K around its register sizes 8, 16, 32, 64 and not a
