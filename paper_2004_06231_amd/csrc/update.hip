@@ -170,21 +170,67 @@ __device__ __forceinline__ void update_leaves_body(int block, float* __restrict_
     }
 }
 
-// The same for categorical leaves: blend, raise to at least 1e-6, renormalise over the V values.  A workgroup takes one
-// (variable, replica) and the [V][K] table of each of its channels in turn; thread (k, part) walks every parts-th value of
-// its column, so that consecutive threads touch consecutive memory, and the column sums meet in LDS.  Bound by memory (the
-// table is read and cleared in the statistics, read and written in the parameters, written as logarithms: 64 MB for 784
-// variables, V = 256, K = 16): 16 us for the M-step of that model; with one thread per column it took 192 us.
+// The same for categorical leaves: blend, raise to at least 1e-6, renormalise over the V values.  `parts` threads share a
+// column, each walking every parts-th of its values, about eight of them, which it requests together; thread (k, part) of a
+// (variable, replica) touches memory consecutive with its neighbours' and the column sums meet in LDS.  A workgroup takes
+// as many (variable, replica) pairs as it has threads for, and the [V][K] tables of a pair's channels in turn.  Bound by
+// memory (the table is read and cleared in the statistics, read and written in the parameters, written as logarithms:
+// 64 MB for 784 variables, V = 256, K = 16): 16 us for the M-step of that model (192 with one thread per column).
+// 512 variables, 40 replicas, V = 5, M-step: 5 us for K = 1, 9 us for K = 4 (5 and 9 with one thread per column, 78 and 39 with
+// a workgroup for every (variable, replica)); V = 16: 9 us and 13 us (16 and 17, 78 and 39).
+__host__ __device__ inline int categorical_parts(int K, int V) {
+    const int most = 256 / K, eights = (V + 7) / 8;                  // (K <= 64)
+    return most < eights ? most : eights;
+}
+__host__ __device__ inline int categorical_pairs(int K, int V) { return 256 / (K * categorical_parts(K, V)); }
+
 __device__ __forceinline__ void update_categorical_body(int block, float* __restrict__ params, float* __restrict__ stats,
                                                         float* __restrict__ theta, int64_t phi_off, int64_t den_off,
                                                         int64_t tot_off, float step, Dims d) {
     __shared__ float red[256];
-    const int parts = 256 / d.K, k = threadIdx.x % d.K, part = threadIdx.x / d.K;
-    const bool in = part < parts;                    // (K <= 64)
-    const int r = block % d.R, var = block / d.R;
+    const int parts = categorical_parts(d.K, d.P), pairs = categorical_pairs(d.K, d.P);
+    const int k = threadIdx.x % d.K, part = (threadIdx.x / d.K) % parts, slot = threadIdx.x / (d.K * parts);
+    const int pair = block * pairs + slot;
+    const bool in = slot < pairs && pair < d.D * d.R;
+    const int var = in ? pair / d.R : 0, r = in ? pair - var * d.R : 0;
     const size_t o = ((size_t)var * d.R + r) * d.K + k;
     const float tot = stats[tot_off + o], den = stats[den_off + o];
     constexpr int U = 8;                             // values in flight per thread
+    if (d.P <= U) {                                  // a thread has a whole column: nothing to meet for
+        for (int c = 0; in && c < d.C; ++c) {
+            const size_t e = (size_t)(var * d.C + c) * d.R + r;
+            const size_t at = e * d.P * d.K + k;
+            float old[U], n[U], nw[U], sum = 0.f;
+#pragma unroll
+            for (int v = 0; v < U; ++v) {
+                const size_t av = phi_off + at + (size_t)v * d.K;
+                old[v] = n[v] = nw[v] = 0.f;
+                if (v < d.P) {
+                    old[v] = params[av];
+                    n[v] = stats[av];
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < U; ++v)
+                if (v < d.P) {
+                    const float hat = tot > 0.f ? (n[v] + (tot - den) * old[v]) / tot : old[v];
+                    nw[v] = fmaxf((1.f - step) * old[v] + step * hat, 1e-6f);
+                    sum += nw[v];
+                }
+            const float inv = 1.f / sum;
+#pragma unroll
+            for (int v = 0; v < U; ++v)
+                if (v < d.P) {
+                    const size_t av = at + (size_t)v * d.K;
+                    const float p = nw[v] * inv;
+                    stats[phi_off + av] = 0.f;
+                    params[phi_off + av] = p;
+                    theta[av] = logf(p);
+                }
+        }
+        if (in) stats[tot_off + o] = stats[den_off + o] = 0.f;
+        return;
+    }
     for (int c = 0; c < d.C; ++c) {
         const size_t e = (size_t)(var * d.C + c) * d.R + r;
         float* ph = params + phi_off + e * d.P * d.K + k;
@@ -195,7 +241,8 @@ __device__ __forceinline__ void update_categorical_body(int block, float* __rest
             float old[U], n[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const size_t at = (size_t)min(v0 + u * parts, d.P - 1) * d.K;
+                const bool live = v0 + u * parts < d.P;
+                const size_t at = (size_t)(live ? v0 + u * parts : v0) * d.K;
                 old[u] = ph[at];
                 n[u] = st[at];
             }
@@ -214,12 +261,12 @@ __device__ __forceinline__ void update_categorical_body(int block, float* __rest
         red[threadIdx.x] = sum;
         __syncthreads();                             // (also: every thread has read tot and den)
         float total = 0.f;
-        for (int q = 0; q < parts; ++q) total += red[q * d.K + k];
+        for (int q = 0; in && q < parts; ++q) total += red[(slot * parts + q) * d.K + k];
         const float inv = 1.f / total;
         for (int v0 = part; in && v0 < d.P; v0 += U * parts) {
             float nw[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) nw[u] = ph[(size_t)min(v0 + u * parts, d.P - 1) * d.K];
+            for (int u = 0; u < U; ++u) nw[u] = ph[(size_t)(v0 + u * parts < d.P ? v0 + u * parts : v0) * d.K];
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (v0 + u * parts < d.P) {
@@ -230,14 +277,16 @@ __device__ __forceinline__ void update_categorical_body(int block, float* __rest
                 }
         }
     }
-    if (part == 0) {
+    if (in && part == 0) {
         stats[tot_off + o] = 0.f;
         stats[den_off + o] = 0.f;
     }
 }
 
-// The whole M-step in one launch: weight rows in the first n_row_blocks workgroups, leaves in the others.
-template <int NPL>
+// The whole M-step in one launch: weight rows in the first n_row_blocks workgroups, leaves in the others.  CAT: categorical
+// leaves, a kernel of its own because their many loads in flight take registers that the rows' workgroups of the other
+// families would pay for in occupancy (39 instead of 118 for K up to 11).
+template <int NPL, bool CAT>
 __global__ __launch_bounds__(256) void k_em_update(int n_row_blocks, const int32_t* __restrict__ row_off,
                                                    const int32_t* __restrict__ row_len, int n_rows, int n_lazy_rows,
                                                    int first_row, float* __restrict__ params,
@@ -247,7 +296,7 @@ __global__ __launch_bounds__(256) void k_em_update(int n_row_blocks, const int32
     if ((int)blockIdx.x < n_row_blocks)
         update_rows_body<NPL>(blockIdx.x, row_off, row_len, n_rows, n_lazy_rows, first_row, params, stats, step,
                               w_floor);
-    else if (d.family == EINET_LEAF_CATEGORICAL)
+    else if constexpr (CAT)
         update_categorical_body(blockIdx.x - n_row_blocks, params, stats, theta, phi_off, den_off, tot_off, step, d);
     else
         update_leaves_body(blockIdx.x - n_row_blocks, params, stats, theta, phi_off, den_off, tot_off, step, min_var,
@@ -332,16 +381,20 @@ void launch_em_update(const DevTables& t, int n_rows, int n_lazy_rows, bool lazy
                       int64_t phi_off, int64_t den_off, int64_t tot_off, float step, float min_var, float max_var,
                       float w_floor, const Dims& d, hipStream_t s) {
     const int n_row_blocks = (n_rows + 3) / 4;
-    const int n_leaf_blocks = d.family == EINET_LEAF_CATEGORICAL ? d.D * d.R : (d.D * d.R * d.K + 255) / 256;
+    const int pairs = d.family == EINET_LEAF_CATEGORICAL ? categorical_pairs(d.K, d.P) : 1;
+    const int n_leaf_blocks = d.family == EINET_LEAF_CATEGORICAL ? (d.D * d.R + pairs - 1) / pairs
+                                                                 : (d.D * d.R * d.K + 255) / 256;
     // registers per lane for a weight row of K*K entries (mixing rows are shorter)
     const int per_lane = (d.K * d.K + 63) / 64;
-#define EINET_LAUNCH(N)                                                                                             \
-    hipLaunchKernelGGL(k_em_update<N>, dim3(n_row_blocks + n_leaf_blocks), dim3(256), 0, s, n_row_blocks, t.row_off, \
-                       t.row_len, n_rows, n_lazy_rows, lazy_rows_are_zero ? n_lazy_rows : 0, params, stats, theta,    \
-                       phi_off, den_off, tot_off, step, min_var, max_var, w_floor, d)
-    if (per_lane <= 2) EINET_LAUNCH(2);
-    else if (per_lane <= 8) EINET_LAUNCH(8);
-    else EINET_LAUNCH(32);
+#define EINET_LAUNCH(N, CAT)                                                                                          \
+    hipLaunchKernelGGL((k_em_update<N, CAT>), dim3(n_row_blocks + n_leaf_blocks), dim3(256), 0, s, n_row_blocks,       \
+                       t.row_off, t.row_len, n_rows, n_lazy_rows, lazy_rows_are_zero ? n_lazy_rows : 0, params, stats, \
+                       theta, phi_off, den_off, tot_off, step, min_var, max_var, w_floor, d)
+#define EINET_LAUNCH_CAT(N) if (d.family == EINET_LEAF_CATEGORICAL) EINET_LAUNCH(N, true); else EINET_LAUNCH(N, false)
+    if (per_lane <= 2) { EINET_LAUNCH_CAT(2); }
+    else if (per_lane <= 8) { EINET_LAUNCH_CAT(8); }
+    else { EINET_LAUNCH_CAT(32); }
+#undef EINET_LAUNCH_CAT
 #undef EINET_LAUNCH
 }
 

@@ -48,6 +48,13 @@ def _check(family, param, spec, K, C, B, mask_kind, seed, stat_rtol=1e-3, atol_r
     (65, dict(kind="pd", H=4, W=6, deltas=[2]), 33, 1, 31, None),
     (129, dict(kind="rat", D=9, depth=1, R=1), 64, 2, 257, "per_sample"),
     (256, dict(kind="pd", H=6, W=6, deltas=[3]), 1, 1, 1, None),
+    # M-step: a column per thread up to eight values, shared columns beyond; several (variable, replica) pairs per workgroup
+    # with some left over, one pair with threads left over
+    (2, dict(kind="rat", D=21, depth=2, R=3), 10, 3, 33, "per_sample"),
+    (8, dict(kind="rat", D=11, depth=2, R=2), 64, 1, 40, None),
+    (9, dict(kind="rat", D=13, depth=2, R=3), 17, 2, 20, None),
+    (255, dict(kind="rat", D=7, depth=1, R=2), 3, 1, 60, "shared"),
+    (100, dict(kind="pd", H=4, W=4, deltas=[2]), 40, 1, 50, None),
 ])
 def test_categorical_statistics_edges(V, spec, K, C, B, mask_kind):
     print("categorical statistics", V, spec, K, C, B, mask_kind, flush=True)
