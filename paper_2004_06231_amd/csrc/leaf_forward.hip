@@ -1087,7 +1087,13 @@ void launch_leaf_forward(const DevTables& t, int n_leaves, int max_scope, const 
     // Otherwise, and for long scopes with sixteen parts: 1024 threads, one sample each.
     const bool many = nch != 16 && (int64_t)n_leaves * d.B * d.K * nch >= 1000000;
     const int tpb = many ? 256 : 1024, rb = many ? 4 : 1;
-    if (many && nch == 1 && d.family != EINET_LEAF_CATEGORICAL && d.B >= 64) {
+    // Few entries of short scopes in several chunks of samples leave the short kernel's thread too little to do for its
+    // gathers: 5120 leaves of one variable, K = 1, 1000 samples: log-density 168 us, 195 with it; two variables, K = 2, 195 and
+    // 212; with a mask per sample, whose gathers are its own, K = 4: 274 and 311; but K = 5, one variable: 349 and 323.
+    const bool thin = d.B > SHORT_SAMPLES && (mask_mode == EINET_MASK_PER_SAMPLE
+                                                  ? d.K <= 4 && pairs <= 3
+                                                  : d.K <= (pairs == 1 ? 3 : pairs == 2 ? 2 : 0));
+    if (many && nch == 1 && d.family != EINET_LEAF_CATEGORICAL && d.B >= 64 && !thin) {
         // (smaller batches would leave lanes idle; a categorical leaf's table does not fit its LDS)
         const bool gauss = d.family == EINET_LEAF_GAUSSIAN, masked = mask_mode != EINET_MASK_NONE;
         const dim3 sgrid(n_leaves, (d.B + SHORT_SAMPLES - 1) / SHORT_SAMPLES);

@@ -117,6 +117,10 @@ def test_many_root_partitions(R, K, B):
     (BERNOULLI, 0, dict(kind="rat", D=20, depth=2, R=20), 64, 1, 257, None),
     (GAUSSIAN, 0, dict(kind="rat", D=16, depth=2, R=30), 33, 3, 255, "per_sample"),
     (GAUSSIAN, 0, dict(kind="rat", D=30, depth=3, R=60), 17, 1, 128, None),
+    # few entries of one or two variables: a thread per entry again beyond one chunk of samples
+    (BERNOULLI, 0, dict(kind="rat", D=64, depth=5, R=160), 1, 1, 200, "per_sample"),
+    (GAUSSIAN, 0, dict(kind="rat", D=32, depth=5, R=160), 3, 1, 129, None),
+    (GAUSSIAN, 0, dict(kind="rat", D=32, depth=5, R=160), 4, 1, 129, None),
 ])
 def test_short_leaf_edges(family, param, spec, K, C, B, mask_kind):
     print("short leaves", family, spec, K, C, B, mask_kind, flush=True)
