@@ -36,14 +36,14 @@ CASES = [
     (dict(kind="pd", H=6, W=6, deltas=[2]), 6, 3, GAUSSIAN, 19, "shared", "mean"),
     (dict(kind="pd", H=8, W=4, deltas=[4, 2]), 9, 1, BERNOULLI, 40, None, "draw"),
     (dict(kind="pd", H=4, W=12, deltas=[4], axes=2), 17, 2, GAUSSIAN, 200, "per_sample", "draw"),
-    # all choices in one launch (larger K): layers of at most 64 regions, dealt to the waves, and of more; sixteen waves per
+    # all choices in one launch: layers of at most 64 regions, dealt to the waves, and of more; sixteen waves per
     # sample up to 256 samples, four beyond
     (dict(kind="pd", H=6, W=6, deltas=[2]), 26, 1, GAUSSIAN, 257, None, "mean"),
     (dict(kind="pd", H=6, W=6, deltas=[2]), 26, 1, GAUSSIAN, 300, "per_sample", "draw"),
     (dict(kind="rat", D=64, depth=4, R=10), 33, 1, BERNOULLI, 200, "per_sample", "draw"),
     (dict(kind="rat", D=64, depth=4, R=10), 33, 1, BERNOULLI, 300, None, "draw"),
     (dict(kind="rat", D=64, depth=4, R=10), 33, 1, BERNOULLI, 300, "per_sample", "draw"),
-    # a launch per layer (deep trees, small K)
+    # a launch per layer (deep trees)
     (dict(kind="rat", D=300, depth=8, R=2), 3, 1, BERNOULLI, 270, None, "draw"),
     (dict(kind="rat", D=300, depth=8, R=2), 5, 1, BERNOULLI, 30, "per_sample", "draw"),
 ]
