@@ -1,11 +1,12 @@
 // Products of float32 matrices on the bfloat16 matrix pipe at float32 precision.
 //
 // A float32 number is the exact sum of three bfloat16 numbers (split_bf16x3: 8 + 8 + 8 mantissa bits), so a product a b is
-// the sum of nine products of bfloat16 numbers, each exact in float32.  The three smallest (mid lo, lo mid, lo lo) are
-// below 2^-26 of the product, a quarter of the rounding error of one float32 product, and are left out; the other six are
-// accumulated in float32 (the scheme of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence
-// Datatype For Higher-Precision Computations", 2019).  All operands of the circuit are non-negative, so no sum cancels
-// and the error of a result is the error of its terms plus that of the float32 accumulation, as with float32 operands.
+// the sum of nine products of bfloat16 numbers, each exact in float32.  The three smallest (mid lo, lo mid, lo lo) are left
+// out: mid is at most 2^-8 of its number and lo 2^-17, so they are at most 2^-24 of the product, what one float32 product
+// is rounded by, and 2^-27.5 in the root mean square over random pairs.  The other six are accumulated in float32 (the
+// scheme of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision
+// Computations", 2019).  All operands of the circuit are non-negative, so no sum cancels and the error of a result is the
+// error of its terms plus that of the float32 accumulation, as with float32 operands.
 // (A rest below 2^-133, the smallest bfloat16, is lost: numbers below 2^-109 would keep fewer bits.  Both operands, the
 // exponentials and the weights, are therefore multiplied by the power of two X6_SCALE before they are split and the sums by
 // X6_UNSCALE at the end: the smallest normal float32 becomes 2^-102, whose last bit is a normal bfloat16.  Sums stay below
@@ -34,10 +35,10 @@ struct X6 {
     static constexpr int KP = 8 * K8;
     static constexpr int NQ = K8 / 4, R2 = (K8 >> 1) & 1, R1 = K8 & 1;
     static constexpr int NR = 3 * NQ + 3 * R2 + 2 * R1;   // operand registers (16 bytes per lane) of a tile, and of a sample
-    static constexpr int NM = 6 * NQ + 3 * R2 + 2 * R1;   // instructions of a tile
     static constexpr int NT = KP / 4;                     // tiles of 16 rows: four outer entries x four of the KP inner ones
     // LDS image of the rows of a tile: octet `oct` of part p (hi, mid, lo) of row m is the 16-byte unit
-    // po * 16 + (m ^ (po & 15)), po = p * K8 + oct: reads of 16 rows and stores of consecutive octets hit different banks
+    // po * 16 + (m ^ (po & 3)), po = p * K8 + oct: a read of 16 rows takes 16 consecutive units in any order, and stores of
+    // consecutive octets of a row go to different banks
     static constexpr int UNITS = 3 * K8 * 16;
     static constexpr int BYTES = UNITS * 16;
 };

@@ -514,7 +514,7 @@ __global__ __launch_bounds__(512, 1) void k_einsum_forward_x(const int32_t* __re
             wdst[x][p] = (i >> 2) * X::UNITS + x6_unit<K8>(p, o, 4 * (i & 3) + kl);
     }
     auto fetch_w = [&](const Pos& q) {
-        const float* W = params + e_rec[q.li * EIN_REC_INTS + 4] + (size_t)q.g * 4 * K * K;
+        const float* W = params + e_rec[q.li * EIN_REC_INTS + 3] + (size_t)q.g * 4 * K * K;
 #pragma unroll
         for (int x = 0; x < NL; ++x) {
             const float* p = W + wsrc[x];
@@ -761,7 +761,7 @@ __global__ __launch_bounds__(256, 3) void k_einsum_forward_small(const int32_t* 
     const int32_t* rec = e_rec + li * EIN_REC_INTS;
     const int left = rec[0], right = rec[1], out = rec[2];
     const int nchunks = (B + 127) >> 7, c0 = grp * cpg, c1 = min(c0 + cpg, nchunks);
-    const float* W = params + rec[4];
+    const float* W = params + rec[3];
 
     floatx4 wv[NL][2];
 #pragma unroll
@@ -898,7 +898,7 @@ __global__ __launch_bounds__(256, 2) void k_einsum_forward_direct(const int32_t*
     const int g = vb % NG, chunk = (vb / NG) % nchunks, li = vb / (NG * nchunks);
     const int32_t* rec = e_rec + li * EIN_REC_INTS;
     const int left = rec[0], right = rec[1], out = rec[2];
-    const float* W = params + rec[4] + (size_t)g * 4 * K * K;
+    const float* W = params + rec[3] + (size_t)g * 4 * K * K;
     // the octets of R that this lane's operand needs, the left entries 4 t + kg, of its two samples
     float rr[2][NO][8], rl[2][NT];
     double off_children[2];

@@ -41,9 +41,8 @@ void launch_leaf_forward(const DevTables& t, int n_leaves, int max_scope, const 
 void launch_einsum_forward(const DevTables& t, int first, int count, bool full_k, const float* params, float* A,
                            double* Off, float* amax, float* logp, const Dims& d, hipStream_t s);
 // Every einsum item also has a record of EIN_REC_INTS ints in ein_rec, which a kernel gets with one scalar load: left node,
-// right node, node of its output, node of its region, offset of W, offset and stride of its mixing weights (ein_voff,
-// ein_vstr), source of its region's posterior (ein_gsrc).
-constexpr int EIN_REC_INTS = 8;
+// right node, node of its output, offset of W.
+constexpr int EIN_REC_INTS = 4;
 // A mixing item with at most MIX_REC_CHILDREN partitions also has a record of MIX_REC_INTS ints in mix_rec:
 // node, entries, offset of its weights, number of partitions, then the nodes of the partitions.  The kernel gets
 // all of it with one request instead of walking three tables one after the other.

@@ -194,8 +194,8 @@ __global__ __launch_bounds__(TPB) void k_leaf_forward(const int32_t* __restrict_
 // from LDS, and that was what the launch spent its time on).  The residuals leave through LDS, so that the stores of a
 // wave are one consecutive run.  The terms of an entry are added in the order of the scope in float64, as above.
 // Bound by the writes, the gathered reads of x and the float64 adds.  Binomial, 2560 leaves of three or four
-// variables, K = 10, 1000 samples (102 MB of residuals): 72 us (207 with a thread per entry);
-// Bernoulli, 100 samples: 12 us (20).
+// variables, K = 10, 1000 samples (102 MB of residuals): 65 us (207 with a thread per entry);
+// Bernoulli, 100 samples: 11 us (20).
 // KM: the least of 8, 16, 32, 64 that holds K.
 constexpr int SHORT_SAMPLES = 128;
 template <int KM>

@@ -415,11 +415,7 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
         rec[0] = p.ein_left[e];
         rec[1] = p.ein_right[e];
         rec[2] = p.ein_out[e];
-        rec[3] = p.ein_reg[e];
-        rec[4] = p.ein_woff[e];
-        rec[5] = p.ein_voff[e];
-        rec[6] = p.ein_vstr[e];
-        rec[7] = p.ein_gsrc[e];
+        rec[3] = p.ein_woff[e];
     }
     // ---- posterior blocks of the leaves (element-wise statistics kernels only: no categorical leaves, scopes below the 512
     // pairs from which the matrix-pipe kernel may be chosen)
