@@ -1,5 +1,5 @@
-"""GPU parity of the einsum kernels with specialised waves over every K they are instantiated for (multiples of 8:
-bottom-up to 48, top-down to 40; K = 48 takes the new kernel one way and the 16x16x4 kernel the other), with batches
+"""GPU parity of the einsum kernels with specialised waves over the multiples of 8 (bottom-up float32 for K = 8, 24 and
+48, split operands for 32 and 40, many small workgroups for 16; top-down to 40, the 16x16x4 kernel for 48), with batches
 that span several chunks of 128 samples and a ragged last one, with statistics added to (two E-steps in a row),
 overwritten (E-step after an M-step) and mixing weights in play (regions with several partitions); and of the
 top-down kernels that add up the posterior blocks of a region's only parent themselves (random binary trees), with
@@ -23,7 +23,7 @@ CASES = [
     (dict(kind="pd", H=6, W=6, deltas=[2]), 32, 1, GAUSSIAN, 77),          # one 32-column tile, nothing left over
     (dict(kind="rat", D=16, depth=2, R=2), 40, 2, GAUSSIAN, 1),            # a single sample
     (dict(kind="pd", H=6, W=4, deltas=[2]), 40, 1, BERNOULLI, 260),        # K = 40 with chunks
-    (dict(kind="rat", D=24, depth=2, R=3), 48, 1, GAUSSIAN, 130),          # new kernel bottom-up, 16x16x4 kernel top-down
+    (dict(kind="rat", D=24, depth=2, R=3), 48, 1, GAUSSIAN, 130),          # specialised waves bottom-up, 16x16x4 kernel top-down
     # few items and many chunks: the chunks of an item side by side, statistics blocks summed by a second launch
     (dict(kind="rat", D=16, depth=2, R=2), 16, 1, BERNOULLI, 1100),        # nine shares of one chunk each
     (dict(kind="pd", H=6, W=6, deltas=[2]), 24, 1, GAUSSIAN, 520),         # three shares of two, two and one chunk
