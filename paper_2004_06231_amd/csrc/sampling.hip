@@ -444,10 +444,10 @@ static bool sample_layer_is_sparse(int count, int reach, int B) {
 
 // One launch for all layers, or one per layer?  In one launch the regions of a layer that do not find a wave of their own
 // wait for each other: a step of a wave takes 3.4 us, more where the rows of W come from memory (K^3).  A launch per layer
-// costs 3.2 us (the call from the host; the kernel 2.4) and the walk over the K^2 products, then the waves' time
+// costs 3.4 us (the call from the host; the kernel 2.4) and the walk over the K^2 products, then the waves' time
 // where they are more than the chip holds.  The constants are fitted to 1812 cases, launched from the host: 1 to 1000
 // samples, K 4 to 64, trees of depth 2 to 9 with 1 to 40 replicas, images; on average the form that is chosen takes 0.7 %
-// longer than the faster one (replayed from a graph 1.9 %: there a launch costs less).  One launch against a launch per layer: 32x32x3 images,
+// longer than the faster one (replayed from a graph 2.5 %: there a launch costs less).  One launch against a launch per layer: 32x32x3 images,
 // 128 samples, K = 40: 29 and 59 us, K = 4: 30 and 27; 1024 variables, depth 9, 16 samples, K = 4: 133 and 33 us, K = 40: 165
 // and 93.
 static bool sample_in_one_launch(int num_layers, const int32_t* layer_ptr, const int32_t* reach, int num_nodes,
@@ -463,7 +463,7 @@ static bool sample_in_one_launch(int num_layers, const int32_t* layer_ptr, const
         looked_at += sample_layer_is_sparse(count, reach[l], d.B) ? reach[l] : count;
     }
     const double one = (3.4 + 2e-5 * K3) * (double)steps;
-    const double each = num_layers * (3.2 + 3e-3 * K * K) +
+    const double each = num_layers * (3.4 + 3e-3 * K * K) +
                         d.B * ((5.5e-5 + 1.2e-10 * K3 * K) * (double)looked_at + (3e-4 + 2e-8 * K3) * (double)choices);
     return one < each;
 }
