@@ -194,7 +194,7 @@ __device__ __forceinline__ void update_categorical_body(int block, float* __rest
     const bool in = slot < pairs && pair < d.D * d.R;
     const int var = in ? pair / d.R : 0, r = in ? pair - var * d.R : 0;
     const size_t o = ((size_t)var * d.R + r) * d.K + k;
-    const float tot = stats[tot_off + o], den = stats[den_off + o];
+    const float tot = in ? stats[tot_off + o] : 0.f, den = in ? stats[den_off + o] : 0.f;
     constexpr int U = 8;                             // values in flight per thread
     if (d.P <= U) {                                  // a thread has a whole column: nothing to meet for
         for (int c = 0; in && c < d.C; ++c) {
