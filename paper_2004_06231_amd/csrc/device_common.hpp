@@ -50,6 +50,47 @@ __device__ __forceinline__ int xcd_contiguous_block() {
     return x * q + min(x, r) + (blockIdx.x >> 3);
 }
 
+// Four registers of four lane groups transposed: register r of group g becomes register g of group r.
+__device__ __forceinline__ void transpose_groups(float (&r)[4]) {
+    auto swap32 = [](float& a, float& b) {
+        const auto v = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+        const uint32_t v0 = v[0], v1 = v[1];
+        a = __builtin_bit_cast(float, v0);
+        b = __builtin_bit_cast(float, v1);
+    };
+    auto swap16 = [](float& a, float& b) {
+        const auto v = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+        const uint32_t v0 = v[0], v1 = v[1];
+        a = __builtin_bit_cast(float, v0);
+        b = __builtin_bit_cast(float, v1);
+    };
+    swap32(r[0], r[2]);
+    swap32(r[1], r[3]);
+    swap16(r[0], r[1]);
+    swap16(r[2], r[3]);
+}
+
+// Entries 4 p .. 4 p + 3 of a row of K entries, p < KQ = ceil(K / 4) (those beyond K hold anything).  QUADS: K is 4 KQ.
+// Otherwise a row's last piece starts at K - 4 and is shifted into place (K below 4: entry by entry).
+template <int KQ, bool QUADS>
+__device__ __forceinline__ void load_piece(const float* row, int p, int K, float (&v)[4]) {
+    if constexpr (QUADS) {
+        const float4 f = *reinterpret_cast<const float4*>(row + 4 * p);
+        v[0] = f.x, v[1] = f.y, v[2] = f.z, v[3] = f.w;
+    } else if constexpr (KQ == 1) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = row[min(c, K - 1)];
+    } else {
+        const int start = min(4 * p, K - 4), d = 4 * p - start;
+        const floatx4 f = *reinterpret_cast<const floatx4u*>(row + start);
+        const float a0 = (d & 2) ? f[2] : f[0], a1 = (d & 2) ? f[3] : f[1], a2 = f[2], a3 = f[3];
+        v[0] = (d & 1) ? a1 : a0;
+        v[1] = (d & 1) ? a2 : a1;                         // (d = 3 leaves one entry, d = 2 two, d = 1 three)
+        v[2] = (d & 1) ? a3 : a2;
+        v[3] = a3;
+    }
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -66,10 +107,14 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 __device__ __forceinline__ float bf16_low(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float bf16_high(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 __device__ __forceinline__ void split_bf16x3(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    // (the packed pair is made opaque: the compiler would convert each half again, alone, to subtract it, and a conversion
+    // takes twice as long as a shift or mask)
     hi = pack_bf16(a, b);
+    asm("" : "+v"(hi));
     a -= bf16_low(hi);
     b -= bf16_high(hi);
     mid = pack_bf16(a, b);
+    asm("" : "+v"(mid));
     a -= bf16_low(mid);
     b -= bf16_high(mid);
     lo = pack_bf16(a, b);

@@ -205,7 +205,7 @@ __global__ __launch_bounds__(512, KQ >= 14 ? 2 : 4) void k_einsum_forward(const 
     }
 }
 
-// ------------------------------------------------------------------ einsum layer, forward, K = 8, 24 and 48
+// ------------------------------------------------------------------ einsum layer, forward, K = 24 and 48
 // The same factorisation on v_mfma_f32_32x32x2_f32 (the fp32 shape that issues at the full rate of the matrix
 // pipe), as one workgroup per compute unit that walks a run of work units.  A tile of the product T has 32 rows
 // (k, i) and 32 samples; with i fastest, groups of 8 rows stay inside one k, and a lane holds four consecutive i of
@@ -725,154 +725,151 @@ __global__ __launch_bounds__(512, 1) void k_einsum_forward_x(const int32_t* __re
     }
 }
 
-// ------------------------------------------------------------------ einsum layer, forward, K from 9 to 16
-// Small items are bound by the chain of requests in front of their arithmetic, so many small workgroups per compute unit
-// take them: four waves per (item, group of chunks), a chunk being 128 samples, 32 per wave.  The whole item's weights are
-// split into LDS once (at most 24 KB); a lane loads the rows of its own samples straight from memory, so nothing but the
-// weights is shared.  Same tiles as above with row m = 4 (k % 4) + i % 4: lane group kg holds output k = 4 q + kg of group
-// q, its four accumulators four consecutive left entries, so a sum of Eq. 4 is complete in one lane.
-// K = 10: 15 / 10 / 7 / 5.7 us for 1280 / 640 / 320 / 160 items and 100 samples (19 / 11.5 / 8 / 5.4 with the float32 kernel),
-// 79 / 44 / 27 / 17 / 11 us for 1280 .. 80 items and 1000 samples (106 / 59 / 33 / 21 / 16).  Registers must not spill: with
-// 128 instead of 168 of them and 28 spilled every launch took 4 us longer.
-struct FwdSmallLayout {
-    using X = X6<2>;
-    static constexpr int KP = X::KP, NT = X::NT;
-    static constexpr int LDS_BYTES = NT * NT * X::BYTES;  // NT groups of four outputs x NT tiles
-    static constexpr int NI = KP * KP * 2;                // octets of the weights
-    static constexpr int NL = (NI + 255) / 256;
+// ------------------------------------------------------------------ einsum layer, forward, K up to 16
+// A whole item fits a workgroup, and its launches are bound by their chain of requests and by the instructions that a compute
+// unit fetches once, so this kernel is kept short: float32 operands on v_mfma_f32_16x16x4_f32 (nothing to split), a wave
+// per 16 samples, all weights of the item in LDS as they are in memory.  A tile of the product T has the rows (four outputs
+// k) x (four left entries i); row m = 4 (k % 4) + i % 4, so lane group g holds output 4 kt + g and its accumulators four left
+// entries: the sum of Eq. 4 is in-lane.  The contraction runs over j = KQ g + s: lane group g needs KQ consecutive entries
+// of its sample's row, which are one load, and of the rows of W, which are one LDS read.
+// A workgroup walks `cpg` chunks of 64 samples and takes all outputs or, where there are few items, a share of them.
+// Microseconds of a launch, against a kernel with operands split into bfloat16 parts (14 KB of instructions) and, for one
+// sample or K = 4, the kernel above: K = 10, 1000 samples, 1280 / 640 / 320 / 160 / 80 / 40 / 20 items: 77.6 / 43.8 / 28.4 / 15.5 /
+// 10.0 / 7.4 / 6.4 (84 / 47.5 / 27 / 17.5 / 11 / 8 / 6.4); K = 16, 64 samples, 48 / 100 / 120 / 80 / 40 items: 4.6 / 5.4 / 5.4 / 5.4 /
+// 4.6 (5.3 / 6.8 / 7.0 / 6.6 / 5.1); one sample: 3.6 to 4.0 (4.2); K = 4, 64 samples, 2 and 1 items: 3.2 and 2.6 (3.9 and 3.8).
+template <int KQ>
+struct FwdCompact {
+    static constexpr int KP = 4 * KQ;
+    static constexpr int SI = 20;                         // row stride of W in LDS; with S 16 modulo 32 the reads of eight lanes
+    static constexpr int S = KP * SI + (KP * SI % 32 == 16 ? 0 : 16);   // .. (two k, four i) hit different banks
 };
 
-__global__ __launch_bounds__(256, 3) void k_einsum_forward_small(const int32_t* __restrict__ e_rec, const float* __restrict__ params,
-                                                               float* __restrict__ A, double* __restrict__ Off,
-                                                               float* __restrict__ amax, int item0, int ngrp, int cpg, int nsplit,
-                                                               int B, int K, int kout) {
-    using LY = FwdSmallLayout;
-    using X = LY::X;
-    constexpr int K8 = 2;
-    constexpr int KP = LY::KP, NT = LY::NT, NL = LY::NL;
-    extern __shared__ __attribute__((aligned(16))) char lds_c[];
-    uint32x4* wl = reinterpret_cast<uint32x4*>(lds_c);
+template <int KQ, bool QUADS>
+__global__ __launch_bounds__(256, 4) void k_einsum_forward_compact(const int32_t* __restrict__ e_rec, const float* __restrict__ params,
+                                                                 float* __restrict__ A, double* __restrict__ Off,
+                                                                 float* __restrict__ amax, int item0, int ngrp, int cpg,
+                                                                 int nsplit, int B, int K_) {
+    using LY = FwdCompact<KQ>;
+    constexpr int KP = LY::KP, SI = LY::SI, S = LY::S;
+    __shared__ __attribute__((aligned(16))) float wl[KP * S];
+    const int K = QUADS ? KP : K_;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c16 = lane & 15, kg = lane >> 4;
+    const int c16 = lane & 15, g = lane >> 4;
     const int vb = xcd_contiguous_block();
     const int part = vb % nsplit, grp = (vb / nsplit) % ngrp, li = vb / (nsplit * ngrp);
-    const int NG = (kout + 3) >> 2, q0 = part * NG / nsplit, q1 = (part + 1) * NG / nsplit;   // groups of four outputs
-    const int ni = (q1 - q0) * 4 * KP * K8;           // octets of their weights
-    const int32_t* rec = e_rec + li * EIN_REC_INTS;
+    const int q0 = part * KQ / nsplit, q1 = (part + 1) * KQ / nsplit;      // groups of four outputs
+    const int32_t* rec = e_rec + (size_t)li * EIN_REC_INTS;
     const int left = rec[0], right = rec[1], out = rec[2];
-    const int nchunks = (B + 127) >> 7, c0 = grp * cpg, c1 = min(c0 + cpg, nchunks);
-    const float* W = params + rec[3];
+    const float* W = params + rec[3] + (size_t)4 * q0 * K * K;
+    const int npiece = min(4 * (q1 - q0), K - 4 * q0) * K * KQ;
+    const size_t blk = (size_t)B * K;
 
-    floatx4 wv[NL][2];
+    // ---- the weights: pieces of rows (k, i), consecutive threads consecutive pieces
+    constexpr int NW = (KP * KP * KQ + 255) / 256;
+    float w[NW][4];
 #pragma unroll
-    for (int x = 0; x < NL; ++x) {
-        if (256 * x >= ni) break;
-        const int f = min(tid + 256 * x, ni - 1);
-        const int o = f % K8, i = (f / K8) % KP, k = 4 * q0 + f / (K8 * KP);
-        const float* p = W + ((size_t)min(k, kout - 1) * K + min(i, K - 1)) * K;
-        p += min(8 * o, K - 8);                       // (the last octet of a row starts at K - 8, as above)
-        wv[x][0] = *reinterpret_cast<const floatx4u*>(p);
-        wv[x][1] = *reinterpret_cast<const floatx4u*>(p + 4);
+    for (int x = 0; x < NW; ++x) {
+        if (256 * x >= npiece) break;
+        const int f = min(tid + 256 * x, npiece - 1);
+        load_piece<KQ, QUADS>(W + (size_t)(f / KQ) * K, f % KQ, K, w[x]);
     }
-    // rows of this lane's samples (two sets of 16): one octet of R, all of L
-    float rr[2][8], rl[2][KP];
-    double off_children[2];
+    // ---- rows of this lane's sample: KQ right entries from KQ g on, all left entries
+    float er[KQ], lp[KQ][4];
+    double off_children = 0.0;
     auto fetch_rows = [&](int chunk) {
+        const int b = min(chunk * 64 + 16 * wave + c16, B - 1);
+        const float* Rp = A + (size_t)right * blk + (size_t)b * K;
+        const float* Lp = A + (size_t)left * blk + (size_t)b * K;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int b = min(chunk * 128 + 32 * wave + 16 * s + c16, B - 1);
-            const float* Lp = A + ((size_t)left * B + b) * K;
-            const float* Rp = A + ((size_t)right * B + b) * K;
-            const int st = (kg & 1) ? K - 8 : 0;
-            const floatx4 r0 = *reinterpret_cast<const floatx4u*>(Rp + st), r1 = *reinterpret_cast<const floatx4u*>(Rp + st + 4);
-            const floatx4 l0 = *reinterpret_cast<const floatx4u*>(Lp), l1 = *reinterpret_cast<const floatx4u*>(Lp + 4);
-            // (the left entries of the tiles 2 and 3 are the row's last eight, those below 8 among them: their weights
-            // are zeros there)
-            const floatx4 l2 = *reinterpret_cast<const floatx4u*>(Lp + K - 8), l3 = *reinterpret_cast<const floatx4u*>(Lp + K - 4);
+        for (int s = 0; s < KQ; ++s) er[s] = Rp[QUADS ? KQ * g + s : min(KQ * g + s, K - 1)];
+#pragma unroll
+        for (int p = 0; p < KQ; ++p) load_piece<KQ, QUADS>(Lp, p, K, lp[p]);
+        off_children = Off[(size_t)left * B + b] + Off[(size_t)right * B + b];
+    };
+    const int c0 = grp * cpg, c1 = min(c0 + cpg, (B + 63) >> 6);
+    fetch_rows(c0);
+    if constexpr (!QUADS) {                               // entries that do not exist are zeros
+        for (int f = tid; f < KP * S / 4; f += 256) *reinterpret_cast<floatx4*>(wl + 4 * f) = floatx4{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();
+    }
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+        const int f = tid + 256 * x, r = f / KQ, p = f % KQ, k = r / K, i = r - k * K;
+        if (f < npiece) {
+            float* dst = wl + (4 * q0 + k) * S + i * SI + 4 * p;
+            if constexpr (QUADS) {
+                *reinterpret_cast<floatx4*>(dst) = floatx4{w[x][0], w[x][1], w[x][2], w[x][3]};
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (4 * p + c < K) dst[c] = w[x][c];
+            }
+        }
+    }
+    __syncthreads();
+    const float* wr = wl + (c16 >> 2) * S + (c16 & 3) * SI + KQ * g;
+    for (int chunk = c0; chunk < c1; ++chunk) {
+        const int b = chunk * 64 + 16 * wave + c16;
+        if (b - c16 >= B) break;                          // (whole waves: no barrier follows)
+        float xr = -INFINITY, xl = -INFINITY, el[KP];
+#pragma unroll
+        for (int s = 0; s < KQ; ++s) {
+            if (!QUADS && KQ * g + s >= K) er[s] = -INFINITY;
+            xr = fmaxf(xr, er[s]);
+        }
+        xr = fmaxf(xr, __shfl_xor(xr, 16, 64));
+        xr = fmaxf(xr, __shfl_xor(xr, 32, 64));
+#pragma unroll
+        for (int p = 0; p < KQ; ++p)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                rr[s][c] = r0[c]; rr[s][4 + c] = r1[c];
-                rl[s][c] = l0[c]; rl[s][4 + c] = l1[c]; rl[s][8 + c] = l2[c]; rl[s][12 + c] = l3[c];
+                el[4 * p + c] = QUADS || 4 * p + c < K ? lp[p][c] : -INFINITY;
+                xl = fmaxf(xl, el[4 * p + c]);
             }
-            off_children[s] = Off[(size_t)left * B + b] + Off[(size_t)right * B + b];
+        if (xr == -INFINITY) xr = 0.f;                    // an all-zero input vector: exp(-inf) = 0, no NaN
+        if (xl == -INFINITY) xl = 0.f;
+#pragma unroll
+        for (int s = 0; s < KQ; ++s) er[s] = __expf(er[s] - xr);
+#pragma unroll
+        for (int i = 0; i < KP; ++i) el[i] = __expf(el[i] - xl);
+        if (part == 0 && g == 0 && b < B) {
+            Off[(size_t)out * B + b] = off_children + (double)xl + (double)xr;
+            amax[(size_t)(item0 + li) * 2 * B + b] = xl;
+            amax[((size_t)(item0 + li) * 2 + 1) * B + b] = xr;
         }
-    };
-    fetch_rows(c0);
+        float erc[KQ];
 #pragma unroll
-    for (int x = 0; x < NL; ++x) {
-        const int f = tid + 256 * x;
-        const int o = f % K8, i = (f / K8) % KP, kl = f / (K8 * KP), k = 4 * q0 + kl;
-        if (f < ni) {
-            float v[8];
-            const bool row = k < kout && i < K;
+        for (int s = 0; s < KQ; ++s) erc[s] = er[s];
+        if (chunk + 1 < c1) fetch_rows(chunk + 1);
+        float sk[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c = 0; c < 8; ++c) v[c] = row && (o == 0 || c >= 16 - K) ? wv[x][c >> 2][c & 3] * X6_SCALE : 0.f;
-            uint32x4 part[3];
-            split_octet(v, part[0], part[1], part[2]);
-            // row slot of the tiles: left entry i < 8 in slot i, i >= 8 in slot 8 + (i - (K - 8)); the slots in between have
-            // no left entry of their own and get the zeros of the rows i >= K
-            const int slot = i < 8 ? i : i < K ? i + 16 - K : 8 + i - K;
-            uint32x4* d = wl + ((kl >> 2) * NT + (slot >> 2)) * X::UNITS;
+        for (int kt = 0; kt < KQ; ++kt) {
+            if (kt >= q0 && kt < q1) {
+                floatx4 acc[KQ];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) d[x6_unit<K8>(p, o, 4 * (kl & 3) + (slot & 3))] = part[p];
-        }
-    }
-    int unit[X::NR];
+                for (int it = 0; it < KQ; ++it) acc[it] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int a = 0; a < X::NR; ++a) unit[a] = x6_row_unit<K8>(a, kg, c16);
-    __syncthreads();
-    for (int chunk = c0; chunk < c1; ++chunk) {
-        if (chunk > c0) fetch_rows(chunk);            // (the other workgroups of the compute unit hide the wait)
-        uint32x4 er[2][X::NR];
-        float el[2][KP];
+                for (int s = 0; s < KQ; ++s)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            float xr = rr[s][0], xl = rl[s][0];
+                    for (int it = 0; it < KQ; ++it)
+                        acc[it] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[4 * kt * S + 4 * it * SI + s], erc[s], acc[it], 0, 0, 0);
 #pragma unroll
-            for (int c = 1; c < 8; ++c) xr = fmaxf(xr, rr[s][c]);
-            xr = fmaxf(xr, __shfl_xor(xr, 16, 64));
+                for (int it = 0; it < KQ; ++it)
 #pragma unroll
-            for (int c = 1; c < KP; ++c) xl = fmaxf(xl, rl[s][c]);
-            if (xr == -INFINITY) xr = 0.f;            // an all-zero input vector: exp(-inf) = 0, no NaN
-            if (xl == -INFINITY) xl = 0.f;
-            float e8[8];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) e8[c] = __expf(rr[s][c] - xr) * X6_SCALE;
-            x6_sample_operand<K8>(kg, [&](int, float* v) {
-#pragma unroll
-                for (int c = 0; c < 8; ++c) v[c] = e8[c];
-            }, er[s]);
-#pragma unroll
-            for (int c = 0; c < KP; ++c) el[s][c] = __expf(rl[s][c] - xl);
-            const int b = chunk * 128 + 32 * wave + 16 * s + c16;
-            if (kg == 0 && b < B && part == 0) {
-                Off[(size_t)out * B + b] = off_children[s] + (double)xl + (double)xr;
-                amax[((size_t)(item0 + li) * 2) * B + b] = xl;
-                amax[((size_t)(item0 + li) * 2 + 1) * B + b] = xr;
+                    for (int c = 0; c < 4; ++c) sk[kt] = fmaf(acc[it][c], el[4 * it + c], sk[kt]);
             }
         }
+        // lane group g holds the outputs k = 4 kt + g
 #pragma unroll
-        for (int ql = 0; ql < NT; ++ql) {
-            if (q0 + ql >= q1) break;
-            float sk[2] = {0.f, 0.f};
+        for (int kt = 0; kt < KQ; ++kt) sk[kt] = __logf(sk[kt]);
+        float* row = A + (size_t)out * blk + (size_t)min(b, B - 1) * K;
+        if constexpr (QUADS) {
+            transpose_groups(sk);                         // .. now 4 g .. 4 g + 3
+            if (b < B && g >= q0 && g < q1) *reinterpret_cast<floatx4*>(row + 4 * g) = floatx4{sk[0], sk[1], sk[2], sk[3]};
+        } else {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                uint32x4 a[X::NR];
-#pragma unroll
-                for (int z = 0; z < X::NR; ++z) a[z] = wl[(ql * NT + t) * X::UNITS + unit[z]];
-                floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-                x6_tile<K8, 2>(a, er, acc);
-#pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) sk[s] = fmaf(acc[s][c], el[s][4 * t + c], sk[s]);
-            }
-            const int k = 4 * (q0 + ql) + kg;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const int b = chunk * 128 + 32 * wave + 16 * s + c16;
-                if (b < B && k < kout) A[((size_t)out * B + b) * K + k] = __logf(sk[s] * X6_UNSCALE);
-            }
+            for (int kt = 0; kt < KQ; ++kt)
+                if (b < B && kt >= q0 && kt < q1 && 4 * kt + g < K) row[4 * kt + g] = sk[kt];
         }
     }
 }
@@ -1158,39 +1155,39 @@ static void launch_einsum_forward_direct(const DevTables& t, int first, int coun
                        t.ein_rec + (size_t)first * EIN_REC_INTS, params, A, Off, amax, first, nchunks, d.B, d.K, kout);
 }
 
-static void launch_einsum_forward_small(const DevTables& t, int first, int count, int kout, const float* params, float* A,
-                                        double* Off, float* amax, const Dims& d, hipStream_t s) {
-    // chunks of an item share its weights as long as four workgroups per compute unit remain
-    const int nchunks = (d.B + 127) / 128, want = (4 * EINET_NUM_CUS + count - 1) / count;
+template <int KQ>
+static void launch_einsum_forward_compact(const DevTables& t, int first, int count, const float* params, float* A, double* Off,
+                                          float* amax, const Dims& d, hipStream_t s) {
+    // chunks of an item share its weights as long as eight workgroups per compute unit remain
+    const int nchunks = (d.B + 63) / 64, want = (8 * EINET_NUM_CUS + count - 1) / count;
     const int cpg = (nchunks + want - 1) / want, ngrp = (nchunks + cpg - 1) / cpg;
     // few items: the groups of four outputs of an item side by side
-    const int groups = (kout + 3) / 4;
-    int nsplit = 2 * EINET_NUM_CUS / (count * ngrp);
-    nsplit = nsplit < 1 ? 1 : nsplit > groups ? groups : nsplit;
-    hipLaunchKernelGGL(k_einsum_forward_small, dim3(count * ngrp * nsplit), dim3(256), FwdSmallLayout::LDS_BYTES, s,
-                       t.ein_rec + (size_t)first * EIN_REC_INTS, params, A, Off, amax, first, ngrp, cpg, nsplit, d.B, d.K, kout);
+    int nsplit = EINET_NUM_CUS / (count * ngrp);
+    nsplit = nsplit < 1 ? 1 : nsplit > KQ ? KQ : nsplit;
+    const int32_t* rec = t.ein_rec + (size_t)first * EIN_REC_INTS;
+    if (d.K == 4 * KQ)
+        hipLaunchKernelGGL((k_einsum_forward_compact<KQ, true>), dim3(count * ngrp * nsplit), dim3(256), 0, s, rec, params, A,
+                           Off, amax, first, ngrp, cpg, nsplit, d.B, d.K);
+    else
+        hipLaunchKernelGGL((k_einsum_forward_compact<KQ, false>), dim3(count * ngrp * nsplit), dim3(256), 0, s, rec, params, A,
+                           Off, amax, first, ngrp, cpg, nsplit, d.B, d.K);
 }
 
 // Which kernel a layer takes.  Microseconds of a log-density of a tree of depth 2 (leaf layer, one layer of `count` items,
 // root: about 8 us besides the layer for few items, 2 to 3 times the layer's for many), measured for K 8 to 48, 2 to 1280
 // items, 1 to 1000 samples.  PLAIN: the float32 kernel with a workgroup per (item, four outputs), which has no operands to
-// split and walks the chunks of 128 samples one after the other.  WAVES: the float32 kernel with specialised waves.
-enum FwdKernel { FWD_PLAIN, FWD_WAVES, FWD_SMALL, FWD_DIRECT, FWD_X };
+// split and walks the chunks of 128 samples one after the other.  WAVES: the float32 kernel with specialised waves.  COMPACT:
+// the short float32 kernel for whole items.
+enum FwdKernel { FWD_PLAIN, FWD_WAVES, FWD_COMPACT, FWD_DIRECT, FWD_X };
 static FwdKernel einsum_forward_kernel(int count, int kout, const Dims& d) {
     const int K = d.K, B = d.B;
     const bool quads = (K & 3) == 0;                  // rows of 16-byte groups
     const int64_t units = (int64_t)count * ((B + 127) / 128) * ((kout + 3) / 4);
-    // K = 8, 20 items, 1000 samples: plain 25, waves 18; 80 items, 256 samples: 23.8, 23.5; 1280 items: 180, 183
-    if (K == 8 && kout == K) return B > 128 && count <= 256 ? FWD_WAVES : FWD_PLAIN;
+    // (one output per item would leave three of four rows of COMPACT's tiles empty; only items below the root have one)
+    if (K <= 16) return kout == K ? FWD_COMPACT : FWD_PLAIN;
     // K = 48, 2 items, 1000 samples: plain 63, waves 19; 320 items, 16 samples: 171, 148; 64 samples: 155, 157
     if (K == 48 && kout == K) return B > 32 && B <= 64 ? FWD_PLAIN : FWD_WAVES;
-    if (K <= 8 || K > 40) return FWD_PLAIN;
-    if (K <= 16) {
-        // K = 16, 320 items: 16 samples plain 50.3, small 53.4; 128 samples 57.0, 55.7; 1000 samples 107, 87
-        if (quads) return B <= 64 ? FWD_PLAIN : FWD_SMALL;
-        // K = 9, 20 items: 16 samples plain 14.8, small 14.2; 320 items, 64 samples 59.5, 61.2; 128 samples 69.8, 69.4
-        return B <= 64 && count >= 64 && (B > 16 || count >= 192) && (K <= 12 || count <= 512) ? FWD_PLAIN : FWD_SMALL;
-    }
+    if (K > 40) return FWD_PLAIN;
     if (K <= 20) {
         // three octets for 17 to 20 entries: the split pays for few items only.  K = 18, 20 items, 16 samples: plain 18.3,
         // direct 16.0; 500 samples 27.6, 23.1; 80 items, 1000 samples: 63.4, persistent 60.5; 1280 items, 1000 samples: 637,
@@ -1219,9 +1216,13 @@ void launch_einsum_forward(const DevTables& t, int first, int count, bool full_k
     // k_root_forward takes)
     switch (einsum_forward_kernel(count, kout, d)) {
 #define EINET_CASE(J, F) case J: F<J>(t, first, count, kout, params, A, Off, amax, d, s); return;
-    case FWD_SMALL:
-        launch_einsum_forward_small(t, first, count, kout, params, A, Off, amax, d, s);
+#undef EINET_CASE
+    case FWD_COMPACT:
+#define EINET_CASE(J) case J: launch_einsum_forward_compact<J>(t, first, count, params, A, Off, amax, d, s); return;
+        switch ((d.K + 3) / 4) { EINET_CASE(1) EINET_CASE(2) EINET_CASE(3) EINET_CASE(4) }
         return;
+#undef EINET_CASE
+#define EINET_CASE(J, F) case J: F<J>(t, first, count, kout, params, A, Off, amax, d, s); return;
     case FWD_DIRECT:
         switch (K8) { EINET_CASE(3, launch_einsum_forward_direct) EINET_CASE(4, launch_einsum_forward_direct) }
         return;
@@ -1233,7 +1234,7 @@ void launch_einsum_forward(const DevTables& t, int first, int count, bool full_k
 #undef EINET_CASE
     case FWD_WAVES:
 #define EINET_CASE(J) case J: launch_einsum_forward_s<J>(t, first, count, params, A, Off, amax, d, s); return;
-        switch (K8) { EINET_CASE(1) EINET_CASE(3) EINET_CASE(6) }
+        switch (K8) { EINET_CASE(3) EINET_CASE(6) }
         return;
 #undef EINET_CASE
     case FWD_PLAIN:
