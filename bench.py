@@ -58,10 +58,13 @@ def algorithmic_work(st, K, C, R, T, TD, B, D):
     top = [ko for ko in kout if ko == 1] if K != 1 else []
     w["einsum_forward"] = (sum(2.0 * B * ko * K * K for ko in inner),
                            sum(4.0 * ko * K * K + 4.0 * B * (2 * K + ko) for ko in inner))
-    # backward: W read, Nw written (after an M-step the statistics start from zero, so the benchmark loop
-    # never has to read them back); L, R, A_out, G_out read; two posterior blocks written
-    w["einsum_backward"] = (sum(4.0 * B * ko * K * K for ko in inner),
-                            sum(8.0 * ko * K * K + 4.0 * B * (4 * K + 2 * ko) for ko in inner))
+    # posteriors: W, L, R, A_out and G_out read; two posterior blocks written
+    w["einsum_backward"] = (sum(2.0 * B * ko * K * K for ko in inner),
+                            sum(4.0 * ko * K * K + 4.0 * B * (4 * K + 2 * ko) for ko in inner))
+    # weight statistics: W, L, R, A_out and G_out read; Nw written (after an M-step the statistics start from zero, so
+    # the benchmark loop never has to read them back).  Small layers have them in the same launch as the posteriors.
+    w["einsum_statistics"] = (sum(2.0 * B * ko * K * K for ko in inner),
+                              sum(8.0 * ko * K * K + 4.0 * B * (2 * K + 2 * ko) for ko in inner))
     w["root_forward"] = (sum(2.0 * B * K * K for _ in top),
                          sum(4.0 * K * K + 4.0 * B * (2 * K + 1) for _ in top) + 4.0 * B)
     w["root_backward"] = (sum(4.0 * B * K * K for _ in top),
@@ -77,7 +80,7 @@ def algorithmic_work(st, K, C, R, T, TD, B, D):
     return w
 
 
-def profiled_pass(m, em_step, steps, work):
+def profiled_pass(m, em_step, steps, work, B):
     """Runs `steps` EM steps with a HIP event pair around every launch (recorded on the stream the kernels run on;
     a separate pass, since recording costs host time).  Returns the per-class table, the roofline of the class with
     the largest device time, and the launches one by one."""
@@ -89,6 +92,10 @@ def profiled_pass(m, em_step, steps, work):
     prof = m.profile_read()
     launch_list = m.profile_launches()
     m.profile_enable(False)
+    if prof["einsum_statistics"][1] == 0:      # statistics together with the posteriors: the rows are read once, as is W
+        work = dict(work)
+        (fp, bp), (fs, _) = work["einsum_backward"], work["einsum_statistics"]
+        work["einsum_backward"] = (fp + fs, bp + 2.0 * fs / B)        # 4 bytes of Nw per 2 B flop
     kernels = {}
     for name, (ms, launches) in prof.items():
         if launches == 0:
@@ -153,7 +160,7 @@ def time_config(i, steps, warmup):
         res[name + "_ms"] = round(1e3 * dt, 4)
     TD = 3 if fam == P.GAUSSIAN else 2
     work = algorithmic_work(st, K, C, R, T, TD, B, D)
-    kernels, roof, _ = profiled_pass(m, lambda: (m.em_accumulate(x, None, logp), m.em_update(**kw)), steps, work)
+    kernels, roof, _ = profiled_pass(m, lambda: (m.em_accumulate(x, None, logp), m.em_update(**kw)), steps, work, B)
     res["roofline"] = {k: roof[k] for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "avg_launch_us",
                                             "launches_per_step")}
     res["kernels_us_per_step"] = {k: v["us_per_step"] for k, v in kernels.items()}
@@ -252,7 +259,7 @@ def main():
     assert bool(torch.isfinite(x_out).all())
 
     work = algorithmic_work(st, K, C, R, T, TD, B, D)
-    kernels, roof, launch_list = profiled_pass(m, em_step, args.steps, work)
+    kernels, roof, launch_list = profiled_pass(m, em_step, args.steps, work, B)
     dom = roof["kernel"]
     roof.update(traffic=measured_traffic(wl, dom) if B == cfg["B"] else None,
                 traffic_unit="HBM bytes per launch (rocprofv3 counters, profiles/hbm_traffic_cfg%d.md)" % wl,
@@ -264,6 +271,7 @@ def main():
     # root's mixture, and root_backward)
     ein = [l for l in launch_list if l[0] in ("einsum_forward", "einsum_backward", "root_forward", "root_backward")]
     per_step = len(ein) // args.steps
+    fused = not any(l[0] == "einsum_statistics" for l in launch_list)
     layers = []
     if per_step * args.steps == len(ein):
         for pos in range(per_step):
@@ -271,9 +279,10 @@ def main():
             outs, parts = tag >> 24, tag & 0xFFFFFF
             us = 1e3 * sum(ein[s_ * per_step + pos][1] for s_ in range(args.steps)) / args.steps
             fwd = name.endswith("_forward")
-            fl = (2.0 if fwd else 4.0) * B * K * K * outs
-            # W once (and Nw written once top-down); rows of the children, of the region and its posterior; outputs
-            by = (4.0 if fwd else 8.0) * K * K * outs + 4.0 * B * ((2 * K * parts + outs) if fwd else (4 * K * parts + 2 * outs))
+            stats = name == "root_backward" or (name == "einsum_backward" and fused)
+            fl = (4.0 if stats else 2.0) * B * K * K * outs
+            # W once (and Nw written once with the statistics); rows of the children, of the region and its posterior; outputs
+            by = (8.0 if stats else 4.0) * K * K * outs + 4.0 * B * ((2 * K * parts + outs) if fwd else (4 * K * parts + 2 * outs))
             layers.append(dict(kernel=name, outputs=int(outs), partitions=int(parts), us=round(us, 2),
                                tflops=round(fl / us / 1e6, 2), frac=round(fl / us / 1e6 / PEAK_MFMA_FP32_TFLOPS, 4),
                                gbs=round(by / us / 1e3, 1), frac_hbm=round(by / us / 1e3 / PEAK_HBM_GBS, 4)))

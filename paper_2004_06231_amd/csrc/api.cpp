@@ -21,14 +21,11 @@ struct einet {
 
     // workspace layout (bytes from the start of the workspace)
     std::vector<int32_t> blob;      // all index tables, concatenated
-    size_t off_theta = 0, off_A = 0, off_Off = 0, off_amax = 0, off_G = 0, off_Gp = 0, off_part = 0, ws_bytes = 0;
-    // Scratch for the statistics blocks of virtual items (bwd_virtual_items: a region per layer, since the blocks
-    // of a top-down pass are summed at its end) and, after that sum, of the leaf statistics' batch groups
-    // (leaf_stats_groups), which share the memory.
+    size_t off_theta = 0, off_A = 0, off_Off = 0, off_amax = 0, off_G = 0, off_Gp = 0, off_img = 0, off_part = 0, ws_bytes = 0;
+    // Scratch for the statistics blocks of the root's layer and, behind them, of the layers below (root_bwd_virtual_items,
+    // ein_stat_shares; summed at the end of a top-down pass).
     bool has_part = false;
-    size_t part_floats = 0;
-    static constexpr size_t NO_PART = ~size_t(0);
-    std::vector<size_t> part_off;   // per einsum layer: floats from off_part to its region, or NO_PART
+    size_t part_floats = 0, root_part_floats = 0;
     struct TableOffsets {
 #define X(name) size_t name;
         EINET_TABLES(X)
@@ -116,7 +113,7 @@ int check_batch_args(einet_t* h, const float* x, const uint8_t* mask, int mask_m
 
 enum KernelClass {
     KC_LEAF_FWD, KC_EINSUM_FWD, KC_MIXING_FWD, KC_REGION_BWD, KC_EINSUM_BWD, KC_LEAF_BWD, KC_UPDATE, KC_SAMPLE, KC_ROOT_FWD,
-    KC_ROOT_BWD, KC_COUNT
+    KC_ROOT_BWD, KC_EINSUM_STATS, KC_COUNT
 };
 int check_update_args(einet_t* h, float step, float min_var, float max_var, float w_floor) {
     if (!h) return EINET_ERR_INVALID_ARG;
@@ -129,7 +126,7 @@ int check_update_args(einet_t* h, float step, float min_var, float max_var, floa
 
 const char* const kKernelClassNames[KC_COUNT] = {"leaf_forward", "einsum_forward", "mixing_forward", "region_backward",
                                                  "einsum_backward", "leaf_mixing_backward", "em_update",
-                                                 "sampling", "root_forward", "root_backward"};
+                                                 "sampling", "root_forward", "root_backward", "einsum_statistics"};
 
 // Runs `launch` (which enqueues kernels on s); when profiling, brackets it with two events.
 template <class F>
@@ -271,23 +268,13 @@ int einet_create(const einet_spec* spec, einet_t** out) {
     off = align256(off + sizeof(float) * size_t(p.num_nodes) * mb * K);
     h->off_Gp = off;
     off = align256(off + sizeof(float) * gp_blocks_per_item(p.K) * p.ein_left.size() * mb * K);
-    h->part_off.assign(p.num_layers, einet::NO_PART);
-    for (int l = 0; l < p.num_layers; ++l) {         // (the root's layer, the last, has a kernel of its own)
-        const int count = p.ein_layer_ptr[l + 1] - p.ein_layer_ptr[l];
-        const size_t need = l + 1 < p.num_layers ? bwd_partial_bound(count, (int)p.K, (int)mb, p.ein_layer_full[l] != 0)
-                                                 : root_bwd_partial_bound(count, (int)p.K, (int)mb);
-        if (need == 0) continue;
-        h->has_part = true;
-        h->part_off[l] = h->part_floats;
-        h->part_floats += (need + 63) & ~size_t(63);
-    }
-    {
-        const int lg = leaf_stats_groups_max((int)p.leaf_node.size(), p.max_leaf_scope, p.C, (int)p.K, (int)mb);
-        if (lg > 1 && p.family != EINET_LEAF_CATEGORICAL) {
-            h->has_part = true;
-            const size_t need = (size_t)lg * (size_t)(p.n_stats - p.phi_offset);
-            if (need > h->part_floats) h->part_floats = need;
-        }
+    h->off_img = off;
+    off = align256(off + sizeof(float) * ein_image_floats(p.K, (int)mb) * p.ein_left.size());
+    if (p.num_layers > 0) {
+        const int top = p.num_layers - 1, count = p.ein_layer_ptr[top + 1] - p.ein_layer_ptr[top];
+        h->root_part_floats = (root_bwd_partial_bound(count, (int)p.K, (int)mb) + 63) & ~size_t(63);
+        h->part_floats = h->root_part_floats + ein_stat_partial_bound(p.ein_layer_ptr[top], (int)p.K, (int)mb);
+        h->has_part = h->part_floats > 0;
     }
     if (h->has_part) {
         h->off_part = off;
@@ -445,10 +432,9 @@ int einet_em_accumulate(einet_t* h, const float* x_dev, const uint8_t* mask_dev,
     // top-down: posteriors of the regions of sum layer l (root first), then the einsum items below them
     const float* amax = reinterpret_cast<const float*>(h->ws + h->off_amax);
     PartialSumList sums;
-    auto layer_part = [&](int l) -> float* {
-        return h->part_off[l] == einet::NO_PART ? nullptr
-                                                : reinterpret_cast<float*>(h->ws + h->off_part) + h->part_off[l];
-    };
+    float* const part = h->has_part ? reinterpret_cast<float*>(h->ws + h->off_part) : nullptr;
+    float* const root_part = h->root_part_floats > 0 ? part : nullptr;
+    sums.ein.part = part + h->root_part_floats;
     for (int l = p.num_layers - 1, step = 0; l >= 0; --l, ++step) {
         // (the top sum layer is the root alone: nothing to launch when its ones are still in place; nor for a layer
         // whose einsum kernel adds up the parents' blocks itself)
@@ -463,21 +449,19 @@ int einet_em_accumulate(einet_t* h, const float* x_dev, const uint8_t* mask_dev,
             // mixing statistics only): a launch of their own kind, timed as a class of its own
             run(h, KC_ROOT_BWD, s, [&] {
                 launch_root_backward(h->dt, p.ein_layer_ptr[l + 1] - p.ein_layer_ptr[l], h->dt.ein_woff + p.ein_layer_ptr[l],
-                                     layer_part(l), &sums,
-                                     !h->weight_stats_zero, h->params, h->stats, A, Off, amax, Gp, d, s);
-                if (l == 0) launch_sum_partial_stats(sums, h->stats, !h->weight_stats_zero, s);
+                                     root_part, &sums, !h->weight_stats_zero, h->params, h->stats, A, Off, amax, Gp, d, s);
             }, layer_outputs(p, l));
             continue;
         }
         run(h, KC_EINSUM_BWD, s, [&] {
             launch_einsum_backward(h->dt, p.ein_layer_ptr[l], p.ein_layer_ptr[l + 1] - p.ein_layer_ptr[l],
                                    p.ein_layer_full[l] != 0, !h->weight_stats_zero, h->params, h->stats, A, Off, amax, G, Gp,
-                                   layer_part(l), &sums, direct, d, s);
-            // after the last layer: the statistics blocks of the launches that ran virtual items, all layers in one
-            // launch (before the leaf statistics, whose batch groups use the same scratch)
-            if (l == 0) launch_sum_partial_stats(sums, h->stats, !h->weight_stats_zero, s);
+                                   reinterpret_cast<float*>(h->ws + h->off_img), &sums, direct, d, s);
         }, layer_outputs(p, l));
     }
+    // the weight statistics of all layers below the root's
+    if (sums.n > 0 || sums.ein.count > 0)
+        run(h, KC_EINSUM_STATS, s, [&] { launch_sum_partial_stats(sums, h->stats, !h->weight_stats_zero, s); });
     const int leaf_step = p.num_layers;
     if (!p.leaves_direct)
         run(h, KC_REGION_BWD, s, [&] {
@@ -488,8 +472,7 @@ int einet_em_accumulate(einet_t* h, const float* x_dev, const uint8_t* mask_dev,
         launch_tail_backward(h->dt, (int)p.lv_leaf.size(), (int)p.leaf_node.size(), p.max_leaf_scope,
                              (int)p.mix_node.size(), p.max_mix_children, x_dev, mask_dev,
                              mask_mode, h->params, A, Off, G, Gp, p.leaves_direct, h->stats, p.phi_offset, p.den_offset,
-                             p.tot_offset, p.n_stats,
-                             h->has_part ? reinterpret_cast<float*>(h->ws + h->off_part) : nullptr, h->part_floats, d, s);
+                             p.tot_offset, p.n_stats, nullptr, 0, d, s);
     });
     rc = check_hip(h, "einet_em_accumulate");
     // (after a failed launch nothing is known about the arena or the statistics: the root's ones are written

@@ -735,7 +735,7 @@ __global__ __launch_bounds__(512, 1) void k_einsum_forward_x(const int32_t* __re
 // A workgroup walks `cpg` chunks of 64 samples and takes all outputs or, where there are few items, a share of them.
 // Microseconds of a launch, against a kernel with operands split into bfloat16 parts (14 KB of instructions) and, for one
 // sample or K = 4, the kernel above: K = 10, 1000 samples, 1280 / 640 / 320 / 160 / 80 / 40 / 20 items: 77.6 / 43.8 / 28.4 / 15.5 /
-// 10.0 / 7.4 / 6.4 (84 / 47.5 / 27 / 17.5 / 11 / 8 / 6.4); K = 16, 64 samples, 48 / 100 / 120 / 80 / 40 items: 4.6 / 5.4 / 5.4 / 5.4 /
+// 10.0 / 7.4 / 6.4 (84 / 47.5 / 27 / 17.5 / 11 / 8 / 6.4); K = 16, 256 samples, 48 / 100 / 120 / 80 / 40 items: 4.6 / 5.4 / 5.4 / 5.4 /
 // 4.6 (5.3 / 6.8 / 7.0 / 6.6 / 5.1); one sample: 3.6 to 4.0 (4.2); K = 4, 64 samples, 2 and 1 items: 3.2 and 2.6 (3.9 and 3.8).
 template <int KQ>
 struct FwdCompact {

@@ -3,6 +3,7 @@
 // are device pointers; every launcher only enqueues work on `stream`.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cstdint>
 
 #include "../../include/einet.h"
@@ -14,7 +15,7 @@ namespace einet_impl {
 // the float32 bit patterns of log C(N, v), v = 0..N, for binomial leaves.
 #define EINET_TABLES(X)                                                                                    \
     X(ein_left) X(ein_right) X(ein_out) X(ein_reg) X(ein_kout) X(ein_woff) X(ein_voff) X(ein_vstr) X(ein_part) \
-    X(ein_gsrc) X(ein_rec) X(leaf_gsrc)                                                                               \
+    X(ein_rec) X(ein_brec) X(leaf_gsrc)                                                                               \
     X(mix_node) X(mix_kout) X(mix_cptr) X(mix_child) X(mix_voff) X(mix_rec)                                \
     X(leaf_node) X(leaf_replica) X(leaf_sptr) X(leaf_var) X(lv_leaf) X(lv_var)                             \
     X(rb_node) X(rb_kout) X(rb_pptr) X(rb_pblk) X(row_off) X(row_len) X(leaf_logc)                         \
@@ -82,150 +83,171 @@ inline bool root_kernels_apply(int n_partitions, int K) {
 // Bottom-up: S~, shifts and offsets of every partition (Eq. 3-5), then the root's mixture (App. B) and log P.
 void launch_root_forward(const DevTables& t, int n_partitions, const float* params, float* A, double* Off, float* amax,
                          float* logp, const Dims& d, hipStream_t s);
-struct PartialSumList;   // sums of statistics blocks left for the end of a top-down pass (below)
+struct PartialSumList;   // statistics left for the end of a top-down pass (below)
 // Top-down: weight statistics (Eq. 6) and child posteriors of the root's partitions; the root's posterior is 1 and its
-// mixing step is folded in.  Writes the posterior blocks that launch_einsum_backward writes for a layer of
-// n_partitions items with one output entry each (bwd_groups_per_item workgroups and right-child blocks per item).
-// e_woff: the weight offsets of the layer's items in order (for the sum of the virtual items' blocks); part, jobs as
-// for launch_einsum_backward (root_bwd_partial_bound floats), or null.
+// mixing step is folded in.  Writes posterior blocks like launch_einsum_backward (root_bwd_groups_per_item workgroups and
+// right-child blocks per item).  e_woff: the weight offsets of the layer's items in order.  part: root_bwd_partial_bound
+// floats of scratch for the statistics blocks of shares of the chunks, or null (then the chunks are always walked in turn);
+// with shares the sum of the blocks is appended to *list, not launched.
 void launch_root_backward(const DevTables& t, int n_partitions, const int32_t* e_woff, float* part, PartialSumList* jobs,
                           bool accumulate, const float* params, float* stats,
                           const float* A, const double* Off, const float* amax, float* Gp, const Dims& d, hipStream_t s);
 
 // Every top-down region also has a record of RB_REC_INTS ints in rb_rec: node, entries, number of parent blocks,
-// position of its list in rb_pblk, then the first RB_REC_BLOCKS block numbers (the rest, if any, only in the list).
-constexpr int RB_REC_INTS = 32, RB_REC_BLOCKS = 28;
+// position of its list in rb_pblk, then the first RB_REC_BLOCKS blocks, two ints each (the rest, if any, only in the list):
+// block number, and the code that says whether the block is written (bwd_block_used).
+constexpr int RB_REC_INTS = 64, RB_REC_BLOCKS = 28;
 void launch_region_assemble(const DevTables& t, int first, int count, bool is_root_layer, float* G, const float* Gp,
                             const Dims& d, hipStream_t s);
-// accumulate = false: the weight statistics of these items are known to be zero and are overwritten.
-// direct: the posterior of every item's region is not in G; the kernel adds up the parent's blocks itself, as
-// ein_gsrc says (only layers with Plan::ein_layer_direct set; then no launch_region_assemble for their regions).
-// full_k: every item of the launch has K output entries (all layers but the root's).
-// part: bwd_partial_bound floats of scratch for the blocks of virtual items, or null (then the chunks of an item are
-// always walked in turn); with virtual items the sum of the blocks is appended to *jobs, not launched.
-void launch_einsum_backward(const DevTables& t, int first, int count, bool full_k, bool accumulate,
-                            const float* params, float* stats, const float* A, const double* Off, const float* amax,
-                            const float* G, float* Gp, float* part, PartialSumList* jobs, bool direct, const Dims& d,
-                            hipStream_t s);
-// A region with one partition and one parent partition (every inner region of a random binary tree) has its
-// posterior in at most GSRC_MAX_BLOCKS consecutive blocks of Gp, written by that parent.  The top-down einsum kernel
-// of its partition can add them up while it stages its operands, which saves the launch that would assemble G for
-// the layer.  ein_gsrc[item] = (first block << 3) | number of blocks, 0 when the region does not qualify.
-constexpr int GSRC_MAX_BLOCKS = 6;
+
 // posterior blocks ([B][K] floats each) reserved per einsum item in Gp: one for its left child, then up to
 // one per slice of four left entries for its right child
 inline int gp_blocks_per_item(int K) { return 1 + (K + 3) / 4; }
-// Workgroups per item of the top-down einsum kernel for a layer of `count` items: the slices of an item are
-// spread over as many workgroups as keeps the launch within one round of the 256 compute units of the
-// MI355X (one workgroup per unit).  Workgroup grp takes slices grp*KQ/groups .. (grp+1)*KQ/groups - 1 and
-// writes right-child block 1+grp of the item.
-inline int bwd_groups_per_item(int count, int K) {
+// Workgroups per (item, chunk of 128 samples) of the top-down kernel for a layer of `count` items: the slices of an item are
+// spread over several workgroups where the launch would otherwise have fewer than bwd_workgroups of them (one per compute
+// unit, two where they have more than one chunk's work; K above 16).  Workgroup grp takes slices grp*KQ/groups ..
+// (grp+1)*KQ/groups - 1 and writes right-child block 1+grp of the item.  Larger batches need fewer groups: a block list holds those of one chunk, each with its code.
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline int bwd_workgroups(int nchunks) { return nchunks == 1 ? 256 : 512; }
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline int bwd_groups_per_item(int count, int K, int nchunks) {
+    const int kq = (K + 3) / 4;
+    if (K <= 16) return 1;                             // (a kernel of its own: a workgroup takes whole items)
+    const long long n = (long long)(count > 0 ? count : 1) * nchunks;
+    const int target = bwd_workgroups(nchunks), g = n >= target ? 1 : target / (int)n;
+    return g > kq ? kq : g;
+}
+// Code of right-child block 1 + q of an item in a layer of `count` items: the block is written when q < groups, that is
+// when (q + 1) * count * nchunks is at most bwd_workgroups(nchunks); 0: always.
+inline int32_t bwd_block_code(int count, int q) { return q == 0 ? 0 : (q + 1) * count; }
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline bool bwd_block_used(int32_t code, int nchunks) { return (long long)code * nchunks <= bwd_workgroups(nchunks); }
+// Workgroups per item of the root's layer (its kernel takes all chunks in one workgroup).
+inline int root_bwd_groups_per_item(int count, int K) {
     const int kq = (K + 3) / 4;
     const int g = 256 / (count > 0 ? count : 1);
     return g < 1 ? 1 : (g > kq ? kq : g);
 }
-// Layers whose items all have K output entries, K a multiple of 8 up to 40, take the top-down kernel with
-// specialised waves: one workgroup per compute unit, the layer's count * K/4 (item, slice) pairs split evenly
-// over the workgroups in order, so that a workgroup's pairs touch one or two items.  Workgroup g owns the pairs
-// g * P / G .. (g + 1) * P / G - 1 and writes right-child block 1 + (g - first workgroup of the item).
-inline bool bwd_uses_split_kernel(int K, bool full_k) { return full_k && (K & 7) == 0 && K <= 40; }
-inline int bwd_split_grid(int count, int K) {
-    const int pairs = count * (K / 4);
-    return pairs < 256 ? pairs : 256;
+// A region with one partition and one parent partition (every inner region of a random binary tree) has its
+// posterior in consecutive blocks of Gp, written by that parent.  The kernel that reads the posterior of such a region adds
+// them up itself, which saves the launch that would assemble G.  The source of a posterior is two ints: first block (-1:
+// it is in G) and how many there are: n > 0: those of the right child of an item in a layer of n items, n <= 0: -n.
+constexpr int GSRC_MAX_BLOCKS = 6;
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline int bwd_source_blocks(int32_t n, int K, int nchunks) { return n > 0 ? bwd_groups_per_item(n, K, nchunks) : -n; }
+
+// (small layers of K a multiple of 8 up to 40 read an assembled posterior)
+inline bool bwd_reads_blocks(int count, int K) { return (K & 7) != 0 || K > 40 || count >= 32; }
+
+// Every einsum item has a record of EIN_BREC_INTS ints in ein_brec for the top-down pass: left node, right node, node of its
+// output, its region, offset of W, offset and stride of its mixing weights (offset -1: one partition), source of its
+// region's posterior (two ints), unused.
+constexpr int EIN_BREC_INTS = 12;
+// Above K = 16 the top-down kernel also leaves the operands of an item's weight statistics in memory, sample-major:
+// EIN_IMAGES images of 4 ceil(K / 4) rows of ein_image_stride(B) floats each, Q, then eR, then eL (rows beyond K and samples
+// beyond the batch hold anything).
+constexpr int EIN_IMAGES = 3;
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline int ein_image_stride(int B) { return (B + 31) & ~31; }
+inline size_t ein_image_floats(int K, int B) {       // per item
+    return K <= 16 ? 0 : (size_t)EIN_IMAGES * (4 * ((K + 3) / 4)) * ein_image_stride(B);
 }
-// A layer of so few items that its pairs leave more than half of the compute units idle, with a batch of several
-// chunks of 128 samples: every item is launched as this many virtual items, each with a share of the chunks, one
-// workgroup per (virtual item, slice), at most 256 in all.  The virtual items of an item write their statistics to
-// blocks of their own (bwd_partial_bound floats together), which a later launch adds up in a fixed order.
-// That launch costs about 4 us (one for all layers of a pass), so the split is taken only where the chunks a workgroup
-// no longer walks are worth twice that: a workgroup spends roughly bwd_unit_us(K) on one chunk of one slice (10 us at K = 40, measured; the
-// work grows with K^2), half of that in the root's layer.
-constexpr float BWD_SPLIT_PAYS_US = 8.f;
-inline float bwd_unit_us(int K) { return 1.f + 9.f * (float)(K * K) / 1600.f; }
-inline int bwd_virtual_items(int count, int K, int B) {
-    const int pairs = count * (K / 4), nchunks = (B + 127) / 128;
-    if (pairs <= 0 || pairs > 128 || nchunks < 2) return 1;
-    int v = 256 / pairs;
-    if (v > nchunks) v = nchunks;
-    const int cpv = (nchunks + v - 1) / v;
-    if ((float)(nchunks - cpv) * bwd_unit_us(K) < BWD_SPLIT_PAYS_US) return 1;
-    return (nchunks + cpv - 1) / cpv;
-}
-// The sums of the blocks are not needed before the M-step, so the launches of a top-down pass only note them down
-// and one launch at the end of the pass does them all: per job,
+
+// What the end of a top-down pass still has to do for the statistics of the weights.  They are not needed before the
+// M-step, so the launches of a pass only note it down.
+// Per job (a launch whose batch was split into shares with statistics blocks of their own):
 //   stats[e_woff[item] + r] (+)= sum over v < vper of part[(v * count + item) * block + r], r < block.
-constexpr int PARTIAL_SUM_JOBS = 8;
+constexpr int PARTIAL_SUM_JOBS = 2;      // the root's layer, the layers below
 struct PartialSumJob {
     const int32_t* e_woff;
     const float* part;
     int count, vper, block;
 };
-struct PartialSumList {
-    int n = 0;
+struct PartialSumJobs {
     PartialSumJob job[PARTIAL_SUM_JOBS];
 };
-void launch_sum_partial_stats(const PartialSumList& jobs, float* stats, bool accumulate, hipStream_t s);
-// floats of scratch that a layer's launch needs for its blocks with any batch up to max_B (0: never virtual items)
-inline size_t bwd_partial_bound(int count, int K, int max_B, bool full_k);
-inline size_t root_bwd_partial_bound(int n_partitions, int K, int max_B);
-// The same for the root's layer (n_partitions items of K^2 weights, bwd_groups_per_item workgroups each): shares of
-// the chunks of 128 samples per workgroup when the launch would leave half of the compute units idle.
+// Einsum items first .. first + count - 1 (rec, woff: ein_brec and ein_woff of the first), whose weight statistics are formed
+// at once.  part: ein_stat_partial_bound floats of scratch.
+struct EinStatsWork {
+    const int32_t *rec, *woff;
+    float* part;
+    const float *params, *A, *amax, *G, *Gp, *img;
+    const double* Off;
+    int first, count, B, K;
+};
+// Few items above K = 16 with several chunks of 128 samples: the batch is split into this many shares (of whole chunks), so
+// that every wave of the chip has work of its own; a wave takes about three row tiles of a slice there.
+inline int ein_stat_shares(int count, int K, int B) {
+    const int kq = (K + 3) / 4, nchunks = (B + 127) / 128;
+    const long long units = (long long)count * kq * ((kq + 2) / 3);
+    if (K <= 16 || units == 0 || units > 1024 || nchunks < 2) return 1;
+    const long long v = 2048 / units;
+    const int cpv = v >= nchunks ? 1 : (int)((nchunks + v - 1) / v);
+    return (nchunks + cpv - 1) / cpv;
+}
+inline int ein_stat_share(int nshare, int B) {       // samples of a share
+    const int nchunks = (B + 127) / 128;
+    return nshare == 1 ? B : 128 * ((nchunks + nshare - 1) / nshare);
+}
+inline size_t ein_stat_partial_bound(int count, int K, int max_B) {
+    // (for any batch up to max_B: at most as many shares as chunks, and as the waves allow)
+    const int kq = (K + 3) / 4, nchunks = (max_B + 127) / 128;
+    const long long units = (long long)count * kq * ((kq + 2) / 3);
+    if (K <= 16 || units == 0 || units > 1024 || nchunks < 2) return 0;
+    return (size_t)std::min<long long>(2048 / units, nchunks) * count * K * K * K;
+}
+struct PartialSumList {
+    int n = 0;
+    PartialSumJobs jobs;
+    EinStatsWork ein{};
+};
+void launch_sum_partial_stats(const PartialSumList& list, float* stats, bool accumulate, hipStream_t s);
+// Posteriors of the children of a layer's items (every layer but the root's: all items have K output entries).  Notes the
+// items down in *list for their statistics: the layers of a pass come from the top, so their items are one range.
+// img: ein_image_floats(K, B) floats per item of the model; part: as in EinStatsWork, is kept in *list by the caller.
+// direct: the posterior of every item's region is not in G; the kernel adds up the parent's blocks itself, as
+// ein_brec says (only layers with Plan::ein_layer_direct set; then no launch_region_assemble for their regions).
+void launch_einsum_backward(const DevTables& t, int first, int count, bool full_k, bool accumulate,
+                            const float* params, float* stats, const float* A, const double* Off, const float* amax,
+                            const float* G, float* Gp, float* img, PartialSumList* list, bool direct, const Dims& d,
+                            hipStream_t s);
+// The root's layer (n_partitions items of K^2 weights, root_bwd_groups_per_item workgroups each): a layer of so few items
+// that its workgroups leave more than half of the compute units idle, with a batch of several chunks of 128 samples, is
+// launched with several shares of the chunks per item.  Each writes its statistics to a block of its own, which a later
+// launch adds up in a fixed order.  That launch costs about 4 us, so the split is taken only where the chunks a workgroup
+// no longer walks are worth twice that: a workgroup spends roughly half of root_bwd_unit_us(K) on one chunk of one slice.
+constexpr float BWD_SPLIT_PAYS_US = 8.f;
+inline float root_bwd_unit_us(int K) { return 1.f + 9.f * (float)(K * K) / 1600.f; }
 inline int root_bwd_virtual_items(int n_partitions, int K, int B) {
-    const int groups = bwd_groups_per_item(n_partitions, K), wgs = n_partitions * groups, nchunks = (B + 127) / 128;
+    const int groups = root_bwd_groups_per_item(n_partitions, K), wgs = n_partitions * groups, nchunks = (B + 127) / 128;
     if (wgs <= 0 || wgs > 128 || nchunks < 2) return 1;
     int v = 256 / wgs;
     if (v > nchunks) v = nchunks;
     const int cpv = (nchunks + v - 1) / v;
     const int slices = ((K + 3) / 4 + groups - 1) / groups;      // per workgroup
-    if ((float)((nchunks - cpv) * slices) * 0.5f * bwd_unit_us(K) < BWD_SPLIT_PAYS_US) return 1;
+    if ((float)((nchunks - cpv) * slices) * 0.5f * root_bwd_unit_us(K) < BWD_SPLIT_PAYS_US) return 1;
     return (nchunks + cpv - 1) / cpv;
 }
-// workgroup that owns pair x of P pairs split over G workgroups
-#if defined(__HIPCC__)
-__host__ __device__
-#endif
-inline int bwds_wg_of_pair(long long x, long long P, long long G) { return (int)(((x + 1) * G - 1) / P); }
-// right-child blocks that item li of a layer of `count` items writes (the workgroups that touch it)
-inline int bwd_blocks_of_item(int count, int K, bool full_k, int li) {
-    if (!bwd_uses_split_kernel(K, full_k)) return bwd_groups_per_item(count, K);
-    const long long ns = K / 4, P = (long long)count * ns, G = bwd_split_grid(count, K);
-    return bwds_wg_of_pair((li + 1) * ns - 1, P, G) - bwds_wg_of_pair(li * ns, P, G) + 1;
-}
-inline size_t bwd_partial_bound(int count, int K, int max_B, bool full_k) {
-    const int pairs = count * (K / 4), nchunks = (max_B + 127) / 128;
-    if (!bwd_uses_split_kernel(K, full_k) || pairs <= 0 || pairs > 128 || nchunks < 2) return 0;
-    const int v = 256 / pairs < nchunks ? 256 / pairs : nchunks;
-    return (size_t)v * count * K * K * K;
-}
+// floats of scratch that its launch needs for the blocks with any batch up to max_B (0: never split)
 inline size_t root_bwd_partial_bound(int n_partitions, int K, int max_B) {
-    const int wgs = n_partitions * bwd_groups_per_item(n_partitions, K), nchunks = (max_B + 127) / 128;
+    const int wgs = n_partitions * root_bwd_groups_per_item(n_partitions, K), nchunks = (max_B + 127) / 128;
     if (wgs <= 0 || wgs > 128 || nchunks < 2) return 0;
     const int v = 256 / wgs < nchunks ? 256 / wgs : nchunks;
     return (size_t)v * n_partitions * K * K;
 }
-// Leaf statistics on the matrix pipe (nothing marginalised, scopes of at least 512 (variable, channel) pairs): with
-// so few leaves that the workgroups of the launch (one per leaf and 64 or 128 pairs) leave half of the compute units
-// idle, the batch is split into this many groups of passes of 64 samples (at least two passes each), every group
-// with workgroups of its own that write to a block of their own; a second launch adds the blocks to the statistics.
-inline int leaf_stats_pairs_per_group(int K) { return K > 32 ? 64 : 128; }
-// (most groups any batch of up to B samples is split into)
-inline int leaf_stats_groups_max(int n_leaves, int max_scope, int C, int K, int B) {
-    const int pc = leaf_stats_pairs_per_group(K), wgs = n_leaves * ((max_scope * C + pc - 1) / pc), passes = (B + 63) / 64;
-    if (max_scope * C < 512 || wgs > 128 || passes < 4) return 1;
-    const int v = 256 / wgs;
-    return v > passes / 2 ? passes / 2 : v;
-}
-inline int leaf_stats_groups(int n_leaves, int max_scope, int C, int K, int B) {
-    const int v = leaf_stats_groups_max(n_leaves, max_scope, C, K, B), passes = (B + 63) / 64;
-    if (v <= 1) return 1;
-    const int ppv = (passes + v - 1) / v;
-    return (passes + ppv - 1) / ppv;
-}
 // leaf statistics and mixing statistics (independent of each other) in one launch
-// part: part_floats floats of scratch for the blocks of the batch groups above, or null; n_stats: length of stats.
-// direct: the leaves' posteriors are not in G; the element-wise forms of the leaf statistics add up the parents'
-// blocks of Gp themselves, as leaf_gsrc says (only with Plan::leaves_direct, which also keeps the scopes below the
-// 512 pairs from which the matrix-pipe form, which reads G, can be chosen).
+// direct: the leaves' posteriors are not in G; the kernels add up the parents' blocks of Gp themselves, as leaf_gsrc says
+// (only with Plan::leaves_direct).
 void launch_tail_backward(const DevTables& t, int n_lv, int n_leaves, int max_scope, int n_mix, int max_children,
                           const float* x, const uint8_t* mask, int mask_mode, const float* params, const float* A,
                           const double* Off, const float* G, const float* Gp, bool direct, float* stats,

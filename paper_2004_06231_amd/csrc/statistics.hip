@@ -83,8 +83,8 @@ __device__ __forceinline__ void mixing_stats_body(int item, int c, const int32_t
 // Posterior-weighted sufficient statistics (Eq. 6-7).  A workgroup of 1024 threads
 // owns 1024/NCH consecutive statistics entries (leaf variable, channel, k); its NCH
 // parts each walk every NCH-th sample and the partial sums meet in LDS.
-// DIRECT: the leaf's posterior is not in G; it is the sum of the blocks of Gp that leaf_gsrc names (first block << 3 |
-// number of blocks, see GSRC_MAX_BLOCKS), added up in the order the assembly launch would take.
+// DIRECT: the leaf's posterior is not in G; it is the sum of the blocks of Gp that leaf_gsrc names (two ints per leaf, see
+// GSRC_MAX_BLOCKS), added up in the order the assembly launch would take.
 template <int NCH, bool DIRECT>
 __device__ __forceinline__ void leaf_backward_body(
     int block, const int32_t* __restrict__ lv_leaf, const int32_t* __restrict__ lv_var, const int32_t* __restrict__ leaf_node,
@@ -100,8 +100,9 @@ __device__ __forceinline__ void leaf_backward_body(
     const int k = valid ? idx % d.K : 0, c = valid ? (idx / d.K) % d.C : 0, e = valid ? idx / (d.K * d.C) : 0;
     const int leaf = lv_leaf[e], var = lv_var[e], r = leaf_replica[leaf];
     const size_t gblk = (size_t)d.B * d.K;
-    const int gsrc = DIRECT ? leaf_gsrc[leaf] : 0, gcnt = gsrc & 7;
-    const float* Gl = (DIRECT ? Gp + (size_t)(gsrc >> 3) * gblk : G + (size_t)leaf_node[leaf] * gblk) + k;
+    const int gsrc = DIRECT ? leaf_gsrc[2 * leaf] : 0;
+    const int gcnt = DIRECT ? bwd_source_blocks(leaf_gsrc[2 * leaf + 1], d.K, (d.B + 127) / 128) : 1;
+    const float* Gl = (DIRECT ? Gp + (size_t)gsrc * gblk : G + (size_t)leaf_node[leaf] * gblk) + k;
     const float* xp = x + (size_t)var * d.C + c;
     const bool shared_obs = mask_mode != EINET_MASK_SHARED || mask[var] != 0;
     float n1 = 0.f, n2 = 0.f, den = 0.f, tot = 0.f;
@@ -270,296 +271,337 @@ __global__ __launch_bounds__(256) void k_leaf_backward_categorical(
     }
 }
 
-// The same statistics for leaves with long scopes (image cells).  A workgroup takes one leaf and a chunk of
-// its (variable, channel) pairs; per pass over 128 samples the leaf's posterior block G[leaf][b][.] (contiguous
-// in memory) and the pairs' values are copied to LDS, then thread (pair, k) walks the samples out of LDS.  The
-// walk of the kernel above waits a full memory latency for every few samples; here it waits for LDS.
-constexpr int CELL_BC = 128;                          // samples per pass
-__host__ __device__ inline int cell_pairs_per_group(int K) { return 1024 / K < 64 ? 1024 / K : 64; }
-// PPT: pairs per thread.  With four, a workgroup covers four times the pairs (for image rows of three channels
-// 400 contiguous bytes of x per sample instead of 100) and the posterior block is copied a quarter as often.
-__host__ __device__ inline size_t cell_lds_bytes(int K, int PPT) {
-    return sizeof(float) * ((size_t)CELL_BC * (K + cell_pairs_per_group(K) * PPT) + cell_pairs_per_group(K) * PPT + 2) +
-           (size_t)CELL_BC * cell_pairs_per_group(K) * PPT;
-}
-
-template <int PPT, bool DIRECT>
-__device__ __forceinline__ void leaf_backward_cells_body(
-    int block, int chunks_per_leaf, const int32_t* __restrict__ leaf_node, const int32_t* __restrict__ leaf_replica,
+// The same statistics for leaves of at least 16 (variable, channel) pairs (image cells and strips, long variable lists):
+// num[pair][k] = sum_b x[b][pair] p[b][k], the same with x^2 for Gaussian leaves (SQ) and with the observation flags (MASK),
+// is a product with the batch as contraction, on the bfloat16 matrix pipe at float32 precision (bf16x6.hpp).  A wave takes
+// 16 pairs (the rows) and all entries k; a lane's operand, eight samples of its pair, comes straight from memory (a load
+// reads 16 pairs side by side) and is requested a step of 64 samples ahead; the flags are exact in bfloat16.  (Posteriors times
+// 2^24, so that the third part of a small one is a normal number; values and flags times 2^-24.)  The leaf's
+// posteriors, which all waves share, are split into bfloat16 parts once per workgroup and step and go through LDS.
+// tot = sum_b p[b][k] is summed on the side.
+// Runs in one launch with the mixing statistics, hence the eight waves; `waves` of them have pairs.
+// Bound by the loads of the values, which no other workgroup reads: strips of 128 x 128 x 3 images, K = 40, 500 samples:
+// 61 us, with the values staged through LDS for float32 matrix instructions and the batch cut into groups 91 + 10 us.
+constexpr int LX_THREADS = 512;
+constexpr int LX_STEP = 64, LX_RB = LX_STEP + 8;       // samples per step; row stride (bfloat16) of the posteriors
+template <bool SQ, bool MASK, int NJ, bool DIRECT>
+__device__ __forceinline__ void leaf_stats_body(
+    int block, int chunks_per_leaf, int waves, const int32_t* __restrict__ leaf_node, const int32_t* __restrict__ leaf_replica,
     const int32_t* __restrict__ leaf_sptr, const int32_t* __restrict__ leaf_var, const float* __restrict__ x,
     const uint8_t* __restrict__ mask, int mask_mode, const float* __restrict__ G, const float* __restrict__ Gp,
-    const int32_t* __restrict__ leaf_gsrc, float* __restrict__ stats,
-    int64_t phi_off, int64_t den_off, int64_t tot_off, Dims d) {
-    extern __shared__ float cell_lds[];
-    const int pc = cell_pairs_per_group(d.K) * PPT;   // pairs per workgroup
-    float* Gs = cell_lds;                             // [CELL_BC][K]
-    float* xs = Gs + CELL_BC * d.K;                   // [CELL_BC][pc]
-    int* vsl = reinterpret_cast<int*>(xs + CELL_BC * pc);          // [pc + 2] variables the chunk's pairs belong to
-    uint8_t* os = reinterpret_cast<uint8_t*>(vsl + pc + 2);        // [CELL_BC][pc] 1 = observed
+    const int32_t* __restrict__ leaf_gsrc, float* __restrict__ stats, int64_t phi_off, int64_t den_off, int64_t tot_off,
+    const Dims& d) {
+    constexpr int NR = 16 * NJ;                        // columns, padded
+    __shared__ __attribute__((aligned(16))) uint16_t ps[2][3][NR][LX_RB];
+    constexpr int NG = LX_STEP / 4, NI = (NR * NG + LX_THREADS - 1) / LX_THREADS;     // groups of four samples; items per thread
+    __shared__ float red[NG][NR];
     const int leaf = block / chunks_per_leaf, chunk = block - leaf * chunks_per_leaf;
     const int s0 = leaf_sptr[leaf], npairs = (leaf_sptr[leaf + 1] - s0) * d.C;
-    const int p0 = chunk * pc;
-    if (p0 >= npairs) return;                         // (whole workgroup) this leaf has fewer chunks
-    const int np = min(pc, npairs - p0);
-    const int tid = threadIdx.x;
-    const int pl = (tid / d.K) * PPT, k = tid % d.K;  // this thread's first pair and its entry
-    const size_t gblk = (size_t)d.B * d.K;
-    const int gsrc = DIRECT ? leaf_gsrc[leaf] : 0, gcnt = gsrc & 7;
-    const float* Gl = DIRECT ? Gp + (size_t)(gsrc >> 3) * gblk : G + (size_t)leaf_node[leaf] * gblk;
-    // the variable numbers go to LDS once, so that the loads of the values do not each wait for one
-    const int vfirst = p0 / d.C, vcount = (p0 + np - 1) / d.C - vfirst + 1;
-    for (int j = tid; j < vcount; j += 1024) vsl[j] = leaf_var[s0 + vfirst + j];
-    __syncthreads();
-    float n1[PPT], n2[PPT], den[PPT], tot = 0.f;
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) n1[q] = n2[q] = den[q] = 0.f;
-    for (int b0 = 0; b0 < d.B; b0 += CELL_BC) {
-        const int nb = min(CELL_BC, d.B - b0);
-        if (b0 > 0) __syncthreads();                  // readers of the previous pass are done
-        for (int i0 = tid; i0 < nb * d.K; i0 += 4 * 1024) {      // four loads in flight per thread
-            float gq[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) gq[q] = i0 + q * 1024 < nb * d.K ? Gl[(size_t)b0 * d.K + i0 + q * 1024] : 0.f;
-            if (DIRECT && gcnt > 1) {
-                for (int y = 1; y < gcnt; ++y) {       // (the same element of the next block, all four together)
-                    float gy[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        gy[q] = i0 + q * 1024 < nb * d.K ? Gl[y * gblk + (size_t)b0 * d.K + i0 + q * 1024] : 0.f;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) gq[q] += gy[q];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (i0 + q * 1024 < nb * d.K) Gs[i0 + q * 1024] = gq[q];
-        }
-#pragma unroll 4
-        for (int i = tid; i < nb * np; i += 1024) {
-            const int bb = i / np, p = i - bb * np;
-            const int pair = p0 + p, v = pair / d.C, c = pair - v * d.C;
-            const int var = vsl[v - vfirst];
-            xs[bb * pc + p] = x[((size_t)(b0 + bb) * d.D + var) * d.C + c];
-            if (mask_mode == EINET_MASK_SHARED) os[bb * pc + p] = mask[var];
-            if (mask_mode == EINET_MASK_PER_SAMPLE) os[bb * pc + p] = mask[(size_t)(b0 + bb) * d.D + var];
-        }
-        __syncthreads();
-        // (pairs beyond np read stale LDS values; their sums are never written)
-        if (pl < np && mask_mode != EINET_MASK_NONE) {
-#pragma unroll 4
-            for (int bb = 0; bb < nb; ++bb) {
-                const float p = Gs[bb * d.K + k];
-                tot += p;
-#pragma unroll
-                for (int q = 0; q < PPT; ++q) {
-                    const float xv = xs[bb * pc + pl + q];
-                    const float pm = os[bb * pc + pl + q] ? p : 0.f;
-                    den[q] += pm;
-                    n1[q] = fmaf(pm, xv, n1[q]);
-                    n2[q] = fmaf(pm * xv, xv, n2[q]);
-                }
-            }
-        } else if (pl < np) {                         // everything observed: no flags to read, den = tot
-#pragma unroll 4
-            for (int bb = 0; bb < nb; ++bb) {
-                const float p = Gs[bb * d.K + k];
-                tot += p;
-#pragma unroll
-                for (int q = 0; q < PPT; ++q) {
-                    const float xv = xs[bb * pc + pl + q];
-                    n1[q] = fmaf(p, xv, n1[q]);
-                    n2[q] = fmaf(p * xv, xv, n2[q]);
-                }
-            }
-        }
-    }
-    if (mask_mode == EINET_MASK_NONE) {
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) den[q] = tot;
-    }
-    const int r = leaf_replica[leaf];
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        if (pl + q >= np) continue;
-        const int pair = p0 + pl + q, v = pair / d.C, c = pair - v * d.C;
-        const int var = vsl[v - vfirst];
-        const size_t ph = phi_off + ((size_t)(var * d.C + c) * d.R + r) * d.T * d.K + k;
-        stats[ph] += n1[q];
-        if (d.T == 2) stats[ph + d.K] += n2[q];
-        if (c == 0) {
-            const size_t o = ((size_t)var * d.R + r) * d.K + k;
-            stats[den_off + o] += den[q];
-            stats[tot_off + o] += tot;
-        }
-    }
-}
-
-// The same statistics for very long scopes (strips of a large image: thousands of (variable, channel) pairs per leaf)
-// when nothing is marginalised: num[pair][k] = sum_b x[b][pair] p[b][k] (and the same with x^2) is a GEMM with the
-// batch as contraction, here on v_mfma_f32_32x32x2_f32: rows = 32 pairs (A operand: the values, staged per pass of 64
-// samples in LDS exactly as above), columns = 32 entries k (B operand: the leaf's posterior block, zero beyond K).
-// A workgroup of four waves takes one leaf and 128 / NCT of its pairs, NCT being the number of column tiles (K <= 32:
-// one); a wave takes one tile of 32 pairs x 32 entries, so that every wave of a launch carries the same number of
-// MFMAs whatever K is.  Three workgroups share a compute unit (one stages while another multiplies); SQ adds the
-// x^2 rows (Gaussian leaves).  tot = den = sum_b p[b][k] is summed on the side.
-typedef float floatx16s __attribute__((ext_vector_type(16)));
-constexpr int LSM_BC = 64;                             // samples per pass
-template <int NCT>
-struct LsmLayout {
-    static constexpr int PC = 128 / NCT;               // pairs per workgroup
-    static constexpr int XS = PC + 8;                  // row stride of the values
-    static constexpr int PH = 256 / PC;                // threads per pair while staging: thread takes every PH-th sample
-    static constexpr size_t LDS_BYTES = sizeof(float) * ((size_t)LSM_BC * 64 + (size_t)LSM_BC * XS + 64) + sizeof(int) * (PC + 2);
-};
-
-template <bool SQ, int NCT>
-__global__ __launch_bounds__(256, NCT == 2 ? 3 : 2) void k_leaf_stats_mfma(
-    const int32_t* __restrict__ leaf_node, const int32_t* __restrict__ leaf_replica, const int32_t* __restrict__ leaf_sptr,
-    const int32_t* __restrict__ leaf_var, const float* __restrict__ x, const float* __restrict__ G,
-    float* __restrict__ stats, int64_t phi_off, int64_t den_off, int64_t tot_off, int chunks_per_leaf, int groups,
-    int group_samples, float* __restrict__ part, int64_t part_stride, Dims d) {
-    using LY = LsmLayout<NCT>;
-    constexpr int PC = LY::PC, XS = LY::XS, PH = LY::PH, NX = LSM_BC / PH;
-    extern __shared__ float lsm_lds[];
-    float* Gs = lsm_lds;                               // [LSM_BC][64], columns beyond K are zero
-    float* xs = Gs + LSM_BC * 64;                      // [LSM_BC][XS]
-    float* tots = xs + LSM_BC * XS;                    // [64]
-    int* vsl = reinterpret_cast<int*>(tots + 64);      // variables of the chunk's pairs
-    // groups > 1: workgroup (leaf, chunk, group) takes the samples [bfirst, bend) and writes (not adds) its sums to
-    // block `group` of part, which is laid out like the leaf part of the statistics (from phi_off on)
-    const int lc = blockIdx.x / groups, group = blockIdx.x - lc * groups;
-    const int leaf = lc / chunks_per_leaf, chunk = lc - leaf * chunks_per_leaf;
-    const int bfirst = group * group_samples, bend = min(d.B, bfirst + group_samples);
-    float* dst = groups > 1 ? part + (size_t)group * part_stride - phi_off : stats;
-    const bool adds = groups == 1;
-    const int s0 = leaf_sptr[leaf], npairs = (leaf_sptr[leaf + 1] - s0) * d.C;
-    const int p0 = chunk * PC;
-    if (p0 >= npairs) return;                          // (whole workgroup) this leaf has fewer chunks
-    const int np = min(PC, npairs - p0);
+    if (16 * waves * chunk >= npairs) return;          // (whole workgroup) this leaf has fewer chunks
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int rt = wave % (4 / NCT), ct = wave / (4 / NCT);   // this wave's tile: pairs 32 rt .., entries 32 ct ..
-    const int n = lane & 31, h = lane >> 5;
-    const float* Gl = G + (size_t)leaf_node[leaf] * d.B * d.K;
-    const int vfirst = p0 / d.C, vcount = (p0 + np - 1) / d.C - vfirst + 1;
-    for (int j = tid; j < vcount; j += 256) vsl[j] = leaf_var[s0 + vfirst + j];
-    floatx16s acc[SQ ? 2 : 1];
-#pragma unroll
-    for (int q = 0; q < (SQ ? 2 : 1); ++q)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
-    float tot = 0.f;                                   // thread (k, quarter): its share of sum_b p[b][k]
-    __syncthreads();
-    // thread (pair = tid % PC, phase = tid / PC) stages every PH-th sample of its pair (part of a column of xs) and 16
-    // entries of the posterior block per pass; the values of the next pass are requested before the MFMAs of the current
-    // one and go to LDS after them
-    size_t xoff = 0;
-    const int sp = tid & (PC - 1), sh = tid / PC;
-    const bool pin = sp < np;
-    if (pin) {
-        const int pair = p0 + sp, vv = pair / d.C, c = pair - vv * d.C;
-        xoff = (size_t)vsl[vv - vfirst] * d.C + c;
-    }
+    const int c16 = lane & 15, kg = lane >> 4;
+    const size_t gblk = (size_t)d.B * d.K;
+    const float* Gl = DIRECT ? Gp + (size_t)leaf_gsrc[2 * leaf] * gblk : G + (size_t)leaf_node[leaf] * gblk;
+    const int gcnt = DIRECT ? bwd_source_blocks(leaf_gsrc[2 * leaf + 1], d.K, (d.B + 127) / 128) : 1;
+    // this lane's pair
+    const int tile = chunk * waves + wave, pair = 16 * tile + c16;
+    const bool work = wave < waves && 16 * tile < npairs;
+    const int pv = min(pair, npairs - 1), var = leaf_var[s0 + pv / d.C];
     const size_t xstride = (size_t)d.D * d.C;
-    float xr[NX], gq[LSM_BC * 64 / 256];
-    auto fetch = [&](int b0) {
-        const int nb = min(LSM_BC, bend - b0);
+    const float* xp = x + (size_t)var * d.C + (pv - pv / d.C * d.C);
+    const uint8_t* mp = MASK ? mask + var : nullptr;
+    // staging: item (entry, four samples) of the posteriors
+    float g[NI][4], xv[LX_STEP / 32][8];
+    uint8_t ob[LX_STEP / 32][8];
+    auto fetch = [&](int s) {
 #pragma unroll
-        for (int q = 0; q < NX; ++q) {
-            const int bb = PH * q + sh;
-            xr[q] = (pin && bb < nb) ? x[(size_t)(b0 + bb) * xstride + xoff] : 0.f;
-        }
+        for (int x = 0; x < NI; ++x) {
+            const int f = tid + LX_THREADS * x, k = f % NR, b = s + 4 * (f / NR);
+            const float* src = Gl + (size_t)b * d.K + k;
 #pragma unroll
-        for (int q = 0; q < LSM_BC * 64 / 256; ++q) {
-            const int i = tid + 256 * q, bb = i >> 6, k = i & 63;
-            gq[q] = (bb < nb && k < d.K) ? Gl[(size_t)(b0 + bb) * d.K + k] : 0.f;
-        }
-    };
-    auto stage = [&]() {
+            for (int q = 0; q < 4; ++q) g[x][q] = k < d.K && f < NR * NG && b + q < d.B ? src[(size_t)q * d.K] : 0.f;
+            for (int y = 1; y < gcnt; ++y) {
+                float m[4];
 #pragma unroll
-        for (int q = 0; q < NX; ++q) xs[(PH * q + sh) * XS + sp] = xr[q];
+                for (int q = 0; q < 4; ++q) m[q] = k < d.K && f < NR * NG && b + q < d.B ? src[y * gblk + (size_t)q * d.K] : 0.f;
 #pragma unroll
-        for (int q = 0; q < LSM_BC * 64 / 256; ++q) Gs[tid + 256 * q] = gq[q];
-    };
-    fetch(bfirst);
-    for (int b0 = bfirst; b0 < bend; b0 += LSM_BC) {
-        if (b0 > bfirst) __syncthreads();              // readers of the previous pass are done
-        stage();
-        __syncthreads();
-        if (b0 + LSM_BC < bend) fetch(b0 + LSM_BC);
-        __builtin_amdgcn_sched_barrier(0);             // (the requests stay ahead of the MFMA loop)
-        {
-            // thread (k = tid % 64, quarter = tid / 64) sums a quarter of the pass (rows beyond the batch are zero)
-            float t4[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int bb = 0; bb < LSM_BC / 4; ++bb) t4[bb & 3] += Gs[(16 * wave + bb) * 64 + lane];
-            tot += (t4[0] + t4[1]) + (t4[2] + t4[3]);
-        }
-        const float* xa = xs + h * XS + 32 * rt + n;   // + 2 s XS
-        const float* pb = Gs + h * 64 + 32 * ct + n;   // + 2 s 64
-        // operands of the next step are requested before the MFMAs of the current one; the squares are formed ahead of
-        // the MFMAs, not between them
-        float a[2], b[2];
-        a[0] = xa[0];
-        b[0] = pb[0];
-#pragma unroll
-        for (int s = 0; s < LSM_BC / 2; ++s) {
-            const int cur = s & 1, nxt = cur ^ 1;
-            if (s + 1 < LSM_BC / 2) {
-                a[nxt] = xa[2 * (s + 1) * XS];
-                b[nxt] = pb[2 * (s + 1) * 64];
+                for (int q = 0; q < 4; ++q) g[x][q] += m[q];
             }
-            const float a2 = a[cur] * a[cur];
-            __builtin_amdgcn_sched_barrier(0);
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur], b[cur], acc[0], 0, 0, 0);
-            if (SQ) acc[SQ ? 1 : 0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a2, b[cur], acc[SQ ? 1 : 0], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
         }
-    }
-    // acc[q][v]: pair = 32 rt + 8 (v / 4) + 4 h + v % 4 of the chunk, entry k = 32 ct + n
-    const int r = leaf_replica[leaf];
-    const int k = 32 * ct + n;
+        if (work) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int p = 32 * rt + 8 * (v >> 2) + 4 * h + (v & 3);
-        if (p < np && k < d.K) {
-            const int pair = p0 + p, vv = pair / d.C, c = pair - vv * d.C;
-            const size_t ph = phi_off + ((size_t)(vsl[vv - vfirst] * d.C + c) * d.R + r) * d.T * d.K;
-            dst[ph + k] = (adds ? dst[ph + k] : 0.f) + acc[0][v];
-            if (SQ) dst[ph + d.K + k] = (adds ? dst[ph + d.K + k] : 0.f) + acc[SQ ? 1 : 0][v];
+            for (int u = 0; u < LX_STEP / 32; ++u)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int b = min(s + 32 * u + 8 * kg + q, d.B - 1);       // (beyond the batch the posteriors are zero)
+                    xv[u][q] = xp[(size_t)b * xstride];
+                    if (MASK) ob[u][q] = mp[mask_mode == EINET_MASK_PER_SAMPLE ? (size_t)b * d.D : 0];
+                }
         }
+    };
+    float tot[NI];
+#pragma unroll
+    for (int x = 0; x < NI; ++x) tot[x] = 0.f;
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int x = 0; x < NI; ++x) {
+            const int f = tid + LX_THREADS * x;
+            if (f >= NR * NG) continue;
+            uint32_t p0[3], p1[3];
+            split_bf16x3(g[x][0] * X6_SCALE, g[x][1] * X6_SCALE, p0[0], p0[1], p0[2]);
+            split_bf16x3(g[x][2] * X6_SCALE, g[x][3] * X6_SCALE, p1[0], p1[1], p1[2]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(&ps[buf][p][f % NR][4 * (f / NR)]) = make_uint2(p0[p], p1[p]);
+            tot[x] += (g[x][0] + g[x][1]) + (g[x][2] + g[x][3]);
+        }
+    };
+    constexpr int NK = 1 + (SQ ? 1 : 0) + (MASK ? 1 : 0);
+    floatx4 acc[NK][NJ];
+#pragma unroll
+    for (int q = 0; q < NK; ++q)
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt) acc[q][jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+    stage(0);
+    for (int s = 0, buf = 0; s < d.B; s += LX_STEP, buf ^= 1) {
+        float xc[LX_STEP / 32][8];
+        uint32x4 one[LX_STEP / 32];
+#pragma unroll
+        for (int u = 0; u < LX_STEP / 32; ++u) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) xc[u][q] = !MASK || ob[u][q] ? xv[u][q] : 0.f;
+            if (MASK) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) one[u][q] = (ob[u][2 * q] ? 0x3380u : 0u) | (ob[u][2 * q + 1] ? 0x33800000u : 0u);
+            }
+        }
+        __syncthreads();                               // the step is staged; readers of the other buffer are done
+        const bool more = s + LX_STEP < d.B;
+        if (more) fetch(s + LX_STEP);
+#pragma unroll
+        for (int u = 0; u < LX_STEP / 32; ++u) {
+            if (!work || s + 32 * u >= d.B) continue;
+            constexpr int NQ = SQ ? 2 : 1, PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};     // (small parts first)
+            uint32x4 a[NQ][3];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                float w[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) w[c] = xc[u][c] * (q == 0 ? 1.f : xc[u][c]) * (1.f / X6_SCALE);
+                split_octet(w, a[q][0], a[q][1], a[q][2]);
+            }
+            // (a column tile at a time and its sums added afterwards: few registers, and one rounding of the sums per step)
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) {
+                uint32x4 pb[3];
+                floatx4 t[NK];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) pb[p] = *reinterpret_cast<const uint32x4*>(&ps[buf][p][16 * jt + c16][32 * u + 8 * kg]);
+#pragma unroll
+                for (int q = 0; q < NK; ++q) t[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int p = 0; p < 6; ++p)
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) t[q] = mfma_bf16(a[q][PA[p]], pb[PB[p]], t[q]);
+                if constexpr (MASK) {
+#pragma unroll
+                    for (int p = 2; p >= 0; --p) t[NK - 1] = mfma_bf16(one[u], pb[p], t[NK - 1]);
+                }
+#pragma unroll
+                for (int q = 0; q < NK; ++q) acc[q][jt] += t[q];
+            }
+        }
+        if (more) stage(buf ^ 1);
     }
-    // den = tot for every variable whose first channel lies in this chunk
-    __syncthreads();                                   // (the last pass has been read: Gs is free)
-    Gs[tid] = tot;
+#pragma unroll
+    for (int x = 0; x < NI; ++x) {
+        const int f = tid + LX_THREADS * x;
+        if (f < NR * NG) red[f / NR][f % NR] = tot[x];
+    }
     __syncthreads();
-    if (tid < 64) tots[tid] = tid < d.K ? (Gs[tid] + Gs[64 + tid]) + (Gs[128 + tid] + Gs[192 + tid]) : 0.f;
-    __syncthreads();
-    const int vlo = (p0 + d.C - 1) / d.C, vhi = (p0 + np - 1) / d.C;      // variables with pair (v, 0) in [p0, p0 + np)
-    for (int i = tid; i < (vhi - vlo + 1) * d.K; i += 256) {
-        const int vv = vlo + i / d.K, kk = i % d.K;
-        const size_t o = ((size_t)vsl[vv - vfirst] * d.R + r) * d.K + kk;
-        dst[den_off + o] = (adds ? dst[den_off + o] : 0.f) + tots[kk];
-        dst[tot_off + o] = (adds ? dst[tot_off + o] : 0.f) + tots[kk];
+    if (!work) return;
+    // acc[q][jt][v]: pair 16 tile + 4 kg + v, entry 16 jt + c16
+    const int r = leaf_replica[leaf];
+#pragma unroll
+    for (int jt = 0; jt < NJ; ++jt) {
+        const int k = 16 * jt + c16;
+        float t = 0.f;
+#pragma unroll
+        for (int h = 0; h < NG; ++h) t += red[h][k];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int p = 16 * tile + 4 * kg + v;
+            if (p >= npairs || k >= d.K) continue;
+            const int vv = leaf_var[s0 + p / d.C], c = p - p / d.C * d.C;
+            const size_t ph = phi_off + ((size_t)(vv * d.C + c) * d.R + r) * d.T * d.K + k;
+            stats[ph] += acc[0][jt][v];
+            if (SQ) stats[ph + d.K] += acc[SQ ? 1 : 0][jt][v];
+            if (c == 0) {
+                const size_t o = ((size_t)vv * d.R + r) * d.K + k;
+                stats[den_off + o] += MASK ? acc[NK - 1][jt][v] : t;
+                stats[tot_off + o] += t;
+            }
+        }
     }
 }
 
-// stats[i] += sum over the blocks of part[.][i], i over the n floats of the leaf part of the statistics (what follows
-// k_leaf_stats_mfma with several batch groups): workgroup blk of n_blocks, in the launch of the mixing statistics
-__device__ __forceinline__ void sum_leaf_blocks_body(int blk, int n_blocks, const float* __restrict__ part,
-                                                     float* __restrict__ stats, int64_t n, int groups) {
-    for (int64_t i = (int64_t)blk * blockDim.x + threadIdx.x; i < n; i += (int64_t)n_blocks * blockDim.x) {
-        float sum = stats[i];
-        for (int v = 0; v < groups; ++v) sum += part[v * n + i];
-        stats[i] = sum;
+// The same for models with few tiles of 16 pairs: a workgroup takes one tile and deals the batch to its eight waves, 32 samples
+// at a time; every wave splits the posteriors of its own samples, so nothing is shared before the waves' sums meet at the end.
+// With mixing statistics, us of the launch (in brackets: both operands staged through LDS, a thread per (pair, entry)): 32x32x3
+// images in cells of 8 x 8, K = 40: 14.5 for 128 samples (14.7), 53 for 1000 (80); 28x28 in cells, K = 16, 256 samples, with flags:
+// 9.4 (18.0); lists of variables, K = 30, 100 samples: 12.8 (14.4).
+template <bool SQ, bool MASK, int NJ>
+struct LeafTileLds {
+    static constexpr int NR = 16 * NJ, NK = 1 + (SQ ? 1 : 0) + (MASK ? 1 : 0);
+    static constexpr int RB = 40;                      // row stride (bfloat16) of a wave's 32 samples
+    static constexpr int WAVE = 3 * NR * RB * 2;       // bytes of a wave's posteriors
+    static constexpr int SUMS = NK * NJ * 1024 + 8 * NR * 4;      // .. of its sums: [kind][jt][lane][4], tot [8][NR]
+    static constexpr int BYTES = 8 * (WAVE > SUMS ? WAVE : SUMS);
+};
+template <bool SQ, bool MASK, int NJ, bool DIRECT>
+__device__ __forceinline__ void leaf_tile_body(
+    int block, int tiles_per_leaf, char* lds, const int32_t* __restrict__ leaf_node, const int32_t* __restrict__ leaf_replica,
+    const int32_t* __restrict__ leaf_sptr, const int32_t* __restrict__ leaf_var, const float* __restrict__ x,
+    const uint8_t* __restrict__ mask, int mask_mode, const float* __restrict__ G, const float* __restrict__ Gp,
+    const int32_t* __restrict__ leaf_gsrc, float* __restrict__ stats, int64_t phi_off, int64_t den_off, int64_t tot_off,
+    const Dims& d) {
+    using LY = LeafTileLds<SQ, MASK, NJ>;
+    constexpr int NR = LY::NR, NK = LY::NK, NI = NR * 8 / 64;        // items (entry, four samples) per lane
+    const int leaf = block / tiles_per_leaf, tile = block - leaf * tiles_per_leaf;
+    const int s0 = leaf_sptr[leaf], npairs = (leaf_sptr[leaf + 1] - s0) * d.C;
+    if (16 * tile >= npairs) return;                   // (whole workgroup) this leaf has fewer tiles
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c16 = lane & 15, kg = lane >> 4;
+    const size_t gblk = (size_t)d.B * d.K;
+    const float* Gl = DIRECT ? Gp + (size_t)leaf_gsrc[2 * leaf] * gblk : G + (size_t)leaf_node[leaf] * gblk;
+    const int gcnt = DIRECT ? bwd_source_blocks(leaf_gsrc[2 * leaf + 1], d.K, (d.B + 127) / 128) : 1;
+    const int pv = min(16 * tile + c16, npairs - 1), var = leaf_var[s0 + pv / d.C];
+    const size_t xstride = (size_t)d.D * d.C;
+    const float* xp = x + (size_t)var * d.C + (pv - pv / d.C * d.C);
+    const uint8_t* mp = MASK ? mask + var : nullptr;
+    uint16_t* ps = reinterpret_cast<uint16_t*>(lds + wave * LY::WAVE);      // [part][entry][RB]
+    floatx4 acc[NK][NJ];
+    float tot[NI];
+#pragma unroll
+    for (int q = 0; q < NK; ++q)
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt) acc[q][jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int y = 0; y < NI; ++y) tot[y] = 0.f;
+    for (int s = 32 * wave; s < d.B; s += 256) {
+        float g[NI][4], xv[8];
+        uint8_t ob[8];
+#pragma unroll
+        for (int y = 0; y < NI; ++y) {
+            const int f = lane + 64 * y, k = f % NR, b = s + 4 * (f / NR);
+            const float* src = Gl + (size_t)b * d.K + k;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) g[y][q] = k < d.K && b + q < d.B ? src[(size_t)q * d.K] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int b = min(s + 8 * kg + q, d.B - 1);           // (samples beyond the batch: their posteriors are zero)
+            xv[q] = xp[(size_t)b * xstride];
+            if (MASK) ob[q] = mp[mask_mode == EINET_MASK_PER_SAMPLE ? (size_t)b * d.D : 0];
+        }
+        for (int z = 1; z < gcnt; ++z) {
+#pragma unroll
+            for (int y = 0; y < NI; ++y) {
+                const int f = lane + 64 * y, k = f % NR, b = s + 4 * (f / NR);
+                const float* src = Gl + z * gblk + (size_t)b * d.K + k;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) g[y][q] += k < d.K && b + q < d.B ? src[(size_t)q * d.K] : 0.f;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // (the LDS serves a wave's requests in order)
+#pragma unroll
+        for (int y = 0; y < NI; ++y) {
+            const int f = lane + 64 * y;
+            uint32_t p0[3], p1[3];
+            split_bf16x3(g[y][0] * X6_SCALE, g[y][1] * X6_SCALE, p0[0], p0[1], p0[2]);
+            split_bf16x3(g[y][2] * X6_SCALE, g[y][3] * X6_SCALE, p1[0], p1[1], p1[2]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                *reinterpret_cast<uint2*>(ps + (p * NR + f % NR) * LY::RB + 4 * (f / NR)) = make_uint2(p0[p], p1[p]);
+            tot[y] += (g[y][0] + g[y][1]) + (g[y][2] + g[y][3]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint32x4 pb[NJ][3];
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) pb[jt][p] = *reinterpret_cast<const uint32x4*>(ps + (p * NR + 16 * jt + c16) * LY::RB + 8 * kg);
+        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};     // (small parts first)
+#pragma unroll
+        for (int q = 0; q < (SQ ? 2 : 1); ++q) {
+            float w[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const float v = !MASK || ob[c] ? xv[c] : 0.f;
+                w[c] = v * (q == 0 ? 1.f : v) * (1.f / X6_SCALE);
+            }
+            uint32x4 a[3];
+            split_octet(w, a[0], a[1], a[2]);
+            floatx4 t[NJ];
+#pragma unroll
+            for (int p = 0; p < 6; ++p)
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt)
+                    t[jt] = mfma_bf16(a[PA[p]], pb[jt][PB[p]], p == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : t[jt]);
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) acc[q][jt] += t[jt];
+        }
+        if constexpr (MASK) {
+            uint32x4 one;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) one[q] = (ob[2 * q] ? 0x3380u : 0u) | (ob[2 * q + 1] ? 0x33800000u : 0u);
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) acc[NK - 1][jt] = mfma_bf16(one, pb[jt][p], acc[NK - 1][jt]);
+        }
+    }
+    __syncthreads();                                   // every wave is done with its posteriors
+    {
+        floatx4* out = reinterpret_cast<floatx4*>(lds + wave * LY::SUMS);
+#pragma unroll
+        for (int q = 0; q < NK; ++q)
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) out[(q * NJ + jt) * 64 + lane] = acc[q][jt];
+        float* t = reinterpret_cast<float*>(lds + wave * LY::SUMS + NK * NJ * 1024);
+#pragma unroll
+        for (int y = 0; y < NI; ++y) t[lane + 64 * y] = tot[y];       // [sample group][entry]
+    }
+    __syncthreads();
+    // block (q, jt) of the sums is finished by one wave: pair 16 tile + 4 kg + v, entry 16 jt + c16
+    const int r = leaf_replica[leaf];
+    for (int blk = wave; blk < NK * NJ; blk += 8) {
+        const int q = blk / NJ, k = 16 * (blk - q * NJ) + c16;
+        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 8; ++w) sum += reinterpret_cast<const floatx4*>(lds + w * LY::SUMS)[blk * 64 + lane];
+        float t = 0.f;
+        if (q == 0 || q == NK - 1)
+            for (int w = 0; w < 8; ++w)
+#pragma unroll
+                for (int h = 0; h < 8; ++h) t += reinterpret_cast<const float*>(lds + w * LY::SUMS + NK * NJ * 1024)[h * NR + k];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int p = 16 * tile + 4 * kg + v;
+            if (p >= npairs || k >= d.K) continue;
+            const int vv = leaf_var[s0 + p / d.C], c = p - p / d.C * d.C;
+            const float value = sum[v];
+            const size_t o = ((size_t)vv * d.R + r) * d.K + k;
+            if (q < (SQ ? 2 : 1)) stats[phi_off + (((size_t)(vv * d.C + c) * d.R + r) * d.T + q) * d.K + k] += value;
+            if (c == 0 && q == 0) stats[tot_off + o] += t;
+            if (c == 0 && q == NK - 1) stats[den_off + o] += MASK ? value : t;
+        }
     }
 }
 
 // Last launch of the top-down pass: leaf statistics in the first n_leaf_blocks workgroups, mixing
-// statistics in the others (item = idx / max_children, child = idx % max_children).  NCH = 0 selects the
-// kernel body for long scopes (chunks_per_leaf workgroups per leaf, PPT pairs per thread), NCH = TAIL_SUMS the sum of
-// the blocks that the batch groups of k_leaf_stats_mfma left in part.
-constexpr int TAIL_SUMS = 64;
-template <int NCH, int PPT, bool DIRECT>
+// statistics in the others (item = idx / max_children, child = idx % max_children).
+template <int NCH, bool DIRECT>
 __global__ __launch_bounds__(1024) void k_tail_backward(
     int n_leaf_blocks, int max_children, const int32_t* __restrict__ lv_leaf, const int32_t* __restrict__ lv_var,
     const int32_t* __restrict__ leaf_node, const int32_t* __restrict__ leaf_replica, int n_lv,
@@ -567,22 +609,41 @@ __global__ __launch_bounds__(1024) void k_tail_backward(
     const float* __restrict__ Gp, const int32_t* __restrict__ leaf_gsrc,
     float* __restrict__ stats, int64_t phi_off, int64_t den_off, int64_t tot_off, const int32_t* __restrict__ m_rec,
     const int32_t* __restrict__ m_cptr, const int32_t* __restrict__ m_child, const float* __restrict__ params,
-    const float* __restrict__ A, const double* __restrict__ Off, const int32_t* __restrict__ leaf_sptr,
-    const int32_t* __restrict__ leaf_var, int chunks_per_leaf, const float* __restrict__ part, int64_t part_n,
-    int groups, Dims d) {
+    const float* __restrict__ A, const double* __restrict__ Off, Dims d) {
     const int blk = blockIdx.x;
     if (blk < n_leaf_blocks) {
-        if constexpr (NCH == TAIL_SUMS)
-            sum_leaf_blocks_body(blk, n_leaf_blocks, part, stats + phi_off, part_n, groups);
-        else if constexpr (NCH == 0)
-            leaf_backward_cells_body<PPT, DIRECT>(blk, chunks_per_leaf, leaf_node, leaf_replica, leaf_sptr, leaf_var, x,
-                                                  mask, mask_mode, G, Gp, leaf_gsrc, stats, phi_off, den_off, tot_off, d);
-        else
-            leaf_backward_body<NCH, DIRECT>(blk, lv_leaf, lv_var, leaf_node, leaf_replica, n_lv, x, mask, mask_mode, G, Gp,
-                                            leaf_gsrc, stats, phi_off, den_off, tot_off, d);
+        leaf_backward_body<NCH, DIRECT>(blk, lv_leaf, lv_var, leaf_node, leaf_replica, n_lv, x, mask, mask_mode, G, Gp,
+                                        leaf_gsrc, stats, phi_off, den_off, tot_off, d);
     } else {
         const int idx = blk - n_leaf_blocks;
         mixing_stats_body<1024>(idx / max_children, idx % max_children, m_rec, m_cptr, m_child, params, stats, A, Off, G,
+                                d.B, d.K);
+    }
+}
+
+// The same with the leaves' statistics as matrix products (TILE: a tile per workgroup).
+template <bool SQ, bool MASK, int NJ, bool DIRECT, bool TILE>
+__global__ __launch_bounds__(LX_THREADS, TILE || MASK || NJ > 3 ? 2 : 4) void k_tail_backward_matrix(
+    int n_leaf_blocks, int chunks_per_leaf, int waves, int max_children, const int32_t* __restrict__ leaf_node,
+    const int32_t* __restrict__ leaf_replica, const int32_t* __restrict__ leaf_sptr, const int32_t* __restrict__ leaf_var,
+    const float* __restrict__ x, const uint8_t* __restrict__ mask, int mask_mode, const float* __restrict__ G,
+    const float* __restrict__ Gp, const int32_t* __restrict__ leaf_gsrc, float* __restrict__ stats, int64_t phi_off,
+    int64_t den_off, int64_t tot_off, const int32_t* __restrict__ m_rec, const int32_t* __restrict__ m_cptr,
+    const int32_t* __restrict__ m_child, const float* __restrict__ params, const float* __restrict__ A,
+    const double* __restrict__ Off, Dims d) {
+    const int blk = blockIdx.x;
+    if (blk < n_leaf_blocks) {
+        if constexpr (TILE) {
+            extern __shared__ __attribute__((aligned(16))) char tile_lds[];
+            leaf_tile_body<SQ, MASK, NJ, DIRECT>(blk, chunks_per_leaf, tile_lds, leaf_node, leaf_replica, leaf_sptr, leaf_var, x,
+                                                 mask, mask_mode, G, Gp, leaf_gsrc, stats, phi_off, den_off, tot_off, d);
+        } else {
+            leaf_stats_body<SQ, MASK, NJ, DIRECT>(blk, chunks_per_leaf, waves, leaf_node, leaf_replica, leaf_sptr, leaf_var, x,
+                                                  mask, mask_mode, G, Gp, leaf_gsrc, stats, phi_off, den_off, tot_off, d);
+        }
+    } else {
+        const int idx = blk - n_leaf_blocks;
+        mixing_stats_body<LX_THREADS>(idx / max_children, idx % max_children, m_rec, m_cptr, m_child, params, stats, A, Off, G,
                                 d.B, d.K);
     }
 }
@@ -592,8 +653,8 @@ __global__ __launch_bounds__(1024) void k_tail_backward(
 void launch_tail_backward(const DevTables& t, int n_lv, int n_leaves, int max_scope, int n_mix, int max_children,
                           const float* x, const uint8_t* mask, int mask_mode, const float* params, const float* A,
                           const double* Off, const float* G, const float* Gp, bool direct, float* stats,
-                          int64_t phi_off, int64_t den_off, int64_t tot_off, int64_t n_stats, float* part,
-                          size_t part_floats, const Dims& d, hipStream_t s) {
+                          int64_t phi_off, int64_t den_off, int64_t tot_off, int64_t, float*, size_t, const Dims& d,
+                          hipStream_t s) {
     const int total = n_lv * d.C * d.K;
     const bool categorical = d.family == EINET_LEAF_CATEGORICAL;
     if (categorical) {   // indicator statistics: a kernel of their own (at most 256 values)
@@ -609,85 +670,78 @@ void launch_tail_backward(const DevTables& t, int n_lv, int n_leaves, int max_sc
         else EINET_CAT(16);
 #undef EINET_CAT
     }
-    // very long scopes, nothing marginalised: the statistics as a GEMM over the batch on the matrix pipe, the mixing
-    // statistics in a launch of their own
-    bool leaves_done = categorical;
-    const int64_t n_leaf_stats = n_stats - phi_off;
-    int groups = part ? leaf_stats_groups(n_leaves, max_scope, d.C, d.K, d.B) : 1;
-    if ((size_t)groups * (size_t)n_leaf_stats > part_floats) groups = 1;
-    if (!categorical && mask_mode == EINET_MASK_NONE && (max_scope * d.C >= 1024 || groups > 1) && d.K <= 64) {
-        static std::once_flag attr_m[EINET_MAX_DEVICES];
-        int dev = 0;
-        (void)hipGetDevice(&dev);
-        std::call_once(attr_m[dev % EINET_MAX_DEVICES], [&] {
-            allow_dynamic_lds(&k_leaf_stats_mfma<true, 1>, LsmLayout<1>::LDS_BYTES);
-            allow_dynamic_lds(&k_leaf_stats_mfma<true, 2>, LsmLayout<2>::LDS_BYTES);
-            allow_dynamic_lds(&k_leaf_stats_mfma<false, 1>, LsmLayout<1>::LDS_BYTES);
-            allow_dynamic_lds(&k_leaf_stats_mfma<false, 2>, LsmLayout<2>::LDS_BYTES);
-        });
-#define EINET_LSM(SQ, NCT)                                                                                       \
-    {                                                                                                            \
-        static_assert(LsmLayout<NCT>::PC == (NCT == 2 ? 64 : 128), "leaf_stats_pairs_per_group");                \
-        const int cpl = (max_scope * d.C + LsmLayout<NCT>::PC - 1) / LsmLayout<NCT>::PC;                         \
-        hipLaunchKernelGGL((k_leaf_stats_mfma<SQ, NCT>), dim3(n_leaves * cpl * groups), dim3(256),               \
-                           LsmLayout<NCT>::LDS_BYTES, s, t.leaf_node, t.leaf_replica, t.leaf_sptr, t.leaf_var, x, G, \
-                           stats, phi_off, den_off, tot_off, cpl, groups, group_samples, part, n_leaf_stats, d);   \
-    }
-        const int passes = (d.B + LSM_BC - 1) / LSM_BC;
-        const int group_samples = groups > 1 ? LSM_BC * ((passes + groups - 1) / groups) : d.B;
-        if (d.T == 2 && d.K > 32) EINET_LSM(true, 2)
-        else if (d.T == 2) EINET_LSM(true, 1)
-        else if (d.K > 32) EINET_LSM(false, 2)
-        else EINET_LSM(false, 1)
-#undef EINET_LSM
-        leaves_done = true;
-    }
-    // long scopes: posterior block and values through LDS; short ones: straight from memory
-    const int pc1 = cell_pairs_per_group(d.K);
-    const int chunks1 = (max_scope * d.C + pc1 - 1) / pc1;
-    // (with fewer than 64 such workgroups the chip is better filled by the element-wise kernel)
-    const bool cells = !categorical && max_scope * d.C >= 32 && n_leaves * chunks1 >= 64;
-    // four pairs per thread when there would be more than a thousand workgroups (and the values still fit LDS)
-    const int ppt = cells && n_leaves * chunks1 >= 1024 && pc1 * 4 <= 128 ? 4 : 1;
-    // (eight parts from 64 samples on: 17.4 -> 15.5 us for 2560 leaves of three variables and 100 samples; sixteen: 21.6 us)
-    const int nch = cells ? 0 : (d.B >= 64 ? 8 : d.B >= 16 ? 4 : 1);
-    const int chunks_per_leaf = cells ? (max_scope * d.C + pc1 * ppt - 1) / (pc1 * ppt) : 1;
-    // (after the matrix kernel with batch groups: the leaf workgroups of this launch add the groups' blocks up)
-    const bool sums = leaves_done && !categorical && groups > 1;
-    const int sum_blocks = (int)((n_leaf_stats + 4095) / 4096 < 256 ? (n_leaf_stats + 4095) / 4096 : 256);
-    const int n_leaf_blocks = sums ? sum_blocks
-                              : leaves_done ? 0 : (cells ? n_leaves * chunks_per_leaf : (total + 1024 / nch - 1) / (1024 / nch));
-    const int blocks = n_leaf_blocks + n_mix * max_children;
-    if (blocks == 0) return;
-    const size_t lds = cells && !sums ? cell_lds_bytes(d.K, ppt) : 0;
-    if (cells && !sums) {
-        static std::once_flag attr_set[EINET_MAX_DEVICES];
-        int dev = 0;
-        (void)hipGetDevice(&dev);
-        std::call_once(attr_set[dev % EINET_MAX_DEVICES], [&] {
-            allow_dynamic_lds(&k_tail_backward<0, 1, false>, 64 * 1024);
-            allow_dynamic_lds(&k_tail_backward<0, 4, false>, 128 * 1024);
-            allow_dynamic_lds(&k_tail_backward<0, 1, true>, 64 * 1024);
-            allow_dynamic_lds(&k_tail_backward<0, 4, true>, 128 * 1024);
-        });
-    }
-#define EINET_LAUNCH_D(N, P, DIR)                                                                                    \
-    hipLaunchKernelGGL((k_tail_backward<N, P, DIR>), dim3(blocks), dim3(1024), lds, s, n_leaf_blocks,                 \
-                       max_children > 0 ? max_children : 1, t.lv_leaf, t.lv_var, t.leaf_node, t.leaf_replica, n_lv, x, \
-                       mask, mask_mode, G, Gp, t.leaf_gsrc, stats, phi_off, den_off, tot_off, t.mix_rec, t.mix_cptr,  \
-                       t.mix_child, params, A, Off, t.leaf_sptr, t.leaf_var, chunks_per_leaf, part, n_leaf_stats,     \
-                       groups, d)
-#define EINET_LAUNCH(N, P)                       \
-    do {                                         \
-        if (direct) EINET_LAUNCH_D(N, P, true);  \
-        else EINET_LAUNCH_D(N, P, false);        \
+    const int mc = max_children > 0 ? max_children : 1, n_mix_blocks = n_mix * max_children;
+    // scopes that fill a tile of 16 pairs: on the matrix pipe.  Few tiles: one per workgroup, so that the batch fills the chip;
+    // otherwise eight waves with a tile each, which split the posteriors once for all.  K = 40, 192 tiles, 128 samples: 14.5 us
+    // and 20.6; 1000 samples 53 and 65; K = 16, 256 samples, flags: 9.4 and 22.3.
+    if (!categorical && max_scope * d.C >= 16) {
+        const int tiles = (max_scope * d.C + 15) / 16;
+        const bool tile = (int64_t)n_leaves * tiles <= 2 * EINET_NUM_CUS;
+        const int waves = LX_THREADS / 64, chunks = tile ? tiles : (tiles + waves - 1) / waves;
+        const int n_leaf_blocks = n_leaves * chunks;
+#define EINET_LAUNCH_T(SQ, MASK, NJ, DIR, TILE)                                                                         \
+    do {                                                                                                                \
+        const size_t lds = TILE ? LeafTileLds<SQ, MASK, NJ>::BYTES : 0;                                                 \
+        if (lds > 64 * 1024) {                                                                                          \
+            static std::once_flag attr_set[EINET_MAX_DEVICES];                                                          \
+            int dev = 0;                                                                                                \
+            (void)hipGetDevice(&dev);                                                                                   \
+            std::call_once(attr_set[dev % EINET_MAX_DEVICES],                                                           \
+                           [&] { allow_dynamic_lds(&k_tail_backward_matrix<SQ, MASK, NJ, DIR, TILE>, lds); });          \
+        }                                                                                                               \
+        hipLaunchKernelGGL((k_tail_backward_matrix<SQ, MASK, NJ, DIR, TILE>), dim3(n_leaf_blocks + n_mix_blocks),       \
+                           dim3(LX_THREADS), lds, s, n_leaf_blocks, chunks, waves, mc, t.leaf_node, t.leaf_replica,     \
+                           t.leaf_sptr, t.leaf_var, x, mask, mask_mode, G, Gp, t.leaf_gsrc, stats, phi_off, den_off,    \
+                           tot_off, t.mix_rec, t.mix_cptr, t.mix_child, params, A, Off, d);                             \
     } while (0)
-    if (sums) EINET_LAUNCH_D(TAIL_SUMS, 1, false);
-    else if (nch == 0 && ppt == 4) EINET_LAUNCH(0, 4);
-    else if (nch == 0) EINET_LAUNCH(0, 1);
-    else if (nch == 8) EINET_LAUNCH(8, 1);
-    else if (nch == 4) EINET_LAUNCH(4, 1);
-    else EINET_LAUNCH(1, 1);
+#define EINET_LAUNCH_D(SQ, MASK, NJ, DIR)                    \
+    do {                                                     \
+        if (tile) EINET_LAUNCH_T(SQ, MASK, NJ, DIR, true);   \
+        else EINET_LAUNCH_T(SQ, MASK, NJ, DIR, false);       \
+    } while (0)
+#define EINET_LAUNCH_M(SQ, MASK, NJ)                         \
+    do {                                                     \
+        if (direct) EINET_LAUNCH_D(SQ, MASK, NJ, true);      \
+        else EINET_LAUNCH_D(SQ, MASK, NJ, false);            \
+    } while (0)
+#define EINET_LAUNCH(NJ)                                                      \
+    do {                                                                      \
+        const bool masked = mask_mode != EINET_MASK_NONE;                     \
+        if (d.T == 2 && masked) EINET_LAUNCH_M(true, true, NJ);               \
+        else if (d.T == 2) EINET_LAUNCH_M(true, false, NJ);                   \
+        else if (masked) EINET_LAUNCH_M(false, true, NJ);                     \
+        else EINET_LAUNCH_M(false, false, NJ);                                \
+    } while (0)
+        switch ((d.K + 15) / 16) {
+            case 1: EINET_LAUNCH(1); break;
+            case 2: EINET_LAUNCH(2); break;
+            case 3: EINET_LAUNCH(3); break;
+            default: EINET_LAUNCH(4); break;
+        }
+#undef EINET_LAUNCH
+#undef EINET_LAUNCH_M
+#undef EINET_LAUNCH_D
+#undef EINET_LAUNCH_T
+        return;
+    }
+    // short scopes: a thread per statistic, straight from memory (eight parts of the batch from 64 samples on: 17.4 -> 15.5 us
+    // for 2560 leaves of three variables and 100 samples; sixteen: 21.6 us)
+    const int nch = d.B >= 64 ? 8 : d.B >= 16 ? 4 : 1;
+    const int n_leaf_blocks = categorical ? 0 : (total + 1024 / nch - 1) / (1024 / nch);
+    const int blocks = n_leaf_blocks + n_mix_blocks;
+    if (blocks == 0) return;
+#define EINET_LAUNCH_D(N, DIR)                                                                                       \
+    hipLaunchKernelGGL((k_tail_backward<N, DIR>), dim3(blocks), dim3(1024), 0, s, n_leaf_blocks, mc, t.lv_leaf, t.lv_var, \
+                       t.leaf_node, t.leaf_replica, n_lv, x, mask, mask_mode, G, Gp, t.leaf_gsrc, stats, phi_off, den_off, \
+                       tot_off, t.mix_rec, t.mix_cptr, t.mix_child, params, A, Off, d)
+#define EINET_LAUNCH(N)                       \
+    do {                                      \
+        if (direct) EINET_LAUNCH_D(N, true);  \
+        else EINET_LAUNCH_D(N, false);        \
+    } while (0)
+    if (nch == 8) EINET_LAUNCH(8);
+    else if (nch == 4) EINET_LAUNCH(4);
+    else EINET_LAUNCH(1);
 #undef EINET_LAUNCH
 #undef EINET_LAUNCH_D
 }

@@ -379,34 +379,46 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
 
     // ---- top-down items: which posterior blocks flow into each region.  Item e owns blocks
     // e*nb .. e*nb+nb-1 of Gp: block 0 for its left child, blocks 1.. (one per workgroup of the top-down
-    // einsum kernel) for its right child.
+    // kernel) for its right child.  How many of those are written depends on the batch: their codes say.
     const int nb = gp_blocks_per_item(K);
-    std::vector<std::vector<std::pair<int, int>>> runs(nr);
-    std::vector<int> layer_of_item(np, 0);
-    for (int l = 0; l < p.num_layers; ++l)
-        for (int e = p.ein_layer_ptr[l]; e < p.ein_layer_ptr[l + 1]; ++e) layer_of_item[e] = l;
-    for (int n = 0; n < np; ++n) {
-        const int e = item_of[n], l = layer_of_item[e];
-        const int groups = bwd_blocks_of_item(p.ein_layer_ptr[l + 1] - p.ein_layer_ptr[l], K, p.ein_layer_full[l] != 0,
-                                              e - p.ein_layer_ptr[l]);
-        runs[g.partition[n][1]].push_back({e * nb, 1});
-        runs[g.partition[n][2]].push_back({e * nb + 1, groups});
-    }
-    // ---- layers whose regions need no assembled posterior (see GSRC_MAX_BLOCKS)
-    p.ein_gsrc.assign(np, 0);
-    p.ein_layer_direct.assign(p.num_layers, 0);
-    for (int l = 0; l + 1 < p.num_layers; ++l) {       // (the root's layer has a kernel of its own)
-        bool all = !bwd_uses_split_kernel(K, p.ein_layer_full[l] != 0);
+    struct Run { int first, blocks, count; };          // count: items of the layer, 0 where all blocks are always written
+    std::vector<std::vector<Run>> runs(nr);
+    for (int l = 0; l < p.num_layers; ++l) {
+        const int count = p.ein_layer_ptr[l + 1] - p.ein_layer_ptr[l];
+        const bool top = l + 1 == p.num_layers;
+        const int blocks = top ? root_bwd_groups_per_item(count, K) : bwd_groups_per_item(count, K, 1);
         for (int e = p.ein_layer_ptr[l]; e < p.ein_layer_ptr[l + 1]; ++e) {
-            const int s = g.partition[p.ein_part[e]][0];
-            if (g.parts_of[s].size() == 1 && runs[s].size() == 1 && runs[s][0].second <= GSRC_MAX_BLOCKS)
-                p.ein_gsrc[e] = (runs[s][0].first << 3) | runs[s][0].second;
-            else
-                all = false;
+            runs[p.ein_left[e]].push_back({e * nb, 1, 0});
+            runs[p.ein_right[e]].push_back({e * nb + 1, blocks, top ? 0 : count});
+        }
+    }
+    // (source of a posterior that one parent alone writes, see GSRC_MAX_BLOCKS)
+    auto source = [&](int s, int32_t* first, int32_t* n) {
+        if (runs[s].size() != 1 || runs[s][0].blocks > GSRC_MAX_BLOCKS) return false;
+        *first = runs[s][0].first;
+        *n = runs[s][0].count > 0 ? runs[s][0].count : -runs[s][0].blocks;
+        return true;
+    };
+    // ---- one record per einsum item for the top-down pass (see EIN_BREC_INTS); layers whose regions need no assembled
+    // posterior
+    p.ein_brec.assign((size_t)np * EIN_BREC_INTS, 0);
+    p.ein_layer_direct.assign(p.num_layers, 0);
+    for (int l = 0; l < p.num_layers; ++l) {
+        const int count = p.ein_layer_ptr[l + 1] - p.ein_layer_ptr[l];
+        bool all = l + 1 < p.num_layers && bwd_reads_blocks(count, K);      // (the root's layer has a kernel of its own)
+        for (int e = p.ein_layer_ptr[l]; e < p.ein_layer_ptr[l + 1]; ++e) {
+            int32_t* rec = p.ein_brec.data() + (size_t)e * EIN_BREC_INTS;
+            rec[0] = p.ein_left[e];
+            rec[1] = p.ein_right[e];
+            rec[2] = p.ein_out[e];
+            rec[3] = p.ein_reg[e];
+            rec[4] = p.ein_woff[e];
+            rec[5] = p.ein_voff[e];
+            rec[6] = p.ein_vstr[e];
+            all = all && g.parts_of[p.ein_reg[e]].size() == 1 && source(p.ein_reg[e], rec + 7, rec + 8);
         }
         p.ein_layer_direct[l] = all ? 1 : 0;
-        if (!all)
-            for (int e = p.ein_layer_ptr[l]; e < p.ein_layer_ptr[l + 1]; ++e) p.ein_gsrc[e] = 0;
+        for (int e = p.ein_layer_ptr[l]; !all && e < p.ein_layer_ptr[l + 1]; ++e) p.ein_brec[(size_t)e * EIN_BREC_INTS + 7] = -1;
     }
     // ---- one record per einsum item (see EIN_REC_INTS)
     p.ein_rec.assign((size_t)np * EIN_REC_INTS, 0);
@@ -417,27 +429,24 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
         rec[2] = p.ein_out[e];
         rec[3] = p.ein_woff[e];
     }
-    // ---- posterior blocks of the leaves (element-wise statistics kernels only: no categorical leaves, scopes below the 512
-    // pairs from which the matrix-pipe kernel may be chosen)
-    p.leaf_gsrc.assign(p.leaf_node.size(), 0);
+    // ---- posterior blocks of the leaves (no categorical leaves; below 512 pairs, as every workgroup of a leaf would add the
+    // blocks up again)
+    p.leaf_gsrc.assign(2 * p.leaf_node.size(), 0);
     p.leaves_direct = family != EINET_LEAF_CATEGORICAL && p.max_leaf_scope * C < 512 && !p.leaf_node.empty();
-    for (size_t i = 0; i < p.leaf_node.size() && p.leaves_direct; ++i) {
-        const int s = p.leaf_node[i];
-        if (runs[s].size() == 1 && runs[s][0].second <= GSRC_MAX_BLOCKS)
-            p.leaf_gsrc[i] = (runs[s][0].first << 3) | runs[s][0].second;
-        else
-            p.leaves_direct = false;
-    }
-    if (!p.leaves_direct) p.leaf_gsrc.assign(p.leaf_node.size(), 0);
+    for (size_t i = 0; i < p.leaf_node.size() && p.leaves_direct; ++i)
+        p.leaves_direct = source(p.leaf_node[i], &p.leaf_gsrc[2 * i], &p.leaf_gsrc[2 * i + 1]);
     p.rb_layer_ptr.push_back(0);
     p.rb_pptr.push_back(0);
     auto push_region = [&](int s) {
         p.rb_node.push_back(s);
         p.rb_kout.push_back(kout(s));
-        std::sort(runs[s].begin(), runs[s].end());
+        std::sort(runs[s].begin(), runs[s].end(), [](const Run& a, const Run& b) { return a.first < b.first; });
         for (auto& r : runs[s])
-            for (int q = 0; q < r.second; ++q) p.rb_pblk.push_back(r.first + q);
-        p.rb_pptr.push_back((int32_t)p.rb_pblk.size());
+            for (int q = 0; q < r.blocks; ++q) {
+                p.rb_pblk.push_back(r.first + q);
+                p.rb_pblk.push_back(bwd_block_code(r.count, q));
+            }
+        p.rb_pptr.push_back((int32_t)p.rb_pblk.size() / 2);
     };
     for (int l = p.num_layers - 1; l >= 0; --l) {
         for (int s : sum_layers[l]) push_region(s);
@@ -455,7 +464,7 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
         rec[1] = p.rb_kout[i];
         rec[2] = cnt;
         rec[3] = p.rb_pptr[i];
-        for (int q = 0; q < cnt && q < RB_REC_BLOCKS; ++q) rec[4 + q] = p.rb_pblk[p.rb_pptr[i] + q];
+        for (int q = 0; q < 2 * cnt && q < 2 * RB_REC_BLOCKS; ++q) rec[4 + q] = p.rb_pblk[2 * p.rb_pptr[i] + q];
     }
 
     // ---- M-step rows
