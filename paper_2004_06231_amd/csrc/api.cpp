@@ -435,6 +435,7 @@ int einet_em_accumulate(einet_t* h, const float* x_dev, const uint8_t* mask_dev,
     float* const part = h->has_part ? reinterpret_cast<float*>(h->ws + h->off_part) : nullptr;
     float* const root_part = h->root_part_floats > 0 ? part : nullptr;
     sums.ein.part = part + h->root_part_floats;
+    sums.ein.total = p.ein_layer_ptr[p.num_layers - 1];
     for (int l = p.num_layers - 1, step = 0; l >= 0; --l, ++step) {
         // (the top sum layer is the root alone: nothing to launch when its ones are still in place; nor for a layer
         // whose einsum kernel adds up the parents' blocks itself)

@@ -874,6 +874,157 @@ __global__ __launch_bounds__(256, 4) void k_einsum_forward_compact(const int32_t
     }
 }
 
+// ------------------------------------------------------------------ einsum layer, forward, K from 13 to 16, large launches
+// Small items are bound by the chain of requests in front of their arithmetic, so many small workgroups per compute unit
+// take them: four waves per (item, group of chunks), a chunk being 128 samples, 32 per wave.  The whole item's weights are
+// split into LDS once (at most 24 KB); a lane loads the rows of its own samples straight from memory, so nothing but the
+// weights is shared.  Same tiles as above with row m = 4 (k % 4) + i % 4: lane group kg holds output k = 4 q + kg of group
+// q, its four accumulators four consecutive left entries, so a sum of Eq. 4 is complete in one lane.
+// Against the short kernel below: see einsum_forward_kernel.  Registers must not spill: with
+// 128 instead of 168 of them and 28 spilled every launch took 4 us longer.
+struct FwdSmallLayout {
+    using X = X6<2>;
+    static constexpr int KP = X::KP, NT = X::NT;
+    static constexpr int LDS_BYTES = NT * NT * X::BYTES;  // NT groups of four outputs x NT tiles
+    static constexpr int NI = KP * KP * 2;                // octets of the weights
+    static constexpr int NL = (NI + 255) / 256;
+};
+
+__global__ __launch_bounds__(256, 3) void k_einsum_forward_small(const int32_t* __restrict__ e_rec, const float* __restrict__ params,
+                                                               float* __restrict__ A, double* __restrict__ Off,
+                                                               float* __restrict__ amax, int item0, int ngrp, int cpg, int nsplit,
+                                                               int B, int K, int kout) {
+    using LY = FwdSmallLayout;
+    using X = LY::X;
+    constexpr int K8 = 2;
+    constexpr int KP = LY::KP, NT = LY::NT, NL = LY::NL;
+    extern __shared__ __attribute__((aligned(16))) char lds_c[];
+    uint32x4* wl = reinterpret_cast<uint32x4*>(lds_c);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c16 = lane & 15, kg = lane >> 4;
+    const int vb = xcd_contiguous_block();
+    const int part = vb % nsplit, grp = (vb / nsplit) % ngrp, li = vb / (nsplit * ngrp);
+    const int NG = (kout + 3) >> 2, q0 = part * NG / nsplit, q1 = (part + 1) * NG / nsplit;   // groups of four outputs
+    const int ni = (q1 - q0) * 4 * KP * K8;           // octets of their weights
+    const int32_t* rec = e_rec + li * EIN_REC_INTS;
+    const int left = rec[0], right = rec[1], out = rec[2];
+    const int nchunks = (B + 127) >> 7, c0 = grp * cpg, c1 = min(c0 + cpg, nchunks);
+    const float* W = params + rec[3];
+
+    floatx4 wv[NL][2];
+#pragma unroll
+    for (int x = 0; x < NL; ++x) {
+        if (256 * x >= ni) break;
+        const int f = min(tid + 256 * x, ni - 1);
+        const int o = f % K8, i = (f / K8) % KP, k = 4 * q0 + f / (K8 * KP);
+        const float* p = W + ((size_t)min(k, kout - 1) * K + min(i, K - 1)) * K;
+        p += min(8 * o, K - 8);                       // (the last octet of a row starts at K - 8, as above)
+        wv[x][0] = *reinterpret_cast<const floatx4u*>(p);
+        wv[x][1] = *reinterpret_cast<const floatx4u*>(p + 4);
+    }
+    // rows of this lane's samples (two sets of 16): one octet of R, all of L
+    float rr[2][8], rl[2][KP];
+    double off_children[2];
+    auto fetch_rows = [&](int chunk) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int b = min(chunk * 128 + 32 * wave + 16 * s + c16, B - 1);
+            const float* Lp = A + ((size_t)left * B + b) * K;
+            const float* Rp = A + ((size_t)right * B + b) * K;
+            const int st = (kg & 1) ? K - 8 : 0;
+            const floatx4 r0 = *reinterpret_cast<const floatx4u*>(Rp + st), r1 = *reinterpret_cast<const floatx4u*>(Rp + st + 4);
+            const floatx4 l0 = *reinterpret_cast<const floatx4u*>(Lp), l1 = *reinterpret_cast<const floatx4u*>(Lp + 4);
+            // (the left entries of the tiles 2 and 3 are the row's last eight, those below 8 among them: their weights
+            // are zeros there)
+            const floatx4 l2 = *reinterpret_cast<const floatx4u*>(Lp + K - 8), l3 = *reinterpret_cast<const floatx4u*>(Lp + K - 4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                rr[s][c] = r0[c]; rr[s][4 + c] = r1[c];
+                rl[s][c] = l0[c]; rl[s][4 + c] = l1[c]; rl[s][8 + c] = l2[c]; rl[s][12 + c] = l3[c];
+            }
+            off_children[s] = Off[(size_t)left * B + b] + Off[(size_t)right * B + b];
+        }
+    };
+    fetch_rows(c0);
+#pragma unroll
+    for (int x = 0; x < NL; ++x) {
+        const int f = tid + 256 * x;
+        const int o = f % K8, i = (f / K8) % KP, kl = f / (K8 * KP), k = 4 * q0 + kl;
+        if (f < ni) {
+            float v[8];
+            const bool row = k < kout && i < K;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) v[c] = row && (o == 0 || c >= 16 - K) ? wv[x][c >> 2][c & 3] * X6_SCALE : 0.f;
+            uint32x4 part[3];
+            split_octet(v, part[0], part[1], part[2]);
+            // row slot of the tiles: left entry i < 8 in slot i, i >= 8 in slot 8 + (i - (K - 8)); the slots in between have
+            // no left entry of their own and get the zeros of the rows i >= K
+            const int slot = i < 8 ? i : i < K ? i + 16 - K : 8 + i - K;
+            uint32x4* d = wl + ((kl >> 2) * NT + (slot >> 2)) * X::UNITS;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) d[x6_unit<K8>(p, o, 4 * (kl & 3) + (slot & 3))] = part[p];
+        }
+    }
+    int unit[X::NR];
+#pragma unroll
+    for (int a = 0; a < X::NR; ++a) unit[a] = x6_row_unit<K8>(a, kg, c16);
+    __syncthreads();
+    for (int chunk = c0; chunk < c1; ++chunk) {
+        if (chunk > c0) fetch_rows(chunk);            // (the other workgroups of the compute unit hide the wait)
+        uint32x4 er[2][X::NR];
+        float el[2][KP];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            float xr = rr[s][0], xl = rl[s][0];
+#pragma unroll
+            for (int c = 1; c < 8; ++c) xr = fmaxf(xr, rr[s][c]);
+            xr = fmaxf(xr, __shfl_xor(xr, 16, 64));
+#pragma unroll
+            for (int c = 1; c < KP; ++c) xl = fmaxf(xl, rl[s][c]);
+            if (xr == -INFINITY) xr = 0.f;            // an all-zero input vector: exp(-inf) = 0, no NaN
+            if (xl == -INFINITY) xl = 0.f;
+            float e8[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) e8[c] = __expf(rr[s][c] - xr) * X6_SCALE;
+            x6_sample_operand<K8>(kg, [&](int, float* v) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) v[c] = e8[c];
+            }, er[s]);
+#pragma unroll
+            for (int c = 0; c < KP; ++c) el[s][c] = __expf(rl[s][c] - xl);
+            const int b = chunk * 128 + 32 * wave + 16 * s + c16;
+            if (kg == 0 && b < B && part == 0) {
+                Off[(size_t)out * B + b] = off_children[s] + (double)xl + (double)xr;
+                amax[((size_t)(item0 + li) * 2) * B + b] = xl;
+                amax[((size_t)(item0 + li) * 2 + 1) * B + b] = xr;
+            }
+        }
+#pragma unroll
+        for (int ql = 0; ql < NT; ++ql) {
+            if (q0 + ql >= q1) break;
+            float sk[2] = {0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                uint32x4 a[X::NR];
+#pragma unroll
+                for (int z = 0; z < X::NR; ++z) a[z] = wl[(ql * NT + t) * X::UNITS + unit[z]];
+                floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                x6_tile<K8, 2>(a, er, acc);
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) sk[s] = fmaf(acc[s][c], el[s][4 * t + c], sk[s]);
+            }
+            const int k = 4 * (q0 + ql) + kg;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int b = chunk * 128 + 32 * wave + 16 * s + c16;
+                if (b < B && k < kout) A[((size_t)out * B + b) * K + k] = __logf(sk[s] * X6_UNSCALE);
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------ einsum layer, forward, K from 17 to 31, short launches
 // A launch with about one unit per compute unit is the chain of requests in front of its arithmetic; the persistent
 // kernel's producer waves and barriers only lengthen it.  Here a workgroup of four waves takes one (item, chunk of 128
@@ -1173,17 +1324,33 @@ static void launch_einsum_forward_compact(const DevTables& t, int first, int cou
                            Off, amax, first, ngrp, cpg, nsplit, d.B, d.K);
 }
 
+static void launch_einsum_forward_small(const DevTables& t, int first, int count, int kout, const float* params, float* A,
+                                        double* Off, float* amax, const Dims& d, hipStream_t s) {
+    // chunks of an item share its weights as long as four workgroups per compute unit remain
+    const int nchunks = (d.B + 127) / 128, want = (4 * EINET_NUM_CUS + count - 1) / count;
+    const int cpg = (nchunks + want - 1) / want, ngrp = (nchunks + cpg - 1) / cpg;
+    // few items: the groups of four outputs of an item side by side
+    const int groups = (kout + 3) / 4;
+    int nsplit = 2 * EINET_NUM_CUS / (count * ngrp);
+    nsplit = nsplit < 1 ? 1 : nsplit > groups ? groups : nsplit;
+    hipLaunchKernelGGL(k_einsum_forward_small, dim3(count * ngrp * nsplit), dim3(256), FwdSmallLayout::LDS_BYTES, s,
+                       t.ein_rec + (size_t)first * EIN_REC_INTS, params, A, Off, amax, first, ngrp, cpg, nsplit, d.B, d.K, kout);
+}
+
 // Which kernel a layer takes.  Microseconds of a log-density of a tree of depth 2 (leaf layer, one layer of `count` items,
 // root: about 8 us besides the layer for few items, 2 to 3 times the layer's for many), measured for K 8 to 48, 2 to 1280
 // items, 1 to 1000 samples.  PLAIN: the float32 kernel with a workgroup per (item, four outputs), which has no operands to
 // split and walks the chunks of 128 samples one after the other.  WAVES: the float32 kernel with specialised waves.  COMPACT:
 // the short float32 kernel for whole items.
-enum FwdKernel { FWD_PLAIN, FWD_WAVES, FWD_COMPACT, FWD_DIRECT, FWD_X };
+enum FwdKernel { FWD_PLAIN, FWD_WAVES, FWD_COMPACT, FWD_SMALL, FWD_DIRECT, FWD_X };
 static FwdKernel einsum_forward_kernel(int count, int kout, const Dims& d) {
     const int K = d.K, B = d.B;
     const bool quads = (K & 3) == 0;                  // rows of 16-byte groups
     const int64_t units = (int64_t)count * ((B + 127) / 128) * ((kout + 3) / 4);
     // (one output per item would leave three of four rows of COMPACT's tiles empty; only items below the root have one)
+    // from 13 entries on and with many workgroups the split operands pay: log-density of a tree of 512 items, K = 13, 1000 samples:
+    // 112 with COMPACT, 90 with SMALL; K = 16, 103 and 95, 300 samples 57 and 59; K = 10: 84 and 85
+    if (K > 12 && K <= 16 && kout == K && units >= (quads ? 8192 : 1024)) return FWD_SMALL;
     if (K <= 16) return kout == K ? FWD_COMPACT : FWD_PLAIN;
     // K = 48, 2 items, 1000 samples: plain 63, waves 19; 320 items, 16 samples: 171, 148; 64 samples: 155, 157
     if (K == 48 && kout == K) return B > 32 && B <= 64 ? FWD_PLAIN : FWD_WAVES;
@@ -1217,6 +1384,7 @@ void launch_einsum_forward(const DevTables& t, int first, int count, bool full_k
     switch (einsum_forward_kernel(count, kout, d)) {
 #define EINET_CASE(J, F) case J: F<J>(t, first, count, kout, params, A, Off, amax, d, s); return;
 #undef EINET_CASE
+    case FWD_SMALL: launch_einsum_forward_small(t, first, count, kout, params, A, Off, amax, d, s); return;
     case FWD_COMPACT:
 #define EINET_CASE(J) case J: launch_einsum_forward_compact<J>(t, first, count, params, A, Off, amax, d, s); return;
         switch ((d.K + 3) / 4) { EINET_CASE(1) EINET_CASE(2) EINET_CASE(3) EINET_CASE(4) }

@@ -210,8 +210,8 @@ void launch_stats_small(const EinStatsWork& w, bool accumulate, float* stats, hi
 // Scales: eR and eL carry 2^24 each, so that the bits of their smallest normal numbers survive the split.  A row k of Q whose
 // largest value in the first step is outside 2^-40 .. 2^40 is multiplied by a power of two that brings it to 1, and by a
 // smaller one (the sums with it) when a later value would pass 2^40; so sums stay below 2^96.
-// Matrix and vector work are nearly additive here (one wave's products wait for its own splits): K = 40, 194 items: 37 us for
-// 128 samples, 224 us for 1000; K = 30, 140 items, 100 samples: 22.4 us.
+// Matrix and vector work are nearly additive here (one wave's products wait for its own splits): K = 40, 194 items: 41 us for
+// 128 samples, 229 us for 1000; K = 30, 140 items, 100 samples: 23 us.
 // STEP: samples that are staged at once.  32, the contraction of one instruction, or ST_WHOLE: the whole of a short batch.
 constexpr int ST_WHOLE = 128;
 template <int KQ, int NH, int STEP>
@@ -522,7 +522,9 @@ void launch_stats_units(const EinStatsWork& w, bool accumulate, float* stats, hi
 
 template <int KQ>
 void launch_stats_kq(const EinStatsWork& w, bool accumulate, float* stats, hipStream_t s) {
-    // a wave takes a whole slice where that gives every compute unit four waves; otherwise about three row tiles of it
+    // a wave takes a whole slice where that gives every compute unit four waves; otherwise about three row tiles of it (K = 40, 7
+    // items, 500 samples: 15.7 us, with whole slices 34.8).  Batches of ST_WHOLE at most in one step: K = 40, 194 items, 128
+    // samples: 40.9 us, in steps of 32 samples 49.2; K = 30, 140 items, 100 samples: 23.1 and 25.4
     constexpr int BIG = KQ > 12 ? 2 : 1, SMALL = (KQ + 2) / 3;
     if ((long long)w.count * KQ < 4 * EINET_NUM_CUS) {
         launch_stats_units<KQ, SMALL, 32>(w, accumulate, stats, s);

@@ -184,6 +184,7 @@ struct EinStatsWork {
     const float *params, *A, *amax, *G, *Gp, *img;
     const double* Off;
     int first, count, B, K;
+    int total;                       // items of all layers below the root's
 };
 // Few items above K = 16 with several chunks of 128 samples: the batch is split into this many shares (of whole chunks), so
 // that every wave of the chip has work of its own; a wave takes about three row tiles of a slice there.

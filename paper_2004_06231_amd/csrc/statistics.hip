@@ -674,7 +674,10 @@ void launch_tail_backward(const DevTables& t, int n_lv, int n_leaves, int max_sc
     // scopes that fill a tile of 16 pairs: on the matrix pipe.  Few tiles: one per workgroup, so that the batch fills the chip;
     // otherwise eight waves with a tile each, which split the posteriors once for all.  K = 40, 192 tiles, 128 samples: 14.5 us
     // and 20.6; 1000 samples 53 and 65; K = 16, 256 samples, flags: 9.4 and 22.3.
-    if (!categorical && max_scope * d.C >= 16) {
+    // Where a thread per entry has few samples to walk it is the shorter chain (64 pairs, K = 20, 100 samples: 6.4 us and 8.4; 16
+    // pairs, 2 samples: 4.7 and 9.4; 32 pairs, K = 30, 5120 variables, 100 samples: 14.4 and 12.8).
+    const bool matrix = max_scope * d.C >= 16 && (max_scope * d.C >= 512 || d.B > 128 || (int64_t)total * d.B > 4 << 20);
+    if (!categorical && matrix) {
         const int tiles = (max_scope * d.C + 15) / 16;
         const bool tile = (int64_t)n_leaves * tiles <= 2 * EINET_NUM_CUS;
         const int waves = LX_THREADS / 64, chunks = tile ? tiles : (tiles + waves - 1) / waves;

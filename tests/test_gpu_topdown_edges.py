@@ -37,6 +37,11 @@ CASES = [
     (rat(64, 5, 16), 9, 1, BERNOULLI, 1100, None, (0.1, 0.9)),             # 256 items, 18 chunks: three chunks per workgroup
     (rat(16, 2, 1), 16, 1, BERNOULLI, 1, None, (0.1, 0.9)),                # an item's outputs over four workgroups
     (rat(32, 2, 2), 20, 1, GAUSSIAN, 900, None, (0.2, 0.8)),               # four items: shares of the batch, the last ragged
+    (rat(16, 2, 1), 24, 1, GAUSSIAN, 128, None, (0.2, 0.8)),               # K 17 to 24, up to 128 samples: with the posteriors
+    (rat(16, 2, 1), 21, 1, GAUSSIAN, 129, None, (0.2, 0.8)),               # one more: in a launch of their own
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 29, 1, GAUSSIAN, 50, None, (0.2, 0.8)),          # K to 32 and few items, assembled posteriors
+    (rat(16, 2, 1), 37, 1, GAUSSIAN, 20, None, (0.2, 0.8)),                # K to 40 and fewer
+    (rat(64, 5, 16), 13, 1, BERNOULLI, 129, None, (0.1, 0.9)),             # split operands bottom-up: 256 items, two chunks
     (rat(600, 2, 2), 24, 1, BERNOULLI, 150, None, (1e-6, 1.0 - 1e-6)),     # posteriors and S~ over hundreds of binary orders
 ]
 
