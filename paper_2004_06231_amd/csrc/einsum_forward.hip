@@ -725,7 +725,7 @@ __global__ __launch_bounds__(512, 1) void k_einsum_forward_x(const int32_t* __re
     }
 }
 
-// ------------------------------------------------------------------ einsum layer, forward, K up to 16
+// ------------------------------------------------------------------ einsum layer, forward, K up to 16 and K = 20
 // A whole item fits a workgroup, and its launches are bound by their chain of requests and by the instructions that a compute
 // unit fetches once, so this kernel is kept short: float32 operands on v_mfma_f32_16x16x4_f32 (nothing to split), a wave
 // per 16 samples, all weights of the item in LDS as they are in memory.  A tile of the product T has the rows (four outputs
@@ -841,7 +841,7 @@ __global__ __launch_bounds__(256, 4) void k_einsum_forward_compact(const int32_t
 #pragma unroll
         for (int s = 0; s < KQ; ++s) erc[s] = er[s];
         if (chunk + 1 < c1) fetch_rows(chunk + 1);
-        float sk[4] = {0.f, 0.f, 0.f, 0.f};
+        float sk[KQ > 4 ? KQ : 4] = {};
 #pragma unroll
         for (int kt = 0; kt < KQ; ++kt) {
             if (kt >= q0 && kt < q1) {
@@ -863,7 +863,7 @@ __global__ __launch_bounds__(256, 4) void k_einsum_forward_compact(const int32_t
 #pragma unroll
         for (int kt = 0; kt < KQ; ++kt) sk[kt] = __logf(sk[kt]);
         float* row = A + (size_t)out * blk + (size_t)min(b, B - 1) * K;
-        if constexpr (QUADS) {
+        if constexpr (QUADS && KQ <= 4) {
             transpose_groups(sk);                         // .. now 4 g .. 4 g + 3
             if (b < B && g >= q0 && g < q1) *reinterpret_cast<floatx4*>(row + 4 * g) = floatx4{sk[0], sk[1], sk[2], sk[3]};
         } else {
@@ -1316,10 +1316,10 @@ static void launch_einsum_forward_compact(const DevTables& t, int first, int cou
     int nsplit = EINET_NUM_CUS / (count * ngrp);
     nsplit = nsplit < 1 ? 1 : nsplit > KQ ? KQ : nsplit;
     const int32_t* rec = t.ein_rec + (size_t)first * EIN_REC_INTS;
-    if (d.K == 4 * KQ)
+    if (KQ > 4 || d.K == 4 * KQ)
         hipLaunchKernelGGL((k_einsum_forward_compact<KQ, true>), dim3(count * ngrp * nsplit), dim3(256), 0, s, rec, params, A,
                            Off, amax, first, ngrp, cpg, nsplit, d.B, d.K);
-    else
+    else if constexpr (KQ <= 4)                           // (17 to 19 entries take other kernels)
         hipLaunchKernelGGL((k_einsum_forward_compact<KQ, false>), dim3(count * ngrp * nsplit), dim3(256), 0, s, rec, params, A,
                            Off, amax, first, ngrp, cpg, nsplit, d.B, d.K);
 }
@@ -1351,15 +1351,16 @@ static FwdKernel einsum_forward_kernel(int count, int kout, const Dims& d) {
     // from 13 entries on and with many workgroups the split operands pay: log-density of a tree of 512 items, K = 13, 1000 samples:
     // 112 with COMPACT, 90 with SMALL; K = 16, 103 and 95, 300 samples 57 and 59; K = 10: 84 and 85
     if (K > 12 && K <= 16 && kout == K && units >= (quads ? 8192 : 1024)) return FWD_SMALL;
-    if (K <= 16) return kout == K ? FWD_COMPACT : FWD_PLAIN;
+    // K = 20 (log-density, 1 / 100 / 1000 samples; COMPACT and the choice below): 194 items 48 / 54 / 109 and 52 / 57 / 129, 512 items
+    // 38 / 49 / 148 and 42 / 54 / 190.  Rows of 17 to 19 entries are not whole pieces: 194 items, 18 entries, 200 samples 68 and 63
+    if (K <= 16 || K == 20) return kout == K ? FWD_COMPACT : FWD_PLAIN;
     // K = 48, 2 items, 1000 samples: plain 63, waves 19; 320 items, 16 samples: 171, 148; 64 samples: 155, 157
     if (K == 48 && kout == K) return B > 32 && B <= 64 ? FWD_PLAIN : FWD_WAVES;
     if (K > 40) return FWD_PLAIN;
     if (K <= 20) {
-        // three octets for 17 to 20 entries: the split pays for few items only.  K = 18, 20 items, 16 samples: plain 18.3,
-        // direct 16.0; 500 samples 27.6, 23.1; 80 items, 1000 samples: 63.4, persistent 60.5; 1280 items, 1000 samples: 637,
-        // 723.  K = 20, 20 items, 64 samples: 15.2, direct 16.4; 256 samples 18.6, 17.2
-        if (units <= 1024 && (count < 64 ? !quads || B > 128 : !quads && B <= 16)) return FWD_DIRECT;
+        // three octets for 17 to 19 entries: the split pays for few items only.  K = 18, 20 items, 16 samples: plain 18.3, direct
+        // 16.0; 500 samples 27.6, 23.1; 80 items, 1000 samples: 63.4, persistent 60.5; 1280 items, 1000 samples: 637, 723
+        if (units <= 1024 && (count < 64 || B <= 16)) return FWD_DIRECT;
         return count <= 128 && B > 512 ? FWD_X : FWD_PLAIN;
     }
     // K = 24, 20 items: 16 samples plain 15.5, direct 15.3, persistent 15.4, waves 15.0; 64 samples 15.6, 16.7, 16.2, 15.8;
@@ -1387,7 +1388,7 @@ void launch_einsum_forward(const DevTables& t, int first, int count, bool full_k
     case FWD_SMALL: launch_einsum_forward_small(t, first, count, kout, params, A, Off, amax, d, s); return;
     case FWD_COMPACT:
 #define EINET_CASE(J) case J: launch_einsum_forward_compact<J>(t, first, count, params, A, Off, amax, d, s); return;
-        switch ((d.K + 3) / 4) { EINET_CASE(1) EINET_CASE(2) EINET_CASE(3) EINET_CASE(4) }
+        switch ((d.K + 3) / 4) { EINET_CASE(1) EINET_CASE(2) EINET_CASE(3) EINET_CASE(4) EINET_CASE(5) }
         return;
 #undef EINET_CASE
 #define EINET_CASE(J, F) case J: F<J>(t, first, count, kout, params, A, Off, amax, d, s); return;

@@ -41,6 +41,8 @@ CASES = [
     (rat(16, 2, 1), 21, 1, GAUSSIAN, 129, None, (0.2, 0.8)),               # one more: in a launch of their own
     (dict(kind="pd", H=6, W=6, deltas=[2]), 29, 1, GAUSSIAN, 50, None, (0.2, 0.8)),          # K to 32 and few items, assembled posteriors
     (rat(16, 2, 1), 37, 1, GAUSSIAN, 20, None, (0.2, 0.8)),                # K to 40 and fewer
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 20, 1, GAUSSIAN, 65, None, (0.2, 0.8)),          # whole items bottom-up, a second chunk of one sample
+    (rat(16, 2, 1), 20, 1, BERNOULLI, 1, None, (0.1, 0.9)),                # its outputs over five workgroups
     (rat(64, 5, 16), 13, 1, BERNOULLI, 129, None, (0.1, 0.9)),             # split operands bottom-up: 256 items, two chunks
     (rat(600, 2, 2), 24, 1, BERNOULLI, 150, None, (1e-6, 1.0 - 1e-6)),     # posteriors and S~ over hundreds of binary orders
 ]
