@@ -208,8 +208,10 @@ void launch_stats_small(const EinStatsWork& w, bool accumulate, float* stats, hi
 // next 32 samples are requested before the products of the current ones and go to the other half of the LDS after them.
 //
 // Scales: eR and eL carry 2^24 each, so that the bits of their smallest normal numbers survive the split.  A row k of Q whose
-// largest value in the first step is outside 2^-40 .. 2^40 is multiplied by a power of two that brings it to 1, and by a
-// smaller one (the sums with it) when a later value would pass 2^40; so sums stay below 2^96.
+// largest value in the first step that has one is outside 2^-40 .. 2^40 is multiplied by a power of two that brings it to 1, and
+// by a smaller one (the sums with it) from the step on whose values would pass 2^40; so sums stay below 2^96.  The threads that
+// stage a row choose its factor from the values as they are in memory, before they multiply: times the factor of the steps
+// before, a value may be beyond the largest float32.
 // Matrix and vector work are nearly additive here (one wave's products wait for its own splits): K = 40, 194 items: 41 us for
 // 128 samples, 229 us for 1000; K = 30, 140 items, 100 samples: 23 us.
 // STEP: samples that are staged at once.  32, the contraction of one instruction, or ST_WHOLE: the whole of a short batch.
@@ -227,13 +229,23 @@ struct StatLayout {
     static constexpr int NSLOT = UI < 7 ? 3 : 2, PER = 8; // most units of a workgroup
     static constexpr int NBUF = SEQ ? 1 : 2;
     static constexpr int OFF_L = NSLOT * SLOT;            // eL [8 waves][4][RF]
-    static constexpr int OFF_M = OFF_L + 8 * 4 * RF * 4;  // per slot: largest Q of the step [64]
+    static constexpr int OFF_M = OFF_L + 8 * 4 * RF * 4;  // per slot: what the factors of Q changed by with the step [64]
     static constexpr int BUF = OFF_M + NSLOT * 64 * 4;
-    static constexpr int OFF_F = NBUF * BUF;                 // per slot: factor, its change [64] each
-    static constexpr int LDS_BYTES = OFF_F + NSLOT * 2 * 64 * 4;
+    static constexpr int OFF_F = NBUF * BUF;              // per slot: factors of the rows of Q [64]
+    static constexpr int LDS_BYTES = OFF_F + NSLOT * 64 * 4;
     static constexpr int ROUNDS = (NSLOT * 2 * KP * 8 + 511) / 512;      // pieces of STEP / 8 samples per thread and step
     static_assert(LDS_BYTES <= 160 * 1024, "the rows fit the LDS of a compute unit");
 };
+
+// Factor of a row of Q, a power of two: top is the largest value of the step, old the factor so far, 0 where all values so far were
+// zero.
+__device__ __forceinline__ float stat_row_factor(float top, float old) {
+    if (top == 0.f) return old;
+    const int ex = (int)(__builtin_bit_cast(uint32_t, top) >> 23) - 127, exo = (int)(__builtin_bit_cast(uint32_t, old) >> 23) - 127;
+    const bool keep = old == 0.f ? top >= 0x1p-40f && top <= 0x1p+40f : ex + exo < 40;
+    if (keep) return old == 0.f ? 1.f : old;
+    return __builtin_bit_cast(float, (uint32_t)(127 - min(max(ex, -125), 125)) << 23);
+}
 
 // Short batches (STEP = ST_WHOLE): the units of a slice are taken one after the other by the same wave, so that the weights of
 // a unit's rows are requested before its products and the statistics of one unit are stored while the next is multiplied.
@@ -268,10 +280,12 @@ __global__ __launch_bounds__(512, 2) void k_einsum_stats(const int32_t* __restri
         return img + (size_t)(item0 + item) * isz + (size_t)(q - item * nshare) * share;
     };
     auto samples_of = [&](int sl) { return min(share, B - (vi0 + sl) % nshare * share); };
-    for (int e = tid; e < NSLOT * 2 * 64; e += 512) sF[e] = 1.f;
 
     // ---- staging: piece f = (row, STEP / 8 samples) of Q and of eR of the items; rows beyond K, samples beyond the batch: zero
     floatx4 x4[LY::ROUNDS][Q4], l4[Q4];
+    float fac[LY::ROUNDS];                             // of the row, if it is one of Q; 0: all its values so far were zero
+#pragma unroll
+    for (int x = 0; x < LY::ROUNDS; ++x) fac[x] = 0.f;
     auto fetch = [&](int s) {
 #pragma unroll
         for (int x = 0; x < LY::ROUNDS; ++x) {
@@ -299,32 +313,38 @@ __global__ __launch_bounds__(512, 2) void k_einsum_stats(const int32_t* __restri
             const int f = tid + 512 * x, b = PS * (f & 7), row = f >> 3, sl = row / (2 * KP), y = row - sl * 2 * KP;
             if (sl < nslot) {
                 char* dst = buf + sl * LY::SLOT;
-                float top = 0.f;
                 const int nsl = samples_of(sl);
-                const float fac = y < KP && s > 0 ? sF[sl * 128 + y] : 1.f;
+                floatx4 v[Q4];
 #pragma unroll
-                for (int q = 0; q < Q4; ++q) {
-                    floatx4 v;
+                for (int q = 0; q < Q4; ++q)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) v[c] = s + b + 4 * q + c < nsl ? x4[x][q][c] : 0.f;
-                    if (y >= KP) {
+                    for (int c = 0; c < 4; ++c) v[q][c] = s + b + 4 * q + c < nsl ? x4[x][q][c] : 0.f;
+                if (y >= KP) {
+#pragma unroll
+                    for (int q = 0; q < Q4; ++q) {
                         uint32_t p0[3], p1[3];
-                        split_bf16x3(v[0] * X6_SCALE, v[1] * X6_SCALE, p0[0], p0[1], p0[2]);
-                        split_bf16x3(v[2] * X6_SCALE, v[3] * X6_SCALE, p1[0], p1[1], p1[2]);
+                        split_bf16x3(v[q][0] * X6_SCALE, v[q][1] * X6_SCALE, p0[0], p0[1], p0[2]);
+                        split_bf16x3(v[q][2] * X6_SCALE, v[q][3] * X6_SCALE, p1[0], p1[1], p1[2]);
                         uint16_t* d = reinterpret_cast<uint16_t*>(dst) + (y - KP) * RB + b + 4 * q;
 #pragma unroll
                         for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(d + p * 16 * NJ * RB) = make_uint2(p0[p], p1[p]);
-                    } else {
-                        v *= fac;
-                        *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(dst + LY::OFF_Q) + y * RF + b + 4 * q) = v;
-                        top = fmaxf(fmaxf(fmaxf(top, v[0]), fmaxf(v[1], v[2])), v[3]);
                     }
-                }
-                if (y < KP) {
-                    top = fmaxf(top, __shfl_xor(top, 1, 64));
+                } else {
+                    float top = 0.f;
+#pragma unroll
+                    for (int q = 0; q < Q4; ++q) top = fmaxf(fmaxf(fmaxf(top, v[q][0]), fmaxf(v[q][1], v[q][2])), v[q][3]);
+                    top = fmaxf(top, __shfl_xor(top, 1, 64));       // (the eight lanes of a row)
                     top = fmaxf(top, __shfl_xor(top, 2, 64));
                     top = fmaxf(top, __shfl_xor(top, 4, 64));
-                    if (b == 0) reinterpret_cast<float*>(buf + LY::OFF_M)[sl * 64 + y] = top;
+                    const float old = fac[x], now = stat_row_factor(top, old);
+                    fac[x] = now;
+                    if (b == 0) {
+                        reinterpret_cast<float*>(buf + LY::OFF_M)[sl * 64 + y] = now == old || old == 0.f ? 1.f : now * (1.f / old);
+                        sF[sl * 64 + y] = now == 0.f ? 1.f : now;
+                    }
+#pragma unroll
+                    for (int q = 0; q < Q4; ++q)
+                        *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(dst + LY::OFF_Q) + y * RF + b + 4 * q) = v[q] * now;
                 }
             }
         }
@@ -399,7 +419,7 @@ __global__ __launch_bounds__(512, 2) void k_einsum_stats(const int32_t* __restri
 #pragma unroll
         for (int r = 0; r < NRT; ++r) {
             const int k = 4 * (kt0 + r) + kg;
-            const float inv = 1.f / sF[slot * 128 + min(k, 63)];
+            const float inv = 1.f / sF[slot * 64 + min(k, KP - 1)];
 #pragma unroll
             for (int jt = 0; jt < NJ; ++jt)
 #pragma unroll
@@ -422,42 +442,15 @@ __global__ __launch_bounds__(512, 2) void k_einsum_stats(const int32_t* __restri
     for (int s = 0; s < share; s += STEP) {
         __syncthreads();                               // the step is staged; readers of the other buffer are done
         char* here = lds_c + buf * LY::BUF;
-        {
-            // (every wave takes the same decision from the same values)
-            bool change = false;
+        if (!SEQ && s > 0 && work) {                   // (s = 0: no sums yet)
+            const float* change = reinterpret_cast<const float*>(here + LY::OFF_M) + slot * 64;
+            if (__any(lane < KP && change[min(lane, KP - 1)] != 1.f)) {
 #pragma unroll
-            for (int sl = 0; sl < NSLOT; ++sl)
-                if (sl < nslot && lane < KP) {
-                    const float m = reinterpret_cast<const float*>(here + LY::OFF_M)[sl * 64 + lane];
-                    if (s == 0) change = change || (m != 0.f && !(m >= 0x1p-40f && m <= 0x1p+40f));
-                    else change = change || !(m <= 0x1p+40f);
-                }
-            if (__any(change ? 1 : 0)) {
-                __syncthreads();                       // everyone has decided
-                if (tid < nslot * 64 && lane < KP) {
-                    const int sl = tid >> 6;
-                    const float m = reinterpret_cast<const float*>(here + LY::OFF_M)[sl * 64 + lane];
-                    const bool plain = m == 0.f || (m <= 0x1p+40f && (s > 0 || m >= 0x1p-40f));
-                    const int ex = min(max((int)(__builtin_bit_cast(uint32_t, m) >> 23) - 127, -125), 125);
-                    const float ch = plain ? 1.f : __builtin_bit_cast(float, (uint32_t)(127 - ex) << 23);
-                    sF[sl * 128 + 64 + lane] = ch;
-                    sF[sl * 128 + lane] *= ch;
-                }
-                __syncthreads();
-                for (int f = tid; f < nslot * KP * (STEP / 4); f += 512) {
-                    const int row = f / (STEP / 4), sl = row / KP, e = row - sl * KP;
-                    floatx4* p = reinterpret_cast<floatx4*>(here + sl * LY::SLOT + LY::OFF_Q) + e * (RF / 4) + f % (STEP / 4);
-                    *p *= sF[sl * 128 + 64 + e];
-                }
-                if (s > 0) {
+                for (int r = 0; r < NRT; ++r) {
+                    const float ch = change[min(4 * (kt0 + r) + kg, KP - 1)];
 #pragma unroll
-                    for (int r = 0; r < NRT; ++r) {
-                        const float ch = sF[slot * 128 + 64 + min(4 * (kt0 + r) + kg, KP - 1)];
-#pragma unroll
-                        for (int jt = 0; jt < NJ; ++jt) acc[r][jt] *= ch;
-                    }
+                    for (int jt = 0; jt < NJ; ++jt) acc[r][jt] *= ch;
                 }
-                __syncthreads();
             }
         }
         if constexpr (SEQ) {
