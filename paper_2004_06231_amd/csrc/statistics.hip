@@ -276,7 +276,8 @@ __global__ __launch_bounds__(256) void k_leaf_backward_categorical(
 // is a product with the batch as contraction, on the bfloat16 matrix pipe at float32 precision (bf16x6.hpp).  A wave takes
 // 16 pairs (the rows) and all entries k; a lane's operand, eight samples of its pair, comes straight from memory (a load
 // reads 16 pairs side by side) and is requested a step of 64 samples ahead; the flags are exact in bfloat16.  (Posteriors times
-// 2^24, so that the third part of a small one is a normal number; values and flags times 2^-24.)  The leaf's
+// 2^24, so that the third part of a small one is a normal number; values and flags times 2^-24.  Squares below 2^-85 would
+// lose bits by that: a wave that has met such values forms its sums again, see leaf_sums_float32.)  The leaf's
 // posteriors, which all waves share, are split into bfloat16 parts once per workgroup and step and go through LDS.
 // tot = sum_b p[b][k] is summed on the side.
 // Runs in one launch with the mixing statistics, hence the eight waves; `waves` of them have pairs.
@@ -284,6 +285,41 @@ __global__ __launch_bounds__(256) void k_leaf_backward_categorical(
 // 61 us, with the values staged through LDS for float32 matrix instructions and the batch cut into groups 91 + 10 us.
 constexpr int LX_THREADS = 512;
 constexpr int LX_STEP = 64, LX_RB = LX_STEP + 8;       // samples per step; row stride (bfloat16) of the posteriors
+// Smallest of `least` and of the values that are not zero, as twice its bits less one.
+__device__ __forceinline__ uint32_t smallest_value(uint32_t least, const float (&v)[8]) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) least = min(least, (__builtin_bit_cast(uint32_t, v[c]) << 1) - 1u);
+    return least;
+}
+__device__ __forceinline__ bool squares_lose_bits(uint32_t least) {
+    return __any(least < (__builtin_bit_cast(uint32_t, 0x1p-42f) << 1) - 1u);
+}
+// The sums of x p and x^2 p of a wave's 16 pairs once more, in float32 throughout: samples first .. first + run - 1 and every
+// `stride` on.  Only waves with values between 0 and 2^-42 come here.  xp, mp: the lane's pair; Gl: the leaf's gcnt blocks.
+template <bool MASK, int NJ>
+__device__ __forceinline__ void leaf_sums_float32(floatx4 (&sum)[2][NJ], int first, int run, int stride, const float* xp,
+                                               size_t xstride, const uint8_t* mp, size_t mstride, const float* Gl, int gcnt, int B,
+                                               int K) {
+    const int lane = threadIdx.x & 63, c16 = lane & 15, kg = lane >> 4;
+    const size_t gblk = (size_t)B * K;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt) sum[q][jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int s = first; s < B; s += stride)
+        for (int u = 0; u < run && s + u < B; u += 4) {
+            const int b = s + u + kg, bc = min(b, B - 1);      // lane group kg: one of four samples
+            const float x = !MASK || mp[bc * mstride] ? xp[bc * xstride] : 0.f;
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) {
+                const int k = 16 * jt + c16;
+                float p = 0.f;
+                for (int y = 0; y < gcnt; ++y) p += b < B && k < K ? Gl[y * gblk + (size_t)bc * K + k] : 0.f;
+                sum[0][jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, p, sum[0][jt], 0, 0, 0);
+                sum[1][jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x * x, p, sum[1][jt], 0, 0, 0);
+            }
+        }
+}
 template <bool SQ, bool MASK, int NJ, bool DIRECT>
 __device__ __forceinline__ void leaf_stats_body(
     int block, int chunks_per_leaf, int waves, const int32_t* __restrict__ leaf_node, const int32_t* __restrict__ leaf_replica,
@@ -361,6 +397,7 @@ __device__ __forceinline__ void leaf_stats_body(
     for (int q = 0; q < NK; ++q)
 #pragma unroll
         for (int jt = 0; jt < NJ; ++jt) acc[q][jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    uint32_t least = ~0u;
     fetch(0);
     stage(0);
     for (int s = 0, buf = 0; s < d.B; s += LX_STEP, buf ^= 1) {
@@ -370,6 +407,7 @@ __device__ __forceinline__ void leaf_stats_body(
         for (int u = 0; u < LX_STEP / 32; ++u) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) xc[u][q] = !MASK || ob[u][q] ? xv[u][q] : 0.f;
+            if (SQ && work) least = smallest_value(least, xc[u]);
             if (MASK) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) one[u][q] = (ob[u][2 * q] ? 0x3380u : 0u) | (ob[u][2 * q + 1] ? 0x33800000u : 0u);
@@ -420,6 +458,16 @@ __device__ __forceinline__ void leaf_stats_body(
     }
     __syncthreads();
     if (!work) return;
+    if constexpr (SQ) {
+        if (squares_lose_bits(least)) {
+            floatx4 sum[2][NJ];
+            leaf_sums_float32<MASK, NJ>(sum, 0, d.B, d.B, xp, xstride, mp, mask_mode == EINET_MASK_PER_SAMPLE ? d.D : 0, Gl, gcnt, d.B, d.K);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) acc[q][jt] = sum[q][jt];
+        }
+    }
     // acc[q][jt][v]: pair 16 tile + 4 kg + v, entry 16 jt + c16
     const int r = leaf_replica[leaf];
 #pragma unroll
@@ -488,6 +536,7 @@ __device__ __forceinline__ void leaf_tile_body(
         for (int jt = 0; jt < NJ; ++jt) acc[q][jt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int y = 0; y < NI; ++y) tot[y] = 0.f;
+    uint32_t least = ~0u;
     for (int s = 32 * wave; s < d.B; s += 256) {
         float g[NI][4], xv[8];
         uint8_t ob[8];
@@ -532,14 +581,16 @@ __device__ __forceinline__ void leaf_tile_body(
 #pragma unroll
             for (int p = 0; p < 3; ++p) pb[jt][p] = *reinterpret_cast<const uint32x4*>(ps + (p * NR + 16 * jt + c16) * LY::RB + 8 * kg);
         constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};     // (small parts first)
+        if (MASK) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) xv[c] = ob[c] ? xv[c] : 0.f;
+        }
+        if (SQ) least = smallest_value(least, xv);
 #pragma unroll
         for (int q = 0; q < (SQ ? 2 : 1); ++q) {
             float w[8];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const float v = !MASK || ob[c] ? xv[c] : 0.f;
-                w[c] = v * (q == 0 ? 1.f : v) * (1.f / X6_SCALE);
-            }
+            for (int c = 0; c < 8; ++c) w[c] = xv[c] * (q == 0 ? 1.f : xv[c]) * (1.f / X6_SCALE);
             uint32x4 a[3];
             split_octet(w, a[0], a[1], a[2]);
             floatx4 t[NJ];
@@ -559,6 +610,17 @@ __device__ __forceinline__ void leaf_tile_body(
             for (int p = 0; p < 3; ++p)
 #pragma unroll
                 for (int jt = 0; jt < NJ; ++jt) acc[NK - 1][jt] = mfma_bf16(one, pb[jt][p], acc[NK - 1][jt]);
+        }
+    }
+    if constexpr (SQ) {
+        if (squares_lose_bits(least)) {
+            floatx4 sum[2][NJ];
+            leaf_sums_float32<MASK, NJ>(sum, 32 * wave, 32, 256, xp, xstride, mp, mask_mode == EINET_MASK_PER_SAMPLE ? d.D : 0, Gl, gcnt,
+                                        d.B, d.K);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) acc[q][jt] = sum[q][jt];
         }
     }
     __syncthreads();                                   // every wave is done with its posteriors

@@ -1,12 +1,14 @@
 """GPU parity of the EM statistics for values at the ends of float32: rows of Q = G / S~ whose size changes by many orders
-within a batch, between the samples that are contracted together.  A binary tree of depth 2 whose einsum items pass entry k
-of both children on (one weight per output), so that the size of every quantity is set by the leaves."""
+within a batch, between the samples that are contracted together, and Gaussian data of which some columns are tiny.  For the
+former a binary tree of depth 2 whose einsum items pass entry k of both children on (one weight per output), so that the size
+of every quantity is set by the leaves."""
 import numpy as np
 import pytest
 import torch
 
-from oracle.einet import BERNOULLI
+from oracle.einet import BERNOULLI, GAUSSIAN
 from tests.common import make_oracle
+import workloads
 from tests.gpu_common import gpu_model, dev, assert_logp_close, assert_stats_close, stat_tensors, STAT_RTOL
 
 pytestmark = pytest.mark.gpu
@@ -92,4 +94,32 @@ def test_smallest_posteriors_keep_their_bits(K, kinds):
         seen = want[name] > 2.0 ** -120
         assert np.sum(seen & (want[name] < 2.0 ** -100)) > 0
         assert np.all(np.abs(got[name] - want[name])[seen] <= STAT_RTOL * want[name][seen]), name
+    m.close()
+
+
+@pytest.mark.parametrize("D,depth,R,K,C,B,mask_kind", [
+    (64, 1, 1, 20, 1, 300, None),                      # a tile of 16 pairs per workgroup
+    (64, 1, 1, 10, 1, 300, "per_sample"),
+    (1024, 1, 9, 17, 1, 140, None),                    # eight tiles per workgroup
+    (1024, 1, 9, 10, 1, 140, "shared"),
+])
+def test_statistics_of_tiny_values(D, depth, R, K, C, B, mask_kind):
+    """Columns whose values are near 1e-14 and 1e-18 throughout, beside ordinary ones, and a column with tiny values in half of
+    its samples: every sum of squares is as accurate as that of ordinary values (float32: 2^-24 for each of the products and of
+    the posterior's exponentials; sums over the batch of one sign)."""
+    spec = dict(kind="rat", D=D, depth=depth, R=R)
+    oracle, flat, rng = make_oracle(spec, K, C, GAUSSIAN, 77, leaf_range=(0.2, 0.8))
+    x = workloads.draw_data(rng, dict(kind="gaussian_mixture", components=3, std=0.3), B, D, C)
+    x[:, 0::5] *= np.float32(1e-14)
+    x[:, 1::5] *= np.float32(1e-18)
+    x[B // 2:, 2::5] *= np.float32(1e-15)
+    mask = workloads.draw_mask(rng, None if mask_kind is None else dict(kind=mask_kind, observed_fraction=0.6), B, D)
+    print("tiny values", D, K, B, mask_kind, flush=True)
+    m = gpu_model(spec, K, C, GAUSSIAN, B, 77, flat)
+    ref = oracle.stats_to_flat(oracle.em_accumulate(x, mask)[0])
+    m.em_accumulate(dev(x), dev(mask), None)
+    got, want = (stat_tensors(f, oracle.layout, m.n_params)["num"] for f in (m.stats.cpu().numpy().astype(np.float64), ref))
+    seen = want > 2.0 ** -120
+    assert want[seen].min() < 1e-30
+    assert np.all(np.abs(got - want)[seen] <= STAT_RTOL * want[seen])
     m.close()
