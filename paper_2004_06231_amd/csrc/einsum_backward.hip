@@ -85,7 +85,7 @@ template <int K8>
 struct PostLayout {
     using X = X6<K8>;
     static constexpr int KP = X::KP, NT = X::NT;
-    static constexpr int SG = K8 == 3 ? 3 : K8 == 4 ? 2 : 1;   // slices per stage
+    static constexpr int SG = post_slices(K8);            // slices per stage
     static constexpr int TU = X::UNITS + 1;               // 16-byte units of a tile: consecutive tiles in different banks
     static constexpr int SLICE = NT * TU;                 // units of a slice
     static constexpr int NBUF = 2 * SG * SLICE * 16 <= 160 * 1024 ? 2 : 1;
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(256, PostLayout<K8>::WAVES) void k_einsum_posterior
 #pragma unroll
         for (int x = 0; x < NL; ++x) {
             if (wsl[x] < SG) {
-            const float* p = W + wsrc[x] + (size_t)(EXACT ? 4 * it + wil[x] : min(4 * it + wil[x], K - 1)) * K;
+            const float* p = W + wsrc[x] + (size_t)post_weight_row<K8, EXACT>(it, wil[x], K) * K;
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) {
                 wv[x][kk] = *reinterpret_cast<const floatx4u*>(p + kk * K * K);
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(256, PostLayout<K8>::WAVES) void k_einsum_posterior
             for (int sl = 0; sl < SG; ++sl) {
                 const int i = 4 * (it + sl);
                 if (quads) {
-                    lraw[s][sl] = *reinterpret_cast<const floatx4u*>(Lp[s] + (EXACT ? i : min(i, K - 4)));
+                    lraw[s][sl] = *reinterpret_cast<const floatx4u*>(Lp[s] + post_left_entry<K8, EXACT>(it + sl, K));
                 } else {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) lraw[s][sl][c] = Lp[s][min(i + c, K - 1)];

@@ -128,6 +128,29 @@ inline int32_t bwd_block_code(int count, int q) { return q == 0 ? 0 : (q + 1) * 
 __host__ __device__
 #endif
 inline bool bwd_block_used(int32_t code, int nchunks) { return (long long)code * nchunks <= bwd_workgroups(nchunks); }
+// The top-down kernel above K = 16 (K8 = ceil(K / 8), EXACT: K is 8 K8) brings in post_slices(K8) slices of an item's weights
+// at a time, whether or not the workgroup has that many left.  Row i of W that row r (0 .. 4 post_slices - 1) of the stage from
+// slice `it` on is read from, and the first of the four left entries read for slice `it`: in range for slices that do not exist.
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+constexpr int post_slices(int K8) { return K8 == 3 ? 3 : K8 == 4 ? 2 : 1; }
+template <int K8, bool EXACT>
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline int post_weight_row(int it, int r, int K) {
+    const int i = 4 * it + r;
+    return (EXACT && post_slices(K8) == 1) || i < K ? i : K - 1;
+}
+template <int K8, bool EXACT>
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline int post_left_entry(int it, int K) {
+    const int i = 4 * it;
+    return (EXACT && post_slices(K8) == 1) || i < K - 4 ? i : K - 4;
+}
 // Workgroups per item of the root's layer (its kernel takes all chunks in one workgroup).
 inline int root_bwd_groups_per_item(int count, int K) {
     const int kq = (K + 3) / 4;

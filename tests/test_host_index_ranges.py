@@ -1,0 +1,61 @@
+"""Index arithmetic that kernels share with the host, run on the CPU for every launch shape: a read whose value is dropped
+shows in no result, and must stay inside the caller's buffers all the same."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2004_06231_amd", "csrc")
+
+PROGRAM = r"""
+#include "kernels.hpp"
+#include <cstdio>
+using namespace einet_impl;
+
+// every stage of every workgroup of an item, as k_einsum_posterior walks them
+template <int K8, bool EXACT>
+int walk(int K) {
+    const int slices = (K + 3) / 4, sg = post_slices(K8);
+    int bad = 0;
+    for (int count = 1; count <= 300; ++count)
+        for (int nchunks = 1; nchunks <= 8; ++nchunks) {
+            const int ngr = bwd_groups_per_item(count, K, nchunks);
+            for (int grp = 0; grp < ngr; ++grp)
+                for (int it = grp * slices / ngr; it < (grp + 1) * slices / ngr; it += sg) {
+                    for (int r = 0; r < 4 * sg; ++r) {
+                        const int row = post_weight_row<K8, EXACT>(it, r, K);
+                        bad += row < 0 || row >= K || (4 * it + r < K && row != 4 * it + r);
+                    }
+                    for (int sl = 0; sl < sg; ++sl) {
+                        const int e = post_left_entry<K8, EXACT>(it + sl, K);
+                        bad += (K & 3) == 0 && (e < 0 || e + 3 >= K || (4 * (it + sl) < K && e != 4 * (it + sl)));
+                    }
+                }
+        }
+    if (bad) printf("K = %d: %d reads outside the item\n", K, bad);
+    return bad;
+}
+template <int K8>
+int walk_k8() {
+    int bad = walk<K8, true>(8 * K8);
+    for (int K = 8 * K8 - 7; K < 8 * K8; ++K) bad += walk<K8, false>(K);
+    return bad;
+}
+int main() {
+    return walk_k8<3>() + walk_k8<4>() + walk_k8<5>() + walk_k8<6>() + walk_k8<7>() + walk_k8<8>() ? 1 : 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"),
+                    reason="needs g++ and the HIP headers")
+def test_reads_of_the_posterior_kernel_stay_inside_the_item(tmp_path):
+    src, exe = tmp_path / "walk.cpp", str(tmp_path / "walk")
+    src.write_text(PROGRAM)
+    res = subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC, str(src),
+                          "-o", exe], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-3000:]
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stdout
