@@ -255,7 +255,7 @@ __global__ __launch_bounds__(512, 2) void k_einsum_stats(const int32_t* __restri
                                                        int item0, int count, int per, int nshare, int share,
                                                        float* __restrict__ part, int B, int K) {
     using LY = StatLayout<KQ, NH, STEP>;
-    constexpr int KP = LY::KP, NJ = LY::NJ, NRT = LY::NRT, RB = LY::RB, RF = LY::RF, NSLOT = LY::NSLOT, UI = LY::UI;
+    constexpr int KP = LY::KP, NJ = LY::NJ, NRT = LY::NRT, RB = LY::RB, RF = LY::RF, UI = LY::UI;
     constexpr bool SEQ = LY::SEQ;
     constexpr int NU = SEQ ? 1 : NH, Q4 = STEP / 32, PS = STEP / 8;      // units per slice, 16-byte groups and samples of a piece
     extern __shared__ __attribute__((aligned(16))) char lds_c[];
