@@ -14,9 +14,9 @@ namespace {
 // the root).  Element-wise, one thread per (region, b, k); summing here instead of
 // scattering from the producers keeps the pass free of atomics.
 __global__ void k_region_assemble(const int32_t* __restrict__ r_rec, const int32_t* __restrict__ r_pblk, int is_root,
-                                  float* __restrict__ G, const float* __restrict__ Gp, int nchunks, int B, int K) {
+                                  float* __restrict__ G, const float* __restrict__ Gp, int limit, int B, int K) {
     // the region's record: node, entries, number of parent blocks, start of its block list, first blocks (block number,
-    // code: see bwd_block_used)
+    // code: used if at most limit)
     const int32_t* rec = r_rec + (size_t)blockIdx.x * RB_REC_INTS;
     const int node = rec[0], kout = rec[1], cnt = rec[2];
     const int e = blockIdx.y * blockDim.x + threadIdx.x;
@@ -35,7 +35,7 @@ __global__ void k_region_assemble(const int32_t* __restrict__ r_rec, const int32
 #pragma unroll
             for (int q = 0; q < RND; ++q) {
                 const int32_t* en = rec + 4 + 2 * (r * RND + q);
-                v[q] = r * RND + q < cnt && bwd_block_used(en[1], nchunks) ? Gp[(size_t)en[0] * blk + o] : 0.f;
+                v[q] = r * RND + q < cnt && en[1] <= limit ? Gp[(size_t)en[0] * blk + o] : 0.f;
             }
 #pragma unroll
             for (int q = 0; q < RND; ++q) g += v[q];
@@ -46,7 +46,7 @@ __global__ void k_region_assemble(const int32_t* __restrict__ r_rec, const int32
         float v[16];
 #pragma unroll
         for (int q = 0; q < 16; ++q)
-            v[q] = p0 + q < cnt && bwd_block_used(list[2 * (p0 + q) + 1], nchunks) ? Gp[(size_t)list[2 * (p0 + q)] * blk + o] : 0.f;
+            v[q] = p0 + q < cnt && list[2 * (p0 + q) + 1] <= limit ? Gp[(size_t)list[2 * (p0 + q)] * blk + o] : 0.f;
 #pragma unroll
         for (int q = 0; q < 16; ++q) g += v[q];
     }
@@ -1079,7 +1079,7 @@ void launch_region_assemble(const DevTables& t, int first, int count, bool is_ro
     if (count == 0) return;
     dim3 grid(count, (d.B * d.K + 255) / 256);
     hipLaunchKernelGGL(k_region_assemble, grid, dim3(256), 0, s, t.rb_rec + (size_t)first * RB_REC_INTS, t.rb_pblk,
-                       is_root_layer ? 1 : 0, G, Gp, (d.B + 127) / 128, d.B, d.K);
+                       is_root_layer ? 1 : 0, G, Gp, bwd_block_limit((d.B + 127) / 128), d.B, d.K);
 }
 
 template <int KQ>

@@ -95,7 +95,7 @@ void launch_root_backward(const DevTables& t, int n_partitions, const int32_t* e
 
 // Every top-down region also has a record of RB_REC_INTS ints in rb_rec: node, entries, number of parent blocks,
 // position of its list in rb_pblk, then the first RB_REC_BLOCKS blocks, two ints each (the rest, if any, only in the list):
-// block number, and the code that says whether the block is written (bwd_block_used).
+// block number, and the code that says whether the block is written (bwd_block_limit).
 constexpr int RB_REC_INTS = 64, RB_REC_BLOCKS = 28;
 void launch_region_assemble(const DevTables& t, int first, int count, bool is_root_layer, float* G, const float* Gp,
                             const Dims& d, hipStream_t s);
@@ -122,12 +122,11 @@ inline int bwd_groups_per_item(int count, int K, int nchunks) {
     return g > kq ? kq : g;
 }
 // Code of right-child block 1 + q of an item in a layer of `count` items: the block is written when q < groups, that is
-// when (q + 1) * count * nchunks is at most bwd_workgroups(nchunks); 0: always.
+// when (q + 1) * count * nchunks is at most bwd_workgroups(nchunks); 0: always.  So the blocks in use are those whose code is at
+// most bwd_block_limit(nchunks) (one comparison per block in the kernel that adds them up; with the product in its place EM
+// steps of 32x32 images, six such launches each, took 1 to 2 % longer: K = 25, one sample 167 us and 165, K = 40: 221 and 219).
 inline int32_t bwd_block_code(int count, int q) { return q == 0 ? 0 : (q + 1) * count; }
-#if defined(__HIPCC__)
-__host__ __device__
-#endif
-inline bool bwd_block_used(int32_t code, int nchunks) { return (long long)code * nchunks <= bwd_workgroups(nchunks); }
+inline int32_t bwd_block_limit(int nchunks) { return bwd_workgroups(nchunks) / nchunks; }
 // The top-down kernel above K = 16 (K8 = ceil(K / 8), EXACT: K is 8 K8) brings in post_slices(K8) slices of an item's weights
 // at a time, whether or not the workgroup has that many left.  Row i of W that row r (0 .. 4 post_slices - 1) of the stage from
 // slice `it` on is read from, and the first of the four left entries read for slice `it`: in range for slices that do not exist.
