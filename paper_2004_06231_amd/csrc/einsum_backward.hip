@@ -100,13 +100,15 @@ struct PostLayout {
 // ------------------------------------------------------------------ the same, K up to 16
 // A whole item fits a workgroup and its launches are bound by their chain of requests and by the instructions that a
 // compute unit fetches once, so this kernel is kept short: float32 operands on v_mfma_f32_16x16x4_f32 (nothing to split or
-// to scale), a wave per 16 samples, all weights of the item in LDS as they are in memory.  Rows come in as one 16-byte
+// to scale), a wave per 16 samples, the weights of the workgroup's slices in LDS as they are in memory.  Rows come in as one 16-byte
 // piece per lane (lane group g: entries 4 g .. 4 g + 3) and are transposed over the lane groups into the operand layout,
 // outputs leave the same way.
 // Us of a launch (in brackets as above): K = 10, 100 samples, 20 / 80 / 160 / 320 / 640 / 1280 items: 5.6 / 5.5 / 6.5 / 8.0 / 10.4 /
 // 16.7 (8.2 / 8.2 / 14.4 / 17.2 / 27.5 / 43.0); K = 16, 256 samples, 40 items: 6.1.
+// Few items: their slices over several workgroups as above.  EM step of 32x32 images (five layers of 20 to 60 items), one / 64
+// samples, K = 10: 99 / 111 us, K = 13: 104 / 115, K = 16: 94 / 108; with a workgroup per item 104 / 113, 114 / 123, 104 / 114 (99 / 111,
+// 100 / 113, 98 / 106).
 // QUADS: K is 4 KQ (see load_piece).
-constexpr int PS_SAMPLES = 64;
 template <int KQ>
 struct PostSmall {
     static constexpr int KP = 4 * KQ;
@@ -116,11 +118,12 @@ struct PostSmall {
 
 // STATS (batches of PS_SAMPLES at most): the workgroup has all operands of its item's weight statistics (Eq. 6) and forms
 // them too, which saves their launch: a wave contracts its 16 samples, the four waves' sums meet in LDS.
-template <int KQ, bool QUADS, bool STATS, bool ACCUM>
+// SPLIT: several workgroups per item (with STATS only, see bwd_groups_per_item).
+template <int KQ, bool QUADS, bool STATS, bool ACCUM, bool SPLIT>
 __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posterior_small(
     const int32_t* __restrict__ e_rec, const float* __restrict__ params, float* __restrict__ stats, const float* __restrict__ A,
     const double* __restrict__ Off, const float* __restrict__ amax, const float* __restrict__ G, float* Gp, int item0,
-    int nchunks, int direct, int nblk, int B, int K_) {
+    int nchunks, int ngr_, int direct, int nblk, int B, int K_) {
     using LY = PostSmall<KQ>;
     constexpr int SI = LY::SI, S = LY::S, KP = LY::KP;
     __shared__ __attribute__((aligned(16))) float wl[KP * S];
@@ -131,19 +134,31 @@ __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posteri
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c16 = lane & 15, g = lane >> 4;
     const int vb = xcd_contiguous_block();
-    const int li = vb / nchunks, chunk = vb - li * nchunks;
+    const int ngr = SPLIT ? ngr_ : 1, grp = vb % ngr, chunk = (vb / ngr) % nchunks, li = vb / (ngr * nchunks);
+    const int it0 = SPLIT ? grp * KQ / ngr : 0, it1 = SPLIT ? (grp + 1) * KQ / ngr : KQ;       // blocks of four left entries
     const int32_t* rec = e_rec + (size_t)li * EIN_BREC_INTS;
     const int left = rec[0], right = rec[1], out = rec[2], reg = rec[3], voff = rec[5], vstr = rec[6], src = rec[7], srcn = rec[8];
     const size_t blk = (size_t)B * K;
     const float* W = params + rec[4];
 
-    // ---- the weights: pieces of rows (k, i), consecutive threads consecutive pieces
+    // ---- the weights: pieces of rows (k, i), consecutive threads consecutive pieces; what does not exist is zeros
     constexpr int NW = (KP * KP * KQ + 255) / 256;
+    const int ni = 4 * (it1 - it0), npiece = KP * ni * KQ;
+    const float rni = 1.f / (float)ni;
+    auto piece_of = [&](int f, int& k, int& i, int& p) {
+        const int r = f / KQ;
+        p = f - r * KQ;
+        k = SPLIT ? (int)(((float)r + 0.5f) * rni) : r / KP;          // r / ni (r < 256)
+        i = 4 * it0 + r - k * ni;
+    };
     float w[NW][4];
 #pragma unroll
     for (int x = 0; x < NW; ++x) {
-        const int f = min(tid + 256 * x, K * K * KQ - 1);
-        load_piece<KQ, QUADS>(W + (size_t)(f / KQ) * K, f % KQ, K, w[x]);
+        if (256 * x < npiece) {
+            int k, i, p;
+            piece_of(min(tid + 256 * x, npiece - 1), k, i, p);
+            load_piece<KQ, QUADS>(W + (size_t)(min(k, K - 1) * K + min(i, K - 1)) * K, p, K, w[x]);
+        }
     }
     // ---- this lane's piece of its sample's rows
     const int b = chunk * PS_SAMPLES + 16 * wave + c16, bc = min(b, B - 1);
@@ -167,8 +182,8 @@ __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posteri
 #pragma unroll
             for (int c = 0; c < 4; ++c) v[c] = params[voff + min(4 * gp + c, K - 1) * vstr];
         }
-        // (the item below the root may have its region's posterior in several blocks, at most KQ)
-        const int gcnt = direct ? bwd_source_blocks(srcn, K, 1) : 1;
+        // (a posterior may be in several blocks, at most KQ)
+        const int gcnt = direct ? bwd_source_blocks(srcn, K, B) : 1;
         float more[KQ][4];
 #pragma unroll
         for (int x = 1; x < KQ; ++x)
@@ -204,22 +219,15 @@ __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posteri
         transpose_groups(q);                              // q[s]: entry k = 4 s + g, er[t]: entry j = 4 t + g
         transpose_groups(er);
     }
-    if constexpr (!QUADS) {                               // entries that do not exist are zeros
-        for (int f = tid; f < KP * S / 4; f += 256) *reinterpret_cast<floatx4*>(wl + 4 * f) = floatx4{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();
-    }
 #pragma unroll
     for (int x = 0; x < NW; ++x) {
-        const int f = tid + 256 * x, r = f / KQ, p = f % KQ, k = r / K, i = r - k * K;
-        if (f < K * K * KQ) {
-            float* dst = wl + k * S + i * SI + 4 * p;
-            if constexpr (QUADS) {
-                *reinterpret_cast<floatx4*>(dst) = floatx4{w[x][0], w[x][1], w[x][2], w[x][3]};
-            } else {
+        int k, i, p;
+        piece_of(tid + 256 * x, k, i, p);
+        if (tid + 256 * x < npiece) {
+            floatx4 v;
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (4 * p + c < K) dst[c] = w[x][c];
-            }
+            for (int c = 0; c < 4; ++c) v[c] = QUADS || (k < K && i < K && 4 * p + c < K) ? w[x][c] : 0.f;
+            *reinterpret_cast<floatx4*>(wl + k * S + i * SI + 4 * p) = v;
         }
     }
     __syncthreads();
@@ -228,6 +236,7 @@ __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posteri
         float gr[4] = {0.f, 0.f, 0.f, 0.f}, glf[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int it = 0; it < KQ; ++it) {
+            if (it < it0 || it >= it1) continue;
             float gl[4] = {0.f, 0.f, 0.f, 0.f};
             floatx4 acc[KQ];
 #pragma unroll
@@ -256,17 +265,15 @@ __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posteri
             transpose_groups(gr);
         }
         float* gleft = Gp + (size_t)(item0 + li) * nblk * blk + (size_t)b * K;
-        float* gright = gleft + blk;
+        float* gright = gleft + (size_t)(1 + grp) * blk;
         if (QUADS) {
-            if (g < KQ && b < B) {
-                *reinterpret_cast<floatx4*>(gleft + 4 * g) = floatx4{glf[0], glf[1], glf[2], glf[3]};
-                *reinterpret_cast<floatx4*>(gright + 4 * g) = floatx4{gr[0], gr[1], gr[2], gr[3]};
-            }
+            if (g >= it0 && g < it1 && b < B) *reinterpret_cast<floatx4*>(gleft + 4 * g) = floatx4{glf[0], glf[1], glf[2], glf[3]};
+            if (g < KQ && b < B) *reinterpret_cast<floatx4*>(gright + 4 * g) = floatx4{gr[0], gr[1], gr[2], gr[3]};
         } else {
 #pragma unroll
             for (int t = 0; t < KQ; ++t)
                 if (4 * t + g < K && b < B) {
-                    gleft[4 * t + g] = glf[t];
+                    if (t >= it0 && t < it1) gleft[4 * t + g] = glf[t];
                     gright[4 * t + g] = gr[t];
                 }
         }
@@ -290,6 +297,7 @@ __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posteri
                 for (int kt = 0; kt < KQ; ++kt) qa[kt] = row[4 * kt + (c16 >> 2)];
 #pragma unroll
                 for (int it = 0; it < KQ; ++it) {
+                    if (it < it0 || it >= it1) continue;
                     const float la = row[512 + 4 * it + (c16 & 3)];
 #pragma unroll
                     for (int kt = 0; kt < KQ; ++kt) acc[it][kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[kt] * la, rb, acc[it][kt], 0, 0, 0);
@@ -301,6 +309,7 @@ __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posteri
         floatx4* red = reinterpret_cast<floatx4*>(sx);    // [wave][kt][lane]
 #pragma unroll
         for (int it = 0; it < KQ; ++it) {
+            if (it < it0 || it >= it1) continue;
             const int k = 4 * wave + g;
             const bool own = wave < KQ && k < K && c16 < K;
             float old[4] = {0.f, 0.f, 0.f, 0.f};
@@ -430,7 +439,7 @@ __global__ __launch_bounds__(256, PostLayout<K8>::WAVES) void k_einsum_posterior
     float* iR = iQ + (size_t)(4 * nte) * Bp;
     float* iL = iR + (size_t)(4 * nte) * Bp;
     if (active) {
-        const int gcnt = direct ? bwd_source_blocks(rec[8], K, nchunks) : 1;
+        const int gcnt = direct ? bwd_source_blocks(rec[8], K, B) : 1;
         const float* Gs = direct ? Gp + (size_t)rec[7] * blk : G + (size_t)reg * blk;
         const float* As = A + (size_t)reg * blk;
         fetch_l(it0);
@@ -641,20 +650,22 @@ template <int KQ>
 void launch_posterior_small(const DevTables& t, int first, int count, bool with_stats, bool accumulate, const float* params,
                             float* stats, const float* A, const double* Off, const float* amax, const float* G, float* Gp,
                             bool direct, const Dims& d, hipStream_t s) {
-    const int nchunks = (d.B + PS_SAMPLES - 1) / PS_SAMPLES;
-#define EINET_LAUNCH(Q, ST, ACC)                                                                                             \
-    hipLaunchKernelGGL((k_einsum_posterior_small<KQ, Q, ST, ACC>), dim3(count * nchunks), dim3(256), 0, s,                    \
-                       t.ein_brec + (size_t)first * EIN_BREC_INTS, params, stats, A, Off, amax, G, Gp, first, nchunks,        \
+    const int nchunks = (d.B + PS_SAMPLES - 1) / PS_SAMPLES, ngr = bwd_groups_per_item(count, d.K, d.B);
+#define EINET_LAUNCH(Q, ST, ACC, SP)                                                                                         \
+    hipLaunchKernelGGL((k_einsum_posterior_small<KQ, Q, ST, ACC, SP>), dim3(count * nchunks * ngr), dim3(256), 0, s,              \
+                       t.ein_brec + (size_t)first * EIN_BREC_INTS, params, stats, A, Off, amax, G, Gp, first, nchunks, ngr,   \
                        direct ? 1 : 0, gp_blocks_per_item(d.K), d.B, d.K)
-    if (d.K == 4 * KQ) {
-        if (!with_stats) EINET_LAUNCH(true, false, false);
-        else if (accumulate) EINET_LAUNCH(true, true, true);
-        else EINET_LAUNCH(true, true, false);
-    } else {
-        if (!with_stats) EINET_LAUNCH(false, false, false);
-        else if (accumulate) EINET_LAUNCH(false, true, true);
-        else EINET_LAUNCH(false, true, false);
-    }
+#define EINET_LAUNCH_Q(Q)                                                     \
+    do {                                                                      \
+        if (!with_stats) EINET_LAUNCH(Q, false, false, false);                \
+        else if (KQ > 2 && ngr > 1 && accumulate) EINET_LAUNCH(Q, true, true, (KQ > 2)); \
+        else if (KQ > 2 && ngr > 1) EINET_LAUNCH(Q, true, false, (KQ > 2));   \
+        else if (accumulate) EINET_LAUNCH(Q, true, true, false);              \
+        else EINET_LAUNCH(Q, true, false, false);                             \
+    } while (0)
+    if (d.K == 4 * KQ) EINET_LAUNCH_Q(true);
+    else EINET_LAUNCH_Q(false);
+#undef EINET_LAUNCH_Q
 #undef EINET_LAUNCH
 }
 
@@ -671,7 +682,7 @@ void launch_posterior_k8(const DevTables& t, int first, int count, const float* 
             allow_dynamic_lds(&k_einsum_posterior<K8, false>, lds);
         });
     }
-    const int nchunks = (d.B + 127) / 128, ngr = bwd_groups_per_item(count, d.K, nchunks);
+    const int nchunks = (d.B + 127) / 128, ngr = bwd_groups_per_item(count, d.K, d.B);
 #define EINET_LAUNCH(EX)                                                                                              \
     hipLaunchKernelGGL((k_einsum_posterior<K8, EX>), dim3(count * nchunks * ngr), dim3(256), lds, s,                    \
                        t.ein_brec + (size_t)first * EIN_BREC_INTS, params, A, Off, amax, G, Gp, img, first, nchunks, ngr, \
@@ -774,7 +785,7 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
     const float* As = A + (size_t)rec[3] * blk;
     // posterior of the item's region: assembled in G, or (DIRECT) the sum of gcnt consecutive blocks that the
     // region's only parent wrote to Gp, added up in the order the assembly launch would take
-    const int gcnt = DIRECT ? bwd_source_blocks(rec[8], K, 1) : 0;
+    const int gcnt = DIRECT ? bwd_source_blocks(rec[8], K, B) : 0;
     const float* Gs = DIRECT ? Gp + (size_t)rec[7] * blk : G + (size_t)rec[3] * blk;
     const float* W = params + rec[4];
     const size_t wbase = (size_t)rec[4];
@@ -1079,7 +1090,7 @@ void launch_region_assemble(const DevTables& t, int first, int count, bool is_ro
     if (count == 0) return;
     dim3 grid(count, (d.B * d.K + 255) / 256);
     hipLaunchKernelGGL(k_region_assemble, grid, dim3(256), 0, s, t.rb_rec + (size_t)first * RB_REC_INTS, t.rb_pblk,
-                       is_root_layer ? 1 : 0, G, Gp, bwd_block_limit((d.B + 127) / 128), d.B, d.K);
+                       is_root_layer ? 1 : 0, G, Gp, bwd_block_limit(d.K, d.B), d.B, d.K);
 }
 
 template <int KQ>
@@ -1102,7 +1113,7 @@ static void launch_backward_fused(const DevTables& t, int first, int count, bool
             allow_dynamic_lds(&k_einsum_backward_fused<KQ, false, false, true>, lds);
         });
     }
-    const int ngroups = bwd_groups_per_item(count, d.K, 1);
+    const int ngroups = bwd_groups_per_item(count, d.K, d.B);
 #define EINET_LAUNCH_D(V, ACC, DIR)                                                                                          \
     hipLaunchKernelGGL((k_einsum_backward_fused<KQ, V, ACC, DIR>), dim3(count * ngroups), dim3(512), lds, s,                  \
                        t.ein_brec + (size_t)first * EIN_BREC_INTS, params, stats, A, Off, amax, G, Gp, first, ngroups, d.B, d.K)

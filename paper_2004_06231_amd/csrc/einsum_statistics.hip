@@ -34,7 +34,7 @@ __device__ __forceinline__ StatRows stat_rows(const int32_t* rec, int item, cons
     r.v = rec[5] >= 0 ? params + rec[5] : nullptr;
     r.vstr = rec[6];
     r.Gs = rec[7] >= 0 ? Gp + (size_t)rec[7] * blk : G + (size_t)rec[3] * blk;
-    r.gcnt = rec[7] >= 0 ? bwd_source_blocks(rec[8], K, (B + 127) / 128) : 1;
+    r.gcnt = rec[7] >= 0 ? bwd_source_blocks(rec[8], K, B) : 1;
     r.aL = amax + (size_t)item * 2 * B;
     r.aR = r.aL + B;
     return r;

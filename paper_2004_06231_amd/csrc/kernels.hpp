@@ -103,30 +103,42 @@ void launch_region_assemble(const DevTables& t, int first, int count, bool is_ro
 // posterior blocks ([B][K] floats each) reserved per einsum item in Gp: one for its left child, then up to
 // one per slice of four left entries for its right child
 inline int gp_blocks_per_item(int K) { return 1 + (K + 3) / 4; }
+constexpr int PS_SAMPLES = 64;       // samples of a workgroup of the top-down kernel for K up to 16
 // Workgroups per (item, chunk of 128 samples) of the top-down kernel for a layer of `count` items: the slices of an item are
 // spread over several workgroups where the launch would otherwise have fewer than bwd_workgroups of them (one per compute
-// unit, two where they have more than one chunk's work; K above 16).  Workgroup grp takes slices grp*KQ/groups ..
-// (grp+1)*KQ/groups - 1 and writes right-child block 1+grp of the item.  Larger batches need fewer groups: a block list holds those of one chunk, each with its code.
+// unit, two where they have more than one chunk's work), see bwd_whole_items.
+// Workgroup grp takes slices grp*KQ/groups .. (grp+1)*KQ/groups - 1 and writes right-child block 1+grp of the item.  Larger
+// batches need fewer groups: a block list holds those of the smallest, each with its code.
 #if defined(__HIPCC__)
 __host__ __device__
 #endif
 inline int bwd_workgroups(int nchunks) { return nchunks == 1 ? 256 : 512; }
+// K up to 16: a workgroup that forms no statistics (beyond PS_SAMPLES samples), or has no more than two slices, has too little
+// to share.  EM step of trees, K = 16, 112 items, 1000 samples, whole items and split ones: 124 and 140 us; K = 8, 64 samples, 4
+// and 112 items: 38 and 42, 55 and 59.
 #if defined(__HIPCC__)
 __host__ __device__
 #endif
-inline int bwd_groups_per_item(int count, int K, int nchunks) {
-    const int kq = (K + 3) / 4;
-    if (K <= 16) return 1;                             // (a kernel of its own: a workgroup takes whole items)
+inline bool bwd_whole_items(int K, int B) { return K <= 8 || (K <= 16 && B > PS_SAMPLES); }
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline int bwd_groups_per_item(int count, int K, int B) {
+    const int kq = (K + 3) / 4, nchunks = (B + 127) / 128;
+    if (bwd_whole_items(K, B)) return 1;
     const long long n = (long long)(count > 0 ? count : 1) * nchunks;
     const int target = bwd_workgroups(nchunks), g = n >= target ? 1 : target / (int)n;
     return g > kq ? kq : g;
 }
 // Code of right-child block 1 + q of an item in a layer of `count` items: the block is written when q < groups, that is
 // when (q + 1) * count * nchunks is at most bwd_workgroups(nchunks); 0: always.  So the blocks in use are those whose code is at
-// most bwd_block_limit(nchunks) (one comparison per block in the kernel that adds them up; with the product in its place EM
+// most bwd_block_limit(K, B) (one comparison per block in the kernel that adds them up; with the product in its place EM
 // steps of 32x32 images, six such launches each, took 1 to 2 % longer: K = 25, one sample 167 us and 165, K = 40: 221 and 219).
 inline int32_t bwd_block_code(int count, int q) { return q == 0 ? 0 : (q + 1) * count; }
-inline int32_t bwd_block_limit(int nchunks) { return bwd_workgroups(nchunks) / nchunks; }
+inline int32_t bwd_block_limit(int K, int B) {
+    const int nchunks = (B + 127) / 128;
+    return bwd_whole_items(K, B) ? 0 : bwd_workgroups(nchunks) / nchunks;
+}
 // The top-down kernel above K = 16 (K8 = ceil(K / 8), EXACT: K is 8 K8) brings in post_slices(K8) slices of an item's weights
 // at a time, whether or not the workgroup has that many left.  Row i of W that row r (0 .. 4 post_slices - 1) of the stage from
 // slice `it` on is read from, and the first of the four left entries read for slice `it`: in range for slices that do not exist.
@@ -164,7 +176,7 @@ constexpr int GSRC_MAX_BLOCKS = 6;
 #if defined(__HIPCC__)
 __host__ __device__
 #endif
-inline int bwd_source_blocks(int32_t n, int K, int nchunks) { return n > 0 ? bwd_groups_per_item(n, K, nchunks) : -n; }
+inline int bwd_source_blocks(int32_t n, int K, int B) { return n > 0 ? bwd_groups_per_item(n, K, B) : -n; }
 
 // (small layers of K a multiple of 8 up to 40 read an assembled posterior)
 inline bool bwd_reads_blocks(int count, int K) { return (K & 7) != 0 || K > 40 || count >= 32; }

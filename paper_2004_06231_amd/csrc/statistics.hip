@@ -101,7 +101,7 @@ __device__ __forceinline__ void leaf_backward_body(
     const int leaf = lv_leaf[e], var = lv_var[e], r = leaf_replica[leaf];
     const size_t gblk = (size_t)d.B * d.K;
     const int gsrc = DIRECT ? leaf_gsrc[2 * leaf] : 0;
-    const int gcnt = DIRECT ? bwd_source_blocks(leaf_gsrc[2 * leaf + 1], d.K, (d.B + 127) / 128) : 1;
+    const int gcnt = DIRECT ? bwd_source_blocks(leaf_gsrc[2 * leaf + 1], d.K, d.B) : 1;
     const float* Gl = (DIRECT ? Gp + (size_t)gsrc * gblk : G + (size_t)leaf_node[leaf] * gblk) + k;
     const float* xp = x + (size_t)var * d.C + c;
     const bool shared_obs = mask_mode != EINET_MASK_SHARED || mask[var] != 0;
@@ -338,7 +338,7 @@ __device__ __forceinline__ void leaf_stats_body(
     const int c16 = lane & 15, kg = lane >> 4;
     const size_t gblk = (size_t)d.B * d.K;
     const float* Gl = DIRECT ? Gp + (size_t)leaf_gsrc[2 * leaf] * gblk : G + (size_t)leaf_node[leaf] * gblk;
-    const int gcnt = DIRECT ? bwd_source_blocks(leaf_gsrc[2 * leaf + 1], d.K, (d.B + 127) / 128) : 1;
+    const int gcnt = DIRECT ? bwd_source_blocks(leaf_gsrc[2 * leaf + 1], d.K, d.B) : 1;
     // this lane's pair
     const int tile = chunk * waves + wave, pair = 16 * tile + c16;
     const bool work = wave < waves && 16 * tile < npairs;
@@ -522,7 +522,7 @@ __device__ __forceinline__ void leaf_tile_body(
     const int c16 = lane & 15, kg = lane >> 4;
     const size_t gblk = (size_t)d.B * d.K;
     const float* Gl = DIRECT ? Gp + (size_t)leaf_gsrc[2 * leaf] * gblk : G + (size_t)leaf_node[leaf] * gblk;
-    const int gcnt = DIRECT ? bwd_source_blocks(leaf_gsrc[2 * leaf + 1], d.K, (d.B + 127) / 128) : 1;
+    const int gcnt = DIRECT ? bwd_source_blocks(leaf_gsrc[2 * leaf + 1], d.K, d.B) : 1;
     const int pv = min(16 * tile + c16, npairs - 1), var = leaf_var[s0 + pv / d.C];
     const size_t xstride = (size_t)d.D * d.C;
     const float* xp = x + (size_t)var * d.C + (pv - pv / d.C * d.C);

@@ -21,7 +21,7 @@ int walk(int K) {
     int bad = 0;
     for (int count = 1; count <= 300; ++count)
         for (int nchunks = 1; nchunks <= 8; ++nchunks) {
-            const int ngr = bwd_groups_per_item(count, K, nchunks);
+            const int ngr = bwd_groups_per_item(count, K, 128 * nchunks);
             for (int grp = 0; grp < ngr; ++grp)
                 for (int it = grp * slices / ngr; it < (grp + 1) * slices / ngr; it += sg) {
                     for (int r = 0; r < 4 * sg; ++r) {
@@ -43,7 +43,23 @@ int walk_k8() {
     for (int K = 8 * K8 - 7; K < 8 * K8; ++K) bad += walk<K8, false>(K);
     return bad;
 }
+// The readers of posterior blocks find as many as the layer's workgroups write, and never more than the plan reserves.
+int blocks() {
+    int bad = 0;
+    for (int K = 1; K <= 64; ++K)
+        for (int count = 1; count <= 600; ++count)
+            for (int B : {1, 2, 63, 64, 65, 127, 128, 129, 256, 257, 384, 385, 640, 1000, 4000}) {
+                const int groups = bwd_groups_per_item(count, K, B), listed = bwd_groups_per_item(count, K, 1);
+                int used = 0;
+                for (int q = 0; q < listed; ++q) used += bwd_block_code(count, q) <= bwd_block_limit(K, B);
+                bad += groups < 1 || groups > listed || 1 + listed > gp_blocks_per_item(K) || used != groups ||
+                       bwd_source_blocks(count, K, B) != groups;
+            }
+    if (bad) printf("posterior blocks: %d cases wrong\n", bad);
+    return bad;
+}
 int main() {
+    if (blocks()) return 1;
     return walk_k8<3>() + walk_k8<4>() + walk_k8<5>() + walk_k8<6>() + walk_k8<7>() + walk_k8<8>() ? 1 : 0;
 }
 """
@@ -51,7 +67,7 @@ int main() {
 
 @pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"),
                     reason="needs g++ and the HIP headers")
-def test_reads_of_the_posterior_kernel_stay_inside_the_item(tmp_path):
+def test_reads_and_blocks_of_the_top_down_kernels(tmp_path):
     src, exe = tmp_path / "walk.cpp", str(tmp_path / "walk")
     src.write_text(PROGRAM)
     res = subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC, str(src),
