@@ -16,7 +16,7 @@ namespace {
 __global__ void k_region_assemble(const int32_t* __restrict__ r_rec, const int32_t* __restrict__ r_pblk, int is_root,
                                   float* __restrict__ G, const float* __restrict__ Gp, int limit, int B, int K) {
     // the region's record: node, entries, number of parent blocks, start of its block list, first blocks (block number,
-    // code: used if at most limit)
+    // code: used if at most limit), in the order of their codes
     const int32_t* rec = r_rec + (size_t)blockIdx.x * RB_REC_INTS;
     const int node = rec[0], kout = rec[1], cnt = rec[2];
     const int e = blockIdx.y * blockDim.x + threadIdx.x;
@@ -30,7 +30,7 @@ __global__ void k_region_assemble(const int32_t* __restrict__ r_rec, const int32
     constexpr int RND = RB_REC_BLOCKS / 2;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        if (r * RND < cnt) {
+        if (r * RND < cnt && rec[4 + 2 * r * RND + 1] <= limit) {
             float v[RND];
 #pragma unroll
             for (int q = 0; q < RND; ++q) {
@@ -41,8 +41,8 @@ __global__ void k_region_assemble(const int32_t* __restrict__ r_rec, const int32
             for (int q = 0; q < RND; ++q) g += v[q];
         }
     }
-    for (int p0 = RB_REC_BLOCKS; p0 < cnt; p0 += 16) {   // the rest of a very long list
-        const int32_t* list = r_pblk + 2 * rec[3];
+    const int32_t* list = r_pblk + 2 * rec[3];
+    for (int p0 = RB_REC_BLOCKS; p0 < cnt && list[2 * p0 + 1] <= limit; p0 += 16) {   // the rest of a very long list
         float v[16];
 #pragma unroll
         for (int q = 0; q < 16; ++q)

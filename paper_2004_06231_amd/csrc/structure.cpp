@@ -440,12 +440,15 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
     auto push_region = [&](int s) {
         p.rb_node.push_back(s);
         p.rb_kout.push_back(kout(s));
-        std::sort(runs[s].begin(), runs[s].end(), [](const Run& a, const Run& b) { return a.first < b.first; });
+        // (by their codes: the blocks that a batch uses are the front of the list)
+        std::vector<std::pair<int32_t, int32_t>> list;
         for (auto& r : runs[s])
-            for (int q = 0; q < r.blocks; ++q) {
-                p.rb_pblk.push_back(r.first + q);
-                p.rb_pblk.push_back(bwd_block_code(r.count, q));
-            }
+            for (int q = 0; q < r.blocks; ++q) list.push_back({bwd_block_code(r.count, q), r.first + q});
+        std::sort(list.begin(), list.end());
+        for (auto& b : list) {
+            p.rb_pblk.push_back(b.second);
+            p.rb_pblk.push_back(b.first);
+        }
         p.rb_pptr.push_back((int32_t)p.rb_pblk.size() / 2);
     };
     for (int l = p.num_layers - 1; l >= 0; --l) {
