@@ -18,7 +18,7 @@ __global__ void k_region_assemble(const int32_t* __restrict__ r_rec, const int32
     // the region's record: node, entries, number of parent blocks, start of its block list, first blocks (block number,
     // code: used if at most limit), in the order of their codes
     const int32_t* rec = r_rec + (size_t)blockIdx.x * RB_REC_INTS;
-    const int node = rec[0], kout = rec[1], cnt = rec[2];
+    const int node = rec[0], kout = rec[1], cnt = limit == 0 ? rec[RB_REC_ALWAYS] : rec[2];
     const int e = blockIdx.y * blockDim.x + threadIdx.x;
     if (e >= B * kout) return;
     const int b = e / kout, k = e - b * kout;
@@ -30,7 +30,7 @@ __global__ void k_region_assemble(const int32_t* __restrict__ r_rec, const int32
     constexpr int RND = RB_REC_BLOCKS / 2;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        if (r * RND < cnt && rec[4 + 2 * r * RND + 1] <= limit) {
+        if (r * RND < cnt && (r == 0 || rec[4 + 2 * r * RND + 1] <= limit)) {
             float v[RND];
 #pragma unroll
             for (int q = 0; q < RND; ++q) {

@@ -95,8 +95,9 @@ void launch_root_backward(const DevTables& t, int n_partitions, const int32_t* e
 
 // Every top-down region also has a record of RB_REC_INTS ints in rb_rec: node, entries, number of parent blocks,
 // position of its list in rb_pblk, then the first RB_REC_BLOCKS blocks, two ints each (the rest, if any, only in the list):
-// block number, and the code that says whether the block is written (bwd_block_limit), in the order of their codes.
-constexpr int RB_REC_INTS = 64, RB_REC_BLOCKS = 28;
+// block number, and the code that says whether the block is written (bwd_block_limit), in the order of their codes; at
+// RB_REC_ALWAYS the number of blocks that are always written.
+constexpr int RB_REC_INTS = 64, RB_REC_BLOCKS = 28, RB_REC_ALWAYS = 60;
 void launch_region_assemble(const DevTables& t, int first, int count, bool is_root_layer, float* G, const float* Gp,
                             const Dims& d, hipStream_t s);
 

@@ -468,6 +468,7 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
         rec[2] = cnt;
         rec[3] = p.rb_pptr[i];
         for (int q = 0; q < 2 * cnt && q < 2 * RB_REC_BLOCKS; ++q) rec[4 + q] = p.rb_pblk[2 * p.rb_pptr[i] + q];
+        for (int q = 0; q < cnt; ++q) rec[RB_REC_ALWAYS] += p.rb_pblk[2 * (p.rb_pptr[i] + q) + 1] == 0;
     }
 
     // ---- M-step rows
