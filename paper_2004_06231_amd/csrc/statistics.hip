@@ -476,18 +476,31 @@ __device__ __forceinline__ void leaf_stats_body(
         float t = 0.f;
 #pragma unroll
         for (int h = 0; h < NG; ++h) t += red[h][k];
+        // (the old statistics of the four pairs are requested before the first store)
+        size_t ph[4], o[4];
+        float old[4][4];
+        bool first[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int p = 16 * tile + 4 * kg + v;
-            if (p >= npairs || k >= d.K) continue;
-            const int vv = leaf_var[s0 + p / d.C], c = p - p / d.C * d.C;
-            const size_t ph = phi_off + ((size_t)(vv * d.C + c) * d.R + r) * d.T * d.K + k;
-            stats[ph] += acc[0][jt][v];
-            if (SQ) stats[ph + d.K] += acc[SQ ? 1 : 0][jt][v];
-            if (c == 0) {
-                const size_t o = ((size_t)vv * d.R + r) * d.K + k;
-                stats[den_off + o] += MASK ? acc[NK - 1][jt][v] : t;
-                stats[tot_off + o] += t;
+            const int p = 16 * tile + 4 * kg + v, pc = min(p, npairs - 1);
+            const int vv = leaf_var[s0 + pc / d.C], c = pc - pc / d.C * d.C;
+            first[v] = c == 0;
+            ph[v] = phi_off + ((size_t)(vv * d.C + c) * d.R + r) * d.T * d.K + k;
+            o[v] = ((size_t)vv * d.R + r) * d.K + k;
+            if (p < npairs && k < d.K) {
+                old[v][0] = stats[ph[v]];
+                if (SQ) old[v][1] = stats[ph[v] + d.K];
+                if (first[v]) old[v][2] = stats[den_off + o[v]], old[v][3] = stats[tot_off + o[v]];
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (16 * tile + 4 * kg + v >= npairs || k >= d.K) continue;
+            stats[ph[v]] = old[v][0] + acc[0][jt][v];
+            if (SQ) stats[ph[v] + d.K] = old[v][1] + acc[SQ ? 1 : 0][jt][v];
+            if (first[v]) {
+                stats[den_off + o[v]] = old[v][2] + (MASK ? acc[NK - 1][jt][v] : t);
+                stats[tot_off + o[v]] = old[v][3] + t;
             }
         }
     }
@@ -647,16 +660,27 @@ __device__ __forceinline__ void leaf_tile_body(
             for (int w = 0; w < 8; ++w)
 #pragma unroll
                 for (int h = 0; h < 8; ++h) t += reinterpret_cast<const float*>(lds + w * LY::SUMS + NK * NJ * 1024)[h * NR + k];
+        // (the old statistics are requested before the first store)
+        size_t ph[4], o[4];
+        float old[4][3];
+        bool in[4], first[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int p = 16 * tile + 4 * kg + v;
-            if (p >= npairs || k >= d.K) continue;
-            const int vv = leaf_var[s0 + p / d.C], c = p - p / d.C * d.C;
-            const float value = sum[v];
-            const size_t o = ((size_t)vv * d.R + r) * d.K + k;
-            if (q < (SQ ? 2 : 1)) stats[phi_off + (((size_t)(vv * d.C + c) * d.R + r) * d.T + q) * d.K + k] += value;
-            if (c == 0 && q == 0) stats[tot_off + o] += t;
-            if (c == 0 && q == NK - 1) stats[den_off + o] += MASK ? value : t;
+            const int p = 16 * tile + 4 * kg + v, pc = min(p, npairs - 1);
+            const int vv = leaf_var[s0 + pc / d.C], c = pc - pc / d.C * d.C;
+            in[v] = p < npairs && k < d.K;
+            first[v] = in[v] && c == 0;
+            ph[v] = phi_off + (((size_t)(vv * d.C + c) * d.R + r) * d.T + q) * d.K + k;
+            o[v] = ((size_t)vv * d.R + r) * d.K + k;
+            if (in[v] && q < (SQ ? 2 : 1)) old[v][0] = stats[ph[v]];
+            if (first[v] && q == 0) old[v][1] = stats[tot_off + o[v]];
+            if (first[v] && q == NK - 1) old[v][2] = stats[den_off + o[v]];
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (in[v] && q < (SQ ? 2 : 1)) stats[ph[v]] = old[v][0] + sum[v];
+            if (first[v] && q == 0) stats[tot_off + o[v]] = old[v][1] + t;
+            if (first[v] && q == NK - 1) stats[den_off + o[v]] = old[v][2] + (MASK ? sum[v] : t);
         }
     }
 }
@@ -733,16 +757,18 @@ void launch_tail_backward(const DevTables& t, int n_lv, int n_leaves, int max_sc
 #undef EINET_CAT
     }
     const int mc = max_children > 0 ? max_children : 1, n_mix_blocks = n_mix * max_children;
-    // scopes that fill a tile of 16 pairs: on the matrix pipe.  Few tiles: one per workgroup, so that the batch fills the chip;
-    // otherwise eight waves with a tile each, which split the posteriors once for all.  K = 40, 192 tiles, 128 samples: 14.5 us
-    // and 20.6; 1000 samples 53 and 65; K = 16, 256 samples, flags: 9.4 and 22.3.
-    // Where a thread per entry has few samples to walk it is the shorter chain (64 pairs, K = 20, 100 samples: 6.4 us and 8.4; 16
-    // pairs, 2 samples: 4.7 and 9.4; 32 pairs, K = 30, 5120 variables, 100 samples: 14.4 and 12.8).
-    const bool matrix = max_scope * d.C >= 16 && (max_scope * d.C >= 512 || d.B > 128 || (int64_t)total * d.B > 4 << 20);
+    // Scopes that fill a tile of 16 pairs: on the matrix pipe, from the batch on that an instruction contracts half of.  Eight
+    // waves with a tile each, which split the posteriors once for all, where that makes enough workgroups and a workgroup of one
+    // tile would give most of its waves no samples (up to 64) or there are many tiles; otherwise a tile per workgroup, whose waves
+    // share the batch.  Us of an EM step, a thread per entry / one tile / eight tiles: 128 leaves of 32 pairs, K = 40, 16 samples
+    // 143 / 144 / 141, 64 samples 170 / 159 / 157, 128 samples 201 / 182 / 186; 64 leaves of 192 pairs, K = 20, 4 samples 159 / 166 /
+    // 161, 64 samples 198 / 187 / 183, 400 samples 433 / 405 / 406; 8 leaves of 128 pairs, K = 40, 16 samples 53 / 55 / 58, 64 samples 58 /
+    // 59 / 63, 200 samples 79 / 78 / 89; 16 leaves of 64 pairs with flags, K = 10, 64 samples 114 / 113 / 112, 128 samples 121 / 117 / 118.
+    const int tiles = (max_scope * d.C + 15) / 16, waves = LX_THREADS / 64, eights = (tiles + waves - 1) / waves;
+    const bool tile = (int64_t)n_leaves * eights < 64 || (d.B > 64 && (int64_t)n_leaves * tiles <= 2 * EINET_NUM_CUS);
+    const bool matrix = max_scope * d.C >= 16 && d.B > (tile ? 16 : 8);
     if (!categorical && matrix) {
-        const int tiles = (max_scope * d.C + 15) / 16;
-        const bool tile = (int64_t)n_leaves * tiles <= 2 * EINET_NUM_CUS;
-        const int waves = LX_THREADS / 64, chunks = tile ? tiles : (tiles + waves - 1) / waves;
+        const int chunks = tile ? tiles : eights;
         const int n_leaf_blocks = n_leaves * chunks;
 #define EINET_LAUNCH_T(SQ, MASK, NJ, DIR, TILE)                                                                         \
     do {                                                                                                                \
