@@ -456,7 +456,7 @@ int einet_em_accumulate(einet_t* h, const float* x_dev, const uint8_t* mask_dev,
         }
         run(h, KC_EINSUM_BWD, s, [&] {
             launch_einsum_backward(h->dt, p.ein_layer_ptr[l], p.ein_layer_ptr[l + 1] - p.ein_layer_ptr[l],
-                                   p.ein_layer_full[l] != 0, !h->weight_stats_zero, h->params, h->stats, A, Off, amax, G, Gp,
+                                   !h->weight_stats_zero, h->params, h->stats, A, Off, amax, G, Gp,
                                    reinterpret_cast<float*>(h->ws + h->off_img), &sums, direct, d, s);
         }, layer_outputs(p, l));
     }

@@ -695,9 +695,11 @@ void launch_posterior_k8(const DevTables& t, int first, int count, const float* 
 // ------------------------------------------------------------------ posteriors and statistics in one launch
 // Batches of one chunk (128 samples) with few entries or few items: the launches are chains of requests, and one more of
 // them for the statistics costs more than what the split operands save (einsum_backward_fused).  One workgroup per (item,
-// run of slices of four left entries): eR^T and Q^T are staged once, sample-major, the slices W[:, 4 i .., :] stream through
-// LDS with the next in flight in registers; both products, statistics (contraction over the batch) and posteriors (over k),
-// read the slice.  The right child's posterior is summed over the workgroup's slices in LDS and written to a block of its own.
+// share of the chunks, run of slices of four left entries): eR^T and Q^T are staged once, sample-major, the slices W[:, 4 i .., :] stream
+// through LDS with the next in flight in registers; both products, statistics (contraction over the batch) and posteriors (over
+// k), read the slice.  The right child's posterior is summed over the workgroup's slices in LDS and written to a block of its
+// own.  With several chunks a workgroup walks `cpv` of them; nshare > 1: every share's statistics go to blocks of their own in
+// `part`, which a later launch adds up.
 template <int KQ>
 struct BwdLayout {
     static constexpr int KP = 4 * KQ;
@@ -709,9 +711,9 @@ struct BwdLayout {
     static constexpr int OFF_R = KP * S;                  // eR^T [16 NJ][ST]
     static constexpr int OFF_Q = OFF_R + 16 * NJ * ST;    // Q^T  [KP][ST]
     static constexpr int OFF_L = OFF_Q + KP * ST;         // eL^T [4][ST] of the current slice
-    static constexpr int OFF_G = OFF_L + 4 * ST;          // Gp_right of the workgroup's slices [BC][KP] ...
-    static constexpr bool LDS_ACC = OFF_G + BC * KP <= 40960;   // ... if it fits in the 160 KB of LDS
-    static constexpr int LDS_FLOATS = OFF_G + (LDS_ACC ? BC * KP : 0);
+    static constexpr int OFF_G = OFF_L + 4 * ST;          // Gp_right of the workgroup's slices [BC][KP]
+    static constexpr int LDS_FLOATS = OFF_G + BC * KP;
+    static_assert(LDS_FLOATS <= 40960, "160 KB of LDS");
     static constexpr int MAXU = (NJ * KQ + 7) / 8;        // GEMM-1 tiles per wave
     static constexpr int NW4 = (KP * 4 * KQ + 511) / 512; // float4 per thread of one W slice
     static constexpr int NW1 = (KP * 4 * KP + 511) / 512; // floats per thread when K is not a multiple of 4
@@ -757,12 +759,13 @@ __device__ __forceinline__ void bwd_gemm1(floatx4* acc1, const float* const* qco
     }
 }
 
-template <int KQ, bool VEC, bool ACCUM, bool DIRECT>
+// LOOP: cpv is more than one (the loop costs registers).
+template <int KQ, bool VEC, bool ACCUM, bool DIRECT, bool LOOP>
 __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
     const int32_t* __restrict__ e_rec,
     const float* __restrict__ params, float* __restrict__ stats, const float* __restrict__ A,
     const double* __restrict__ Off, const float* __restrict__ amax, const float* __restrict__ G, float* __restrict__ Gp,
-    int item0, int ngroups, int B, int K) {
+    int item0, int ngroups, int nshare, int cpv, int total, float* __restrict__ part, int nblk, int B, int K) {
     using LY = BwdLayout<KQ>;
     constexpr int KP = LY::KP, SI = LY::SI, S = LY::S, ST = LY::ST, BC = LY::BC, MAXU = LY::MAXU;
     extern __shared__ float lds[];
@@ -773,11 +776,10 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
     float* sG = lds + LY::OFF_G;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int vb = xcd_contiguous_block();
-    const int li = vb / ngroups, grp = vb - li * ngroups;
+    const int grp = vb % ngroups, share = (vb / ngroups) % nshare, li = vb / (ngroups * nshare);
     const int it0 = grp * KQ / ngroups, it1 = (grp + 1) * KQ / ngroups;     // this workgroup's slices
     const bool multi = it1 - it0 > 1;   // several slices: their shares of Gp_right are summed in LDS first
     const int item = item0 + li;
-    const int kout = K, nkt = (kout + 3) >> 2;
     const int32_t* rec = e_rec + (size_t)li * EIN_BREC_INTS;
     const size_t blk = (size_t)B * K;
     const float* Lp = A + (size_t)rec[0] * blk;
@@ -794,7 +796,6 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
     const float* aR = aL + B;
     const double* Oo = Off + (size_t)rec[2] * B;
     const double* Os = Off + (size_t)rec[3] * B;
-    const int nblk = 1 + KQ;
 
     // registers that carry the next W slice
     float4 w4[VEC ? LY::NW4 : 1];
@@ -806,7 +807,7 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                 const int q = tid + 512 * n;
                 const int j4 = q % KQ, il = (q / KQ) & 3, k = q / (4 * KQ);
                 w4[n] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (k < kout) w4[n] = *reinterpret_cast<const float4*>(W + ((size_t)k * K + 4 * it + il) * K + 4 * j4);
+                if (k < K) w4[n] = *reinterpret_cast<const float4*>(W + ((size_t)k * K + 4 * it + il) * K + 4 * j4);
             }
         } else {
 #pragma unroll
@@ -814,7 +815,7 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                 const int q = tid + 512 * n;
                 const int j = q % KP, il = (q / KP) & 3, k = q / (4 * KP);
                 const int i = 4 * it + il;
-                w1[n] = (k < kout && i < K && j < K) ? W[((size_t)k * K + i) * K + j] : 0.f;
+                w1[n] = (k < K && i < K && j < K) ? W[((size_t)k * K + i) * K + j] : 0.f;
             }
         }
     };
@@ -839,8 +840,8 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
 
     const int c = lane & 15, g = lane >> 4;
     const int gm = c >> 2, rm = c & 3;
-    // GEMM-1 tiles of this wave: u = jt * nkt + kt
-    const int U = LY::NJ * nkt;
+    // GEMM-1 tiles of this wave: u = jt * KQ + kt
+    constexpr int U = LY::NJ * KQ;
     const int u0 = wave * U / 8, nu = (wave + 1) * U / 8 - u0;
     const float* qcol[MAXU];
     const float* rcol[MAXU];
@@ -849,27 +850,28 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
 #pragma unroll
     for (int q = 0; q < MAXU; ++q) {
         const int u = min(u0 + q, U - 1);
-        const int jt = u / nkt, ukt = u - jt * nkt;
+        const int jt = u / KQ, ukt = u - jt * KQ;
         qcol[q] = sQ + (4 * ukt + gm) * ST;     // + g*RG + s
         rcol[q] = sR + (16 * jt + c) * ST;
         const int k = 4 * ukt + g, j = 16 * jt + c;
-        uok[q] = q < nu && k < kout && j < K;
+        uok[q] = q < nu && k < K && j < K;
         uoff[q] = uok[q] ? (k * K) * K + j : 0;
         uwl[q] = uok[q] ? k * S + j : 0;
     }
-    float* Nw = stats + wbase;
+    float* Nw = nshare > 1 ? part + ((size_t)share * total + item) * ((size_t)K * K * K) : stats + wbase;
 
     // staging of eR and Q
     const int srow = tid >> 2, sq = tid & 3;
     constexpr int NF = (BC * KQ + 511) / 512;      // float4 of a [BC][K] block per thread
 
-    for (int b0 = 0; b0 < B; b0 += BC) {
+    const int bfirst = share * (LOOP ? cpv : 1) * BC, bend = min(bfirst + (LOOP ? cpv : 1) * BC, B);
+    for (int b0 = bfirst; LOOP ? b0 < bend : b0 == bfirst; b0 += BC) {
         const int nb = min(BC, B - b0);
         const int rg = (((nb + 3) >> 2) + 3) & ~3;         // samples per lane group in GEMM-1, multiple of 4
         const bool rok = srow < nb;
         const int ro = (b0 + min(srow, nb - 1)) * K;       // a valid row even for the idle tail threads
         const float al = aL[b0 + min(srow, nb - 1)];
-        __syncthreads();                                   // readers of the previous pass are done
+        if (LOOP && b0 > bfirst) __syncthreads();                  // readers of the chunk before are done
         if constexpr (VEC) {
             // the [nb][K] blocks are contiguous: 16-byte loads, consecutive threads consecutive addresses
             float4 r4[NF], g4[NF], a4[NF], v4[NF];
@@ -900,10 +902,10 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                 ddn[n] = (float)(Oo[b0 + row] - Os[b0 + row]);
                 v4[n] = make_float4(1.f, 1.f, 1.f, 1.f);
                 if (voff >= 0) {
-                    v4[n].x = params[voff + min(4 * k4 + 0, kout - 1) * vstr];
-                    v4[n].y = params[voff + min(4 * k4 + 1, kout - 1) * vstr];
-                    v4[n].z = params[voff + min(4 * k4 + 2, kout - 1) * vstr];
-                    v4[n].w = params[voff + min(4 * k4 + 3, kout - 1) * vstr];
+                    v4[n].x = params[voff + min(4 * k4 + 0, K - 1) * vstr];
+                    v4[n].y = params[voff + min(4 * k4 + 1, K - 1) * vstr];
+                    v4[n].z = params[voff + min(4 * k4 + 2, K - 1) * vstr];
+                    v4[n].w = params[voff + min(4 * k4 + 3, K - 1) * vstr];
                 }
             }
 #pragma unroll
@@ -922,12 +924,12 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                         const float e = __expf(rr[c4] - arn[n]);
                         const float q = gg[c4] * vv[c4] * __expf(ddn[n] - aa[c4]);
                         sR[k * ST + row] = in ? e : 0.f;
-                        sQ[k * ST + row] = (in && k < kout && gg[c4] != 0.f) ? q : 0.f;
+                        sQ[k * ST + row] = (in && k < K && gg[c4] != 0.f) ? q : 0.f;
                     }
                 }
             }
             for (int j = KP + sq; j < 16 * LY::NJ; j += 4) sR[j * ST + srow] = 0.f;   // rows beyond the padded K
-            if (multi && LY::LDS_ACC)
+            if (multi)
                 for (int u = 0; u < KQ; ++u) sG[srow * KP + sq * KQ + u] = 0.f;
         } else {
             const float ar = aR[b0 + min(srow, nb - 1)];
@@ -938,28 +940,28 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                 const int k = sq * KQ + u;
                 const int kc = min(k, K - 1);
                 rv[u] = Rp[ro + kc];
-                gv[u] = Gs[ro + min(kc, kout - 1)];
+                gv[u] = Gs[ro + min(kc, K - 1)];
                 if (DIRECT && gcnt > 1) {
                     float gx[GSRC_MAX_BLOCKS - 1];
 #pragma unroll
-                    for (int x = 1; x < GSRC_MAX_BLOCKS; ++x) gx[x - 1] = x < gcnt ? Gs[x * blk + ro + min(kc, kout - 1)] : 0.f;
+                    for (int x = 1; x < GSRC_MAX_BLOCKS; ++x) gx[x - 1] = x < gcnt ? Gs[x * blk + ro + min(kc, K - 1)] : 0.f;
 #pragma unroll
                     for (int x = 1; x < GSRC_MAX_BLOCKS; ++x)
                         if (x < gcnt) gv[u] += gx[x - 1];
                 }
-                av[u] = As[ro + min(kc, kout - 1)];
+                av[u] = As[ro + min(kc, K - 1)];
             }
 #pragma unroll
             for (int u = 0; u < KQ; ++u) {
                 const int k = sq * KQ + u;
-                const float vw = (voff >= 0 && k < kout) ? params[voff + k * vstr] : 1.f;
+                const float vw = (voff >= 0 && k < K) ? params[voff + k * vstr] : 1.f;
                 const float e = __expf(rv[u] - ar);
                 const float q = gv[u] * vw * __expf(dd - av[u]);
                 sR[k * ST + srow] = (rok && k < K) ? e : 0.f;
-                sQ[k * ST + srow] = (rok && k < kout && gv[u] != 0.f) ? q : 0.f;
+                sQ[k * ST + srow] = (rok && k < K && gv[u] != 0.f) ? q : 0.f;
             }
             for (int j = KP + sq; j < 16 * LY::NJ; j += 4) sR[j * ST + srow] = 0.f;   // rows beyond the padded K
-            if (multi && LY::LDS_ACC)
+            if (multi)
                 for (int u = 0; u < KQ; ++u) sG[srow * KP + sq * KQ + u] = 0.f;
         }
 
@@ -971,9 +973,9 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                 sL[sq * ST + srow] = (rok && 4 * it + sq < K) ? e : 0.f;
             }
             __syncthreads();
-            // next slice of this pass, or the first slice of the next pass, goes in flight now
+            // the next slice, or the first one for the next chunk, goes in flight now
             if (it + 1 < it1) fetch_w(it + 1);
-            else if (b0 + BC < B) fetch_w(it0);
+            else if (LOOP && b0 + BC < bend) fetch_w(it0);
 
             // statistics this wave will update, fetched early (not needed when they are known to be zero)
             float nw[MAXU][4];
@@ -982,8 +984,8 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int i = VEC ? 4 * it + r : min(4 * it + r, K - 1);
-                    // (units that are not ours read a valid dummy; later passes over the batch always add)
-                    nw[q][r] = (ACCUM || b0 > 0) ? Nw[uoff[q] + i * K] : 0.f;
+                    // (units that are not ours read a valid dummy; later chunks always add)
+                    nw[q][r] = ACCUM || (LOOP && b0 > bfirst) ? Nw[uoff[q] + i * K] : 0.f;
                 }
 
             // ---- GEMM-1
@@ -1019,22 +1021,12 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                 floatx4 acc[KQ];
 #pragma unroll
                 for (int jt = 0; jt < KQ; ++jt) acc[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (nkt == KQ) {
 #pragma unroll 2
-                    for (int s = 0; s < KQ; ++s) {
-                        const float qs = qrow[4 * s * ST];
+                for (int s = 0; s < KQ; ++s) {
+                    const float qs = qrow[4 * s * ST];
 #pragma unroll
-                        for (int jt = 0; jt < KQ; ++jt)
-                            acc[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wl[4 * s * S + 4 * jt], qs, acc[jt], 0, 0, 0);
-                    }
-                } else {
-                    // an item of the root has one output entry: the other contraction steps would add zeros
-                    for (int s = 0; s < nkt; ++s) {
-                        const float qs = qrow[4 * s * ST];
-#pragma unroll
-                        for (int jt = 0; jt < KQ; ++jt)
-                            acc[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wl[4 * s * S + 4 * jt], qs, acc[jt], 0, 0, 0);
-                    }
+                    for (int jt = 0; jt < KQ; ++jt)
+                        acc[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wl[4 * s * S + 4 * jt], qs, acc[jt], 0, 0, 0);
                 }
                 // acc[jt][r] = U[b][i = 4it+r][j = 4jt+g]
                 float gl0 = 0.f, gl1 = 0.f, gl2 = 0.f, gl3 = 0.f;
@@ -1043,10 +1035,9 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
 #pragma unroll
                 for (int jt = 0; jt < KQ; ++jt) {
                     const float t = acc[jt][0] * e4.x + acc[jt][1] * e4.y + acc[jt][2] * e4.z + acc[jt][3] * e4.w;
-                    // this lane owns the entry in every slice: no race, in LDS or (for the largest K, where the
-                    // accumulator does not fit) in the block itself
-                    if (multi && LY::LDS_ACC) racc[4 * jt + g] += erg[jt] * t;
-                    else if (ok && 4 * jt + g < K) right[4 * jt + g] = erg[jt] * t + (it > it0 ? right[4 * jt + g] : 0.f);
+                    // this lane owns the entry in every slice: no race
+                    if (multi) racc[4 * jt + g] += erg[jt] * t;
+                    else if (ok && 4 * jt + g < K) right[4 * jt + g] = erg[jt] * t;
                     gl0 = fmaf(acc[jt][0], erg[jt], gl0);
                     gl1 = fmaf(acc[jt][1], erg[jt], gl1);
                     gl2 = fmaf(acc[jt][2], erg[jt], gl2);
@@ -1072,7 +1063,7 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                 }
             }
         }
-        if (multi && LY::LDS_ACC) {                        // Gp_right of the workgroup's slices, row by row
+        if (multi) {                        // Gp_right of the workgroup's slices, row by row
             __syncthreads();
             float* right = Gp + ((size_t)(item * nblk + 1 + grp) * B + b0) * K;
             for (int e = tid; e < nb * K; e += 512) {
@@ -1093,67 +1084,90 @@ void launch_region_assemble(const DevTables& t, int first, int count, bool is_ro
                        is_root_layer ? 1 : 0, G, Gp, bwd_block_limit(d.K, d.B), d.B, d.K);
 }
 
+// Whether the layers take that form; `total`: items of all layers below the root's (all layers of a model take the same one).
+// Us of an EM step with one launch per layer and with two forms of launches:
+//   one chunk, 28 / 112 / 194 / 496 items: K = 22, 128 samples: 92 / 111 / 172 / 210 and 109 / 126 / 189 / 219; K = 32, 64: 89 / 100 /
+//     180 / 225 and 95 / 111 / 182 / 224, 128: 101 / 123 / 208 / 282 and 107 / 132 / 201 / 252; K = 40, 16: 97 / 125 / 208 / 296 and
+//     107 / 141 / 222 / 340, 128: 123 / 186 / 281 / 473 and 124 / 181 / 258 / 437;
+//   256 samples, a block per chunk, 8 / 24 items: K = 20 53 / 66 and 65 / 78, K = 32 62 / 91 and 70 / 99, K = 40 77 / 109 and 85 / 119;
+//     both chunks in turn, 112 / 194 items: K = 20 136 / 196 and 148 / 210, K = 28 172 / 266 and 191 / 264, K = 36 279 / 414 and 244 /
+//     336;
+//   640 samples, a block per chunk, 4 / 8 / 16 items: K = 24 61 / 64 / 83 and 71 / 74 / 96, K = 40 75 / 103 / 143 and 82 / 106 / 143.
+static bool einsum_backward_fused(int total, int K, int B) {
+    const bool quads = (K & 3) == 0;                      // (rows of other K are staged entry by entry, from registers that spill)
+    if (K <= 16 || K > 48 || (K > 40 && !quads)) return false;
+    const int nchunks = (B + 127) / 128;
+    if (nchunks > 1) {
+        if (ein_stat_shares(total, K, B) == nchunks) return K <= 32 || nchunks == 2 || total <= 8 || (nchunks == 3 && total <= 16);
+        return nchunks == 2 && ((K <= 20 && total <= 256) || (K == 28 && total <= 128));
+    }
+    if (total <= 32 || K <= 24) return true;
+    if (total <= 128) return K <= 32 || B <= 64;
+    return (K <= 28 && total <= 256) || B <= 32 || (B <= 64 && quads);
+}
+// Shares of the chunks there: as many as chunks, or all chunks in turn where their blocks do not fit the scratch.
+static int fused_shares(int total, int K, int B) {
+    const int nchunks = (B + 127) / 128;
+    return ein_stat_shares(total, K, B) == nchunks ? nchunks : 1;
+}
+
 template <int KQ>
 static void launch_backward_fused(const DevTables& t, int first, int count, bool accumulate, const float* params, float* stats,
-                                  const float* A, const double* Off, const float* amax, const float* G, float* Gp, bool direct,
-                                  const Dims& d, hipStream_t s) {
-    const size_t lds = sizeof(float) * BwdLayout<KQ>::LDS_FLOATS;
-    if (lds > 64 * 1024) {
-        static std::once_flag attr_set[EINET_MAX_DEVICES];
-        int dev = 0;
-        (void)hipGetDevice(&dev);
-        std::call_once(attr_set[dev % EINET_MAX_DEVICES], [&] {
-            allow_dynamic_lds(&k_einsum_backward_fused<KQ, true, true, false>, lds);
-            allow_dynamic_lds(&k_einsum_backward_fused<KQ, false, true, false>, lds);
-            allow_dynamic_lds(&k_einsum_backward_fused<KQ, true, false, false>, lds);
-            allow_dynamic_lds(&k_einsum_backward_fused<KQ, false, false, false>, lds);
-            allow_dynamic_lds(&k_einsum_backward_fused<KQ, true, true, true>, lds);
-            allow_dynamic_lds(&k_einsum_backward_fused<KQ, false, true, true>, lds);
-            allow_dynamic_lds(&k_einsum_backward_fused<KQ, true, false, true>, lds);
-            allow_dynamic_lds(&k_einsum_backward_fused<KQ, false, false, true>, lds);
-        });
-    }
-    const int ngroups = bwd_groups_per_item(count, d.K, d.B);
-#define EINET_LAUNCH_D(V, ACC, DIR)                                                                                          \
-    hipLaunchKernelGGL((k_einsum_backward_fused<KQ, V, ACC, DIR>), dim3(count * ngroups), dim3(512), lds, s,                  \
-                       t.ein_brec + (size_t)first * EIN_BREC_INTS, params, stats, A, Off, amax, G, Gp, first, ngroups, d.B, d.K)
-#define EINET_LAUNCH(V, ACC)                      \
-    do {                                          \
-        if (direct) EINET_LAUNCH_D(V, ACC, true); \
-        else EINET_LAUNCH_D(V, ACC, false);       \
+                                  const float* A, const double* Off, const float* amax, const float* G, float* Gp, float* part, int total,
+                                  bool direct, const Dims& d, hipStream_t s) {
+    constexpr size_t lds = sizeof(float) * BwdLayout<KQ>::LDS_FLOATS;
+    constexpr bool ENTRIES = KQ <= 10, TURNS = KQ == 5 || KQ == 7;       // forms that einsum_backward_fused asks for
+    const int ngroups = bwd_groups_per_item(count, d.K, d.B), nchunks = (d.B + 127) / 128;
+    const int nshare = fused_shares(total, d.K, d.B), cpv = (nchunks + nshare - 1) / nshare;
+    const bool adds = accumulate && nshare == 1;                          // (blocks of shares are written, not added to)
+#define EINET_LAUNCH_L(V, ACC, DIR, L)                                                                                      \
+    do {                                                                                                                    \
+        if (lds > 64 * 1024) {                                                                                              \
+            static std::once_flag attr_set[EINET_MAX_DEVICES];                                                              \
+            int dev = 0;                                                                                                    \
+            (void)hipGetDevice(&dev);                                                                                       \
+            std::call_once(attr_set[dev % EINET_MAX_DEVICES],                                                               \
+                           [&] { allow_dynamic_lds(&k_einsum_backward_fused<KQ, V, ACC, DIR, L>, lds); });                  \
+        }                                                                                                                   \
+        hipLaunchKernelGGL((k_einsum_backward_fused<KQ, V, ACC, DIR, L>), dim3(count * nshare * ngroups), dim3(512), lds, s, \
+                           t.ein_brec + (size_t)first * EIN_BREC_INTS, params, stats, A, Off, amax, G, Gp, first, ngroups,  \
+                           nshare, cpv, total, part, gp_blocks_per_item(d.K), d.B, d.K);                                    \
+    } while (0)
+#define EINET_LAUNCH_A(V, DIR, L)                              \
+    do {                                                       \
+        if (adds) EINET_LAUNCH_L(V, true, DIR, L);             \
+        else EINET_LAUNCH_L(V, false, DIR, L);                 \
+    } while (0)
+#define EINET_LAUNCH(V)                                        \
+    do {                                                       \
+        if (TURNS && cpv > 1 && direct) EINET_LAUNCH_A(V, true, TURNS);       \
+        else if (TURNS && cpv > 1) EINET_LAUNCH_A(V, false, TURNS);           \
+        else if (direct) EINET_LAUNCH_A(V, true, false);       \
+        else EINET_LAUNCH_A(V, false, false);                  \
     } while (0)
     if ((d.K & 3) == 0) {
-        if (accumulate) EINET_LAUNCH(true, true);
-        else EINET_LAUNCH(true, false);
-    } else {
-        if (accumulate) EINET_LAUNCH(false, true);
-        else EINET_LAUNCH(false, false);
+        EINET_LAUNCH(true);
+    } else if constexpr (ENTRIES) {
+        EINET_LAUNCH(false);
     }
 #undef EINET_LAUNCH
-#undef EINET_LAUNCH_D
+#undef EINET_LAUNCH_A
+#undef EINET_LAUNCH_L
 }
 
-// `total`: items of all layers below the root's (all layers of a model take the same form).  Us of an EM step with one launch
-// per layer and with two forms of launches: K = 20, 4 / 28 / 112 / 194 items, 2 samples: 40 / 71 / 71 / 125 and 52 / 89 / 88 / 147; 100
-// samples: 51 / 81 / 95 / 155 and 61 / 101 / 106 / 173; 300 samples (two chunks in turn): 81 / 135 / 183 / 243 and 72 / 122 / 169 / 253;
-// K = 30, 4 / 112 items, 60 samples 56 / 117 and 62 / 121, 194 items 196 and 192; K = 40, 4 items 52 and 62, 28 items 102 and 112, 112
-// items, 100 samples: 177 and 174.
-static bool einsum_backward_fused(int total, int K, int B) {
-    return K > 16 && B <= 128 && (K <= 24 || (K <= 32 && total <= 128) || (K <= 40 && total <= 32));
-}
-
-void launch_einsum_backward(const DevTables& t, int first, int count, bool, bool accumulate, const float* params, float* stats, const float* A,
+void launch_einsum_backward(const DevTables& t, int first, int count, bool accumulate, const float* params, float* stats, const float* A,
                             const double* Off, const float* amax, const float* G, float* Gp, float* img, PartialSumList* list,
                             bool direct, const Dims& d, hipStream_t s) {
     if (count == 0) return;
     // (one workgroup per item: it takes the statistics with it)
-    const bool fused = einsum_backward_fused(list->ein.total, d.K, d.B);
+    EinStatsWork& w = list->ein;
+    const bool fused = einsum_backward_fused(w.total, d.K, d.B);
     const bool with_stats = fused || (d.K <= 16 && d.B <= PS_SAMPLES);
     if (fused) {
         switch ((d.K + 3) / 4) {
 #define EINET_CASE(J) \
-    case J: launch_backward_fused<J>(t, first, count, accumulate, params, stats, A, Off, amax, G, Gp, direct, d, s); break;
-            EINET_CASE(5) EINET_CASE(6) EINET_CASE(7) EINET_CASE(8) EINET_CASE(9) EINET_CASE(10)
+    case J: launch_backward_fused<J>(t, first, count, accumulate, params, stats, A, Off, amax, G, Gp, w.part, w.total, direct, d, s); break;
+            EINET_CASE(5) EINET_CASE(6) EINET_CASE(7) EINET_CASE(8) EINET_CASE(9) EINET_CASE(10) EINET_CASE(11) EINET_CASE(12)
 #undef EINET_CASE
         }
     } else if (d.K <= 16) {
@@ -1171,10 +1185,9 @@ void launch_einsum_backward(const DevTables& t, int first, int count, bool, bool
 #undef EINET_CASE
         }
     }
-    if (with_stats) return;
-    EinStatsWork& w = list->ein;
+    if (with_stats && (!fused || fused_shares(w.total, d.K, d.B) == 1)) return;
     w = EinStatsWork{t.ein_brec + (size_t)first * EIN_BREC_INTS, t.ein_woff + first, w.part, params, A, amax, G, Gp, img, Off, first,
-                     w.count + count, d.B, d.K, w.total};
+                     w.count + count, d.B, d.K, w.total, fused};
 }
 
 }  // namespace einet_impl

@@ -556,7 +556,7 @@ void launch_sum_partial_stats(const PartialSumList& list, float* stats, bool acc
     int n = list.n;
     if (list.ein.count > 0) {
         const EinStatsWork& w = list.ein;
-        launch_statistics(w, accumulate, stats, s);
+        if (!w.formed) launch_statistics(w, accumulate, stats, s);
         const int nshare = ein_stat_shares(w.count, w.K, w.B);
         if (nshare > 1) jobs.job[n++] = PartialSumJob{w.woff, w.part, w.count, nshare, w.K * w.K * w.K};
     }

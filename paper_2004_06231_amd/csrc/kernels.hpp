@@ -179,8 +179,10 @@ __host__ __device__
 #endif
 inline int bwd_source_blocks(int32_t n, int K, int B) { return n > 0 ? bwd_groups_per_item(n, K, B) : -n; }
 
-// (small layers of K a multiple of 8 up to 40 read an assembled posterior)
-inline bool bwd_reads_blocks(int count, int K) { return (K & 7) != 0 || K > 40 || count >= 32; }
+// (K = 16, few items: their posteriors have up to four blocks, which the statistics would add up again for every sample.  EM step
+// of trees, 4 items, assembled and read from the blocks: 1000 samples 68.6 and 74.9 us, 300 samples 54.1 and 54.4; but 64 samples
+// 39.5 and 37.4.)
+inline bool bwd_reads_blocks(int count, int K) { return K != 16 || count >= 32; }
 
 // Every einsum item has a record of EIN_BREC_INTS ints in ein_brec for the top-down pass: left node, right node, node of its
 // output, its region, offset of W, offset and stride of its mixing weights (offset -1: one partition), source of its
@@ -220,6 +222,7 @@ struct EinStatsWork {
     const double* Off;
     int first, count, B, K;
     int total;                       // items of all layers below the root's
+    bool formed;                     // chunk by chunk, in `part`: only to be added up
 };
 // Few items above K = 16 with several chunks of 128 samples: the batch is split into this many shares (of whole chunks), so
 // that every wave of the chip has work of its own; a wave takes about three row tiles of a slice there.
@@ -253,7 +256,7 @@ void launch_sum_partial_stats(const PartialSumList& list, float* stats, bool acc
 // img: ein_image_floats(K, B) floats per item of the model; part: as in EinStatsWork, is kept in *list by the caller.
 // direct: the posterior of every item's region is not in G; the kernel adds up the parent's blocks itself, as
 // ein_brec says (only layers with Plan::ein_layer_direct set; then no launch_region_assemble for their regions).
-void launch_einsum_backward(const DevTables& t, int first, int count, bool full_k, bool accumulate,
+void launch_einsum_backward(const DevTables& t, int first, int count, bool accumulate,
                             const float* params, float* stats, const float* A, const double* Off, const float* amax,
                             const float* G, float* Gp, float* img, PartialSumList* list, bool direct, const Dims& d,
                             hipStream_t s);

@@ -282,7 +282,7 @@ __global__ __launch_bounds__(256) void k_leaf_backward_categorical(
 // tot = sum_b p[b][k] is summed on the side.
 // Runs in one launch with the mixing statistics, hence the eight waves; `waves` of them have pairs.
 // Bound by the loads of the values, which no other workgroup reads: strips of 128 x 128 x 3 images, K = 40, 500 samples:
-// 61 us, with the values staged through LDS for float32 matrix instructions and the batch cut into groups 91 + 10 us.
+// 51 us, with the values staged through LDS for float32 matrix instructions and the batch cut into groups 91 + 10 us.
 constexpr int LX_THREADS = 512;
 constexpr int LX_STEP = 64, LX_RB = LX_STEP + 8;       // samples per step; row stride (bfloat16) of the posteriors
 // Smallest of `least` and of the values that are not zero, as twice its bits less one.
@@ -509,8 +509,8 @@ __device__ __forceinline__ void leaf_stats_body(
 // The same for models with few tiles of 16 pairs: a workgroup takes one tile and deals the batch to its eight waves, 32 samples
 // at a time; every wave splits the posteriors of its own samples, so nothing is shared before the waves' sums meet at the end.
 // With mixing statistics, us of the launch (in brackets: both operands staged through LDS, a thread per (pair, entry)): 32x32x3
-// images in cells of 8 x 8, K = 40: 14.5 for 128 samples (14.7), 53 for 1000 (80); 28x28 in cells, K = 16, 256 samples, with flags:
-// 9.4 (18.0); lists of variables, K = 30, 100 samples: 12.8 (14.4).
+// images in cells of 8 x 8, K = 40: 12.5 for 128 samples (14.7), 47 for 1000 (80); 28x28 in cells, K = 16, 256 samples, with flags:
+// 8.0 (18.0); lists of variables, K = 20, 200 samples: 9.3 (16.8).
 template <bool SQ, bool MASK, int NJ>
 struct LeafTileLds {
     static constexpr int NR = 16 * NJ, NK = 1 + (SQ ? 1 : 0) + (MASK ? 1 : 0);
