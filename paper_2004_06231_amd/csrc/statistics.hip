@@ -657,7 +657,8 @@ __device__ __forceinline__ void leaf_tile_body(
         for (int w = 0; w < 8; ++w) sum += reinterpret_cast<const floatx4*>(lds + w * LY::SUMS)[blk * 64 + lane];
         float t = 0.f;
         if (q == 0 || q == NK - 1)
-            for (int w = 0; w < 8; ++w)
+#pragma unroll 2
+            for (int w = 0; w < 8; ++w)                // (all at once would take 64 registers)
 #pragma unroll
                 for (int h = 0; h < 8; ++h) t += reinterpret_cast<const float*>(lds + w * LY::SUMS + NK * NJ * 1024)[h * NR + k];
         // (the old statistics are requested before the first store)
