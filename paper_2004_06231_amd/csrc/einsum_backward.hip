@@ -157,7 +157,8 @@ __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posteri
         if (256 * x < npiece) {
             int k, i, p;
             piece_of(min(tid + 256 * x, npiece - 1), k, i, p);
-            load_piece<KQ, QUADS>(W + (size_t)(min(k, K - 1) * K + min(i, K - 1)) * K, p, K, w[x]);
+            const int row = QUADS ? k * K + i : min(k, K - 1) * K + min(i, K - 1);
+            load_piece<KQ, QUADS>(W + (size_t)row * K, p, K, w[x]);
         }
     }
     // ---- this lane's piece of its sample's rows

@@ -46,7 +46,8 @@ __device__ __forceinline__ StatRows stat_rows(const int32_t* rec, int item, cons
 // row tiles of its samples: rows come in as 16-byte pieces (lane = (sample, piece)), pass through a wave-private LDS
 // tile, [sample][16] as they are in memory, and only the sums of the four waves meet at the end.  Entries beyond K are
 // rows and columns of the product that nobody reads; samples beyond the batch have Q = 0.  The row tiles of an item
-// (blocks of four left entries) are spread over nsplit workgroups where there are few items.
+// (blocks of four left entries) are spread over nsplit workgroups where there are few items, and the batch over nshare where
+// that is not enough (statistics in blocks of their own, [nshare][count][K^3], which a later launch adds up).
 // Bound by the instructions besides the matrix ones (rows to operands).  K = 10, 2540 items, 100 samples: 29.8 us; K = 16, 388
 // items, 256 samples: 18.4 us.  (Sum of the top-down launches with it 87.9 us, with the statistics in every launch 126.6.)
 template <int KQ, bool QUADS, bool ACCUM>
@@ -54,14 +55,16 @@ __global__ __launch_bounds__(256, 3) void k_einsum_stats_small(const int32_t* __
                                                              float* __restrict__ stats, const float* __restrict__ A,
                                                              const double* __restrict__ Off, const float* __restrict__ amax,
                                                              const float* __restrict__ G, const float* __restrict__ Gp,
-                                                             int item0, int nsplit, int B, int K_) {
+                                                             int item0, int count, int nsplit, int nshare, int share,
+                                                             float* __restrict__ part_blocks, int B, int K_) {
     constexpr int KP = 4 * KQ, WT = 32 * 16;           // floats of a wave's tile
     __shared__ __attribute__((aligned(16))) float lds[4 * 3 * WT];
     const int K = QUADS ? KP : K_;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c16 = lane & 15, g = lane >> 4;
     const int vb = xcd_contiguous_block();
-    const int li = vb / nsplit, part = vb - li * nsplit;
+    const int part = vb % nsplit, sh = (vb / nsplit) % nshare, li = vb / (nsplit * nshare);
+    const int bs = sh * share, be = min(bs + share, B);       // this workgroup's samples
     const int i0 = part * KQ / nsplit, i1 = (part + 1) * KQ / nsplit;
     const int32_t* rec = e_rec + (size_t)li * EIN_BREC_INTS;
     const StatRows rows = stat_rows(rec, item0 + li, params, A, Off, amax, G, Gp, B, K);
@@ -101,12 +104,12 @@ __global__ __launch_bounds__(256, 3) void k_einsum_stats_small(const int32_t* __
     for (int it = 0; it < KQ; ++it)
 #pragma unroll
         for (int kt = 0; kt < KQ; ++kt) acc[it][kt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if (32 * wave < B) fetch(32 * wave);
-    for (int b0 = 32 * wave; b0 < B; b0 += 128) {
+    if (bs + 32 * wave < be) fetch(bs + 32 * wave);
+    for (int b0 = bs + 32 * wave; b0 < be; b0 += 128) {
         __builtin_amdgcn_wave_barrier();               // (the LDS serves a wave's requests in order)
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const bool in = b0 + 16 * u + ls < B;
+            const bool in = b0 + 16 * u + ls < be;
             floatx4 q, r, l;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -121,10 +124,10 @@ __global__ __launch_bounds__(256, 3) void k_einsum_stats_small(const int32_t* __
                 *reinterpret_cast<floatx4*>(sL + o) = l;
             }
         }
-        if (b0 + 128 < B) fetch(b0 + 128);
+        if (b0 + 128 < be) fetch(b0 + 128);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        const int steps = min(32, B - b0);
+        const int steps = min(32, be - b0);
         for (int s = 0; s < steps; s += 4) {           // lane group g: sample s + g
             const float* q0 = sQ + (s + g) * 16 + (c16 >> 2);
             const float* l0 = sL + (s + g) * 16 + (c16 & 3);
@@ -147,7 +150,7 @@ __global__ __launch_bounds__(256, 3) void k_einsum_stats_small(const int32_t* __
     // The four waves' sums of the tiles of one block of left entries at a time; wave w finishes tile kt = w:
     // acc[it][kt][c]: k = 4 kt + g, i = 4 it + c, j = c16
     const float* W = params + rec[4];
-    float* Nw = stats + rec[4];
+    float* Nw = nshare > 1 ? part_blocks + ((size_t)sh * count + li) * (K * K * K) : stats + rec[4];
     floatx4* red = reinterpret_cast<floatx4*>(lds);    // [wave][kt][lane]
     static_assert(4 * KQ * 64 * 4 <= 4 * 3 * WT, "the sums fit where the rows were");
 #pragma unroll
@@ -183,14 +186,16 @@ template <int KQ>
 void launch_stats_small(const EinStatsWork& w, bool accumulate, float* stats, hipStream_t s) {
     // three workgroups per compute unit
     const int want = (3 * EINET_NUM_CUS + w.count - 1) / w.count, nsplit = want > KQ ? KQ : want;
+    const int nshare = ein_stat_shares(w.count, w.K, w.B), share = ein_stat_share(nshare, w.B);
 #define EINET_LAUNCH(Q, ACC)                                                                                          \
-    hipLaunchKernelGGL((k_einsum_stats_small<KQ, Q, ACC>), dim3(w.count * nsplit), dim3(256), 0, s, w.rec, w.params, stats, \
-                       w.A, w.Off, w.amax, w.G, w.Gp, w.first, nsplit, w.B, w.K)
+    hipLaunchKernelGGL((k_einsum_stats_small<KQ, Q, ACC>), dim3(w.count * nsplit * nshare), dim3(256), 0, s, w.rec, w.params, \
+                       stats, w.A, w.Off, w.amax, w.G, w.Gp, w.first, w.count, nsplit, nshare, share, w.part, w.B, w.K)
+    const bool adds = accumulate && nshare == 1;       // (blocks of shares are written, not added to)
     if (w.K == 4 * KQ) {
-        if (accumulate) EINET_LAUNCH(true, true);
+        if (adds) EINET_LAUNCH(true, true);
         else EINET_LAUNCH(true, false);
     } else {
-        if (accumulate) EINET_LAUNCH(false, true);
+        if (adds) EINET_LAUNCH(false, true);
         else EINET_LAUNCH(false, false);
     }
 #undef EINET_LAUNCH

@@ -224,15 +224,23 @@ struct EinStatsWork {
     int total;                       // items of all layers below the root's
     bool formed;                     // chunk by chunk, in `part`: only to be added up
 };
-// Few items above K = 16 with several chunks of 128 samples: the batch is split into this many shares (of whole chunks), so
-// that every wave of the chip has work of its own; a wave takes about three row tiles of a slice there.
+// Few items with several chunks of 128 samples: the batch is split into shares (of whole chunks), as many as give every wave of
+// the chip work of its own; above K = 16 a wave takes about three row tiles of a slice there.  Up to K = 16 the workgroups walk the
+// batch 128 samples at a time (about 2 us), which a sum of blocks is worth from four chunks on: K = 16, 28 items, 1000 samples:
+// 21.8 us in one share, 11.0 in four and 3.9 for the sum.
+inline long long ein_stat_units(int count, int K) {
+    const int kq = (K + 3) / 4;
+    return (long long)count * kq * (K <= 16 ? 1 : (kq + 2) / 3);
+}
+inline long long ein_stat_most_shares(int count, int K, int B) {
+    const long long units = ein_stat_units(count, K), nchunks = (B + 127) / 128;
+    if (units == 0 || nchunks < (K <= 16 ? 4 : 2) || units > (K <= 16 ? 384 : 1024)) return 1;
+    return std::min<long long>((K <= 16 ? 768 : 2048) / units, nchunks);
+}
 inline int ein_stat_shares(int count, int K, int B) {
-    const int kq = (K + 3) / 4, nchunks = (B + 127) / 128;
-    const long long units = (long long)count * kq * ((kq + 2) / 3);
-    if (K <= 16 || units == 0 || units > 1024 || nchunks < 2) return 1;
-    const long long v = 2048 / units;
-    const int cpv = v >= nchunks ? 1 : (int)((nchunks + v - 1) / v);
-    return (nchunks + cpv - 1) / cpv;
+    const int nchunks = (B + 127) / 128, v = (int)ein_stat_most_shares(count, K, B);
+    const int cpv = v < 1 ? nchunks : (nchunks + v - 1) / v;
+    return cpv < 1 ? 1 : (nchunks + cpv - 1) / cpv;
 }
 inline int ein_stat_share(int nshare, int B) {       // samples of a share
     const int nchunks = (B + 127) / 128;
@@ -240,10 +248,8 @@ inline int ein_stat_share(int nshare, int B) {       // samples of a share
 }
 inline size_t ein_stat_partial_bound(int count, int K, int max_B) {
     // (for any batch up to max_B: at most as many shares as chunks, and as the waves allow)
-    const int kq = (K + 3) / 4, nchunks = (max_B + 127) / 128;
-    const long long units = (long long)count * kq * ((kq + 2) / 3);
-    if (K <= 16 || units == 0 || units > 1024 || nchunks < 2) return 0;
-    return (size_t)std::min<long long>(2048 / units, nchunks) * count * K * K * K;
+    const long long v = ein_stat_most_shares(count, K, max_B);
+    return v < 2 ? 0 : (size_t)v * count * K * K * K;
 }
 struct PartialSumList {
     int n = 0;

@@ -58,8 +58,24 @@ int blocks() {
     if (bad) printf("posterior blocks: %d cases wrong\n", bad);
     return bad;
 }
+// Shares of the batch: whole chunks, none empty, together the batch; their blocks fit the scratch of any larger batch.
+int shares() {
+    int bad = 0;
+    for (int K = 1; K <= 64; ++K)
+        for (int count : {1, 2, 3, 4, 7, 8, 14, 16, 24, 28, 32, 48, 60, 64, 96, 97, 112, 128, 194, 384, 385, 1000, 2540})
+            for (int most : {1, 128, 129, 300, 512, 1000, 4096}) {
+                const size_t room = ein_stat_partial_bound(count, K, most);
+                for (int B = 1; B <= most; B += most > 512 ? 37 : 1) {
+                    const int n = ein_stat_shares(count, K, B), share = ein_stat_share(n, B);
+                    bad += n < 1 || (long)n * share < B || (n > 1 && (share % 128 != 0 || (long)(n - 1) * share >= B ||
+                                                                      (size_t)n * count * K * K * K > room));
+                }
+            }
+    if (bad) printf("shares: %d cases wrong\n", bad);
+    return bad;
+}
 int main() {
-    if (blocks()) return 1;
+    if (blocks() || shares()) return 1;
     return walk_k8<3>() + walk_k8<4>() + walk_k8<5>() + walk_k8<6>() + walk_k8<7>() + walk_k8<8>() ? 1 : 0;
 }
 """
@@ -67,7 +83,7 @@ int main() {
 
 @pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"),
                     reason="needs g++ and the HIP headers")
-def test_reads_and_blocks_of_the_top_down_kernels(tmp_path):
+def test_reads_blocks_and_shares_of_the_top_down_kernels(tmp_path):
     src, exe = tmp_path / "walk.cpp", str(tmp_path / "walk")
     src.write_text(PROGRAM)
     res = subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC, str(src),
