@@ -5,8 +5,9 @@
 // out: mid is at most 2^-8 of its number and lo 2^-17, so they are at most 2^-24 of the product, what one float32 product
 // is rounded by, and 2^-27.5 in the root mean square over random pairs.  The other six are accumulated in float32 (the
 // scheme of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision
-// Computations", 2019).  All operands of the circuit are non-negative, so no sum cancels and the error of a result is the
-// error of its terms plus that of the float32 accumulation, as with float32 operands.
+// Computations", 2019).  Weights, exponentials and posteriors are non-negative, so their sums do not cancel and the error of a
+// result is the error of its terms plus that of the float32 accumulation, as with float32 operands.  Values of Gaussian leaves
+// may be negative; sums of them cancel as they do in float32, from terms that are as accurate.
 // (A rest below 2^-133, the smallest bfloat16, is lost: numbers below 2^-109 would keep fewer bits.  Both operands, the
 // exponentials and the weights, are therefore multiplied by the power of two X6_SCALE before they are split and the sums by
 // X6_UNSCALE at the end: the smallest normal float32 becomes 2^-102, whose last bit is a normal bfloat16.  Sums stay below

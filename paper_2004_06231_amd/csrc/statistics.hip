@@ -620,9 +620,12 @@ __device__ __forceinline__ void leaf_tile_body(
 #pragma unroll
             for (int q = 0; q < 4; ++q) one[q] = (ob[2 * q] ? 0x3380u : 0u) | (ob[2 * q + 1] ? 0x33800000u : 0u);
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
+            for (int jt = 0; jt < NJ; ++jt) {              // (small parts first, one rounding of the sums per step)
+                floatx4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int jt = 0; jt < NJ; ++jt) acc[NK - 1][jt] = mfma_bf16(one, pb[jt][p], acc[NK - 1][jt]);
+                for (int p = 2; p >= 0; --p) t = mfma_bf16(one, pb[jt][p], t);
+                acc[NK - 1][jt] += t;
+            }
         }
     }
     if constexpr (SQ) {
