@@ -267,10 +267,10 @@ int einet_create(const einet_spec* spec, einet_t** out) {
     h->off_G = off;
     off = align256(off + sizeof(float) * size_t(p.num_nodes) * mb * K);
     h->off_Gp = off;
-    off = align256(off + sizeof(float) * gp_blocks_per_item(p.K) * p.ein_left.size() * mb * K);
+    off = align256(off + sizeof(float) * (size_t)p.gp_blocks * mb * K);
     h->off_img = off;
-    off = align256(off + sizeof(float) * ein_image_floats(p.K, (int)mb) * p.ein_left.size());
     if (p.num_layers > 0) {
+        off = align256(off + sizeof(float) * ein_image_floats(p.ein_layer_ptr[p.num_layers - 1], (int)p.K, (int)mb));
         const int top = p.num_layers - 1, count = p.ein_layer_ptr[top + 1] - p.ein_layer_ptr[top];
         h->root_part_floats = (root_bwd_partial_bound(count, (int)p.K, (int)mb) + 63) & ~size_t(63);
         h->part_floats = h->root_part_floats + ein_stat_partial_bound(p.ein_layer_ptr[top], (int)p.K, (int)mb);

@@ -123,7 +123,7 @@ template <int KQ, bool QUADS, bool STATS, bool ACCUM, bool SPLIT>
 __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posterior_small(
     const int32_t* __restrict__ e_rec, const float* __restrict__ params, float* __restrict__ stats, const float* __restrict__ A,
     const double* __restrict__ Off, const float* __restrict__ amax, const float* __restrict__ G, float* Gp, int item0,
-    int nchunks, int ngr_, int direct, int nblk, int B, int K_) {
+    int nchunks, int ngr_, int direct, int B, int K_) {
     using LY = PostSmall<KQ>;
     constexpr int SI = LY::SI, S = LY::S, KP = LY::KP;
     __shared__ __attribute__((aligned(16))) float wl[KP * S];
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(256, STATS && KQ > 2 ? 2 : 4) void k_einsum_posteri
             transpose_groups(glf);
             transpose_groups(gr);
         }
-        float* gleft = Gp + (size_t)(item0 + li) * nblk * blk + (size_t)b * K;
+        float* gleft = Gp + (size_t)rec[9] * blk + (size_t)b * K;
         float* gright = gleft + (size_t)(1 + grp) * blk;
         if (QUADS) {
             if (g >= it0 && g < it1 && b < B) *reinterpret_cast<floatx4*>(gleft + 4 * g) = floatx4{glf[0], glf[1], glf[2], glf[3]};
@@ -339,7 +339,7 @@ template <int K8, bool EXACT>
 __global__ __launch_bounds__(256, PostLayout<K8>::WAVES) void k_einsum_posterior(
     const int32_t* __restrict__ e_rec, const float* __restrict__ params, const float* __restrict__ A,
     const double* __restrict__ Off, const float* __restrict__ amax, const float* __restrict__ G, float* Gp, float* __restrict__ img,
-    int item0, int nchunks, int ngr, int direct, int nblk, int B, int K_) {
+    int item0, int nchunks, int ngr, int direct, int B, int K_) {
     const int K = EXACT ? 8 * K8 : K_;
     using LY = PostLayout<K8>;
     using X = X6<K8>;
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(256, PostLayout<K8>::WAVES) void k_einsum_posterior
     int unit[X::NR];
 #pragma unroll
     for (int a = 0; a < X::NR; ++a) unit[a] = x6_row_unit<K8>(a, kg, c16);
-    float* gleft = Gp + (size_t)(item0 + li) * nblk * blk;
+    float* gleft = Gp + (size_t)rec[9] * blk;
     float* gright = gleft + (size_t)(1 + grp) * blk;
 
     int buf = 0;
@@ -655,7 +655,7 @@ void launch_posterior_small(const DevTables& t, int first, int count, bool with_
 #define EINET_LAUNCH(Q, ST, ACC, SP)                                                                                         \
     hipLaunchKernelGGL((k_einsum_posterior_small<KQ, Q, ST, ACC, SP>), dim3(count * nchunks * ngr), dim3(256), 0, s,              \
                        t.ein_brec + (size_t)first * EIN_BREC_INTS, params, stats, A, Off, amax, G, Gp, first, nchunks, ngr,   \
-                       direct ? 1 : 0, gp_blocks_per_item(d.K), d.B, d.K)
+                       direct ? 1 : 0, d.B, d.K)
 #define EINET_LAUNCH_Q(Q)                                                     \
     do {                                                                      \
         if (!with_stats) EINET_LAUNCH(Q, false, false, false);                \
@@ -687,7 +687,7 @@ void launch_posterior_k8(const DevTables& t, int first, int count, const float* 
 #define EINET_LAUNCH(EX)                                                                                              \
     hipLaunchKernelGGL((k_einsum_posterior<K8, EX>), dim3(count * nchunks * ngr), dim3(256), lds, s,                    \
                        t.ein_brec + (size_t)first * EIN_BREC_INTS, params, A, Off, amax, G, Gp, img, first, nchunks, ngr, \
-                       direct ? 1 : 0, gp_blocks_per_item(d.K), d.B, d.K)
+                       direct ? 1 : 0, d.B, d.K)
     if (d.K == 8 * K8) EINET_LAUNCH(true);
     else EINET_LAUNCH(false);
 #undef EINET_LAUNCH
@@ -765,8 +765,8 @@ template <int KQ, bool VEC, bool ACCUM, bool DIRECT, bool LOOP>
 __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
     const int32_t* __restrict__ e_rec,
     const float* __restrict__ params, float* __restrict__ stats, const float* __restrict__ A,
-    const double* __restrict__ Off, const float* __restrict__ amax, const float* __restrict__ G, float* __restrict__ Gp,
-    int item0, int ngroups, int nshare, int cpv, int total, float* __restrict__ part, int nblk, int B, int K) {
+    const double* __restrict__ Off, const float* __restrict__ amax, const float* __restrict__ G, float* Gp,
+    int item0, int ngroups, int nshare, int cpv, int total, float* __restrict__ part, int B, int K) {
     using LY = BwdLayout<KQ>;
     constexpr int KP = LY::KP, SI = LY::SI, S = LY::S, ST = LY::ST, BC = LY::BC, MAXU = LY::MAXU;
     extern __shared__ float lds[];
@@ -790,6 +790,8 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
     // region's only parent wrote to Gp, added up in the order the assembly launch would take
     const int gcnt = DIRECT ? bwd_source_blocks(rec[8], K, B) : 0;
     const float* Gs = DIRECT ? Gp + (size_t)rec[7] * blk : G + (size_t)rec[3] * blk;
+    float* gleft = Gp + (size_t)rec[9] * blk;
+    float* gright = gleft + (size_t)(1 + grp) * blk;
     const float* W = params + rec[4];
     const size_t wbase = (size_t)rec[4];
     const int voff = rec[5], vstr = rec[6];
@@ -1031,7 +1033,7 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                 }
                 // acc[jt][r] = U[b][i = 4it+r][j = 4jt+g]
                 float gl0 = 0.f, gl1 = 0.f, gl2 = 0.f, gl3 = 0.f;
-                float* right = Gp + ((size_t)(item * nblk + 1 + grp) * B + b0 + bl) * K;
+                float* right = gright + (size_t)(b0 + bl) * K;
                 float* racc = sG + bl * KP;
 #pragma unroll
                 for (int jt = 0; jt < KQ; ++jt) {
@@ -1049,7 +1051,7 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
                 gl2 += __shfl_xor(gl2, 16, 64); gl2 += __shfl_xor(gl2, 32, 64);
                 gl3 += __shfl_xor(gl3, 16, 64); gl3 += __shfl_xor(gl3, 32, 64);
                 const float glr = g == 0 ? gl0 * e4.x : (g == 1 ? gl1 * e4.y : (g == 2 ? gl2 * e4.z : gl3 * e4.w));
-                if (ok && 4 * it + g < K) Gp[((size_t)(item * nblk) * B + b0 + bl) * K + 4 * it + g] = glr;
+                if (ok && 4 * it + g < K) gleft[(size_t)(b0 + bl) * K + 4 * it + g] = glr;
             }
 
             // ---- GEMM-1 epilogue: Nw += W * acc
@@ -1066,7 +1068,7 @@ __global__ __launch_bounds__(512, 2) void k_einsum_backward_fused(
         }
         if (multi) {                        // Gp_right of the workgroup's slices, row by row
             __syncthreads();
-            float* right = Gp + ((size_t)(item * nblk + 1 + grp) * B + b0) * K;
+            float* right = gright + (size_t)b0 * K;
             for (int e = tid; e < nb * K; e += 512) {
                 const int b = e / K, j = e - b * K;
                 right[e] = sG[b * KP + j];
@@ -1083,33 +1085,6 @@ void launch_region_assemble(const DevTables& t, int first, int count, bool is_ro
     dim3 grid(count, (d.B * d.K + 255) / 256);
     hipLaunchKernelGGL(k_region_assemble, grid, dim3(256), 0, s, t.rb_rec + (size_t)first * RB_REC_INTS, t.rb_pblk,
                        is_root_layer ? 1 : 0, G, Gp, bwd_block_limit(d.K, d.B), d.B, d.K);
-}
-
-// Whether the layers take that form; `total`: items of all layers below the root's (all layers of a model take the same one).
-// Us of an EM step with one launch per layer and with two forms of launches:
-//   one chunk, 28 / 112 / 194 / 496 items: K = 22, 128 samples: 92 / 111 / 172 / 210 and 109 / 126 / 189 / 219; K = 32, 64: 89 / 100 /
-//     180 / 225 and 95 / 111 / 182 / 224, 128: 101 / 123 / 208 / 282 and 107 / 132 / 201 / 252; K = 40, 16: 97 / 125 / 208 / 296 and
-//     107 / 141 / 222 / 340, 128: 123 / 186 / 281 / 473 and 124 / 181 / 258 / 437;
-//   256 samples, a block per chunk, 8 / 24 items: K = 20 53 / 66 and 65 / 78, K = 32 62 / 91 and 70 / 99, K = 40 77 / 109 and 85 / 119;
-//     both chunks in turn, 112 / 194 items: K = 20 136 / 196 and 148 / 210, K = 28 172 / 266 and 191 / 264, K = 36 279 / 414 and 244 /
-//     336;
-//   640 samples, a block per chunk, 4 / 8 / 16 items: K = 24 61 / 64 / 83 and 71 / 74 / 96, K = 40 75 / 103 / 143 and 82 / 106 / 143.
-static bool einsum_backward_fused(int total, int K, int B) {
-    const bool quads = (K & 3) == 0;                      // (rows of other K are staged entry by entry, from registers that spill)
-    if (K <= 16 || K > 48 || (K > 40 && !quads)) return false;
-    const int nchunks = (B + 127) / 128;
-    if (nchunks > 1) {
-        if (ein_stat_shares(total, K, B) == nchunks) return K <= 32 || nchunks == 2 || total <= 8 || (nchunks == 3 && total <= 16);
-        return nchunks == 2 && ((K <= 20 && total <= 256) || (K == 28 && total <= 128));
-    }
-    if (total <= 32 || K <= 24) return true;
-    if (total <= 128) return K <= 32 || B <= 64;
-    return (K <= 28 && total <= 256) || B <= 32 || (B <= 64 && quads);
-}
-// Shares of the chunks there: as many as chunks, or all chunks in turn where their blocks do not fit the scratch.
-static int fused_shares(int total, int K, int B) {
-    const int nchunks = (B + 127) / 128;
-    return ein_stat_shares(total, K, B) == nchunks ? nchunks : 1;
 }
 
 template <int KQ>
@@ -1132,7 +1107,7 @@ static void launch_backward_fused(const DevTables& t, int first, int count, bool
         }                                                                                                                   \
         hipLaunchKernelGGL((k_einsum_backward_fused<KQ, V, ACC, DIR, L>), dim3(count * nshare * ngroups), dim3(512), lds, s, \
                            t.ein_brec + (size_t)first * EIN_BREC_INTS, params, stats, A, Off, amax, G, Gp, first, ngroups,  \
-                           nshare, cpv, total, part, gp_blocks_per_item(d.K), d.B, d.K);                                    \
+                           nshare, cpv, total, part, d.B, d.K);                                                             \
     } while (0)
 #define EINET_LAUNCH_A(V, DIR, L)                              \
     do {                                                       \

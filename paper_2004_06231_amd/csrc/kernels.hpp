@@ -56,8 +56,8 @@ void launch_mixing_forward(const DevTables& t, int first, int count, int max_chi
 // single output entry each); root_rec lists them: number of partitions, the root's node, the offset of its mixing
 // weights (-1: one partition), unused, then ROOT_REC_STRIDE ints per partition: einsum item, left node, right node,
 // node of the partition's own output (the root's node when it is the only one), offset of W, position among the
-// root's mixing weights.
-constexpr int ROOT_REC_STRIDE = 6;
+// root's mixing weights, first of its posterior blocks.
+constexpr int ROOT_REC_STRIDE = 7;
 // Row stride (floats) of the LDS copies of these kernels: a multiple of 4 whose quarter is odd, so that 16-byte reads
 // of eight consecutive rows fall into different banks.
 #if defined(__HIPCC__)
@@ -101,9 +101,8 @@ constexpr int RB_REC_INTS = 64, RB_REC_BLOCKS = 28, RB_REC_ALWAYS = 60;
 void launch_region_assemble(const DevTables& t, int first, int count, bool is_root_layer, float* G, const float* Gp,
                             const Dims& d, hipStream_t s);
 
-// posterior blocks ([B][K] floats each) reserved per einsum item in Gp: one for its left child, then up to
-// one per slice of four left entries for its right child
-inline int gp_blocks_per_item(int K) { return 1 + (K + 3) / 4; }
+// Posterior blocks ([B][K] floats each) of an einsum item in Gp: one for its left child, then one per workgroup that takes some of
+// its slices for its right child; reserved are those of the smallest batch.  A record names an item's first block.
 constexpr int PS_SAMPLES = 64;       // samples of a workgroup of the top-down kernel for K up to 16
 // Workgroups per (item, chunk of 128 samples) of the top-down kernel for a layer of `count` items: the slices of an item are
 // spread over several workgroups where the launch would otherwise have fewer than bwd_workgroups of them (one per compute
@@ -186,7 +185,7 @@ inline bool bwd_reads_blocks(int count, int K) { return K != 16 || count >= 32; 
 
 // Every einsum item has a record of EIN_BREC_INTS ints in ein_brec for the top-down pass: left node, right node, node of its
 // output, its region, offset of W, offset and stride of its mixing weights (offset -1: one partition), source of its
-// region's posterior (two ints), unused.
+// region's posterior (two ints), first of its own posterior blocks, unused.
 constexpr int EIN_BREC_INTS = 12;
 // Above K = 16 the top-down kernel also leaves the operands of an item's weight statistics in memory, sample-major:
 // EIN_IMAGES images of 4 ceil(K / 4) rows of ein_image_stride(B) floats each, Q, then eR, then eL (rows beyond K and samples
@@ -196,9 +195,6 @@ constexpr int EIN_IMAGES = 3;
 __host__ __device__
 #endif
 inline int ein_image_stride(int B) { return (B + 31) & ~31; }
-inline size_t ein_image_floats(int K, int B) {       // per item
-    return K <= 16 ? 0 : (size_t)EIN_IMAGES * (4 * ((K + 3) / 4)) * ein_image_stride(B);
-}
 
 // What the end of a top-down pass still has to do for the statistics of the weights.  They are not needed before the
 // M-step, so the launches of a pass only note it down.
@@ -251,6 +247,40 @@ inline size_t ein_stat_partial_bound(int count, int K, int max_B) {
     const long long v = ein_stat_most_shares(count, K, max_B);
     return v < 2 ? 0 : (size_t)v * count * K * K * K;
 }
+// Above K = 16 the layers take one of two forms: posteriors and statistics in one launch per layer (k_einsum_backward_fused), or
+// posteriors per layer and the statistics of all layers at the end.  total: items of all layers below the root's (all layers of a model take the same
+// form).  Us of an EM step, one launch per layer and the other form:
+//   one chunk, 28 / 112 / 194 / 496 items: K = 22, 128 samples: 92 / 111 / 172 / 210 and 109 / 126 / 189 / 219; K = 32, 64: 89 / 100 /
+//     180 / 225 and 95 / 111 / 182 / 224, 128: 101 / 123 / 208 / 282 and 107 / 132 / 201 / 252; K = 40, 16: 97 / 125 / 208 / 296 and
+//     107 / 141 / 222 / 340, 128: 123 / 186 / 281 / 473 and 124 / 181 / 258 / 437;
+//   256 samples, a block per chunk, 8 / 24 items: K = 20 53 / 66 and 65 / 78, K = 32 62 / 91 and 70 / 99, K = 40 77 / 109 and 85 / 119;
+//     both chunks in turn, 112 / 194 items: K = 20 136 / 196 and 148 / 210, K = 28 172 / 266 and 191 / 264, K = 36 279 / 414 and 244 /
+//     336;
+//   640 samples, a block per chunk, 4 / 8 / 16 items: K = 24 61 / 64 / 83 and 71 / 74 / 96, K = 40 75 / 103 / 143 and 82 / 106 / 143.
+inline bool einsum_backward_fused(int total, int K, int B) {
+    const bool quads = (K & 3) == 0;                      // (rows of other K are staged entry by entry, from registers that spill)
+    if (K <= 16 || K > 48 || (K > 40 && !quads)) return false;
+    const int nchunks = (B + 127) / 128;
+    if (nchunks > 1) {
+        if (ein_stat_shares(total, K, B) == nchunks) return K <= 32 || nchunks == 2 || total <= 8 || (nchunks == 3 && total <= 16);
+        return nchunks == 2 && ((K <= 20 && total <= 256) || (K == 28 && total <= 128));
+    }
+    if (total <= 32 || K <= 24) return true;
+    if (total <= 128) return K <= 32 || B <= 64;
+    return (K <= 28 && total <= 256) || B <= 32 || (B <= 64 && quads);
+}
+// Shares of the chunks in one launch per layer: as many as chunks, or all chunks in turn where their blocks do not fit the scratch.
+inline int fused_shares(int total, int K, int B) {
+    const int nchunks = (B + 127) / 128;
+    return ein_stat_shares(total, K, B) == nchunks ? nchunks : 1;
+}
+
+// Floats of images (EIN_IMAGES) for batches of up to max_B, of which some take the other form
+inline size_t ein_image_floats(int total, int K, int max_B) {
+    int B = K <= 16 ? 0 : max_B;
+    while (B > 0 && einsum_backward_fused(total, K, B)) --B;
+    return (size_t)total * EIN_IMAGES * (4 * ((K + 3) / 4)) * ein_image_stride(B);
+}
 struct PartialSumList {
     int n = 0;
     PartialSumJobs jobs;
@@ -259,7 +289,7 @@ struct PartialSumList {
 void launch_sum_partial_stats(const PartialSumList& list, float* stats, bool accumulate, hipStream_t s);
 // Posteriors of the children of a layer's items (every layer but the root's: all items have K output entries).  Notes the
 // items down in *list for their statistics: the layers of a pass come from the top, so their items are one range.
-// img: ein_image_floats(K, B) floats per item of the model; part: as in EinStatsWork, is kept in *list by the caller.
+// img: ein_image_floats floats; part: as in EinStatsWork, is kept in *list by the caller.
 // direct: the posterior of every item's region is not in G; the kernel adds up the parent's blocks itself, as
 // ein_brec says (only layers with Plan::ein_layer_direct set; then no launch_region_assemble for their regions).
 void launch_einsum_backward(const DevTables& t, int first, int count, bool accumulate,

@@ -227,9 +227,8 @@ __global__ __launch_bounds__(RB_THREADS) void k_root_backward(const int32_t* __r
     const float* aR = aL + B;
     const float* W = params + woff;
     float* Nw = vper > 1 ? part + ((size_t)vg * n_partitions + p) * ((size_t)K * K) : stats + woff;
-    const int nblk = 1 + KQ;
-    float* gleft = Gp + (size_t)item * nblk * blk;
-    float* gright = Gp + ((size_t)item * nblk + 1 + grp) * blk;
+    float* gleft = Gp + (size_t)q[6] * blk;
+    float* gright = gleft + (size_t)(1 + grp) * blk;
     const bool vec = (K & 3) == 0;
     // Roles within a pass (they run side by side): threads 0 .. 127 stage QL and take the left child (one sample each),
     // threads 128 .. 128 + 4K - 1 take the statistics (entry (il, j) each; the first K4 of them also bring the W rows in),

@@ -377,10 +377,10 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
         p.leaf_sptr.push_back((int32_t)p.leaf_var.size());
     }
 
-    // ---- top-down items: which posterior blocks flow into each region.  Item e owns blocks
-    // e*nb .. e*nb+nb-1 of Gp: block 0 for its left child, blocks 1.. (one per workgroup of the top-down
-    // kernel) for its right child.  How many of those are written depends on the batch: their codes say.
-    const int nb = gp_blocks_per_item(K);
+    // ---- top-down items: which posterior blocks flow into each region.  Item e owns the blocks of Gp from
+    // first_block[e] on: one for its left child, then those for its right child (one per workgroup of the top-down
+    // kernel).  How many of those are written depends on the batch: their codes say.
+    std::vector<int32_t> first_block(np, 0);
     struct Run { int first, blocks, count; };          // count: items of the layer, 0 where all blocks are always written
     std::vector<std::vector<Run>> runs(nr);
     for (int l = 0; l < p.num_layers; ++l) {
@@ -388,8 +388,11 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
         const bool top = l + 1 == p.num_layers;
         const int blocks = top ? root_bwd_groups_per_item(count, K) : bwd_groups_per_item(count, K, 1);
         for (int e = p.ein_layer_ptr[l]; e < p.ein_layer_ptr[l + 1]; ++e) {
-            runs[p.ein_left[e]].push_back({e * nb, 1, 0});
-            runs[p.ein_right[e]].push_back({e * nb + 1, blocks, top ? 0 : count});
+            first_block[e] = p.gp_blocks;
+            if (top) p.root_rec[4 + (size_t)(e - p.ein_layer_ptr[l]) * ROOT_REC_STRIDE + 6] = p.gp_blocks;
+            runs[p.ein_left[e]].push_back({p.gp_blocks, 1, 0});
+            runs[p.ein_right[e]].push_back({p.gp_blocks + 1, blocks, top ? 0 : count});
+            p.gp_blocks += 1 + blocks;
         }
     }
     // (source of a posterior that one parent alone writes, see GSRC_MAX_BLOCKS)
@@ -415,6 +418,7 @@ bool compile_plan(const RegionGraph& g, int K, int C, int family, int leaf_param
             rec[4] = p.ein_woff[e];
             rec[5] = p.ein_voff[e];
             rec[6] = p.ein_vstr[e];
+            rec[9] = first_block[e];
             all = all && g.parts_of[p.ein_reg[e]].size() == 1 && source(p.ein_reg[e], rec + 7, rec + 8);
         }
         p.ein_layer_direct[l] = all ? 1 : 0;

@@ -49,6 +49,7 @@ struct Plan {
 #define X(name) std::vector<int32_t> name;
     EINET_TABLES(X)
 #undef X
+    int32_t gp_blocks = 0;                          // posterior blocks of all einsum items
     std::vector<int32_t> ein_layer_ptr;             // [num_layers+1]
     std::vector<uint8_t> ein_layer_full;            // [num_layers]: every item of the layer has K output entries
     std::vector<uint8_t> ein_layer_direct;          // [num_layers]: the layer's top-down kernel reads its regions'

@@ -52,7 +52,7 @@ int blocks() {
                 const int groups = bwd_groups_per_item(count, K, B), listed = bwd_groups_per_item(count, K, 1);
                 int used = 0;
                 for (int q = 0; q < listed; ++q) used += bwd_block_code(count, q) <= bwd_block_limit(K, B);
-                bad += groups < 1 || groups > listed || 1 + listed > gp_blocks_per_item(K) || used != groups ||
+                bad += groups < 1 || groups > listed || used != groups ||
                        bwd_source_blocks(count, K, B) != groups;
             }
     if (bad) printf("posterior blocks: %d cases wrong\n", bad);
