@@ -473,7 +473,7 @@ int einet_em_accumulate(einet_t* h, const float* x_dev, const uint8_t* mask_dev,
         launch_tail_backward(h->dt, (int)p.lv_leaf.size(), (int)p.leaf_node.size(), p.max_leaf_scope,
                              (int)p.mix_node.size(), p.max_mix_children, x_dev, mask_dev,
                              mask_mode, h->params, A, Off, G, Gp, p.leaves_direct, h->stats, p.phi_offset, p.den_offset,
-                             p.tot_offset, p.n_stats, nullptr, 0, d, s);
+                             p.tot_offset, d, s);
     });
     rc = check_hip(h, "einet_em_accumulate");
     // (after a failed launch nothing is known about the arena or the statistics: the root's ones are written

@@ -1383,8 +1383,6 @@ void launch_einsum_forward(const DevTables& t, int first, int count, bool full_k
     // (only the plain kernel writes logp: an item that writes the root's own node is the root's only partition, which
     // k_root_forward takes)
     switch (einsum_forward_kernel(count, kout, d)) {
-#define EINET_CASE(J, F) case J: F<J>(t, first, count, kout, params, A, Off, amax, d, s); return;
-#undef EINET_CASE
     case FWD_SMALL: launch_einsum_forward_small(t, first, count, kout, params, A, Off, amax, d, s); return;
     case FWD_COMPACT:
 #define EINET_CASE(J) case J: launch_einsum_forward_compact<J>(t, first, count, params, A, Off, amax, d, s); return;

@@ -743,8 +743,7 @@ __global__ __launch_bounds__(LX_THREADS, TILE || MASK || NJ > 3 ? 2 : 4) void k_
 void launch_tail_backward(const DevTables& t, int n_lv, int n_leaves, int max_scope, int n_mix, int max_children,
                           const float* x, const uint8_t* mask, int mask_mode, const float* params, const float* A,
                           const double* Off, const float* G, const float* Gp, bool direct, float* stats,
-                          int64_t phi_off, int64_t den_off, int64_t tot_off, int64_t, float*, size_t, const Dims& d,
-                          hipStream_t s) {
+                          int64_t phi_off, int64_t den_off, int64_t tot_off, const Dims& d, hipStream_t s) {
     const int total = n_lv * d.C * d.K;
     const bool categorical = d.family == EINET_LEAF_CATEGORICAL;
     if (categorical) {   // indicator statistics: a kernel of their own (at most 256 values)

@@ -49,6 +49,8 @@ struct Plan {
 #define X(name) std::vector<int32_t> name;
     EINET_TABLES(X)
 #undef X
+    // per einsum item and per top-down region, on the host only (kernels get them with the records)
+    std::vector<int32_t> ein_reg, ein_voff, ein_vstr, rb_node, rb_kout, rb_pptr;
     int32_t gp_blocks = 0;                          // posterior blocks of all einsum items
     std::vector<int32_t> ein_layer_ptr;             // [num_layers+1]
     std::vector<uint8_t> ein_layer_full;            // [num_layers]: every item of the layer has K output entries
