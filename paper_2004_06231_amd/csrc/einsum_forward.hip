@@ -1350,9 +1350,12 @@ static FwdKernel einsum_forward_kernel(int count, int kout, const Dims& d) {
     // (one output per item would leave three of four rows of COMPACT's tiles empty; only items below the root have one)
     // from 13 entries on and with many workgroups the split operands pay: log-density of a tree of 512 items, K = 13, 1000 samples:
     // 112 with COMPACT, 90 with SMALL; K = 16, 103 and 95, 300 samples 57 and 59; K = 10: 84 and 85
-    if (K > 12 && K <= 16 && kout == K && units >= (quads ? 8192 : 1024)) return FWD_SMALL;
+    // (rows that are not whole pieces: beyond 64 samples for smaller launches too.  K = 14, 300 samples, 112 / 496 items: 43 and 40, 59
+    // and 55)
+    if (K > 12 && K <= 16 && kout == K && units >= (quads ? 8192 : B > 64 ? 256 : 1024)) return FWD_SMALL;
     // K = 20 (log-density, 1 / 100 / 1000 samples; COMPACT and the choice below): 194 items 48 / 54 / 109 and 52 / 57 / 129, 512 items
     // 38 / 49 / 148 and 42 / 54 / 190.  Rows of 17 to 19 entries are not whole pieces: 194 items, 18 entries, 200 samples 68 and 63
+    // (24 and 28 entries are whole pieces too; their weights take 48 and 63 KB of LDS instead of 33, and they were not measured)
     if (K <= 16 || K == 20) return kout == K ? FWD_COMPACT : FWD_PLAIN;
     // K = 48, 2 items, 1000 samples: plain 63, waves 19; 320 items, 16 samples: 171, 148; 64 samples: 155, 157
     if (K == 48 && kout == K) return B > 32 && B <= 64 ? FWD_PLAIN : FWD_WAVES;
