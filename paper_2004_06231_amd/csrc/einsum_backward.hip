@@ -77,8 +77,9 @@ __global__ void k_region_assemble(const int32_t* __restrict__ r_rec, const int32
 // The items of a short launch are cut into several workgroups (bwd_groups_per_item): each writes the left child's entries of its
 // slices and a block of its own with its share of the right child's, which the reader adds up.
 //
-// Bound by the splits and the issue of the matrix instructions together: at two waves per SIMD they hardly overlap.  Us of a
-// launch (in brackets: kernel that formed the statistics in the same launch, float32 matrix instructions): K = 40, 128 samples,
+// Bound by latency: at two waves per SIMD the counters show the matrix pipes busy 11 to 15 % of a launch of 128 samples and waves
+// that wait for something 42 % of their time (at 1000 samples 27 to 34 % and 37 to 40 %); a wave's products wait for its splits and
+// its loads.  Us of a launch (in brackets: kernel that formed the statistics in the same launch, float32 matrix instructions): K = 40, 128 samples,
 // 20 / 40 / 50 / 60 items: 12.8 / 16.8 / 17.8 / 21.9 (16.8 / 29.3 / 30.8 / 40.2), K = 40, 1000 samples: 33.8 / 66.9 / 70.6 / 72.5
 // (104 / 200 / 207 / 278); K = 30, 100 samples, 20 / 40 / 80 items: 12.8 / 14.0 / 18.0 (15.6 / 25.4 / 37.8).
 template <int K8>

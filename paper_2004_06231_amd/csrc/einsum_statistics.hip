@@ -217,8 +217,9 @@ void launch_stats_small(const EinStatsWork& w, bool accumulate, float* stats, hi
 // by a smaller one (the sums with it) from the step on whose values would pass 2^40; so sums stay below 2^96.  The threads that
 // stage a row choose its factor from the values as they are in memory, before they multiply: times the factor of the steps
 // before, a value may be beyond the largest float32.
-// Matrix and vector work are nearly additive here (one wave's products wait for its own splits): K = 40, 194 items: 41 us for
-// 128 samples, 229 us for 1000; K = 30, 140 items, 100 samples: 23 us.
+// K = 40, 194 items: 37 us for 128 samples, 202 us for 1000.  The counters show the matrix pipes busy 33 and 42 % of that time, waves
+// that wait for something 28 to 31 % of theirs and for an instruction to issue another 31 to 33 %: one wave's products wait for its
+// own splits.  K = 30, 140 items, 100 samples: 23 us.
 // STEP: samples that are staged at once.  32, the contraction of one instruction, or ST_WHOLE: the whole of a short batch.
 constexpr int ST_WHOLE = 128;
 template <int KQ, int NH, int STEP>

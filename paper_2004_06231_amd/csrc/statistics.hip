@@ -509,7 +509,7 @@ __device__ __forceinline__ void leaf_stats_body(
 // The same for models with few tiles of 16 pairs: a workgroup takes one tile and deals the batch to its eight waves, 32 samples
 // at a time; every wave splits the posteriors of its own samples, so nothing is shared before the waves' sums meet at the end.
 // With mixing statistics, us of the launch (in brackets: both operands staged through LDS, a thread per (pair, entry)): 32x32x3
-// images in cells of 8 x 8, K = 40: 12.5 for 128 samples (14.7), 47 for 1000 (80); 28x28 in cells, K = 16, 256 samples, with flags:
+// images in cells of 8 x 8, K = 40: 13.3 for 128 samples (14.7), 47 for 1000 (80); 28x28 in cells, K = 16, 256 samples, with flags:
 // 8.0 (18.0); lists of variables, K = 20, 200 samples: 9.3 (16.8).
 template <bool SQ, bool MASK, int NJ>
 struct LeafTileLds {

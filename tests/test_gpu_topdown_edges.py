@@ -1,6 +1,7 @@
 """GPU parity of the EM statistics where the kernels of the top-down pass change over: weight statistics formed with the
-posteriors (K to 16, batches to 64), in a launch of their own (K to 16), from a whole batch at once (to 128 samples) or step
-by step, and over shares of the batch; leaf statistics entry by entry (below 16 (variable, channel) pairs), with a tile of 16
+posteriors (K to 16, batches to 64, an item in one workgroup or its slices over several; K 17 to 48, chunks of the batch with a
+block each or in turn), in a launch of their own from a whole batch at once (to 128 samples) or step by step, and over shares of
+the batch; leaf statistics entry by entry (below 16 (variable, channel) pairs), with a tile of 16
 pairs per workgroup (to 512 tiles) or with eight, with and without flags, from assembled posteriors and from the parents'
 blocks; the bottom-up kernel for small items with several chunks of 64 samples per workgroup and with an item's outputs
 dealt to several workgroups.  The tolerance is the one of the statistics everywhere: float32 rounding of sums over the batch,
@@ -37,14 +38,26 @@ CASES = [
     (rat(64, 5, 16), 9, 1, BERNOULLI, 1100, None, (0.1, 0.9)),             # 256 items, 18 chunks: three chunks per workgroup
     (rat(16, 2, 1), 16, 1, BERNOULLI, 1, None, (0.1, 0.9)),                # an item's outputs over four workgroups
     (rat(32, 2, 2), 20, 1, GAUSSIAN, 900, None, (0.2, 0.8)),               # four items: shares of the batch, the last ragged
-    (rat(16, 2, 1), 24, 1, GAUSSIAN, 128, None, (0.2, 0.8)),               # K 17 to 24, up to 128 samples: with the posteriors
-    (rat(16, 2, 1), 21, 1, GAUSSIAN, 129, None, (0.2, 0.8)),               # one more: in a launch of their own
-    (dict(kind="pd", H=6, W=6, deltas=[2]), 29, 1, GAUSSIAN, 50, None, (0.2, 0.8)),          # K to 32 and few items, assembled posteriors
-    (rat(16, 2, 1), 37, 1, GAUSSIAN, 20, None, (0.2, 0.8)),                # K to 40 and fewer
+    (rat(16, 2, 1), 24, 1, GAUSSIAN, 128, None, (0.2, 0.8)),               # K from 17, one chunk: posteriors and statistics in one launch
+    (rat(16, 2, 1), 21, 1, GAUSSIAN, 129, None, (0.2, 0.8)),               # one more, rows read entry by entry: a block per chunk
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 29, 1, GAUSSIAN, 50, None, (0.2, 0.8)),          # the same, from assembled posteriors
+    (rat(16, 2, 1), 37, 1, GAUSSIAN, 20, None, (0.2, 0.8)),                # the same, three column tiles
     (dict(kind="pd", H=6, W=6, deltas=[2]), 20, 1, GAUSSIAN, 65, None, (0.2, 0.8)),          # whole items bottom-up, a second chunk of one sample
     (rat(16, 2, 1), 20, 1, BERNOULLI, 1, None, (0.1, 0.9)),                # its outputs over five workgroups
     (rat(64, 5, 16), 13, 1, BERNOULLI, 129, None, (0.1, 0.9)),             # split operands bottom-up: 256 items, two chunks
     (rat(600, 2, 2), 24, 1, BERNOULLI, 150, None, (1e-6, 1.0 - 1e-6)),     # posteriors and S~ over hundreds of binary orders
+    (rat(64, 3, 20), 20, 1, GAUSSIAN, 200, None, (0.2, 0.8)),              # 120 items in one launch per layer, both chunks in turn
+    (rat(64, 2, 32), 28, 1, GAUSSIAN, 129, None, (0.2, 0.8)),              # the same, the second chunk of one sample
+    (rat(64, 2, 32), 22, 1, GAUSSIAN, 129, None, (0.2, 0.8)),              # as many items, statistics in a launch of their own
+    (rat(16, 2, 2), 44, 1, GAUSSIAN, 33, None, (0.2, 0.8)),                # one launch per layer, K from 41
+    (rat(16, 2, 1), 48, 1, GAUSSIAN, 150, None, (0.2, 0.8)),               # the same, a block per chunk
+    (rat(16, 2, 1), 49, 1, GAUSSIAN, 40, None, (0.2, 0.8)),                # beyond it: in a launch of their own
+    (rat(16, 2, 1), 56, 1, GAUSSIAN, 300, None, (0.2, 0.8)),               # the same, over shares of the batch
+    (rat(16, 2, 1), 16, 1, BERNOULLI, 700, None, (0.1, 0.9)),              # K to 16, few items, many samples: shares of the batch
+    (rat(32, 2, 2), 7, 1, BERNOULLI, 513, None, (0.1, 0.9)),               # the same, the last share of one sample, pieces that overlap
+    (dict(kind="pd", H=6, W=6, deltas=[2]), 13, 1, GAUSSIAN, 64, None, (0.2, 0.8)),   # K 9 to 16, to 64 samples: an item's slices over several workgroups
+    (rat(64, 5, 16), 15, 1, BERNOULLI, 63, None, (0.1, 0.9)),              # many items: one workgroup each
+    (rat(1100, 5, 9), 7, 1, GAUSSIAN, 20, "per_sample", (0.2, 0.8)),       # eight tiles per workgroup, part of a step
 ]
 
 
