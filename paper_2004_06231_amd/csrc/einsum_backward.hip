@@ -1093,7 +1093,7 @@ static void launch_backward_fused(const DevTables& t, int first, int count, bool
                                   const float* A, const double* Off, const float* amax, const float* G, float* Gp, float* part, int total,
                                   bool direct, const Dims& d, hipStream_t s) {
     constexpr size_t lds = sizeof(float) * BwdLayout<KQ>::LDS_FLOATS;
-    constexpr bool ENTRIES = KQ <= 10, TURNS = KQ == 5 || KQ == 7;       // forms that einsum_backward_fused asks for
+    constexpr bool ENTRIES = KQ <= 10, TURNS = KQ == 7;       // forms that einsum_backward_fused asks for
     const int ngroups = bwd_groups_per_item(count, d.K, d.B), nchunks = (d.B + 127) / 128;
     const int nshare = fused_shares(total, d.K, d.B), cpv = (nchunks + nshare - 1) / nshare;
     const bool adds = accumulate && nshare == 1;                          // (blocks of shares are written, not added to)

@@ -563,7 +563,7 @@ void launch_sum_partial_stats(const PartialSumList& list, float* stats, bool acc
     if (list.ein.count > 0) {
         const EinStatsWork& w = list.ein;
         if (!w.formed) launch_statistics(w, accumulate, stats, s);
-        const int nshare = ein_stat_shares(w.count, w.K, w.B);
+        const int nshare = w.formed ? fused_shares(w.count, w.K, w.B) : ein_stat_shares(w.count, w.K, w.B);
         if (nshare > 1) jobs.job[n++] = PartialSumJob{w.woff, w.part, w.count, nshare, w.K * w.K * w.K};
     }
     if (n == 0) return;

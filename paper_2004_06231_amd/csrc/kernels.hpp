@@ -242,11 +242,6 @@ inline int ein_stat_share(int nshare, int B) {       // samples of a share
     const int nchunks = (B + 127) / 128;
     return nshare == 1 ? B : 128 * ((nchunks + nshare - 1) / nshare);
 }
-inline size_t ein_stat_partial_bound(int count, int K, int max_B) {
-    // (for any batch up to max_B: at most as many shares as chunks, and as the waves allow)
-    const long long v = ein_stat_most_shares(count, K, max_B);
-    return v < 2 ? 0 : (size_t)v * count * K * K * K;
-}
 // Above K = 16 the layers take one of two forms: posteriors and statistics in one launch per layer (k_einsum_backward_fused), or
 // posteriors per layer and the statistics of all layers at the end.  total: items of all layers below the root's (all layers of a model take the same
 // form).  Us of an EM step, one launch per layer and the other form:
@@ -254,25 +249,50 @@ inline size_t ein_stat_partial_bound(int count, int K, int max_B) {
 //     180 / 225 and 95 / 111 / 182 / 224, 128: 101 / 123 / 208 / 282 and 107 / 132 / 201 / 252; K = 40, 16: 97 / 125 / 208 / 296 and
 //     107 / 141 / 222 / 340, 128: 123 / 186 / 281 / 473 and 124 / 181 / 258 / 437;
 //   256 samples, a block per chunk, 8 / 24 items: K = 20 53 / 66 and 65 / 78, K = 32 62 / 91 and 70 / 99, K = 40 77 / 109 and 85 / 119;
-//     both chunks in turn, 112 / 194 items: K = 20 136 / 196 and 148 / 210, K = 28 172 / 266 and 191 / 264, K = 36 279 / 414 and 244 /
-//     336;
+//     both chunks in turn, 112 / 194 items: K = 28 172 / 266 and 191 / 264, K = 36 279 / 414 and 244 / 336;
 //   640 samples, a block per chunk, 4 / 8 / 16 items: K = 24 61 / 64 / 83 and 71 / 74 / 96, K = 40 75 / 103 / 143 and 82 / 106 / 143.
+// More blocks than the statistics' own launch is cut into (FUSED_UNITS: up to 35 MB) pay up to K = 24 for any number of items, above for
+// few:
+//   200 samples, 194 / 240 items: K = 20 179 / 154 and in turn 187 / 164, K = 22 216 / 197 and 248 / 213, K = 23 223 / 206 and 254 / 219,
+//     K = 24 213 / 181 and 218 / 182; 160 samples, K = 24 210 / 182 and 210 / 176;
+//   500 samples, 24 / 28 / 64 items: K = 22 - / - / 132 and - / - / 145, K = 28 - / 122 / - and - / 138 / -, K = 32 103 / 133 / 168 and
+//     118 / 138 / 161; 1000 samples, 24 / 28 items: K = 24 160 / 119 and 176 / 129, K = 32 141 / 166 and 156 / 161;
+//   300 samples, 24 / 28 items: K = 36 121 / 145 and 127 / 145, K = 40 124 / 154 and 128 / 137, K = 44 178 / 194 and 191 / 190, K = 48 - / 227
+//     and - / 207; 16 items, K = 44 142 and 157.
+constexpr long long FUSED_UNITS = 6144;
+inline bool fused_more_blocks(int total, int K, int nchunks) {
+    const long long n = ein_stat_units(total, K) * nchunks;
+    if (n == 0 || n > FUSED_UNITS) return false;
+    if (K == 24) return n <= 5400;                        // (whole pieces of eight: the other form is the faster of its neighbours)
+    if (K <= 32) return K < 24 || total <= 24 || (total <= 32 && n <= 4096);
+    return K <= 44 && (K & 3) == 0 && total <= 24 && nchunks <= 3;
+}
 inline bool einsum_backward_fused(int total, int K, int B) {
     const bool quads = (K & 3) == 0;                      // (rows of other K are staged entry by entry, from registers that spill)
     if (K <= 16 || K > 48 || (K > 40 && !quads)) return false;
     const int nchunks = (B + 127) / 128;
     if (nchunks > 1) {
+        if (fused_more_blocks(total, K, nchunks)) return true;
         if (ein_stat_shares(total, K, B) == nchunks) return K <= 32 || nchunks == 2 || total <= 8 || (nchunks == 3 && total <= 16);
-        return nchunks == 2 && ((K <= 20 && total <= 256) || (K == 28 && total <= 128));
+        return nchunks == 2 && K == 28 && total <= 128;
     }
     if (total <= 32 || K <= 24) return true;
     if (total <= 128) return K <= 32 || B <= 64;
     return (K <= 28 && total <= 256) || B <= 32 || (B <= 64 && quads);
 }
-// Shares of the chunks in one launch per layer: as many as chunks, or all chunks in turn where their blocks do not fit the scratch.
+// Shares of the chunks in one launch per layer: as many as chunks, or all chunks in turn where that is not worth their blocks.
 inline int fused_shares(int total, int K, int B) {
     const int nchunks = (B + 127) / 128;
-    return ein_stat_shares(total, K, B) == nchunks ? nchunks : 1;
+    return nchunks > 1 && (fused_more_blocks(total, K, nchunks) || ein_stat_shares(total, K, B) == nchunks) ? nchunks : 1;
+}
+// Floats of scratch for the blocks of statistics of either form, for batches of up to max_B: ein_stat_shares never has more of them
+// than ein_stat_most_shares for a larger batch.
+inline size_t ein_stat_partial_bound(int count, int K, int max_B) {
+    long long v = ein_stat_most_shares(count, K, max_B);
+    if (K > 16)
+        for (int n = 2; n <= (max_B + 127) / 128 && ein_stat_units(count, K) * n <= FUSED_UNITS; ++n)
+            if (fused_more_blocks(count, K, n) && einsum_backward_fused(count, K, 128 * n)) v = std::max<long long>(v, n);
+    return v < 2 ? 0 : (size_t)v * count * K * K * K;
 }
 
 // Floats of images (EIN_IMAGES) for batches of up to max_B, of which some take the other form

@@ -46,9 +46,14 @@ CASES = [
     (rat(16, 2, 1), 20, 1, BERNOULLI, 1, None, (0.1, 0.9)),                # its outputs over five workgroups
     (rat(64, 5, 16), 13, 1, BERNOULLI, 129, None, (0.1, 0.9)),             # split operands bottom-up: 256 items, two chunks
     (rat(600, 2, 2), 24, 1, BERNOULLI, 150, None, (1e-6, 1.0 - 1e-6)),     # posteriors and S~ over hundreds of binary orders
-    (rat(64, 3, 20), 20, 1, GAUSSIAN, 200, None, (0.2, 0.8)),              # 120 items in one launch per layer, both chunks in turn
-    (rat(64, 2, 32), 28, 1, GAUSSIAN, 129, None, (0.2, 0.8)),              # the same, the second chunk of one sample
-    (rat(64, 2, 32), 22, 1, GAUSSIAN, 129, None, (0.2, 0.8)),              # as many items, statistics in a launch of their own
+    (rat(64, 3, 20), 20, 1, GAUSSIAN, 200, None, (0.2, 0.8)),              # 120 items in one launch per layer, a block per chunk
+    (rat(64, 2, 32), 28, 1, GAUSSIAN, 129, None, (0.2, 0.8)),              # 64 items, both chunks in turn, the second of one sample
+    (rat(64, 2, 32), 22, 1, GAUSSIAN, 129, None, (0.2, 0.8)),              # as many items, a block per chunk, rows read entry by entry
+    (rat(64, 3, 32), 24, 1, GAUSSIAN, 257, None, (0.2, 0.8)),              # three chunks of 192 items: statistics in a launch of their own
+    (rat(16, 2, 12), 32, 1, GAUSSIAN, 385, None, (0.2, 0.8)),              # 24 items, four blocks each
+    (rat(16, 2, 13), 32, 1, GAUSSIAN, 513, None, (0.2, 0.8)),              # 26 items, five blocks each
+    (rat(16, 2, 12), 44, 1, GAUSSIAN, 300, None, (0.2, 0.8)),              # 24 items, K from 41, three blocks each
+    (rat(16, 2, 12), 40, 1, GAUSSIAN, 400, None, (0.2, 0.8)),              # the same, a chunk more: statistics in a launch of their own
     (rat(16, 2, 2), 44, 1, GAUSSIAN, 33, None, (0.2, 0.8)),                # one launch per layer, K from 41
     (rat(16, 2, 1), 48, 1, GAUSSIAN, 150, None, (0.2, 0.8)),               # the same, a block per chunk
     (rat(16, 2, 1), 49, 1, GAUSSIAN, 40, None, (0.2, 0.8)),                # beyond it: in a launch of their own

@@ -66,7 +66,8 @@ int shares() {
             for (int most : {1, 128, 129, 300, 512, 1000, 4096}) {
                 const size_t room = ein_stat_partial_bound(count, K, most);
                 for (int B = 1; B <= most; B += most > 512 ? 37 : 1) {
-                    const int n = ein_stat_shares(count, K, B), share = ein_stat_share(n, B);
+                    const int n = einsum_backward_fused(count, K, B) ? fused_shares(count, K, B) : ein_stat_shares(count, K, B);
+                    const int share = ein_stat_share(n, B);
                     bad += n < 1 || (long)n * share < B || (n > 1 && (share % 128 != 0 || (long)(n - 1) * share >= B ||
                                                                       (size_t)n * count * K * K * K > room));
                 }
